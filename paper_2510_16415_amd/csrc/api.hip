@@ -304,15 +304,15 @@ GemmProblem prob(const void* A0, const void* A1, int64_t lda, const void* B0, co
 }
 
 // A store launch into the library's own buffers (row stride == ldc of every problem), cut along K
-// into `splits` parts when that fills the chip better.
-mecefo_status_t launch_store_split(const Ctx& c, const Bufs& bf, GemmLaunch& g, int splits, hipStream_t s) {
+// into up to `most` parts (what the workspace holds partials for) when that fills the chip better.
+mecefo_status_t launch_store_split(const Ctx& c, const Bufs& bf, GemmLaunch& g, int most, hipStream_t s) {
+  const int splits = most > 1 && c.bf16 ? bf16_plan_splits(g, most) : most;
   if (splits <= 1) {
     HIP_TRY(launch_gemm(g, s));
     return MECEFO_OK;
   }
   g.epi = EPI_SPLIT_F32;
   g.splits = splits;
-  g.force_large = true;
   g.partial = (float*)(bf.base + bf.w.partial);
   void* C[3];
   int64_t poff = 0;
@@ -426,19 +426,24 @@ mecefo_status_t lowrank_wgrad(const Ctx& c, const Bufs& bf, const void* U, int64
     TRY(launch_store_split(c, bf, g, store_splits_project(c, rr, side), s));
   }
   {  // contract over tokens: C = (Gy or X)^T T   [rows x r], K = b
-    const int splits = b > 0 ? bf.w.splits : 1;
-    GemmLaunch g = new_launch(c, false, false, splits > 1 ? EPI_SPLIT_F32 : EPI_STORE);
+    GemmLaunch g = new_launch(c, false, false, EPI_STORE);
     g.nprob = n_lr;
-    g.splits = splits;
-    g.partial = (float*)(base + bf.w.partial);
-    int64_t poff = 0;
     for (int j = 0; j < n_lr; ++j) {
       const int i = lr[j];
       const int rows = in ? m_out[i] : n_in[i];
       g.p[j] = prob(in ? Gy[i] : X[i], nullptr, in ? ldgy[i] : ldx[i], T[i], nullptr, ldt[i], C[i], nullptr,
                     nullptr, ldt[i], rows, P[i].r, b, 1);
+    }
+    // the workspace holds partials for up to bf.w.splits parts
+    const int most = b > 0 ? bf.w.splits : 1;
+    const int splits = most > 1 && c.bf16 ? bf16_plan_splits(g, most) : most;
+    if (splits > 1) g.epi = EPI_SPLIT_F32;
+    g.splits = splits;
+    g.partial = (float*)(base + bf.w.partial);
+    int64_t poff = 0;
+    for (int j = 0; j < n_lr; ++j) {
       g.partial_off[j] = poff;
-      poff += (int64_t)splits * rows * ldt[i];
+      poff += (int64_t)splits * g.p[j].M * g.p[j].ldc;
     }
     {
       STAGE(MECEFO_STAGE_CONTRACT, s);

@@ -1,7 +1,7 @@
 // bf16 MFMA GEMM for gfx950 with direct-to-LDS operand staging.
 //
-// Same tiling as gemm_bf16.hip.h (256 x 256 output tile, eight wavefronts of 64 x 128), with two
-// differences.  The products run on v_mfma_f32_16x16x32_bf16: on Gaussian operands the matrix cores
+// One workgroup computes a 256 x 256 (eight wavefronts of 64 x 128), 128 x 128 (eight of 32 x 64) or
+// 64 x 64 (four of 32 x 32) output tile.  Two differences to gemm_bf16.hip.h.  The products run on v_mfma_f32_16x16x32_bf16: on Gaussian operands the matrix cores
 // are power-limited, and this shape moves half the accumulator bytes per multiply-add of the 32x32x16
 // one -- a bare MFMA loop on random operands sustains 2100 TFLOP/s at 2.1 GHz with it against 1860 at
 // 1.83 GHz.  And the operand tiles never pass through registers:
@@ -18,8 +18,8 @@
 //     k-rows of 16 elements into four K-consecutive values per lane); their 16-byte chunks are
 //     XOR-swizzled by k so that the eight k-rows of a 32-lane pass fall into different banks.
 // Rows and K positions outside the matrices are fetched from outside the buffer (zeros).
-// A ragged K inside a 16-byte chunk cannot be masked on this path: the host only selects it
-// when K is a multiple of 8 or the bytes behind K are known to be zero.
+// A K-contiguous operand whose K ends inside a 16-byte chunk has that chunk cleaned in LDS after it has
+// landed (clear_tail); the host says which problems need it.
 #pragma once
 #include "gemm_bf16.hip.h"
 
@@ -68,7 +68,7 @@ __device__ inline void wait_fills_leave(int stages_left) {
   else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(3 * FPS) : "memory");
 }
 
-// ---- direct-to-LDS fill of one operand tile (256 rows x BK) --------------------------------
+// ---- direct-to-LDS fill of one operand tile (ROWS rows x BK) -------------------------------
 // Swizzle of the K-contiguous layout [rows][BK]: physical 16-byte chunk = logical ^ kc_swz(row).
 // A 16-byte read of the 16x16x32 operand (lane l: row l % 16, chunk l / 16 of the step) is served 16
 // lanes per clock, and the lanes of a clock are eight rows at one chunk plus the other eight rows of
@@ -81,10 +81,10 @@ template <int BK> __device__ inline int kc_swz(int row) {
   else return ((row >> 1) ^ (row >> 3)) & 3;               // 4 chunks per 64-byte row
 }
 
-template <int BK, int NT, bool DUAL>
+template <int BK, int NT, int ROWS, bool DUAL>
 struct DmaKC {   // K-contiguous source; one wave instruction covers RPI consecutive rows
   static constexpr int ROWB = BK * 2, CH = ROWB / 16, RPI = 1024 / ROWB;
-  static constexpr int NW = NT / 64, NI = (256 / RPI) / NW;
+  static constexpr int NW = NT / 64, NI = (ROWS / RPI) / NW;
   static_assert(NI >= 1 && (!DUAL || NI % 2 == 0), "unsupported stage size");
   uint32_t voff[NI];
   int c;       // logical 16-byte chunk this lane fetches (the same for all its instructions)
@@ -92,11 +92,11 @@ struct DmaKC {   // K-contiguous source; one wave instruction covers RPI consecu
   __device__ inline void init(int lane, int wave, int row_base, int rows_total, int64_t ld) {
     w = wave;
     const int rsub = lane / CH;
-    c = (lane % CH) ^ kc_swz<BK>(w * RPI + rsub);   // instructions q*NW + w differ by multiples of 64 rows
+    c = (lane % CH) ^ kc_swz<BK>(w * RPI + rsub);   // instructions q*NW + w differ by multiples of NW * RPI rows
 #pragma unroll
     for (int q = 0; q < NI; ++q) {
       const int row = (q * NW + w) * RPI + rsub;
-      const int gr = row_base + (DUAL ? (row & 127) : row);
+      const int gr = row_base + (DUAL ? (row & (ROWS / 2 - 1)) : row);
       voff[q] = gr < rows_total ? (uint32_t)(((int64_t)gr * ld + c * 8) * 2) : kOOB;
     }
   }
@@ -108,32 +108,47 @@ struct DmaKC {   // K-contiguous source; one wave instruction covers RPI consecu
       fill_lds_16B((DUAL && q >= NI / 2) ? r1 : r0, tile + (q * NW + w) * 1024, off, (uint32_t)k0 * 2);
     }
   }
+  // A ragged K ends inside a 16-byte chunk, whose rest holds bytes from behind the rows: zero the last
+  // 8 - rem elements of that chunk (index kend / 8 of the stage, rem = kend % 8) in every row of a landed tile.
+  static __device__ inline void clear_tail(uint8_t* tile, int t, int kend) {
+    for (int row = t; row < ROWS; row += NT) {
+      __bf16* chunk = (__bf16*)(tile + row * ROWB + (((kend >> 3) ^ kc_swz<BK>(row)) << 4));
+      for (int e = kend & 7; e < 8; ++e) chunk[e] = (__bf16)0.f;
+    }
+  }
 };
 
-__device__ inline int ks_swz(int k) { return ((k & 7) << 1) ^ (k & 8); }   // XOR on the 16-byte chunk index
-// Physical 16-byte chunk of logical chunk c (0..31, eight columns each) in k row k, and back.  A
-// transposing read takes, per pass of 32 lanes, 32 bytes (two chunks) of each of eight k rows: four
-// consecutive ones and the four that lie eight further on (the two 16-lane groups of a pass hold
-// neighbouring K groups of the 16x16x32 operand).  LDS serves 256 bytes per clock from 64 banks, so
-// the 16 chunks of a pass must differ in their low four bits: bit 0 is the chunk of the pair, the k
-// row fills bits 1-2 (XOR with its low bits) and bit 3 (XOR with k bits 2 and 3); the second chunk
-// pair of a row (bit 1 of c) also goes to the other half of the banks.  The map is its own inverse.
-__device__ inline int ks_fold(int c) { return c ^ ((c & 2) << 2); }
-__device__ inline int ks_phys(int c, int k) { return (ks_fold(c) ^ ks_swz(k)) & 31; }
-__device__ inline int ks_logical(int pos, int k) { return ks_fold((pos ^ ks_swz(k)) & 31); }
+// Physical 16-byte chunk of logical chunk c (eight columns each) in k row k of a K-strided tile
+// [BK k][ROWS], and back.  A transposing read takes, per pass of 32 lanes, 32 bytes (two chunks) of each
+// of eight k rows: four consecutive ones and the four that lie eight further on (the two 16-lane groups of
+// a pass hold neighbouring K groups of the 16x16x32 operand).  LDS serves 256 bytes per clock from 64
+// banks, so the 16 chunks of a pass must fall on different sixteenths of 256 bytes.  Rows of 256 or 512
+// bytes: bit 0 is the chunk of the pair, the k row fills bits 1-2 (XOR with its low bits) and bit 3 (XOR
+// with k bits 2 and 3); the second chunk pair of a row (bit 1 of c) also goes to the other half of the
+// banks.  Rows of 128 bytes: k bit 0 is the half of the banks by itself, k bits 1 and 3 fill chunk bits 1-2.
+// The map is its own inverse.
+template <int ROWS> struct KsMap {
+  static constexpr int CH = ROWS / 8;
+  static_assert(ROWS == 64 || ROWS == 128 || ROWS == 256, "unsupported tile width");
+  static __device__ inline int fold(int c) { return ROWS == 64 ? c : c ^ ((c & 2) << 2); }
+  static __device__ inline int swz(int k) { return ROWS == 64 ? (k & 2) | ((k & 8) >> 1) : ((k & 7) << 1) ^ (k & 8); }
+  static __device__ inline int phys(int c, int k) { return (fold(c) ^ swz(k)) & (CH - 1); }
+  static __device__ inline int logical(int pos, int k) { return fold((pos ^ swz(k)) & (CH - 1)); }
+};
 
-template <int BK, int NT>
-struct DmaKS {   // K-strided source; wave instruction g covers k rows 2g, 2g+1 (512 bytes each)
-  static constexpr int NW = NT / 64, NI = (BK / 2) / NW;
-  static_assert(NI >= 1 && NW == 8, "unsupported stage size");
-  uint32_t voff;      // lane offset for q = 0; instruction q adds 2*NW*q rows
+template <int BK, int NT, int ROWS>
+struct DmaKS {   // K-strided source; one wave instruction covers KPI k rows of 2 * ROWS bytes
+  static constexpr int ROWB = ROWS * 2, CH = ROWB / 16, KPI = 1024 / ROWB;
+  static constexpr int NW = NT / 64, NI = (BK / KPI) / NW;
+  static_assert(NI >= 1 && (NI == 1 || (NW * KPI) % 16 == 0), "unsupported stage size");
+  uint32_t voff;      // lane offset for q = 0; instruction q adds NW * KPI * q rows
   uint32_t ld2;
   int krow0;          // k row of this lane for q = 0
   int w;
   __device__ inline void init(int lane, int wave, int row_base, int rows_total, int64_t ld) {
     w = wave;
-    krow0 = 2 * w + (lane >> 5);
-    const int cm = ks_logical(lane & 31, krow0);     // rows 16 q apart share k & 7
+    krow0 = KPI * w + lane / CH;
+    const int cm = KsMap<ROWS>::logical(lane % CH, krow0);     // the swizzle sees k % 16 only: the same for every q
     const int m = row_base + cm * 8;
     ld2 = (uint32_t)(ld * 2);
     voff = m < rows_total ? (uint32_t)(((int64_t)krow0 * ld + m) * 2) : kOOB;
@@ -142,23 +157,24 @@ struct DmaKS {   // K-strided source; wave instruction g covers k rows 2g, 2g+1 
     const uint32_t soff = (uint32_t)k0 * ld2;
 #pragma unroll
     for (int q = 0; q < NI; ++q) {
-      const bool kvalid = !tail || (k0 + krow0 + 2 * NW * q < K);
-      const uint32_t off = (kvalid && voff != kOOB) ? voff + (uint32_t)(2 * NW * q) * ld2 : kOOB;
+      const bool kvalid = !tail || (k0 + krow0 + NW * KPI * q < K);
+      const uint32_t off = (kvalid && voff != kOOB) ? voff + (uint32_t)(NW * KPI * q) * ld2 : kOOB;
       fill_lds_16B(r0, tile + (q * NW + w) * 1024, off, soff);
     }
   }
+  static __device__ inline void clear_tail(uint8_t*, int, int) {}   // whole k rows are masked by the fills
 };
 
-template <int BK, int NT, bool KC, bool DUAL> struct DmaSel { using type = DmaKC<BK, NT, DUAL>; };
-template <int BK, int NT, bool DUAL> struct DmaSel<BK, NT, false, DUAL> {
+template <int BK, int NT, int ROWS, bool KC, bool DUAL> struct DmaSel { using type = DmaKC<BK, NT, ROWS, DUAL>; };
+template <int BK, int NT, int ROWS, bool DUAL> struct DmaSel<BK, NT, ROWS, false, DUAL> {
   static_assert(!DUAL, "dual products need K-contiguous B");
-  using type = DmaKS<BK, NT>;
+  using type = DmaKS<BK, NT, ROWS>;
 };
 
 // ---- MFMA operand fetch from LDS ------------------------------------------------------
 // Operands of v_mfma_f32_16x16x32_bf16: NB blocks of 16 rows; lane l holds row l % 16 and the eight
 // K values 8 (l / 16) .. + 7 of a 32-K step.  K-contiguous tiles: one ds_read_b128 per block and step.
-template <int BK, int NB>
+template <int BK, int NB, int ROWS>
 struct FragKC {
   int base[NB];
   // rows[i]: first tile row of block i for this wave
@@ -174,11 +190,12 @@ struct FragKC {
   }
 };
 
-// K-strided tiles ([BK k][256 rows], 512 bytes per k): two transposing 8-byte reads per block.  Within
+// K-strided tiles ([BK k][ROWS]): two transposing 8-byte reads per block.  Within
 // a 16-lane group source lane 4 kq + q4 supplies rows 4 q4 .. + 3 at k row kq; the read hands result
 // lane i the four K-consecutive values of row i.
-template <int BK, int NB>
+template <int BK, int NB, int ROWS>
 struct FragKS {
+  static constexpr int ROWB = ROWS * 2;
   int base[NB][2];
   __device__ inline void init(int lane, const int (&rows)[NB]) {
     const int kq = (lane & 15) >> 2, g = lane >> 4, q4 = lane & 3;
@@ -188,42 +205,45 @@ struct FragKS {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int k = 8 * g + 4 * h + kq;
-        base[i][h] = k * 512 + (ks_phys(m >> 3, k) << 4) + ((m & 7) << 1);
+        base[i][h] = k * ROWB + (KsMap<ROWS>::phys(m >> 3, k) << 4) + ((m & 7) << 1);
       }
     }
   }
   __device__ inline bf16x8_t fetch_one(int i, const uint8_t* tile, int step) const {
     typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
-    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(tile + base[i][0] + step * 32 * 512));
-    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(tile + base[i][1] + step * 32 * 512));
+    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(tile + base[i][0] + step * 32 * ROWB));
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(tile + base[i][1] + step * 32 * ROWB));
     typedef __attribute__((ext_vector_type(8))) short s16x8_t;
     const s16x8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     return __builtin_bit_cast(bf16x8_t, v);
   }
 };
 
-template <int BK, int NB, bool KC> struct FragSel { using type = FragKC<BK, NB>; };
-template <int BK, int NB> struct FragSel<BK, NB, false> { using type = FragKS<BK, NB>; };
+template <int BK, int NB, int ROWS, bool KC> struct FragSel { using type = FragKC<BK, NB, ROWS>; };
+template <int BK, int NB, int ROWS> struct FragSel<BK, NB, ROWS, false> { using type = FragKS<BK, NB, ROWS>; };
 
-// Pipeline shape of the direct-to-LDS kernel: K elements per stage and number of LDS buffers.
-template <int BK_, int NS_> struct DtlPipe {
-  static constexpr int BK = BK_, NS = NS_;
-  static constexpr int A_BYTES = 256 * BK * 2, STAGE_BYTES = 2 * A_BYTES;
-  // per-wave LDS slice of the staged epilogue: 32 rows x (128 + 8) floats, or 2 x 32 x (64 + 8)
-  static constexpr int EP_WAVE_BYTES = 2 * 32 * 72 * 4;
-  static constexpr int LDS_BYTES = NS * STAGE_BYTES > 8 * EP_WAVE_BYTES ? NS * STAGE_BYTES : 8 * EP_WAVE_BYTES;
-  static_assert(NS >= 2 && NS <= 4 && (BK == 32 || BK == 64) && LDS_BYTES <= 160 * 1024, "bad pipeline");
-  static_assert(32 * 136 * 4 <= EP_WAVE_BYTES, "epilogue slice too small");
+// Pipeline shape of the direct-to-LDS kernel for a tile: 64 K elements per stage, NS LDS buffers.
+template <class Cfg, int NS_> struct DtlPipe {
+  static constexpr int BK = 64, NS = NS_;
+  static constexpr int A_BYTES = Cfg::BM * BK * 2, B_BYTES = Cfg::BN * BK * 2, STAGE_BYTES = A_BYTES + B_BYTES;
+  static constexpr int NW = Cfg::NT / 64;
+  static constexpr int FPS = STAGE_BYTES / 1024 / NW;      // fill instructions per wave and stage
+  // per-wave LDS slice of the staged epilogue: 32 rows x (WN + 4) floats, or 2 x 32 x (WN / 2 + 4)
+  static constexpr int EP_WAVE_BYTES = 32 * (Cfg::WN + 8) * 4;
+  static constexpr int LDS_BYTES = NS * STAGE_BYTES > NW * EP_WAVE_BYTES ? NS * STAGE_BYTES : NW * EP_WAVE_BYTES;
+  static_assert(NS >= 2 && NS <= 4 && LDS_BYTES <= 160 * 1024 && (NS - 1) * FPS <= 63, "bad pipeline");
 };
 
-template <class Cfg, class Pipe, bool AKC, bool BKC, int EPI>
-__global__ __launch_bounds__(Cfg::NT) void gemm_bf16_dtl_kernel(const KArgs args) {
+// RAGGED: K may end inside a 16-byte chunk (the instantiation without it keeps the large tile's loop free of the
+// test: 0.5 % of the 7B-shaped layer).
+template <class Cfg, class Pipe, bool AKC, bool BKC, int EPI, bool RAGGED>
+__global__ __launch_bounds__(Cfg::NT, 2) void gemm_bf16_dtl_kernel(const KArgs args) {
   constexpr bool DUAL = epi_is_dual(EPI);
   constexpr int BM = Cfg::BM, BN = Cfg::BN, NT = Cfg::NT;
   constexpr int TM = Cfg::WM / 16, TN = Cfg::WN / 16;     // 16x16 MFMA blocks per wave
-  constexpr int BK = Pipe::BK, NS = Pipe::NS, KS = BK / 32, FPS = BK / 8;
+  constexpr int BK = Pipe::BK, NS = Pipe::NS, KS = BK / 32, FPS = Pipe::FPS;
   constexpr int A_BYTES = Pipe::A_BYTES, STAGE = Pipe::STAGE_BYTES;
-  static_assert(BM == 256 && BN == 256 && NT == 512, "direct-to-LDS path is built for 256x256 tiles, 8 waves");
+  static_assert(TM % 2 == 0 && TN % (DUAL ? 2 : 1) == 0, "the epilogue takes 32 rows at a time");
   constexpr int BN_OUT = DUAL ? BN / 2 : BN;
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
 
@@ -250,8 +270,10 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_bf16_dtl_kernel(const KArgs args
   int kt_end = min(kt_total, kt_begin + kt_chunk);
   causal_clip(p, m0, n0, BM, BK, kt_begin, kt_end);
 
-  typename DmaSel<BK, NT, AKC, false>::type da;
-  typename DmaSel<BK, NT, BKC, DUAL>::type db;
+  using DmaA = typename DmaSel<BK, NT, BM, AKC, false>::type;
+  using DmaB = typename DmaSel<BK, NT, BN, BKC, DUAL>::type;
+  DmaA da;
+  DmaB db;
   da.init(lane, wave, m0, p.M, p.lda);
   db.init(lane, wave, n0, p.N, p.ldb);
   const u32x4_t ra0 = make_rsrc_words(p.A[0]);
@@ -270,8 +292,8 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_bf16_dtl_kernel(const KArgs args
     if constexpr (DUAL) b_rows[j] = (j >= TN / 2 ? BN / 2 : 0) + wn * (Cfg::WN / 2) + (j % (TN / 2)) * 16;
     else b_rows[j] = wn * Cfg::WN + j * 16;
   }
-  typename FragSel<BK, TM, AKC>::type fa;
-  typename FragSel<BK, TN, BKC>::type fb;
+  typename FragSel<BK, TM, BM, AKC>::type fa;
+  typename FragSel<BK, TN, BN, BKC>::type fb;
   fa.init(lane, a_rows);
   fb.init(lane, b_rows);
 
@@ -334,6 +356,16 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_bf16_dtl_kernel(const KArgs args
     int k = kt_begin + i + rot;
     return k >= kt_end ? k - nst : k;
   };
+  // K-contiguous operands whose K is no multiple of 8: the last stage of a segment is cleaned in LDS once
+  // it has landed, behind one more barrier (the bytes behind K may hold anything, also in one operand only).
+  const bool ragged = RAGGED && (AKC || BKC) && (K & 7) && !p.kpad_ok;
+  auto clear_ragged = [&](int kt, uint8_t* stage) {
+    const int seg = (kt >= kt_per_seg ? 1 : 0) + (kt >= 2 * kt_per_seg ? 1 : 0);
+    if (!ragged || kt != (seg + 1) * kt_per_seg - 1) return;
+    DmaA::clear_tail(stage, t, K % BK);
+    DmaB::clear_tail(stage + A_BYTES, t, K % BK);
+    __syncthreads();
+  };
   if (nst > 0) {
     // Fill every buffer of the ring, wait for the first stage only.
 #pragma unroll
@@ -341,6 +373,7 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_bf16_dtl_kernel(const KArgs args
       if (s < nst) issue(kmap(s), smem_addr + s * STAGE);
     wait_fills_leave<FPS>(min(NS, nst) - 1);
     __syncthreads();
+    clear_ragged(kmap(0), smem);
 #pragma unroll
     for (int i = 0; i < TM; ++i) af[0][i] = fa.fetch_one(i, smem, 0);
 #pragma unroll
@@ -356,6 +389,7 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_bf16_dtl_kernel(const KArgs args
       wait_fills_leave<FPS>(min(NS - 2, kt_end - kt - 2));
       __syncthreads();
       if (kt + NS < kt_end) issue(kmap(kt - kt_begin + NS), smem_addr + buf * STAGE);
+      if (ragged && kt + 1 < kt_end) clear_ragged(kmap(kt - kt_begin + 1), smem + nbuf * STAGE);
       step(1, smem + nbuf * STAGE, 0);
       buf = nbuf;
     }

@@ -1,56 +1,17 @@
 // Host-side launch helpers for the bf16 MFMA GEMM instantiations.
 #pragma once
+#include <math.h>
+
 #include "gemm_bf16_dtl.hip.h"
 
 namespace mecefo {
 
-using CfgL4 = TileCfg<256, 256, 2, 2>;   // 4 waves x (128 x 128): fewest LDS reads per MFMA
+using CfgL4 = TileCfg<256, 256, 2, 2>;   // register staging, forced by the "tile" option only
 using CfgL8 = TileCfg<256, 256, 4, 2>;   // 8 waves x (64 x 128): two waves per SIMD hide latency
-using CfgS = TileCfg<128, 128, 2, 2>;    // small problems: 4 waves x (64 x 64), more blocks
+using CfgM = TileCfg<128, 128, 4, 2>;    // 8 waves x (32 x 64): two workgroups per CU
+using CfgT = TileCfg<64, 64, 2, 2>;      // 4 waves x (32 x 32): three workgroups per CU
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
-
-// Total 256x256 tiles of a launch; below this many the 128x128 configuration is used.
-inline int bf16_tiles(const GemmLaunch& g, int bm, int bn) {
-  const bool dual = epi_is_dual(g.epi);
-  int t = 0;
-  for (int i = 0; i < g.nprob; ++i)
-    t += cdiv(g.p[i].M, bm) * cdiv(g.p[i].N, dual ? bn / 2 : bn) * (g.p[i].batch > 1 ? g.p[i].batch : 1);
-  return t;
-}
-// 256 x 256 tiles (direct-to-LDS kernel) when they give at least half of the 256 CUs a tile; a
-// split-K launch counts its parts, provided each keeps eight or more K stages.  Below that the
-// 128 x 128 configuration fills the chip better.
-inline bool bf16_use_large(const GemmLaunch& g) {
-  const int tl = bf16_tiles(g, 256, 256);
-  if (tl >= 128) return true;
-  if (g.epi == EPI_SPLIT_F32 && g.splits > 1) {
-    int stages = 1 << 30;
-    for (int i = 0; i < g.nprob; ++i) {
-      const int st = cdiv(g.p[i].K, 64) * (g.p[i].nseg > 1 ? g.p[i].nseg : 1);
-      if (st < stages) stages = st;
-    }
-    return tl * g.splits >= 128 && stages / g.splits >= 8;
-  }
-  return false;
-}
-
-// The direct-to-LDS kernel cannot mask a ragged K inside a 16-byte chunk.
-inline bool bf16_dtl_ok(const GemmLaunch& g) {
-  for (int i = 0; i < g.nprob; ++i)
-    if ((g.a_kcontig || g.b_kcontig) && (g.p[i].K % 8) && !g.p[i].kpad_ok) return false;
-  return true;
-}
-
-// 0: 128x128 / 4 waves, 1: 256x256 / 4 waves, 2: 256x256 / 8 waves (register staging),
-// 3: 256x256 / 8 waves, direct-to-LDS, 2 x 64-K stages.  mecefo_set_option("tile", ...) forces one.
-inline int bf16_tile_choice(const GemmLaunch& g) {
-  int c = (bf16_use_large(g) || g.force_large) ? 3 : 0;
-  const int forced = options().tile.load(std::memory_order_relaxed);
-  if (forced >= 1 && forced <= 4) c = forced - 1;
-  if (c >= 3 && !bf16_dtl_ok(g)) c = 2;
-  return c;
-}
 
 // Two 64 KiB stages, refilled one stage ahead.  Measured alternatives that lost: four 32-K stages
 // (64-byte row pieces double the L2 request count); rings of three buffers, symmetric or A2+B3 /
@@ -59,17 +20,101 @@ inline int bf16_tile_choice(const GemmLaunch& g) {
 // loop (a fills-only loop runs a stage in 0.9-1.3 us, the full loop gives it 1.4): LDS traffic of
 // fills plus fragment reads and MFMA issue are both near a stage's length, and on Gaussian operands
 // the matrix cores are power-limited.
-using PipeA = DtlPipe<64, 2>;
+using PipeL = DtlPipe<CfgL8, 2>;
+using PipeM2 = DtlPipe<CfgM, 2>;   // 74 KiB: two workgroups per CU cover each other's waits
+using PipeM4 = DtlPipe<CfgM, 4>;   // 128 KiB: one workgroup per CU, three stages in flight
+using PipeT = DtlPipe<CfgT, 3>;    // 48 KiB
+
+// ---- choice of the tile ------------------------------------------------------------------------
+// What bounds a launch depends on how many workgroups it gives a CU.  One 256 x 256 workgroup per CU has
+// the best rate (fewest operand bytes per multiply-add), but a K stage takes it 1.4 to 1.8 us however few
+// of them there are, so a launch that fills a quarter of the chip pays the full length of K at that pace:
+// smaller tiles walk K two to four times faster and give the idle CUs work.  The choice is the smallest
+// modelled time over the four configurations,
+//     fixed + per_round * n + stages * max(stage_alone, stage_shared * n),   n = workgroups per CU,
+// with constants fitted to a sweep of 50 launches over every operand layout (K 32 to 11008, 2 to 2752
+// workgroups; the model is within 15 % of nearly all of them).  Sides measured, in us (256^2 / 128^2
+// two-stage / 128^2 four-stage / 64^2): [2048 x 2048], K 2048: 49 / 27 / 27 / 35; the same three in one
+// launch: 54 / 60 / 73 / 84; [512 x 512], K 2048: 47 / 23 / 25 / 15; [2048 x 2048], K 5461: 135 / 80 / 61 /
+// 101; [2048 x 512], K 1376: 33 / 16 / 17 / 11; SwiGLU recompute of 2048 tokens, d 2048, f 5461: 119 / 111 /
+// 138 / 156; [4096 x 4096], K 8192: 248 / 310 / 383 / 456.  The register-staged 128 x 128 kernel that the
+// small launches ran on before took 51, 81, 51, 99, 23, 143 and 624 us.
+enum TileConfig : int { TILE_L = 0, TILE_M2 = 1, TILE_M4 = 2, TILE_T = 3, TILE_COUNT = 4 };
+
+struct TileModel { int bm, bn, slots; float fixed, per_round, stage_alone, stage_shared; };
+inline const TileModel& tile_model(int c) {
+  static const TileModel m[TILE_COUNT] = {{256, 256, 1, 3.5f, 2.5f, 1.45f, 1.75f},
+                                          {128, 128, 2, 3.0f, 1.2f, 0.78f, 0.62f},
+                                          {128, 128, 1, 3.0f, 1.2f, 0.70f, 0.72f},
+                                          {64, 64, 3, 2.5f, 0.5f, 0.44f, 0.28f}};
+  return m[c];
+}
+
+// Output tiles of a launch, and the K stages of its longest problem.
+inline int bf16_tiles(const GemmLaunch& g, int bm, int bn) {
+  const bool dual = epi_is_dual(g.epi);
+  int t = 0;
+  for (int i = 0; i < g.nprob; ++i)
+    t += cdiv(g.p[i].M, bm) * cdiv(g.p[i].N, dual ? bn / 2 : bn) * (g.p[i].batch > 1 ? g.p[i].batch : 1);
+  return t;
+}
+inline int bf16_stages(const GemmLaunch& g) {
+  int st = 0;
+  for (int i = 0; i < g.nprob; ++i) {
+    const int s = cdiv(g.p[i].K, kBK) * (g.p[i].nseg > 1 && !epi_is_dual(g.epi) ? g.p[i].nseg : 1);
+    if (s > st) st = s;
+  }
+  return st;
+}
+
+// Modelled time in us of the launch cut along K into `splits` parts, on configuration c.
+inline float bf16_tile_cost(const GemmLaunch& g, int c, int splits) {
+  const TileModel& m = tile_model(c);
+  const float blocks = (float)bf16_tiles(g, m.bm, m.bn) * splits;
+  float n = blocks / 256.f;
+  if (n < 4.f) n = (float)(int)(n + 0.999f);   // few workgroups per CU: the fullest CU sets the time
+  const float stage = n <= 1.f ? m.stage_alone : fmaxf(m.stage_alone, m.stage_shared * n);
+  return m.fixed + m.per_round * n + (float)cdiv(bf16_stages(g), splits) * stage;
+}
+inline int bf16_best_tile(const GemmLaunch& g, int splits, float* cost = nullptr) {
+  int best = TILE_L;
+  float t = bf16_tile_cost(g, TILE_L, splits);
+  for (int c = 1; c < TILE_COUNT; ++c) {
+    const float x = bf16_tile_cost(g, c, splits);
+    if (x < t) { t = x; best = c; }
+  }
+  if (cost) *cost = t;
+  return best;
+}
+
+// K splits of a launch that may be cut into up to `most` parts: every part keeps four or more stages, and
+// the fp32 partials (written, read back and summed by one more launch: about 5 us and their bytes at
+// 3 TB/s) have to be paid for by a shorter K loop.
+inline int bf16_plan_splits(const GemmLaunch& g, int most) {
+  double out = 0;
+  for (int i = 0; i < g.nprob; ++i) out += (double)g.p[i].M * g.p[i].ldc * 4;
+  const int stages = bf16_stages(g);
+  int best = 1;
+  float t;
+  bf16_best_tile(g, 1, &t);
+  for (int s = 2; s <= most && stages / s >= 4; ++s) {
+    float x;
+    bf16_best_tile(g, s, &x);
+    x += 5.f + (float)(out * s * 2 / 3e6);
+    if (x < t) { t = x; best = s; }
+  }
+  return best;
+}
 
 struct NoPipe { static constexpr int LDS_BYTES = 0; };
 
 // One kernel instantiation: its entry point, its dynamic LDS size and the once-per-device limit raise.
-template <class Cfg, bool AKC, bool BKC, int EPI, class Pipe>
+template <class Cfg, bool AKC, bool BKC, int EPI, class Pipe, bool RAGGED>
 struct Bf16Kernel {
   static constexpr bool DTL = Pipe::LDS_BYTES > 0;
   static constexpr int LDS = DTL ? Pipe::LDS_BYTES : Cfg::LDS_BYTES;
   static auto entry() -> void (*)(const KArgs) {
-    if constexpr (DTL) return gemm_bf16_dtl_kernel<Cfg, Pipe, AKC, BKC, EPI>;
+    if constexpr (DTL) return gemm_bf16_dtl_kernel<Cfg, Pipe, AKC, BKC, EPI, RAGGED>;
     else return gemm_bf16_kernel<Cfg, AKC, BKC, EPI>;
   }
   static hipError_t prepare() {
@@ -78,9 +123,16 @@ struct Bf16Kernel {
   }
 };
 
-template <class Cfg, bool AKC, bool BKC, int EPI, class Pipe = NoPipe>
+// A K that is no multiple of 8 and not padded with zeros behind a K-contiguous operand.
+inline bool bf16_ragged(const GemmLaunch& g) {
+  for (int i = 0; i < g.nprob; ++i)
+    if ((g.a_kcontig || g.b_kcontig) && (g.p[i].K % 8) && !g.p[i].kpad_ok) return true;
+  return false;
+}
+
+template <class Cfg, bool AKC, bool BKC, int EPI, class Pipe = NoPipe, bool RAGGED = true>
 hipError_t run_bf16(GemmLaunch& g, hipStream_t stream) {
-  using Kern = Bf16Kernel<Cfg, AKC, BKC, EPI, Pipe>;
+  using Kern = Bf16Kernel<Cfg, AKC, BKC, EPI, Pipe, RAGGED>;
   constexpr int LDS = Kern::LDS;
   constexpr bool DUAL = epi_is_dual(EPI);
   KArgs a;
@@ -113,23 +165,38 @@ hipError_t run_bf16(GemmLaunch& g, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Limit raise for the four configurations of one (layout, epilogue) pair.
+// Limit raise for the configurations of one (layout, epilogue) pair.
 template <bool AKC, bool BKC, int EPI>
 hipError_t prepare_bf16() {
-  hipError_t e = Bf16Kernel<CfgS, AKC, BKC, EPI, NoPipe>::prepare();
-  if (e == hipSuccess) e = Bf16Kernel<CfgL4, AKC, BKC, EPI, NoPipe>::prepare();
-  if (e == hipSuccess) e = Bf16Kernel<CfgL8, AKC, BKC, EPI, NoPipe>::prepare();
-  if (e == hipSuccess) e = Bf16Kernel<CfgL8, AKC, BKC, EPI, PipeA>::prepare();
+  hipError_t e = Bf16Kernel<CfgL8, AKC, BKC, EPI, PipeL, false>::prepare();
+  if (e == hipSuccess && (AKC || BKC)) e = Bf16Kernel<CfgL8, AKC, BKC, EPI, PipeL, AKC || BKC>::prepare();
+  if (e == hipSuccess) e = Bf16Kernel<CfgM, AKC, BKC, EPI, PipeM2, true>::prepare();
+  if (e == hipSuccess) e = Bf16Kernel<CfgM, AKC, BKC, EPI, PipeM4, true>::prepare();
+  if (e == hipSuccess) e = Bf16Kernel<CfgT, AKC, BKC, EPI, PipeT, true>::prepare();
+  if (e == hipSuccess) e = Bf16Kernel<CfgL4, AKC, BKC, EPI, NoPipe, true>::prepare();
+  if (e == hipSuccess) e = Bf16Kernel<CfgL8, AKC, BKC, EPI, NoPipe, true>::prepare();
   return e;
 }
 
+// mecefo_set_option("tile", ...) forces 1: 128 x 128, 2 and 3: 256 x 256 register-staged with four or
+// eight waves, 4: 256 x 256 direct-to-LDS; otherwise the model decides.
 template <bool AKC, bool BKC, int EPI>
 hipError_t run_bf16_auto(GemmLaunch& g, hipStream_t stream) {
-  switch (bf16_tile_choice(g)) {
-    case 1: return run_bf16<CfgL4, AKC, BKC, EPI>(g, stream);
-    case 2: return run_bf16<CfgL8, AKC, BKC, EPI>(g, stream);
-    case 3: return run_bf16<CfgL8, AKC, BKC, EPI, PipeA>(g, stream);
-    default: return run_bf16<CfgS, AKC, BKC, EPI>(g, stream);
+  int c;
+  switch (options().tile.load(std::memory_order_relaxed)) {
+    case 1: c = TILE_M2; break;
+    case 2: return run_bf16<CfgL4, AKC, BKC, EPI>(g, stream);
+    case 3: return run_bf16<CfgL8, AKC, BKC, EPI>(g, stream);
+    case 4: c = TILE_L; break;
+    default: c = bf16_best_tile(g, EPI == EPI_SPLIT_F32 && g.splits > 1 ? g.splits : 1);
+  }
+  switch (c) {
+    case TILE_M2: return run_bf16<CfgM, AKC, BKC, EPI, PipeM2>(g, stream);
+    case TILE_M4: return run_bf16<CfgM, AKC, BKC, EPI, PipeM4>(g, stream);
+    case TILE_T: return run_bf16<CfgT, AKC, BKC, EPI, PipeT>(g, stream);
+    default:
+      if (bf16_ragged(g)) return run_bf16<CfgL8, AKC, BKC, EPI, PipeL, AKC || BKC>(g, stream);
+      return run_bf16<CfgL8, AKC, BKC, EPI, PipeL, false>(g, stream);
   }
 }
 

@@ -61,7 +61,6 @@ struct GemmLaunch {
   int splits;       // EPI_SPLIT_F32: number of K splits (partials laid out [split][M x ldc] per problem)
   float* partial;   // EPI_SPLIT_F32: base of the partial buffer; problem i starts at partial_off[i]
   int64_t partial_off[3];
-  bool force_large; // bf16: use the 256 x 256 direct-to-LDS configuration even for few tiles (split launches)
   uint32_t* clk;    // measurement: 64 (cycles, wall ticks) pairs written by the direct-to-LDS kernel, or NULL
 };
 
@@ -87,8 +86,8 @@ struct LdsLimitOnce {
 
 // Process-wide switches behind mecefo_set_option (tests and measurements; 0 = the library decides).
 struct Options {
-  std::atomic<int> tile{0};        // bf16 GEMM configuration: 1 = 128x128, 2 = 256x256 / 4 waves, 3 = 256x256 / 8 waves
-                                   // register-staged, 4 = 256x256 / 8 waves direct-to-LDS
+  std::atomic<int> tile{0};        // bf16 GEMM configuration: 1 = 128x128 direct-to-LDS, 2 = 256x256 / 4 waves and
+                                   // 3 = 256x256 / 8 waves register-staged, 4 = 256x256 direct-to-LDS
   std::atomic<int> attn_gemm{0};   // 1: attention through batched GEMM launches instead of the fused kernels
 };
 Options& options();

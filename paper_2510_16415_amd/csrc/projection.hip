@@ -9,6 +9,7 @@
 #include <string.h>
 
 #include "../../include/mecefo.h"
+#include "gemm_bf16_launch.hip.h"
 #include "mecefo_internal.h"
 
 namespace mecefo {
@@ -150,18 +151,14 @@ GemmLaunch product(const Plan& pl, bool akc, bool bkc, const void* A_hi, const v
   return g;
 }
 
-// Products with fewer than 160 tiles of 256 x 256 and a long contraction are cut along K so that
-// every CU gets a block; the fp32 partials are then summed in a fixed order.
+// Products with few output tiles and a long contraction are cut along K when that pays for summing the
+// fp32 partials (in a fixed order), into no more parts than the plan's partial buffer holds.
 hipError_t run_product(const Plan& pl, char* base, GemmLaunch& g, hipStream_t s) {
   GemmProblem& p = g.p[0];
-  const int tiles = ((p.M + 255) / 256) * ((p.N + 255) / 256);
-  const int stages = ((p.K + 63) / 64) * p.nseg;
   int splits = 1;
-  if (pl.bf16 && !g.accumulate && tiles < 160 && stages >= 64) {
-    splits = (256 + tiles - 1) / tiles;
-    if (splits > stages / 8) splits = stages / 8;
-    if (splits > kMaxSplits) splits = kMaxSplits;
-    while (splits > 1 && (int64_t)splits * p.M * p.ldc * 4 > (int64_t)kMaxSplits * (pl.dim > pl.other ? pl.dim : pl.other) * pl.ldx * 4) --splits;
+  if (pl.bf16 && !g.accumulate) {
+    const int64_t most = (int64_t)kMaxSplits * (pl.dim > pl.other ? pl.dim : pl.other) * pl.ldx / ((int64_t)p.M * p.ldc);
+    splits = bf16_plan_splits(g, most < 16 ? (int)most : 16);
   }
   if (splits <= 1) return launch_gemm(g, s);
   float* C = (float*)p.C[0];
@@ -169,7 +166,6 @@ hipError_t run_product(const Plan& pl, char* base, GemmLaunch& g, hipStream_t s)
   g.splits = splits;
   g.partial = (float*)(base + pl.partial);
   g.partial_off[0] = 0;
-  g.force_large = true;
   hipError_t e = launch_gemm(g, s);
   if (e != hipSuccess) return e;
   return launch_splitk_reduce(false, g.partial, splits, (int64_t)p.M * p.ldc, C, s);

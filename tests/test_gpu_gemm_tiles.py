@@ -1,0 +1,74 @@
+"""The tile configurations of the bf16 GEMM core behind its size rule, through the public FFN calls: sizes for
+which the rule takes 64 x 64, 128 x 128 (two and four LDS stages) and 256 x 256 tiles, with rows, columns and
+contractions that end inside a tile, inside a 16-byte chunk of K (with NaN behind it), or just past an edge."""
+import pytest
+import torch
+
+from paper_2510_16415_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def padded(rows, cols, std, gen):
+    """[rows x cols] bf16 values in rows of a multiple of eight elements, NaN behind the columns."""
+    t = torch.full((rows, (cols + 7) // 8 * 8), float("nan"), dtype=torch.bfloat16, device="cuda")
+    t[:, :cols] = (torch.randn(rows, cols, generator=gen, device="cuda") * std).to(torch.bfloat16)
+    return t
+
+
+def relerr(got, want):
+    return float((got.double() - want.double()).norm() / want.double().norm())
+
+
+# (tokens, d, f): edges of the 64, 128 and 256 tiles and one past them; then one larger size per configuration
+SIZES = [(1, 8, 1), (63, 64, 65), (64, 72, 7), (129, 128, 63), (255, 136, 257), (257, 264, 129),
+         (700, 1000, 1111),      # 64 x 64, several workgroups per CU
+         (3000, 2504, 1107),     # 128 x 128, two per CU
+         (2048, 1536, 2741),     # 128 x 128, long K, one per CU
+         (4100, 4096, 1037)]     # 256 x 256
+
+
+@pytest.mark.parametrize("b,d,f", SIZES)
+def test_forward_products_with_a_ragged_contraction(b, d, f):
+    """A = silu(U Wg^T) * (U Wu^T) and Y = A Wd^T: both operands K-contiguous, K = f ends anywhere.  Error: one
+    bf16 rounding of A, one of Y (2^-9 each) and the fp32 sums: the gate of 1e-2 leaves a factor of two."""
+    gen = torch.Generator(device="cuda").manual_seed(b * 7 + f)
+    U = padded(b, d, 1.0, gen)
+    Wg, Wu, Wd = padded(f, d, d ** -0.5, gen), padded(f, d, d ** -0.5, gen), padded(d, f, f ** -0.5, gen)
+    ldf = Wd.shape[1]
+    desc = B.make_desc(b, d, f, B.BF16, B.F32, d, ldf, d, ldf, 1e-6)
+    A = torch.full((b, ldf), float("nan"), dtype=torch.bfloat16, device="cuda")
+    Y = torch.full((b, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    B.mecefo_ffn_fwd_recompute(desc, U, Wg, Wu, Wd, None, None, A, Y)
+    torch.cuda.synchronize()
+    g, z = U.float() @ Wg.float().T, U.float() @ Wu.float().T
+    want = torch.nn.functional.silu(g) * z
+    assert relerr(A[:, :f].float(), want) <= 1e-2
+    assert bool((A[:, f:] == 0).all())
+    assert relerr(Y.float(), A[:, :f].float() @ Wd[:, :f].float().T) <= 1e-2
+
+
+@pytest.mark.parametrize("b,d,f", SIZES)
+def test_exact_backward_products(b, d, f):
+    """dA (K-strided B), the fused SwiGLU backward, dU (two K segments) and the three weight gradients (both
+    operands K-strided) against the same steps in fp32 torch.  The library keeps dA, dG, dZ and A in bf16: 2^-9
+    per rounding, at most three in a row, below 1e-2 in the norm."""
+    gen = torch.Generator(device="cuda").manual_seed(b + 13 * f)
+    U, dY = padded(b, d, 1.0, gen), padded(b, d, 1.0, gen)
+    Wg, Wu, Wd = padded(f, d, d ** -0.5, gen), padded(f, d, d ** -0.5, gen), padded(d, f, f ** -0.5, gen)
+    ldf = Wd.shape[1]
+    desc = B.make_desc(b, d, f, B.BF16, B.F32, d, ldf, d, ldf, 1e-6)
+    ws = torch.full((B.mecefo_workspace_bytes(desc, 0, 0, 0),), 255, dtype=torch.uint8, device="cuda")
+    dU = torch.full((b, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    dWg, dWu = (torch.full((f, d), float("nan"), device="cuda") for _ in range(2))
+    dWd = torch.full((d, ldf), float("nan"), device="cuda")
+    B.mecefo_ffn_bwd_exact(desc, U, dY, Wg, Wu, Wd, None, None, dU, dWg, dWu, dWd, 0, ws)
+    torch.cuda.synchronize()
+    u, dy, wg, wu, wd = U.float(), dY.float(), Wg.float(), Wu.float(), Wd[:, :f].float()
+    g, z, da = u @ wg.T, u @ wu.T, dy @ wd
+    sg = torch.sigmoid(g)
+    dg, dz, a = da * z * sg * (1 + g * (1 - sg)), da * g * sg, g * sg * z
+    assert relerr(dU.float(), dg @ wg + dz @ wu) <= 1e-2
+    assert relerr(dWg, dg.T @ u) <= 1e-2
+    assert relerr(dWu, dz.T @ u) <= 1e-2
+    assert relerr(dWd[:, :f], dy.T @ a) <= 1e-2
