@@ -8,7 +8,8 @@ namespace mecefo {
 
 using CfgL4 = TileCfg<256, 256, 2, 2>;   // register staging, forced by the "tile" option only
 using CfgL8 = TileCfg<256, 256, 4, 2>;   // 8 waves x (64 x 128): two waves per SIMD hide latency
-using CfgM = TileCfg<128, 128, 4, 2>;    // 8 waves x (32 x 64): two workgroups per CU
+using CfgM = TileCfg<128, 128, 2, 2>;    // 4 waves x (64 x 64): two workgroups per CU
+using CfgM8 = TileCfg<128, 128, 4, 2>;   // 8 waves x (32 x 64): one workgroup per CU
 using CfgT = TileCfg<64, 64, 2, 2>;      // 4 waves x (32 x 32): three workgroups per CU
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
@@ -21,8 +22,8 @@ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 // fills plus fragment reads and MFMA issue are both near a stage's length, and on Gaussian operands
 // the matrix cores are power-limited.
 using PipeL = DtlPipe<CfgL8, 2>;
-using PipeM2 = DtlPipe<CfgM, 2>;   // 74 KiB: two workgroups per CU cover each other's waits
-using PipeM4 = DtlPipe<CfgM, 4>;   // 128 KiB: one workgroup per CU, three stages in flight
+using PipeM2 = DtlPipe<CfgM, 2>;   // 64 KiB: two workgroups per CU cover each other's waits
+using PipeM4 = DtlPipe<CfgM8, 4>;   // 128 KiB: one workgroup per CU, three stages in flight
 using PipeT = DtlPipe<CfgT, 3>;    // 48 KiB
 
 // ---- choice of the tile ------------------------------------------------------------------------
@@ -44,8 +45,8 @@ enum TileConfig : int { TILE_L = 0, TILE_M2 = 1, TILE_M4 = 2, TILE_T = 3, TILE_C
 struct TileModel { int bm, bn, slots; float fixed, per_round, stage_alone, stage_shared; };
 inline const TileModel& tile_model(int c) {
   static const TileModel m[TILE_COUNT] = {{256, 256, 1, 3.5f, 2.5f, 1.45f, 1.75f},
-                                          {128, 128, 2, 3.0f, 1.2f, 0.78f, 0.62f},
-                                          {128, 128, 1, 3.0f, 1.2f, 0.70f, 0.72f},
+                                          {128, 128, 2, 3.0f, 1.2f, 0.88f, 0.62f},
+                                          {128, 128, 1, 4.5f, 1.2f, 0.70f, 0.72f},
                                           {64, 64, 3, 2.5f, 0.5f, 0.44f, 0.28f}};
   return m[c];
 }
@@ -171,7 +172,7 @@ hipError_t prepare_bf16() {
   hipError_t e = Bf16Kernel<CfgL8, AKC, BKC, EPI, PipeL, false>::prepare();
   if (e == hipSuccess && (AKC || BKC)) e = Bf16Kernel<CfgL8, AKC, BKC, EPI, PipeL, AKC || BKC>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgM, AKC, BKC, EPI, PipeM2, true>::prepare();
-  if (e == hipSuccess) e = Bf16Kernel<CfgM, AKC, BKC, EPI, PipeM4, true>::prepare();
+  if (e == hipSuccess) e = Bf16Kernel<CfgM8, AKC, BKC, EPI, PipeM4, true>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgT, AKC, BKC, EPI, PipeT, true>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgL4, AKC, BKC, EPI, NoPipe, true>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgL8, AKC, BKC, EPI, NoPipe, true>::prepare();
@@ -192,7 +193,7 @@ hipError_t run_bf16_auto(GemmLaunch& g, hipStream_t stream) {
   }
   switch (c) {
     case TILE_M2: return run_bf16<CfgM, AKC, BKC, EPI, PipeM2>(g, stream);
-    case TILE_M4: return run_bf16<CfgM, AKC, BKC, EPI, PipeM4>(g, stream);
+    case TILE_M4: return run_bf16<CfgM8, AKC, BKC, EPI, PipeM4>(g, stream);
     case TILE_T: return run_bf16<CfgT, AKC, BKC, EPI, PipeT>(g, stream);
     default:
       if (bf16_ragged(g)) return run_bf16<CfgL8, AKC, BKC, EPI, PipeL, AKC || BKC>(g, stream);
