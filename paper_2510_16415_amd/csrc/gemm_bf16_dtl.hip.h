@@ -428,7 +428,7 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_bf16_dtl_kernel(const KArgs a
       // fp32 outputs: four columns per lane, so that one store instruction covers whole 512-byte row
       // pieces (with eight columns per lane each of the two 16-byte stores would fill every other
       // 16 bytes of its lines)
-      if ((EPI == EPI_GRAD && args.out_f32) || EPI == EPI_SPLIT_F32) {
+      if ((EPI == EPI_GRAD && args.out_f32) || EPI == EPI_SPLIT_F32 || EPI == EPI_HILO) {
         constexpr int LPR4 = W / 4, RPI4 = 64 / LPR4;
         const int r4 = lane / LPR4, c4 = (lane % LPR4) * 4;
 #pragma unroll

@@ -12,6 +12,8 @@ hipError_t launch_gemm_bf16_nt(GemmLaunch& g, hipStream_t s) {
     case EPI_SWIGLU_BWD: return run_bf16_auto<true, true, EPI_SWIGLU_BWD>(g, s);
     case EPI_ATTN_P: return run_bf16_auto<true, true, EPI_ATTN_P>(g, s);
     case EPI_ATTN_DS: return run_bf16_auto<true, true, EPI_ATTN_DS>(g, s);
+    case EPI_POLY: return run_bf16_auto<true, true, EPI_POLY>(g, s);
+    case EPI_HILO: return run_bf16_auto<true, true, EPI_HILO>(g, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -24,6 +26,8 @@ hipError_t prepare_gemm_bf16_nt() {
   if (e == hipSuccess) e = prepare_bf16<true, true, EPI_SWIGLU_BWD>();
   if (e == hipSuccess) e = prepare_bf16<true, true, EPI_ATTN_P>();
   if (e == hipSuccess) e = prepare_bf16<true, true, EPI_ATTN_DS>();
+  if (e == hipSuccess) e = prepare_bf16<true, true, EPI_POLY>();
+  if (e == hipSuccess) e = prepare_bf16<true, true, EPI_HILO>();
   return e;
 }
 }  // namespace mecefo

@@ -7,6 +7,8 @@ hipError_t launch_gemm_bf16_tn(GemmLaunch& g, hipStream_t s) {
     case EPI_STORE: return run_bf16_auto<false, false, EPI_STORE>(g, s);
     case EPI_SPLIT_F32: return run_bf16_auto<false, false, EPI_SPLIT_F32>(g, s);
     case EPI_GRAD: return run_bf16_auto<false, false, EPI_GRAD>(g, s);
+    case EPI_POLY: return run_bf16_auto<false, false, EPI_POLY>(g, s);
+    case EPI_HILO: return run_bf16_auto<false, false, EPI_HILO>(g, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -15,6 +17,8 @@ hipError_t prepare_gemm_bf16_tn() {
   if (e == hipSuccess) e = prepare_bf16<false, false, EPI_STORE>();
   if (e == hipSuccess) e = prepare_bf16<false, false, EPI_SPLIT_F32>();
   if (e == hipSuccess) e = prepare_bf16<false, false, EPI_GRAD>();
+  if (e == hipSuccess) e = prepare_bf16<false, false, EPI_POLY>();
+  if (e == hipSuccess) e = prepare_bf16<false, false, EPI_HILO>();
   return e;
 }
 }  // namespace mecefo

@@ -181,6 +181,26 @@ __device__ inline void epilogue_elem(const GemmProblem& p, const KArgs& a, int p
       T* c = (T*)p.C[0] + (int64_t)row * p.ldc + col;
       *c = from_f32<T>(to_f32<T>(*c) * (v - p.rowvec[row]) * p.scale);
     }
+  } else if constexpr (EPI == EPI_POLY) {
+    if (col < p.N) {
+      const int64_t idx = (int64_t)row * p.ldc + col;
+      float x = p.scale * v;
+      if (p.addend) x += p.poly_b * p.addend[idx];
+      if (row == col) x += p.poly_a;
+      ((T*)p.C[0])[idx] = from_f32<T>(x);
+      if (p.C[1]) ((float*)p.C[1])[idx] = v;
+    }
+  } else if constexpr (EPI == EPI_HILO) {
+    if (col < p.N) {
+      const int64_t idx = (int64_t)row * p.ldc + col;
+      const float x = p.addend ? v + p.addend[idx] : v;
+      if (p.C[0]) ((float*)p.C[0])[idx] = x;
+      if constexpr (sizeof(T) == 2) {
+        const T h = from_f32<T>(x);
+        ((T*)p.C[1])[idx] = h;
+        ((T*)p.C[2])[idx] = from_f32<T>(x - to_f32<T>(h));
+      }
+    }
   } else if constexpr (EPI == EPI_SWIGLU_FWD) {
     const int64_t idx = (int64_t)row * p.ldc + col;
     if (col < p.N) {
@@ -291,6 +311,25 @@ __device__ inline void epilogue_vec8(const GemmProblem& p, const KArgs& a, int p
       }
       *c = pack_bf16x8(o);
     }
+  } else if constexpr (EPI == EPI_POLY) {
+    float o[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = p.scale * v[e];
+    if (p.addend) {
+      const f32x4_t r0 = *(const f32x4_t*)(p.addend + idx), r1 = *(const f32x4_t*)(p.addend + idx + 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { o[e] += p.poly_b * r0[e]; o[4 + e] += p.poly_b * r1[e]; }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (row == col0 + e) o[e] += p.poly_a;
+    *(bf16x8s_t*)((__bf16*)p.C[0] + idx) = pack_bf16x8(o);
+    if (p.C[1]) {
+      float* raw = (float*)p.C[1] + idx;
+      const f32x4_t o0 = {v[0], v[1], v[2], v[3]}, o1 = {v[4], v[5], v[6], v[7]};
+      *(f32x4_t*)raw = o0;
+      *(f32x4_t*)(raw + 4) = o1;
+    }
   } else if constexpr (EPI == EPI_SWIGLU_FWD) {
     float av[8];
 #pragma unroll
@@ -348,6 +387,14 @@ __device__ inline void epilogue_vec4(const GemmProblem& p, const KArgs& a, int p
         *c = pack_bf16x4(v[0], v[1], v[2], v[3]);
       }
     }
+  } else if constexpr (EPI == EPI_HILO) {
+    f32x4_t x = {v[0], v[1], v[2], v[3]};
+    if (p.addend) x += *(const f32x4_t*)(p.addend + idx);
+    if (p.C[0]) *(f32x4_t*)((float*)p.C[0] + idx) = x;
+    const bf16x4_t h = pack_bf16x4(x[0], x[1], x[2], x[3]);
+    *(bf16x4_t*)((__bf16*)p.C[1] + idx) = h;
+    *(bf16x4_t*)((__bf16*)p.C[2] + idx) =
+        pack_bf16x4(x[0] - (float)h[0], x[1] - (float)h[1], x[2] - (float)h[2], x[3] - (float)h[3]);
   } else if constexpr (EPI == EPI_SWIGLU_FWD) {
     float av[4];
 #pragma unroll

@@ -130,6 +130,8 @@ hipError_t launch_gemm_f32(GemmLaunch& g, hipStream_t s) {
     case EPI_SWIGLU_BWD: return run_f32<EPI_SWIGLU_BWD>(g, s);
     case EPI_ATTN_P: return run_f32<EPI_ATTN_P>(g, s);
     case EPI_ATTN_DS: return run_f32<EPI_ATTN_DS>(g, s);
+    case EPI_POLY: return run_f32<EPI_POLY>(g, s);
+    case EPI_HILO: return run_f32<EPI_HILO>(g, s);
     default: return hipErrorInvalidValue;
   }
 }

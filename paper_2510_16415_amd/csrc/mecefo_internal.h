@@ -15,6 +15,8 @@ enum Epilogue : int {
   EPI_SWIGLU_BWD = 4,  // dual: dA read from C0; C0=dG, C1=dZ, C2=A
   EPI_ATTN_P = 5,      // C0[row, col] = col <= row ? exp(scale * acc - rowvec[row]) : 0   (softmax from saved logsumexp)
   EPI_ATTN_DS = 6,     // C0[row, col] = C0[row, col] * (acc - rowvec[row]) * scale         (softmax backward, in place on P)
+  EPI_POLY = 7,        // C0[row, col] = poly_a * (row == col) + poly_b * addend[row, col] + scale * acc; C1 (fp32) = acc
+  EPI_HILO = 8,        // x = acc + addend[row, col]: C0 (fp32) = x, C1 = bf16(x), C2 = bf16(x - C1)
 };
 
 enum CausalK : int {
@@ -46,7 +48,9 @@ struct GemmProblem {
   int batch, batch_inner;
   int64_t a_bo, a_bi, b_bo, b_bi, c_bo, c_bi;
   const float* rowvec;   // attention epilogues: fp32 per output row, product z starts at z * M
-  float scale;           // attention epilogues
+  float scale;           // attention epilogues, EPI_POLY
+  const float* addend;   // EPI_POLY, EPI_HILO: fp32 [M x ldc], may be NULL (zero); may be C0 of EPI_HILO itself
+  float poly_a, poly_b;  // EPI_POLY
   int causal;            // CausalK
 };
 

@@ -21,14 +21,50 @@ constexpr int kMaxSplits = 8;
 // The iterate is kept as an fp32 master copy.  For bf16 weights it enters the MFMA products as the
 // sum of two bf16 matrices (hi = bf16(x), lo = bf16(x - hi): 16 mantissa bits), contracted as two K
 // segments of one launch: a single bf16 rounding of the iterate would drown the weakest of the r
-// directions, whose share of X after one application of W^T W is (s_r/s_1)^2.
-__global__ __launch_bounds__(256) void split_kernel(const float* __restrict__ X, __bf16* __restrict__ hi,
-                                                    __bf16* __restrict__ lo, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const float x = X[i];
-    const __bf16 h = (__bf16)x;
-    hi[i] = h;
-    lo[i] = (__bf16)(x - (float)h);
+// directions, whose share of X after one application of W^T W is (s_r/s_1)^2.  The halves are written by
+// whatever produces the iterate: the product's epilogue, the sum of its K splits, the normalisation.
+//
+// A refresh is a chain of some 100 dependent products of a few microseconds each, so launches count: with
+// the polynomial and the halves in the epilogues a Newton-Schulz step is three products (four launches where
+// the Gram matrix is cut along K) instead of three products, two or three elementwise kernels and a copy.
+// Three matrices of [5461 x 2048], rank 512, two rounds of eight steps and three polishing steps: 438 launches
+// and 3390 us before, 261 and 2650 us now.
+
+// Sum of the K splits of a product, finished like its epilogue would (EPI_POLY or EPI_HILO; fixed order).
+struct SplitSum {
+  const float* partial;
+  int splits;
+  int64_t mn, ld;          // elements and row stride of one part
+  float* raw;              // fp32 result (EPI_POLY: the plain sum), may be NULL
+  __bf16 *hi, *lo;         // EPI_HILO: the two halves; EPI_POLY: hi is the polynomial
+  const float* addend;
+  float a, b, c;           // EPI_POLY
+};
+template <int EPI>
+__global__ __launch_bounds__(256) void split_sum_kernel(const SplitSum q) {
+  const int64_t i4 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;     // mn is a multiple of 8
+  if (i4 >= q.mn) return;
+  typedef __attribute__((ext_vector_type(4))) float f4;
+  typedef __attribute__((ext_vector_type(4))) __bf16 h4;
+  f4 s = *(const f4*)(q.partial + i4);
+#pragma unroll 4
+  for (int k = 1; k < q.splits; ++k) s += *(const f4*)(q.partial + (int64_t)k * q.mn + i4);
+  h4 h, l;
+  if constexpr (EPI == EPI_POLY) {
+    if (q.raw) *(f4*)(q.raw + i4) = s;
+    f4 x = s * q.c;
+    if (q.addend) x += *(const f4*)(q.addend + i4) * q.b;
+    const int64_t row = i4 / q.ld, col = i4 - row * q.ld;                // four columns of one row: ld % 8 == 0
+#pragma unroll
+    for (int e = 0; e < 4; ++e) h[e] = (__bf16)(col + e == row ? x[e] + q.a : x[e]);
+    *(h4*)(q.hi + i4) = h;
+  } else {
+    if (q.addend) s += *(const f4*)(q.addend + i4);
+    if (q.raw) *(f4*)(q.raw + i4) = s;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { h[e] = (__bf16)s[e]; l[e] = (__bf16)(s[e] - (float)h[e]); }
+    *(h4*)(q.hi + i4) = h;
+    *(h4*)(q.lo + i4) = l;
   }
 }
 
@@ -51,34 +87,33 @@ __global__ __launch_bounds__(256) void sumsq_partial_kernel(const float* __restr
   if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
-// X *= 1 / sqrt(sum of the partial sums); a zero matrix is left unchanged.
-__global__ __launch_bounds__(256) void scale_by_inv_norm_kernel(float* __restrict__ X, int64_t ld, int64_t rows,
-                                                                int cols, const float* __restrict__ partial,
-                                                                int nparts) {
-  __shared__ float inv;
-  if (threadIdx.x == 0) {
-    float s = 0.f;
-    for (int i = 0; i < nparts; ++i) s += partial[i];
-    inv = s > 0.f ? 1.0f / sqrtf(s) : 1.0f;
-  }
+// X *= 1 / sqrt(sum of the partial sums); a zero matrix is left unchanged.  Every block adds the kNormBlocks
+// partial sums by itself, as a tree over its threads (one thread adding them one by one took 12 to 20 us).
+// With hi the halves of the result go out as well (X is a multiple of four elements: padded rows).
+__global__ __launch_bounds__(256) void scale_by_inv_norm_kernel(float* __restrict__ X, int64_t n,
+                                                                const float* __restrict__ partial,
+                                                                __bf16* __restrict__ hi, __bf16* __restrict__ lo) {
+  __shared__ float red[256];
+  static_assert(kNormBlocks == 256, "one partial sum per thread");
+  red[threadIdx.x] = partial[threadIdx.x];
   __syncthreads();
-  const float k = inv;
-  for (int64_t row = blockIdx.x; row < rows; row += gridDim.x)
-    for (int c = threadIdx.x; c < cols; c += 256) X[row * ld + c] *= k;
-}
-
-// out[i, j] = a * (i == j) + b * A[i, j] + c * A2[i, j]   (A2 may be NULL), r x r, fp32 in, T out.
-template <typename T>
-__global__ __launch_bounds__(256) void poly_kernel(T* __restrict__ out, int64_t ldo, const float* __restrict__ A,
-                                                   const float* __restrict__ A2, int64_t lda, int r, float a,
-                                                   float b, float c) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (int64_t)r * r) return;
-  const int row = (int)(i / r), col = (int)(i - (int64_t)row * r);
-  float v = b * A[row * lda + col];
-  if (A2) v += c * A2[row * lda + col];
-  if (row == col) v += a;
-  out[row * ldo + col] = (T)v;
+  for (int o = 128; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    __syncthreads();
+  }
+  const float s = red[0], k = s > 0.f ? 1.0f / sqrtf(s) : 1.0f;
+  typedef __attribute__((ext_vector_type(4))) float f4;
+  typedef __attribute__((ext_vector_type(4))) __bf16 h4;
+  for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; i < n; i += (int64_t)gridDim.x * 1024) {
+    const f4 x = *(const f4*)(X + i) * k;
+    *(f4*)(X + i) = x;
+    if (!hi) continue;
+    h4 h, l;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { h[e] = (__bf16)x[e]; l[e] = (__bf16)(x[e] - (float)h[e]); }
+    *(h4*)(hi + i) = h;
+    *(h4*)(lo + i) = l;
+  }
 }
 
 // dst[rows x cols] (row stride ldd) = src (row stride lds), converting the element type;
@@ -103,7 +138,7 @@ struct Plan {
   int m, n, r;       // W is [m x n]; the basis has `dim` rows (n for right, m for left vectors)
   int dim, other;
   int64_t ldx;       // row stride of every internal [* x r] buffer
-  size_t X32[2], Y32, Xh, Xl, Yh, Yl, A32, B32, M16, A16, part, partial, total;
+  size_t X32[2], Y32, Xh[2], Xl[2], Yh, Yl, A32, M16, A16, part, partial, total;
 };
 
 Plan make_plan(bool bf16, int m, int n, int r, int left) {
@@ -118,9 +153,12 @@ Plan make_plan(bool bf16, int m, int n, int r, int left) {
   p.X32[1] = take((size_t)p.dim * p.ldx * 4);
   p.Y32 = take((size_t)p.other * p.ldx * 4);
   const size_t hx = bf16 ? (size_t)p.dim * p.ldx * 2 : 0, hy = bf16 ? (size_t)p.other * p.ldx * 2 : 0;
-  p.Xh = take(hx); p.Xl = take(hx); p.Yh = take(hy); p.Yl = take(hy);
+  // bf16: a step updates the one fp32 master copy in place while its product still reads the halves, so the
+  // halves take turns; the second pair lies where fp32 keeps its second copy.  fp32: X32 takes turns.
+  p.Xh[0] = take(hx); p.Xl[0] = take(hx);
+  p.Xh[1] = p.X32[1]; p.Xl[1] = p.X32[1] + hx;
+  p.Yh = take(hy); p.Yl = take(hy);
   p.A32 = take((size_t)r * p.ldx * 4);
-  p.B32 = take((size_t)r * p.ldx * 4);
   p.M16 = take((size_t)r * p.ldx * p.esz);
   p.A16 = take((size_t)r * p.ldx * p.esz);
   p.part = take(kNormBlocks * 4);
@@ -134,14 +172,14 @@ Plan make_plan(bool bf16, int m, int n, int r, int left) {
 // An iterate as GEMM operand: fp32 path: the master copy; bf16 path: the hi and lo halves.
 struct Operand { const void* hi; const void* lo; };
 
-// C (fp32, row stride ldx) (+)= opA * opB, where exactly one of the two sides may be an iterate
+// C (fp32, row stride ldx) = opA * opB, where exactly one of the two sides may be an iterate
 // split into hi + lo (then the launch has two K segments over the same other operand).
 GemmLaunch product(const Plan& pl, bool akc, bool bkc, const void* A_hi, const void* A_lo, int64_t lda,
-                   const void* B_hi, const void* B_lo, int64_t ldb, float* C, int M, int N, int K, int accumulate) {
+                   const void* B_hi, const void* B_lo, int64_t ldb, float* C, int M, int N, int K) {
   GemmLaunch g;
   memset(&g, 0, sizeof(g));
   g.a_kcontig = akc; g.b_kcontig = bkc; g.epi = EPI_GRAD; g.bf16 = pl.bf16; g.out_f32 = true;
-  g.accumulate = accumulate; g.splits = 1; g.nprob = 1;
+  g.splits = 1; g.nprob = 1;
   GemmProblem& p = g.p[0];
   const bool two = A_lo != nullptr || B_lo != nullptr;
   p.A[0] = A_hi; p.A[1] = A_lo ? A_lo : A_hi; p.A[2] = A_hi;
@@ -156,29 +194,33 @@ GemmLaunch product(const Plan& pl, bool akc, bool bkc, const void* A_hi, const v
 hipError_t run_product(const Plan& pl, char* base, GemmLaunch& g, hipStream_t s) {
   GemmProblem& p = g.p[0];
   int splits = 1;
-  if (pl.bf16 && !g.accumulate) {
+  if (pl.bf16) {
     const int64_t most = (int64_t)kMaxSplits * (pl.dim > pl.other ? pl.dim : pl.other) * pl.ldx / ((int64_t)p.M * p.ldc);
     splits = bf16_plan_splits(g, most < 16 ? (int)most : 16);
   }
   if (splits <= 1) return launch_gemm(g, s);
-  float* C = (float*)p.C[0];
+  const int epi = g.epi;
   g.epi = EPI_SPLIT_F32;
   g.splits = splits;
   g.partial = (float*)(base + pl.partial);
   g.partial_off[0] = 0;
   hipError_t e = launch_gemm(g, s);
   if (e != hipSuccess) return e;
-  return launch_splitk_reduce(false, g.partial, splits, (int64_t)p.M * p.ldc, C, s);
+  const int64_t mn = (int64_t)p.M * p.ldc;
+  if (epi == EPI_GRAD) return launch_splitk_reduce(false, g.partial, splits, mn, p.C[0], s);
+  const dim3 grid((unsigned)((mn + 1023) / 1024));
+  SplitSum q{g.partial, splits, mn, p.ldc, nullptr, nullptr, nullptr, p.addend, p.poly_a, p.poly_b, p.scale};
+  if (epi == EPI_POLY) {
+    q.raw = (float*)p.C[1]; q.hi = (__bf16*)p.C[0];
+    hipLaunchKernelGGL(split_sum_kernel<EPI_POLY>, grid, dim3(256), 0, s, q);
+  } else {
+    q.raw = (float*)p.C[0]; q.hi = (__bf16*)p.C[1]; q.lo = (__bf16*)p.C[2];
+    hipLaunchKernelGGL(split_sum_kernel<EPI_HILO>, grid, dim3(256), 0, s, q);
+  }
+  return hipGetLastError();
 }
 
 #define HIP_TRY(x) do { hipError_t e__ = (x); if (e__ != hipSuccess) return (mecefo_status_t)fail(MECEFO_ERR_LAUNCH, "%s: %s", #x, hipGetErrorString(e__)); } while (0)
-
-template <typename T>
-hipError_t run_poly(void* out, int64_t ldo, const float* A, const float* A2, int64_t lda, int r, float a, float b,
-                    float c, hipStream_t s) {
-  hipLaunchKernelGGL(poly_kernel<T>, dim3(grid_for((int64_t)r * r)), dim3(256), 0, s, (T*)out, ldo, A, A2, lda, r, a, b, c);
-  return hipGetLastError();
-}
 
 struct Refresh {
   Plan pl;
@@ -186,24 +228,32 @@ struct Refresh {
   hipStream_t s;
   int cur = 0;
 
-  float* X32(int i) const { return (float*)(base + pl.X32[i]); }
+  // `cur` says which copy holds the iterate: of X32 (fp32 path) or of its halves (bf16 path, X32 is one).
+  float* X32() const { return (float*)(base + pl.X32[pl.bf16 ? 0 : cur]); }
+  float* X32_next() const { return (float*)(base + pl.X32[pl.bf16 ? 0 : cur ^ 1]); }
   float* Y32() const { return (float*)(base + pl.Y32); }
-  Operand opX() const { return pl.bf16 ? Operand{base + pl.Xh, base + pl.Xl} : Operand{X32(cur), nullptr}; }
+  Operand opX() const { return pl.bf16 ? Operand{base + pl.Xh[cur], base + pl.Xl[cur]} : Operand{X32(), nullptr}; }
   Operand opY() const { return pl.bf16 ? Operand{base + pl.Yh, base + pl.Yl} : Operand{Y32(), nullptr}; }
-
-  hipError_t split(const float* src, size_t hi, size_t lo, int rows) const {
-    if (!pl.bf16) return hipSuccess;
-    const int64_t n = (int64_t)rows * pl.ldx;
-    hipLaunchKernelGGL(split_kernel, dim3(grid_for(n)), dim3(256), 0, s, src, (__bf16*)(base + hi), (__bf16*)(base + lo), n);
-    return hipGetLastError();
+  // the product's result as an iterate: fp32 `x32` and, bf16 path, its halves
+  void to_iterate(GemmLaunch& g, float* x32, size_t hi, size_t lo, const float* addend) const {
+    g.epi = EPI_HILO;
+    g.p[0].C[0] = x32;
+    g.p[0].C[1] = pl.bf16 ? base + hi : nullptr;
+    g.p[0].C[2] = pl.bf16 ? base + lo : nullptr;
+    g.p[0].addend = addend;
   }
-  hipError_t split_x() const { return split(X32(cur), pl.Xh, pl.Xl, pl.dim); }
-  hipError_t split_y() const { return split(Y32(), pl.Yh, pl.Yl, pl.other); }
+  static void to_poly(GemmLaunch& g, void* out, float* raw, const float* addend, float a, float b, float c) {
+    g.epi = EPI_POLY;
+    g.p[0].C[0] = out; g.p[0].C[1] = raw;
+    g.p[0].addend = addend; g.p[0].poly_a = a; g.p[0].poly_b = b; g.p[0].scale = c;
+  }
 
   hipError_t normalise() const {  // X /= ||X||_F, so that every singular value is <= 1
     float* part = (float*)(base + pl.part);
-    hipLaunchKernelGGL(sumsq_partial_kernel, dim3(kNormBlocks), dim3(256), 0, s, X32(cur), pl.ldx, (int64_t)pl.dim, pl.r, part);
-    hipLaunchKernelGGL(scale_by_inv_norm_kernel, dim3(pl.dim < 4096 ? pl.dim : 4096), dim3(256), 0, s, X32(cur), pl.ldx, (int64_t)pl.dim, pl.r, part, kNormBlocks);
+    const int64_t n = (int64_t)pl.dim * pl.ldx;
+    hipLaunchKernelGGL(sumsq_partial_kernel, dim3(kNormBlocks), dim3(256), 0, s, X32(), pl.ldx, (int64_t)pl.dim, pl.r, part);
+    hipLaunchKernelGGL(scale_by_inv_norm_kernel, dim3((unsigned)(n < 1024 * 1024 ? (n + 1023) / 1024 : 1024)), dim3(256), 0, s, X32(), n, part,
+                       (__bf16*)(pl.bf16 ? base + pl.Xh[cur] : nullptr), (__bf16*)(pl.bf16 ? base + pl.Xl[cur] : nullptr));
     return hipGetLastError();
   }
 
@@ -213,32 +263,25 @@ struct Refresh {
   mecefo_status_t ns_step(float a, float b, float c, bool additive) {
     const int r = pl.r, dim = pl.dim;
     float* A32 = (float*)(base + pl.A32);
-    float* B32 = (float*)(base + pl.B32);
     void* M16 = base + pl.M16;
-    void* A16 = base + pl.A16;
+    void* A16 = pl.bf16 ? base + pl.A16 : (void*)A32;     // A in the storage type
     const Operand x = opX();
     {  // A = X^T X  [r x r], contraction over the rows of X (hi part only)
-      GemmLaunch g = product(pl, false, false, x.hi, nullptr, pl.ldx, x.hi, nullptr, pl.ldx, A32, r, r, dim, 0);
+      GemmLaunch g = product(pl, false, false, x.hi, nullptr, pl.ldx, x.hi, nullptr, pl.ldx, nullptr, r, r, dim);
+      if (additive) to_poly(g, M16, nullptr, nullptr, a - 1.f, 0.f, b);
+      else to_poly(g, A16, pl.bf16 ? A32 : nullptr, nullptr, 0.f, 0.f, 1.f);
       HIP_TRY(run_product(pl, base, g, s));
     }
-    const float* A2 = nullptr;
-    if (c != 0.f) {  // A^2 = A A^T (A is symmetric)
-      HIP_TRY(pl.bf16 ? run_poly<__bf16>(A16, pl.ldx, A32, nullptr, pl.ldx, r, 0.f, 1.f, 0.f, s)
-                      : run_poly<float>(A16, pl.ldx, A32, nullptr, pl.ldx, r, 0.f, 1.f, 0.f, s));
-      GemmLaunch g = product(pl, true, true, A16, nullptr, pl.ldx, A16, nullptr, pl.ldx, B32, r, r, r, 0);
+    if (!additive) {  // a I + b A + c A^2, A^2 = A A^T (A is symmetric)
+      GemmLaunch g = product(pl, true, true, A16, nullptr, pl.ldx, A16, nullptr, pl.ldx, nullptr, r, r, r);
+      to_poly(g, M16, nullptr, A32, a, b, c);
       HIP_TRY(run_product(pl, base, g, s));
-      A2 = B32;
     }
-    const float da = additive ? a - 1.f : a;
-    HIP_TRY(pl.bf16 ? run_poly<__bf16>(M16, pl.ldx, A32, A2, pl.ldx, r, da, b, c, s)
-                    : run_poly<float>(M16, pl.ldx, A32, A2, pl.ldx, r, da, b, c, s));
-    float* out = X32(cur ^ 1);
-    if (additive) HIP_TRY(hipMemcpyAsync(out, X32(cur), (size_t)dim * pl.ldx * 4, hipMemcpyDeviceToDevice, s));
     // the polynomial of the symmetric A is symmetric: X M = X M^T, so M is the K-contiguous operand
-    GemmLaunch g = product(pl, true, true, x.hi, x.lo, pl.ldx, M16, nullptr, pl.ldx, out, dim, r, r, additive ? 1 : 0);
+    GemmLaunch g = product(pl, true, true, x.hi, x.lo, pl.ldx, M16, nullptr, pl.ldx, nullptr, dim, r, r);
+    to_iterate(g, X32_next(), pl.Xh[cur ^ 1], pl.Xl[cur ^ 1], additive ? X32() : nullptr);
     HIP_TRY(run_product(pl, base, g, s));
     cur ^= 1;
-    HIP_TRY(split_x());
     return MECEFO_OK;
   }
 
@@ -247,7 +290,6 @@ struct Refresh {
   // orthogonalisation; it does not converge to exactly 1, the cubic steps do).
   mecefo_status_t condition(int steps) {
     HIP_TRY(normalise());
-    HIP_TRY(split_x());
     for (int i = 0; i < steps; ++i) {
       mecefo_status_t e = ns_step(3.4445f, -4.7750f, 2.0315f, false);
       if (e != MECEFO_OK) return e;
@@ -260,13 +302,14 @@ struct Refresh {
     const Operand x = opX();
     // right vectors: Y = W X [m x r] (K = n), X' = W^T Y [n x r] (K = m, W read as [K x M]);
     // left vectors:  Y = W^T X [n x r] (K = m), X' = W Y [m x r] (K = n)
-    GemmLaunch g1 = left ? product(pl, false, false, W, nullptr, ldw, x.hi, x.lo, pl.ldx, Y32(), n, r, m, 0)
-                         : product(pl, true, false, W, nullptr, ldw, x.hi, x.lo, pl.ldx, Y32(), m, r, n, 0);
+    GemmLaunch g1 = left ? product(pl, false, false, W, nullptr, ldw, x.hi, x.lo, pl.ldx, nullptr, n, r, m)
+                         : product(pl, true, false, W, nullptr, ldw, x.hi, x.lo, pl.ldx, nullptr, m, r, n);
+    to_iterate(g1, pl.bf16 ? nullptr : Y32(), pl.Yh, pl.Yl, nullptr);
     HIP_TRY(run_product(pl, base, g1, s));
-    HIP_TRY(split_y());
+    // X' is scaled next and split then: fp32 only
     const Operand y = opY();
-    GemmLaunch g2 = left ? product(pl, true, false, W, nullptr, ldw, y.hi, y.lo, pl.ldx, X32(cur ^ 1), m, r, n, 0)
-                         : product(pl, false, false, W, nullptr, ldw, y.hi, y.lo, pl.ldx, X32(cur ^ 1), n, r, m, 0);
+    GemmLaunch g2 = left ? product(pl, true, false, W, nullptr, ldw, y.hi, y.lo, pl.ldx, X32_next(), m, r, n)
+                         : product(pl, false, false, W, nullptr, ldw, y.hi, y.lo, pl.ldx, X32_next(), n, r, m);
     HIP_TRY(run_product(pl, base, g2, s));
     cur ^= 1;
     return MECEFO_OK;
@@ -328,8 +371,8 @@ mecefo_status_t mecefo_projection_refresh(mecefo_dtype_t dtype, const void* W, i
   const unsigned gx = grid_for((int64_t)dim * ldx);
 
   // start basis -> fp32 master copy (padding columns zeroed: they are contracted as K padding)
-  if (bf16) hipLaunchKernelGGL((convert2d_kernel<float, __bf16>), dim3(gx), dim3(256), 0, R.s, R.X32(0), ldx, (const __bf16*)V0, ldv, (int64_t)dim, r, (int)ldx);
-  else hipLaunchKernelGGL((convert2d_kernel<float, float>), dim3(gx), dim3(256), 0, R.s, R.X32(0), ldx, (const float*)V0, ldv, (int64_t)dim, r, (int)ldx);
+  if (bf16) hipLaunchKernelGGL((convert2d_kernel<float, __bf16>), dim3(gx), dim3(256), 0, R.s, R.X32(), ldx, (const __bf16*)V0, ldv, (int64_t)dim, r, (int)ldx);
+  else hipLaunchKernelGGL((convert2d_kernel<float, float>), dim3(gx), dim3(256), 0, R.s, R.X32(), ldx, (const float*)V0, ldv, (int64_t)dim, r, (int)ldx);
   HIP_TRY(hipGetLastError());
   // The start basis is only normalised: a previous projection is orthonormal already and Gaussian
   // noise is well conditioned; without power rounds it is conditioned for the polishing steps.
@@ -346,8 +389,8 @@ mecefo_status_t mecefo_projection_refresh(mecefo_dtype_t dtype, const void* W, i
     if (st != MECEFO_OK) return st;
   }
   const unsigned gp = grid_for((int64_t)dim * r);
-  if (bf16) hipLaunchKernelGGL((convert2d_kernel<__bf16, float>), dim3(gp), dim3(256), 0, R.s, (__bf16*)P, ldp, R.X32(R.cur), ldx, (int64_t)dim, r, r);
-  else hipLaunchKernelGGL((convert2d_kernel<float, float>), dim3(gp), dim3(256), 0, R.s, (float*)P, ldp, R.X32(R.cur), ldx, (int64_t)dim, r, r);
+  if (bf16) hipLaunchKernelGGL((convert2d_kernel<__bf16, float>), dim3(gp), dim3(256), 0, R.s, (__bf16*)P, ldp, R.X32(), ldx, (int64_t)dim, r, r);
+  else hipLaunchKernelGGL((convert2d_kernel<float, float>), dim3(gp), dim3(256), 0, R.s, (float*)P, ldp, R.X32(), ldx, (int64_t)dim, r, r);
   HIP_TRY(hipGetLastError());
   return MECEFO_OK;
 }
