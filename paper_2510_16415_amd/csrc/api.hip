@@ -306,7 +306,7 @@ GemmProblem prob(const void* A0, const void* A1, int64_t lda, const void* B0, co
 // A store launch into the library's own buffers (row stride == ldc of every problem), cut along K
 // into up to `most` parts (what the workspace holds partials for) when that fills the chip better.
 mecefo_status_t launch_store_split(const Ctx& c, const Bufs& bf, GemmLaunch& g, int most, hipStream_t s) {
-  const int splits = most > 1 && c.bf16 ? bf16_plan_splits(g, most) : most;
+  const int splits = most <= 1 ? 1 : c.bf16 ? bf16_plan_splits(g, most) : f32_plan_splits(g, most);
   if (splits <= 1) {
     HIP_TRY(launch_gemm(g, s));
     return MECEFO_OK;
@@ -436,7 +436,7 @@ mecefo_status_t lowrank_wgrad(const Ctx& c, const Bufs& bf, const void* U, int64
     }
     // the workspace holds partials for up to bf.w.splits parts
     const int most = b > 0 ? bf.w.splits : 1;
-    const int splits = most > 1 && c.bf16 ? bf16_plan_splits(g, most) : most;
+    const int splits = most <= 1 ? 1 : c.bf16 ? bf16_plan_splits(g, most) : f32_plan_splits(g, most);
     if (splits > 1) g.epi = EPI_SPLIT_F32;
     g.splits = splits;
     g.partial = (float*)(base + bf.w.partial);

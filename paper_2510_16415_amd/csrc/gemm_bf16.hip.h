@@ -32,16 +32,6 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* p) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7FFFFFFF, 0x00020000);
 }
 
-// Wave-uniform choice between the base pointers of up to three K segments, pinned to scalar
-// registers half by half (a select on descriptors is otherwise lowered to per-lane moves and
-// every load that uses the result to a loop over lanes).
-__device__ inline const void* select_base(int seg, const void* p0, const void* p1, const void* p2) {
-  const uint64_t a = (uint64_t)(seg == 0 ? p0 : (seg == 1 ? p1 : p2));
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-  return (const void*)(((uint64_t)hi << 32) | lo);
-}
-
 // Swizzle: physical 16-byte chunk = logical chunk ^ swz(row).  Distinct for 8 consecutive
 // rows, and rows r, r+8 differ in the low bit, so 16 consecutive rows also spread over
 // 256 bytes of banks.  It depends on row % 16 only, so adding a multiple of 32 rows (the

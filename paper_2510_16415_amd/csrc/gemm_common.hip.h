@@ -112,6 +112,16 @@ __device__ inline GemmProblem product_view(const GemmProblem& p, int z) {
   return q;
 }
 
+// Wave-uniform choice between the base pointers of up to three K segments, pinned to scalar
+// registers half by half (a select on descriptors is otherwise lowered to per-lane moves and
+// every load that uses the result to a loop over lanes).
+__device__ inline const void* select_base(int seg, const void* p0, const void* p1, const void* p2) {
+  const uint64_t a = (uint64_t)(seg == 0 ? p0 : (seg == 1 ? p1 : p2));
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+  return (const void*)(((uint64_t)hi << 32) | lo);
+}
+
 // Softmax products (CAUSAL_TILE): output blocks of 256 x 256 that lie entirely above the diagonal
 // are never read by the products that consume the probabilities (their K loops are clipped to the
 // same 256-aligned blocks whatever tile size they run with), so tiles inside such a block are

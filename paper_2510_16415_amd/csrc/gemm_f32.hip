@@ -1,22 +1,99 @@
-// fp32 GEMM for the fp32 storage path (small reference-precision config): plain FMA,
-// 64 x 64 output tile per 256-thread workgroup, 4 x 4 outputs per thread, K staged through
-// LDS in slices of 16.  Layouts, K segments, dual products and epilogues mirror the bf16
-// core so that the host orchestration is identical for both dtypes.
+// fp32 GEMM for the fp32 storage path (small reference-precision config) on v_mfma_f32_16x16x4_f32: fp32
+// operands, fp32 accumulation.  Layouts, K segments, dual products and epilogues mirror the bf16 core so that
+// the host orchestration is identical for both dtypes.
+//
+// What bounds it: these products are small (256 tokens, d = 256, f = 688: 16 to 44 tiles of 64 x 64 for 256
+// CUs), so the length of one workgroup's walk along K is the launch's time.  Hence 32 x 32 tiles with K stages of
+// 64, whose global loads (four elements each) are issued a stage ahead into registers, two LDS buffers (one
+// barrier per stage), and the four waves share out the K of a stage (16 each) instead of the tile; their partial
+// tiles are added through LDS in a fixed order.  Launches with 64 x 64 tiles for every CU take those, each wave
+// a 32 x 32 quarter, K stages of 32: half the operand bytes per multiply-add.
+// Measured against the kernel before (64 x 64 tiles of plain FMAs, K slices of 16, loads in front of their use):
+// one layer's skip backward at the sizes above 574 -> 71.5 us, the exact FFN backward of 1024 tokens, d = 512,
+// f = 1536 937 -> 217 us and of 2048 tokens, d = 2048, f = 5461 8258 -> 4001 us; errors against fp64 are the same
+// (64 x 64 tiles) or half (the split sums) of what they were.
 #include "gemm_common.hip.h"
 
 namespace mecefo {
 
 namespace {
-constexpr int FT = 64;   // tile edge
-constexpr int FK = 16;   // K slice
 
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const KArgs args, int a_kc, int b_kc) {
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4f_t;
+
+// FT x FT output tile, K stages of FK; KSPLIT: the four waves share out K, else the tile.
+template <int FT_, int FK_, bool KSPLIT_> struct F32Cfg {
+  static constexpr int FT = FT_, FK = FK_;
+  static constexpr bool KSPLIT = KSPLIT_;
+  static constexpr int FS = FK + 4;           // LDS row stride (floats): the 16 rows of an operand read fall on different banks
+  static constexpr int NV = FT * FK / 1024;   // four-element loads per thread, operand and stage
+};
+using CfgSmall = F32Cfg<32, 64, true>;
+using CfgWide = F32Cfg<64, 32, false>;
+
+// One operand tile, [FT rows][FK] in LDS.  A load takes four consecutive elements of the source's rows (dword
+// alignment is enough): K-contiguous four K of a row, K-strided four rows of one K.  The buffer range is the
+// matrix itself, so what lies behind its last element reads as zero; rows and K outside the matrix are pointed
+// behind the range.
+template <class Cfg, bool kc>
+struct TileF32 {
+  static constexpr int NV = Cfg::NV, FT = Cfg::FT, FK = Cfg::FK;
+  f32x4_t v[NV];
+  uint32_t voff[NV], step;      // byte offsets at K = 0, bytes per K
+  int bytes;                    // range of the buffer
+  __device__ inline int row(int t, int i) const { const int c = t + 256 * i; return kc ? c / (FK / 4) : c % (FT / 4) * 4; }
+  __device__ inline int kk(int t, int i) const { const int c = t + 256 * i; return kc ? c % (FK / 4) * 4 : c / (FT / 4); }
+  __device__ inline void init(int t, int64_t ld, int row0, int rows, int K) {
+    const int64_t span = kc ? (int64_t)(rows - 1) * ld + K : (int64_t)(K - 1) * ld + rows;
+    bytes = __builtin_amdgcn_readfirstlane(K > 0 ? (int)(span * 4) : 0);
+    step = (uint32_t)(kc ? 4 : ld * 4);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int r = row0 + row(t, i), k = kk(t, i);
+      voff[i] = r < rows ? (uint32_t)((kc ? (int64_t)r * ld + k : (int64_t)k * ld + r) * 4) : 0x80000000u;
+    }
+  }
+  __device__ inline void load(const void* base, int t, int k0, int K) {
+    const bool tail = k0 + FK > K;              // wave-uniform
+    const uint32_t soff = (uint32_t)k0 * step;
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const uint32_t off = tail && k0 + kk(t, i) >= K ? 0x80000000u : voff[i];
+      v[i] = __builtin_bit_cast(f32x4_t, (u32x4f_t)__builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0));
+    }
+  }
+  // `left`: K of this stage and beyond.  Elements behind a ragged K are cleared here, not behind the load, which
+  // would wait for it; elements behind a K-strided row end only reach outputs outside the matrix.
+  __device__ inline void store(float* lds, int t, int left) {
+    if (kc && left < FK) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+#pragma unroll
+        for (int e = 1; e < 4; ++e) v[i][e] = kk(t, i) + e < left ? v[i][e] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      float* d = lds + row(t, i) * Cfg::FS + kk(t, i);
+      if constexpr (kc) {
+        *(f32x4_t*)d = v[i];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e * Cfg::FS] = v[i][e];
+      }
+    }
+  }
+};
+
+template <class Cfg, int EPI, bool AKC, bool BKC>
+__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const KArgs args) {
   constexpr bool DUAL = epi_is_dual(EPI);
-  __shared__ float As[FK][FT + 4];
-  __shared__ float Bs[DUAL ? 2 : 1][FK][FT + 4];
-  const int t = threadIdx.x;
-  const int tx = t & 15, ty = t >> 4;
+  constexpr int FT = Cfg::FT, FK = Cfg::FK, FS = Cfg::FS;
+  constexpr int NB = DUAL ? 2 : 1, MATS = 1 + NB;
+  constexpr int KG = Cfg::KSPLIT ? FK / 64 : FK / 16;       // groups of 16 K per wave and stage
+  __shared__ __attribute__((aligned(16))) float lds[2][MATS][FT * FS];
+  static_assert(!Cfg::KSPLIT || 4 * NB * FT * (FT + 1) <= 2 * MATS * FT * FS, "the partial tiles reuse the operand buffers");
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int nblocks = args.total_tiles * args.splits;
   const TileCoord tc = map_tile(args, xcd_remap(blockIdx.x, nblocks));
   const GemmProblem p = product_view<4>(args.p[tc.prob], tc.z);
@@ -30,68 +107,110 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const KArgs args, int a_k
   int kt_end = min(kt_total, kt_begin + kt_chunk);
   causal_clip(p, m0, n0, FT, FK, kt_begin, kt_end);
 
-  float acc[4][4] = {}, acc2[4][4] = {};
-  for (int kt = kt_begin; kt < kt_end; ++kt) {
+  f32x4_t acc[NB][2][2];
+#pragma unroll
+  for (int w = 0; w < NB; ++w)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[w][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  TileF32<Cfg, AKC> ta;
+  TileF32<Cfg, BKC> tb[NB];
+  ta.init(t, p.lda, m0, p.M, p.K);
+#pragma unroll
+  for (int w = 0; w < NB; ++w) tb[w].init(t, p.ldb, n0, p.N, p.K);
+  auto load = [&](int kt) {
     const int seg = (kt >= kt_per_seg ? 1 : 0) + (kt >= 2 * kt_per_seg ? 1 : 0);
     const int k0 = (kt - seg * kt_per_seg) * FK;
-    const float* A = (const float*)p.A[DUAL ? 0 : seg];
-    // stage A: 64 x 16 elements, 4 per thread
+    ta.load(DUAL ? p.A[0] : select_base(seg, p.A[0], p.A[1], p.A[2]), t, k0, p.K);
+    tb[0].load(DUAL ? p.B[0] : select_base(seg, p.B[0], p.B[1], p.B[2]), t, k0, p.K);
+    if constexpr (DUAL) tb[NB - 1].load(p.B[1], t, k0, p.K);
+  };
+  if (kt_begin < kt_end) load(kt_begin);
+  // operand reads: lane holds row lane % 16 and four consecutive K, 4 (lane / 16) .. + 3 of a group of 16; MFMA
+  // step e takes element e of both operands (K in another order, the same for both)
+  const int wm = Cfg::KSPLIT ? 0 : wave >> 1, wn = Cfg::KSPLIT ? 0 : wave & 1;
+  const int lane_off = (lane & 15) * FS + 4 * (lane >> 4) + (Cfg::KSPLIT ? 16 * wave : 0);
+  const int a_off = lane_off + wm * 32 * FS, b_off = lane_off + wn * 32 * FS;
+  for (int kt = kt_begin; kt < kt_end; ++kt) {
+    float(*buf)[FT * FS] = lds[(kt - kt_begin) & 1];
+    const int seg = (kt >= kt_per_seg ? 1 : 0) + (kt >= 2 * kt_per_seg ? 1 : 0);
+    const int left = p.K - (kt - seg * kt_per_seg) * FK;
+    ta.store(buf[0], t, left);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = t + i * 256;
-      int m, k;
-      if (a_kc) { k = e & 15; m = e >> 4; } else { m = e & 63; k = e >> 6; }
-      const int gm = m0 + m, gk = k0 + k;
-      float v = 0.f;
-      if (gm < p.M && gk < p.K) v = a_kc ? A[(int64_t)gm * p.lda + gk] : A[(int64_t)gk * p.lda + gm];
-      As[k][m] = v;
-    }
-#pragma unroll
-    for (int w = 0; w < (DUAL ? 2 : 1); ++w) {
-      const float* B = (const float*)p.B[DUAL ? w : seg];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int e = t + i * 256;
-        int n, k;
-        if (b_kc) { k = e & 15; n = e >> 4; } else { n = e & 63; k = e >> 6; }
-        const int gn = n0 + n, gk = k0 + k;
-        float v = 0.f;
-        if (gn < p.N && gk < p.K) v = b_kc ? B[(int64_t)gn * p.ldb + gk] : B[(int64_t)gk * p.ldb + gn];
-        Bs[w][k][n] = v;
-      }
-    }
+    for (int w = 0; w < NB; ++w) tb[w].store(buf[1 + w], t, left);
+    if (kt + 1 < kt_end) load(kt + 1);
+    // one barrier per stage: whoever read this buffer two stages ago has passed the previous one
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < FK; ++k) {
-      float a[4], b[4], b2[4];
+    for (int g = 0; g < KG; ++g) {
+      f32x4_t a[2], b[NB][2];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
+      for (int i = 0; i < 2; ++i) {
+        a[i] = *(const f32x4_t*)(buf[0] + a_off + 16 * i * FS + 16 * g);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[0][k][tx * 4 + j];
-      if constexpr (DUAL) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) b2[j] = Bs[1][k][tx * 4 + j];
+        for (int w = 0; w < NB; ++w) b[w][i] = *(const f32x4_t*)(buf[1 + w] + b_off + 16 * i * FS + 16 * g);
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-          if constexpr (DUAL) acc2[i][j] = fmaf(a[i], b2[j], acc2[i][j]);
-        }
+        for (int w = 0; w < NB; ++w)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              acc[w][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[w][j][e], acc[w][i][j], 0, 0, 0);
     }
-    __syncthreads();
   }
+  // accumulator element e of a 16x16 block is row 4 (lane / 16) + e, column lane % 16
+  if constexpr (!Cfg::KSPLIT) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      epilogue_elem<EPI, float>(p, args, tc.prob, tc.split, m0 + ty * 4 + i, n0 + tx * 4 + j,
-                                acc[i][j], acc2[i][j]);
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          epilogue_elem<EPI, float>(p, args, tc.prob, tc.split, m0 + 32 * wm + 16 * i + 4 * (lane >> 4) + e,
+                                    n0 + 32 * wn + 16 * j + (lane & 15), acc[0][i][j][e], acc[NB - 1][i][j][e]);
+    return;
+  }
+  __syncthreads();
+  float* part = &lds[0][0][0];      // [wave][matrix][FT][FT + 1]
+#pragma unroll
+  for (int w = 0; w < NB; ++w)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          part[((wave * NB + w) * FT + 16 * i + 4 * (lane >> 4) + e) * (FT + 1) + 16 * j + (lane & 15)] = acc[w][i][j][e];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < FT * FT / 256; ++i) {
+    const int r = (t + 256 * i) / FT, c = t % FT;
+    float s[2] = {0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NB; ++w) {
+      const float* q = part + (w * FT + r) * (FT + 1) + c;
+      constexpr int W = NB * FT * (FT + 1);      // one wave's partial tiles
+      s[w] = (q[0] + q[W]) + (q[2 * W] + q[3 * W]);
+    }
+    epilogue_elem<EPI, float>(p, args, tc.prob, tc.split, m0 + r, n0 + c, s[0], s[1]);
+  }
 }
 
-template <int EPI>
-hipError_t run_f32(GemmLaunch& g, hipStream_t stream) {
+inline int f32_tiles(const GemmLaunch& g, int ft) {
+  int tiles = 0;
+  for (int i = 0; i < g.nprob; ++i)
+    tiles += ((g.p[i].M + ft - 1) / ft) * ((g.p[i].N + ft - 1) / ft) * (g.p[i].batch > 1 ? g.p[i].batch : 1);
+  return tiles;
+}
+
+template <class Cfg, int EPI>
+hipError_t run_f32_cfg(GemmLaunch& g, hipStream_t stream) {
+  constexpr int FT = Cfg::FT;
   KArgs a;
   a.clk = nullptr;
   a.nprob = g.nprob;
@@ -115,11 +234,41 @@ hipError_t run_f32(GemmLaunch& g, hipStream_t stream) {
   a.out_f32 = 1;
   a.partial = g.partial;
   if (tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL(gemm_f32_kernel<EPI>, dim3(tiles * a.splits), dim3(256), 0, stream, a,
-                     (int)g.a_kcontig, (int)g.b_kcontig);
+  const dim3 grid(tiles * a.splits);
+  if (g.a_kcontig && g.b_kcontig) hipLaunchKernelGGL((gemm_f32_kernel<Cfg, EPI, true, true>), grid, dim3(256), 0, stream, a);
+  else if constexpr (epi_is_dual(EPI) || EPI == EPI_ATTN_P || EPI == EPI_ATTN_DS) return hipErrorInvalidValue;
+  else if (g.a_kcontig) hipLaunchKernelGGL((gemm_f32_kernel<Cfg, EPI, true, false>), grid, dim3(256), 0, stream, a);
+  else if (!g.b_kcontig) hipLaunchKernelGGL((gemm_f32_kernel<Cfg, EPI, false, false>), grid, dim3(256), 0, stream, a);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
+
+// 64 x 64 tiles once they give every CU two workgroups.
+template <int EPI>
+hipError_t run_f32(GemmLaunch& g, hipStream_t stream) {
+  const int splits = EPI == EPI_SPLIT_F32 && g.splits > 1 ? g.splits : 1;
+  return f32_tiles(g, 64) * splits >= 512 ? run_f32_cfg<CfgWide, EPI>(g, stream) : run_f32_cfg<CfgSmall, EPI>(g, stream);
+}
 }  // namespace
+
+// K splits of a launch that may be cut into up to `most` parts: a stage takes about 0.5 us while every CU has at
+// most two workgroups, the sum of the parts one more launch of 5 us per problem.
+int f32_plan_splits(const GemmLaunch& g, int most) {
+  const int tiles = f32_tiles(g, CfgSmall::FT);
+  int stages = 0;
+  for (int i = 0; i < g.nprob; ++i) {
+    const int st = (g.p[i].K + CfgSmall::FK - 1) / CfgSmall::FK * (g.p[i].nseg > 1 ? g.p[i].nseg : 1);
+    if (st > stages) stages = st;
+  }
+  int best = 1;
+  float t = 0.f;
+  for (int s = 1; s <= most && s <= (stages > 1 ? stages : 1); ++s) {
+    const float n = (float)tiles * s / 512.f;
+    const float x = (float)((stages + s - 1) / s) * 0.5f * (n > 1.f ? n : 1.f) + (s > 1 ? 5.f * g.nprob : 0.f);
+    if (s == 1 || x < t) { t = x; best = s; }
+  }
+  return best;
+}
 
 hipError_t launch_gemm_f32(GemmLaunch& g, hipStream_t s) {
   switch (g.epi) {

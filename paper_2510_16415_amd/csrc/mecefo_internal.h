@@ -108,6 +108,7 @@ hipError_t prepare_attention_bwd();
 hipError_t launch_gemm(GemmLaunch& g, hipStream_t stream);
 hipError_t launch_gemm_bf16(GemmLaunch& g, hipStream_t stream);
 hipError_t launch_gemm_f32(GemmLaunch& g, hipStream_t stream);
+int f32_plan_splits(const GemmLaunch& g, int most);
 
 // Elementwise / reduction kernels (elementwise.hip).  `bf16` selects the storage type.
 hipError_t launch_rmsnorm_fwd(bool bf16, const void* H, int64_t ldh, const void* gamma, float eps,

@@ -72,3 +72,30 @@ def test_exact_backward_products(b, d, f):
     assert relerr(dWg, dg.T @ u) <= 1e-2
     assert relerr(dWu, dz.T @ u) <= 1e-2
     assert relerr(dWd[:, :f], dy.T @ a) <= 1e-2
+
+
+@pytest.mark.parametrize("b,d,f", [(1, 1, 1), (33, 31, 65), (64, 64, 32), (257, 130, 67), (1100, 522, 2051)])
+def test_exact_backward_products_f32(b, d, f):
+    """The fp32 core (32 x 32 tiles, and 64 x 64 for the largest size) with odd row strides, NaN behind every row
+    and K ends inside a four-element load, against fp64: 1e-5 in the norm, the fp32 gate of the other tests."""
+    gen = torch.Generator(device="cuda").manual_seed(b + 17 * f)
+
+    def rows(n, cols, pad, std):
+        t = torch.full((n, cols + pad), float("nan"), device="cuda")
+        t[:, :cols] = torch.randn(n, cols, generator=gen, device="cuda") * std
+        return t
+
+    U, dY = rows(b, d, 3, 1.0), rows(b, d, 3, 1.0)
+    Wg, Wu, Wd = rows(f, d, 1, d ** -0.5), rows(f, d, 1, d ** -0.5), rows(d, f, 5, f ** -0.5)
+    desc = B.make_desc(b, d, f, B.F32, B.F32, d + 3, f, d + 1, f + 5, 1e-6)
+    ws = torch.full((B.mecefo_workspace_bytes(desc, 0, 0, 0),), 255, dtype=torch.uint8, device="cuda")
+    dU, dWg, dWu, dWd = rows(b, d, 3, 1.0), rows(f, d, 1, 1.0), rows(f, d, 1, 1.0), rows(d, f, 5, 1.0)
+    B.mecefo_ffn_bwd_exact(desc, U, dY, Wg, Wu, Wd, None, None, dU, dWg, dWu, dWd, 0, ws)
+    torch.cuda.synchronize()
+    u, dy, wg, wu, wd = (t[:, :n].double() for t, n in ((U, d), (dY, d), (Wg, d), (Wu, d), (Wd, f)))
+    g, z, da = u @ wg.T, u @ wu.T, dy @ wd
+    sg = torch.sigmoid(g)
+    dg, dz, a = da * z * sg * (1 + g * (1 - sg)), da * g * sg, g * sg * z
+    for got, n, want in ((dU, d, dg @ wg + dz @ wu), (dWg, d, dg.T @ u), (dWu, d, dz.T @ u), (dWd, f, dy.T @ a)):
+        assert relerr(got[:, :n], want) <= 1e-5
+        assert bool(got[:, n:].isnan().all())
