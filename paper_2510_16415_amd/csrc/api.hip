@@ -574,6 +574,12 @@ FwdWs fwd_layout(const Ctx& c, const mecefo_attn_desc_t& a) {
   return w;
 }
 
+// The block forward behind mecefo_block_fwd; tables_ready: the workspace holds the rotary tables of a previous
+// layer of the same public call.
+mecefo_status_t block_fwd(const mecefo_ffn_desc_t* desc, const mecefo_attn_desc_t* attn,
+                          const mecefo_block_fwd_inputs_t* in, const mecefo_block_fwd_outputs_t* out, void* ws,
+                          size_t ws_bytes, void* hip_stream, bool tables_ready);
+
 mecefo_status_t check_lowrank_args(const Ctx& c, const mecefo_proj_t P[3], mecefo_side_t side, int exact_mask = 0) {
   if (side != MECEFO_SIDE_INPUT && side != MECEFO_SIDE_OUTPUT) return fail(MECEFO_ERR_INVALID_ARG, "side must be MECEFO_SIDE_INPUT or MECEFO_SIDE_OUTPUT");
   const bool in = side == MECEFO_SIDE_INPUT;
@@ -1084,6 +1090,15 @@ mecefo_status_t mecefo_block_fwd_workspace_bytes(const mecefo_ffn_desc_t* desc, 
 mecefo_status_t mecefo_block_fwd(const mecefo_ffn_desc_t* desc, const mecefo_attn_desc_t* attn,
                                  const mecefo_block_fwd_inputs_t* in, const mecefo_block_fwd_outputs_t* out,
                                  void* ws, size_t ws_bytes, void* hip_stream) {
+  return block_fwd(desc, attn, in, out, ws, ws_bytes, hip_stream, false);
+}
+
+}  // extern "C"
+
+namespace {
+mecefo_status_t block_fwd(const mecefo_ffn_desc_t* desc, const mecefo_attn_desc_t* attn,
+                          const mecefo_block_fwd_inputs_t* in, const mecefo_block_fwd_outputs_t* out, void* ws,
+                          size_t ws_bytes, void* hip_stream, bool tables_ready) {
   Ctx c;
   TRY(check_desc(desc, &c));
   TRY(check_attn(c, attn));
@@ -1117,20 +1132,26 @@ mecefo_status_t mecefo_block_fwd(const mecefo_ffn_desc_t* desc, const mecefo_att
   float* cs = (float*)(base + w.cs); float* sn = (float*)(base + w.sn);
   float* S32 = (float*)(base + w.S32);
   void* P = base + w.P;
-  const size_t rowbytes = (size_t)dm * c.esz;
 
   HIP_TRY(launch_rmsnorm_fwd(c.bf16, in->X, d.ld_act_d, in->g_attn, d.rms_eps, Xn, dm, rstd, c.b, dm, s));
-  {  // Q, K, V = Xn Wq^T, Xn Wk^T, Xn Wv^T  [b x d], K = d
+  if (!tables_ready) HIP_TRY(launch_rope_tables(cs, sn, S, dh, (double)a.rope_theta, s));
+  {  // Q, K, V = Xn Wq^T, Xn Wk^T, Xn Wv^T  [b x d], K = d; Q and K rotated in the epilogue where its waves hold whole heads
     GemmLaunch g = new_launch(c, true, true, EPI_STORE);
     g.nprob = 3;
     void* dst[3] = {Q, K, V};
     const void* wt[3] = {in->Wq, in->Wk, in->Wv};
     for (int i = 0; i < 3; ++i) g.p[i] = prob(Xn, nullptr, dm, wt[i], nullptr, a.ld_w_dd, dst[i], nullptr, nullptr, ldq, b, dm, dm, 1);
+    const bool rotate = c.bf16 && gemm_bf16_rope_ok(g, dh);
+    if (rotate) {
+      g.epi = EPI_ROPE;
+      for (int i = 0; i < 2; ++i) { g.p[i].rope_half = dh / 2; g.p[i].rope_seq = S; g.p[i].rowvec = cs; g.p[i].addend = sn; }
+    }
     HIP_TRY(launch_gemm(g, s));
+    if (!rotate) {
+      HIP_TRY(launch_rope(c.bf16, Q, ldq, cs, sn, c.b, S, a.heads, dh, false, s));
+      HIP_TRY(launch_rope(c.bf16, K, ldq, cs, sn, c.b, S, a.heads, dh, false, s));
+    }
   }
-  HIP_TRY(launch_rope_tables(cs, sn, S, dh, (double)a.rope_theta, s));
-  HIP_TRY(launch_rope(c.bf16, Q, ldq, cs, sn, c.b, S, a.heads, dh, false, s));
-  HIP_TRY(launch_rope(c.bf16, K, ldq, cs, sn, c.b, S, a.heads, dh, false, s));
   const float scale = 1.0f / sqrtf((float)dh);
   const bool fused = fwd_attention_fused(c, a);
   if (fused) HIP_TRY(launch_attn_fwd(Q, K, V, O, ldq, L, a.batch, S, a.heads, dh, scale, s));
@@ -1164,14 +1185,10 @@ mecefo_status_t mecefo_block_fwd(const mecefo_ffn_desc_t* desc, const mecefo_att
         HIP_TRY(launch_gemm(g, s));
       }
     }
-  // H = X + O Wo^T: the product accumulates onto a copy of X
-  HIP_TRY(hipMemcpy2DAsync(out->H, (size_t)d.ld_act_d * c.esz, in->X, (size_t)d.ld_act_d * c.esz, rowbytes, (size_t)b, hipMemcpyDeviceToDevice, s));
-  {
-    GemmLaunch g = new_launch(c, true, true, EPI_GRAD);
-    g.out_f32 = false;
-    g.accumulate = 1;
+  {  // H = X + O Wo^T
+    GemmLaunch g = new_launch(c, true, true, EPI_RESID);
     g.nprob = 1;
-    g.p[0] = prob(O, nullptr, ldq, in->Wo, nullptr, a.ld_w_dd, out->H, nullptr, nullptr, d.ld_act_d, b, dm, dm, 1);
+    g.p[0] = prob(O, nullptr, ldq, in->Wo, nullptr, a.ld_w_dd, out->H, const_cast<void*>(in->X), nullptr, d.ld_act_d, b, dm, dm, 1);
     HIP_TRY(launch_gemm(g, s));
   }
   // FFN: U = norm(H), A = silu(U Wg^T) * (U Wu^T), Out = H + A Wd^T
@@ -1183,17 +1200,17 @@ mecefo_status_t mecefo_block_fwd(const mecefo_ffn_desc_t* desc, const mecefo_att
     g.p[0] = prob(Xn, nullptr, dm, in->Wg, in->Wu, d.ld_w_fd, nullptr, nullptr, AA, c.ldf, b, c.ff, dm, 1, (int)c.ldf);
     HIP_TRY(launch_gemm(g, s));
   }
-  HIP_TRY(hipMemcpy2DAsync(out->Out, (size_t)d.ld_act_d * c.esz, out->H, (size_t)d.ld_act_d * c.esz, rowbytes, (size_t)b, hipMemcpyDeviceToDevice, s));
   {
-    GemmLaunch g = new_launch(c, true, true, EPI_GRAD);
-    g.out_f32 = false;
-    g.accumulate = 1;
+    GemmLaunch g = new_launch(c, true, true, EPI_RESID);
     g.nprob = 1;
-    g.p[0] = prob(AA, nullptr, c.ldf, in->Wd, nullptr, d.ld_w_df, out->Out, nullptr, nullptr, d.ld_act_d, b, dm, c.ff, 1);
+    g.p[0] = prob(AA, nullptr, c.ldf, in->Wd, nullptr, d.ld_w_df, out->Out, out->H, nullptr, d.ld_act_d, b, dm, c.ff, 1);
     HIP_TRY(launch_gemm(g, s));
   }
   return MECEFO_OK;
 }
+}  // namespace
+
+extern "C" {
 
 mecefo_status_t mecefo_stack_workspace_bytes(const mecefo_ffn_desc_t* desc, const mecefo_attn_desc_t* attn,
                                              int r_gate, int r_up, int r_down, size_t* out_bytes) {
@@ -1232,7 +1249,8 @@ mecefo_status_t mecefo_stack_fwd_neighbor(const mecefo_ffn_desc_t* desc, const m
     mecefo_block_fwd_inputs_t in = {x, w.g_attn, w.g_ffn, w.Wq, w.Wk, w.Wv, w.Wo, w.Wg, w.Wu, w.Wd};
     void* y = l == n_layers - 1 ? X_out : pp[l & 1];
     mecefo_block_fwd_outputs_t out = {y, H[l], nullptr, nullptr, nullptr, nullptr, nullptr};
-    mecefo_status_t st = mecefo_block_fwd(desc, attn, &in, &out, inner_ws, ws_bytes - lead - 2 * act, hip_stream);
+    // every layer of the call uses the same workspace: the angle tables of the first one serve them all
+    mecefo_status_t st = block_fwd(desc, attn, &in, &out, inner_ws, ws_bytes - lead - 2 * act, hip_stream, l > 0);
     if (st != MECEFO_OK) return st;
     x = y;
   }

@@ -453,6 +453,14 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_bf16_dtl_kernel(const KArgs a
 #pragma unroll
           for (int e = 0; e < 4; ++e) { v2[e] = z0[e]; v2[4 + e] = z1[e]; }
         }
+        if constexpr (EPI == EPI_ROPE) {     // the wave's columns are whole heads: the other half of the pairs is in its slice
+          if (p.rope_half) {
+            const float* other = ep + rl * RS + (rd_c8 ^ p.rope_half);
+            const f32x4_t z0 = *(const f32x4_t*)other, z1 = *(const f32x4_t*)(other + 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { v2[e] = z0[e]; v2[4 + e] = z1[e]; }
+          }
+        }
         epilogue_vec8<EPI>(p, args, tc.prob, tc.split, row_w + i * 32 + rl, col_w, v, v2);
       }
     }

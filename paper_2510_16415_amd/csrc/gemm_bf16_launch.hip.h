@@ -179,17 +179,25 @@ hipError_t prepare_bf16() {
   return e;
 }
 
+// The configuration of a launch that may be forced to a direct-to-LDS one (1: 128 x 128, 4: 256 x 256); -1 for the
+// register-staged ones.
+inline int bf16_tile_choice(const GemmLaunch& g) {
+  switch (options().tile.load(std::memory_order_relaxed)) {
+    case 1: return TILE_M2;
+    case 2: case 3: return -1;
+    case 4: return TILE_L;
+    default: return bf16_best_tile(g, g.epi == EPI_SPLIT_F32 && g.splits > 1 ? g.splits : 1);
+  }
+}
+
 // mecefo_set_option("tile", ...) forces 1: 128 x 128, 2 and 3: 256 x 256 register-staged with four or
 // eight waves, 4: 256 x 256 direct-to-LDS; otherwise the model decides.
 template <bool AKC, bool BKC, int EPI>
 hipError_t run_bf16_auto(GemmLaunch& g, hipStream_t stream) {
-  int c;
-  switch (options().tile.load(std::memory_order_relaxed)) {
-    case 1: c = TILE_M2; break;
-    case 2: return run_bf16<CfgL4, AKC, BKC, EPI>(g, stream);
-    case 3: return run_bf16<CfgL8, AKC, BKC, EPI>(g, stream);
-    case 4: c = TILE_L; break;
-    default: c = bf16_best_tile(g, EPI == EPI_SPLIT_F32 && g.splits > 1 ? g.splits : 1);
+  const int c = bf16_tile_choice(g);
+  if (c < 0) {
+    return options().tile.load(std::memory_order_relaxed) == 2 ? run_bf16<CfgL4, AKC, BKC, EPI>(g, stream)
+                                                               : run_bf16<CfgL8, AKC, BKC, EPI>(g, stream);
   }
   switch (c) {
     case TILE_M2: return run_bf16<CfgM, AKC, BKC, EPI, PipeM2>(g, stream);

@@ -3,6 +3,20 @@
 // attention-score products Q K^T and dO V^T of the standard-mode backward.
 #include "gemm_bf16_launch.hip.h"
 namespace mecefo {
+// The rotation pairs columns of one head: a wave of the epilogue must hold whole heads, which the 128 columns
+// of a 256 x 256 tile's wave and the 64 of a 128 x 128 one do for head dimensions 64 and 128 or 64.
+bool gemm_bf16_rope_ok(const GemmLaunch& g, int dh) {
+  const int c = bf16_tile_choice(g);
+  return (dh == 64 && c >= 0 && c != TILE_T) || (dh == 128 && c == TILE_L);
+}
+static hipError_t run_rope(GemmLaunch& g, hipStream_t s) {
+  switch (bf16_tile_choice(g)) {
+    case TILE_L: return run_bf16<CfgL8, true, true, EPI_ROPE, PipeL, false>(g, s);
+    case TILE_M2: return run_bf16<CfgM, true, true, EPI_ROPE, PipeM2>(g, s);
+    case TILE_M4: return run_bf16<CfgM8, true, true, EPI_ROPE, PipeM4>(g, s);
+    default: return hipErrorInvalidValue;
+  }
+}
 hipError_t launch_gemm_bf16_nt(GemmLaunch& g, hipStream_t s) {
   switch (g.epi) {
     case EPI_STORE: return run_bf16_auto<true, true, EPI_STORE>(g, s);
@@ -14,6 +28,8 @@ hipError_t launch_gemm_bf16_nt(GemmLaunch& g, hipStream_t s) {
     case EPI_ATTN_DS: return run_bf16_auto<true, true, EPI_ATTN_DS>(g, s);
     case EPI_POLY: return run_bf16_auto<true, true, EPI_POLY>(g, s);
     case EPI_HILO: return run_bf16_auto<true, true, EPI_HILO>(g, s);
+    case EPI_RESID: return run_bf16_auto<true, true, EPI_RESID>(g, s);
+    case EPI_ROPE: return run_rope(g, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -28,6 +44,10 @@ hipError_t prepare_gemm_bf16_nt() {
   if (e == hipSuccess) e = prepare_bf16<true, true, EPI_ATTN_DS>();
   if (e == hipSuccess) e = prepare_bf16<true, true, EPI_POLY>();
   if (e == hipSuccess) e = prepare_bf16<true, true, EPI_HILO>();
+  if (e == hipSuccess) e = prepare_bf16<true, true, EPI_RESID>();
+  if (e == hipSuccess) e = Bf16Kernel<CfgL8, true, true, EPI_ROPE, PipeL, false>::prepare();
+  if (e == hipSuccess) e = Bf16Kernel<CfgM, true, true, EPI_ROPE, PipeM2, true>::prepare();
+  if (e == hipSuccess) e = Bf16Kernel<CfgM8, true, true, EPI_ROPE, PipeM4, true>::prepare();
   return e;
 }
 }  // namespace mecefo

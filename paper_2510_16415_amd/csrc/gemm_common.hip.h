@@ -191,6 +191,11 @@ __device__ inline void epilogue_elem(const GemmProblem& p, const KArgs& a, int p
       T* c = (T*)p.C[0] + (int64_t)row * p.ldc + col;
       *c = from_f32<T>(to_f32<T>(*c) * (v - p.rowvec[row]) * p.scale);
     }
+  } else if constexpr (EPI == EPI_RESID) {
+    if (col < p.N) {
+      const int64_t idx = (int64_t)row * p.ldc + col;
+      ((T*)p.C[0])[idx] = from_f32<T>(v + to_f32<T>(((const T*)p.C[1])[idx]));
+    }
   } else if constexpr (EPI == EPI_POLY) {
     if (col < p.N) {
       const int64_t idx = (int64_t)row * p.ldc + col;
@@ -321,6 +326,27 @@ __device__ inline void epilogue_vec8(const GemmProblem& p, const KArgs& a, int p
       }
       *c = pack_bf16x8(o);
     }
+  } else if constexpr (EPI == EPI_RESID) {
+    const bf16x8s_t r = *(const bf16x8s_t*)((const __bf16*)p.C[1] + idx);
+    float o[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = v[e] + (float)r[e];
+    *(bf16x8s_t*)((__bf16*)p.C[0] + idx) = pack_bf16x8(o);
+  } else if constexpr (EPI == EPI_ROPE) {      // v2: the partner columns
+    float o[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = v[e];
+    if (p.rope_half) {
+      const int64_t at = (int64_t)(row % p.rope_seq) * p.rope_half + (col0 & (p.rope_half - 1));
+      const float sgn = (col0 & p.rope_half) ? 1.f : -1.f;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const f32x4_t c = *(const f32x4_t*)(p.rowvec + at + 4 * q), s = *(const f32x4_t*)(p.addend + at + 4 * q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[4 * q + e] = v[4 * q + e] * c[e] + sgn * v2[4 * q + e] * s[e];
+      }
+    }
+    *(bf16x8s_t*)((__bf16*)p.C[0] + idx) = pack_bf16x8(o);
   } else if constexpr (EPI == EPI_POLY) {
     float o[8];
 #pragma unroll

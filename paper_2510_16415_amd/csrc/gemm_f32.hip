@@ -281,6 +281,7 @@ hipError_t launch_gemm_f32(GemmLaunch& g, hipStream_t s) {
     case EPI_ATTN_DS: return run_f32<EPI_ATTN_DS>(g, s);
     case EPI_POLY: return run_f32<EPI_POLY>(g, s);
     case EPI_HILO: return run_f32<EPI_HILO>(g, s);
+    case EPI_RESID: return run_f32<EPI_RESID>(g, s);
     default: return hipErrorInvalidValue;
   }
 }

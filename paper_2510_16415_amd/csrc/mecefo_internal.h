@@ -17,6 +17,8 @@ enum Epilogue : int {
   EPI_ATTN_DS = 6,     // C0[row, col] = C0[row, col] * (acc - rowvec[row]) * scale         (softmax backward, in place on P)
   EPI_POLY = 7,        // C0[row, col] = poly_a * (row == col) + poly_b * addend[row, col] + scale * acc; C1 (fp32) = acc
   EPI_HILO = 8,        // x = acc + addend[row, col]: C0 (fp32) = x, C1 = bf16(x), C2 = bf16(x - C1)
+  EPI_RESID = 9,       // C0[row, col] = acc + C1[row, col]   (activation dtype; C1 may be C0)
+  EPI_ROPE = 10,       // C0 = acc rotated: pairs (j, j + rope_half) of every head by the angle of position row % rope_seq
 };
 
 enum CausalK : int {
@@ -51,6 +53,8 @@ struct GemmProblem {
   float scale;           // attention epilogues, EPI_POLY
   const float* addend;   // EPI_POLY, EPI_HILO: fp32 [M x ldc], may be NULL (zero); may be C0 of EPI_HILO itself
   float poly_a, poly_b;  // EPI_POLY
+  int rope_half, rope_seq;   // EPI_ROPE: half the head dimension (0: plain store) and the sequence length; rowvec and
+                             // addend are the cosine and sine tables [rope_seq][rope_half]
   int causal;            // CausalK
 };
 
@@ -101,6 +105,8 @@ Options& options();
 hipError_t prepare_gemm_bf16_nt();
 hipError_t prepare_gemm_bf16_nn();
 hipError_t prepare_gemm_bf16_tn();
+// Whether the bf16 launch (NT layout) may carry EPI_ROPE for heads of dimension dh.
+bool gemm_bf16_rope_ok(const GemmLaunch& g, int dh);
 hipError_t prepare_attention_fwd();
 hipError_t prepare_attention_bwd();
 
