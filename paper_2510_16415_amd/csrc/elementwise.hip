@@ -132,67 +132,76 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const T* __restrict__ 
   }
 }
 
+// Rows per workgroup of the norm backward, and so rows per entry of its gain-gradient partials.
+constexpr int kDgammaRows = 16;
+
 // Norm backward, residual add and the gain-gradient partials in one pass over dU, H and dOut: a
-// workgroup owns rows_per_block consecutive rows, its four waves take them in turn with the rows of
-// dU and H in registers (ITERS vectors per lane), and every lane sums dU * N of its columns over
-// the wave's rows.  The four waves' sums are combined through LDS in a fixed order into
-// partial[block][col] (results do not depend on scheduling).  partial may be NULL.
+// workgroup owns kDgammaRows consecutive rows, each of its four waves four of them.  2048 to 8192 rows are
+// only 128 to 512 workgroups, so a wave's rows one after the other, a memory latency each, set the time
+// (11 us for [4096 x 1024], 6.9 us for [2048 x 512]); here a wave has all four rows in flight at once
+// (the 8-layer stack of the latter 1371 -> 1362 us, the two calls of the former 550 -> 549).  Rows of dU, H and dOut stay in registers (ITERS vectors per lane and row), and
+// every lane sums dU * N of its columns over the wave's rows.  The four waves' sums are combined through LDS in
+// a fixed order into partial[block][col] (results do not depend on scheduling).  partial may be NULL.
 template <typename T, int VEC, int ITERS>
 __global__ __launch_bounds__(256, 2) void rmsnorm_bwd_fused_kernel(const T* __restrict__ dU, int64_t lddu,
                                                                    const T* __restrict__ H, int64_t ldh,
                                                                    const float* __restrict__ rstd,
                                                                    const T* __restrict__ gamma,
                                                                    const T* dOut, int64_t lddo, T* dX, int64_t lddx,
-                                                                   float* __restrict__ partial, int64_t b, int d,
-                                                                   int rows_per_block) {
+                                                                   float* __restrict__ partial, int64_t b, int d) {
   extern __shared__ float comb[];      // [3][d]: the column sums of waves 1-3
+  constexpr int RB = kDgammaRows / 4;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nv = d / VEC;
-  Vec<T, VEC> g[ITERS];
+  const int64_t r0 = (int64_t)blockIdx.x * kDgammaRows + wave;
+  // rows r0, r0 + 4, ...: all are read before the first of them is written (dX may be dOut).  The loads carry no
+  // branch (rows and columns outside the matrix read the last row or first column, unused): behind a branch
+  // the compiler waits for each load before the next.
+  Vec<T, VEC> g[ITERS], a[RB][ITERS], x[RB][ITERS], r[RB][ITERS];
+  float rs[RB];
+#pragma unroll
+  for (int q = 0; q < RB; ++q) {
+    const int64_t row = r0 + 4 * q < b ? r0 + 4 * q : b - 1;
+    rs[q] = rstd[row];
+#pragma unroll
+    for (int k = 0; k < ITERS; ++k) {
+      const int i = k * 64 + lane < nv ? k * 64 + lane : 0;
+      a[q][k] = *(const Vec<T, VEC>*)(dU + row * lddu + i * VEC);
+      x[q][k] = *(const Vec<T, VEC>*)(H + row * ldh + i * VEC);
+      r[q][k] = *(const Vec<T, VEC>*)(dOut + row * lddo + i * VEC);
+    }
+  }
   float acc[ITERS][VEC];
 #pragma unroll
   for (int k = 0; k < ITERS; ++k) {
-    const int i = k * 64 + lane;
-    if (i < nv) g[k] = *(const Vec<T, VEC>*)(gamma + i * VEC);
+    g[k] = *(const Vec<T, VEC>*)(gamma + (k * 64 + lane < nv ? k * 64 + lane : 0) * VEC);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) acc[k][e] = 0.f;
   }
-  const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
-  const int64_t r1 = r0 + rows_per_block < b ? r0 + rows_per_block : b;
-  for (int64_t row = r0 + wave; row < r1; row += 4) {
-    const T* du = dU + row * lddu;
-    const T* h = H + row * ldh;
-    const T* go = dOut + row * lddo;
-    Vec<T, VEC> a[ITERS], x[ITERS];
 #pragma unroll
-    for (int k = 0; k < ITERS; ++k) {
-      const int i = k * 64 + lane;
-      if (i < nv) {
-        a[k] = *(const Vec<T, VEC>*)(du + i * VEC);
-        x[k] = *(const Vec<T, VEC>*)(h + i * VEC);
-      }
-    }
-    const float rs = rstd[row];
+  for (int q = 0; q < RB; ++q) {
+    const int64_t row = r0 + 4 * q;
+    if (row >= b) break;               // the same for the whole wave
     float dot = 0.f;
 #pragma unroll
-    for (int k = 0; k < ITERS; ++k)
-      if (k * 64 + lane < nv) {
+    for (int k = 0; k < ITERS; ++k) {
+      float s = 0.f;
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) dot += (float)a[k].e[e] * (float)g[k].e[e] * ((float)x[k].e[e] * rs);
-      }
+      for (int e = 0; e < VEC; ++e) s += (float)a[q][k].e[e] * (float)g[k].e[e] * ((float)x[q][k].e[e] * rs[q]);
+      dot += k * 64 + lane < nv ? s : 0.f;
+    }
     const float c = wave_sum(dot) / (float)d;
     T* dx = dX + row * lddx;
 #pragma unroll
     for (int k = 0; k < ITERS; ++k) {
       const int i = k * 64 + lane;
       if (i < nv) {
-        const Vec<T, VEC> r = *(const Vec<T, VEC>*)(go + i * VEC);    // read before the store: dX may alias dOut
         Vec<T, VEC> o;
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
-          const float n = (float)x[k].e[e] * rs;
-          o.e[e] = (T)((float)r.e[e] + rs * ((float)a[k].e[e] * (float)g[k].e[e] - n * c));
-          acc[k][e] += (float)a[k].e[e] * n;
+          const float n = (float)x[q][k].e[e] * rs[q];
+          o.e[e] = (T)((float)r[q][k].e[e] + rs[q] * ((float)a[q][k].e[e] * (float)g[k].e[e] - n * c));
+          acc[k][e] += (float)a[q][k].e[e] * n;
         }
         *(Vec<T, VEC>*)(dx + i * VEC) = o;
       }
@@ -225,86 +234,97 @@ __global__ __launch_bounds__(256, 2) void rmsnorm_bwd_fused_kernel(const T* __re
   }
 }
 
-// The same for long rows: the whole workgroup works on one row at a time (thread t owns vectors
-// t, t + 256, ...), the row dot product is combined across the four waves through LDS (one barrier
-// per row, alternating slots), and the next row's dU and H are fetched while the current row is
-// finished.  Every thread owns its columns for all rows of the block, so its sums go straight to
-// partial[block][col].
-template <typename T, int VEC, int ITERS>
+// The same for long rows: the whole workgroup works on RB rows at a time (thread t owns vectors
+// t, t + 256, ...), the row dot products are combined across the four waves through LDS (one barrier
+// per group of rows, alternating slots), and the next group's rows are fetched while the current one is
+// finished.  RB keeps about four vectors of each operand per thread in flight and a barrier per 8 to 24 KB
+// (one row at a time: 21 us for [2048 x 2048]; the skip call around it went from 465 to 458 us, the standard
+// one with two of them from 757 to 739).  Every thread owns its columns for all rows
+// of the block, so its sums go straight to partial[block][col].
+template <typename T, int VEC, int ITERS, int RB>
 __global__ __launch_bounds__(256) void rmsnorm_bwd_block_kernel(const T* __restrict__ dU, int64_t lddu,
                                                                 const T* __restrict__ H, int64_t ldh,
                                                                 const float* __restrict__ rstd,
                                                                 const T* __restrict__ gamma,
                                                                 const T* dOut, int64_t lddo, T* dX, int64_t lddx,
-                                                                float* __restrict__ partial, int64_t b, int d,
-                                                                int rows_per_block) {
-  __shared__ float red[2][4];
+                                                                float* __restrict__ partial, int64_t b, int d) {
+  __shared__ float red[2][RB][4];
+  static_assert(kDgammaRows % (2 * RB) == 0, "two groups per turn of the loop");
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int nv = d / VEC;
-  Vec<T, VEC> g[ITERS], a[ITERS], x[ITERS], r[ITERS];
+  struct Rows { Vec<T, VEC> a[RB][ITERS], x[RB][ITERS], r[RB][ITERS]; float rs[RB]; };
+  Vec<T, VEC> g[ITERS];
   float acc[ITERS][VEC];
 #pragma unroll
   for (int k = 0; k < ITERS; ++k) {
-    const int i = k * 256 + t;
-    if (i < nv) g[k] = *(const Vec<T, VEC>*)(gamma + i * VEC);
+    g[k] = *(const Vec<T, VEC>*)(gamma + (k * 256 + t < nv ? k * 256 + t : 0) * VEC);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) acc[k][e] = 0.f;
   }
-  const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
-  const int64_t r1 = r0 + rows_per_block < b ? r0 + rows_per_block : b;
-  // dOut of a row is read a whole row ahead of the store of that row's dX, which may be the same memory
-  auto fetch = [&](int64_t row, Vec<T, VEC> (&aa)[ITERS], Vec<T, VEC> (&xx)[ITERS], Vec<T, VEC> (&rr)[ITERS]) {
+  const int64_t r0 = (int64_t)blockIdx.x * kDgammaRows;
+  const int64_t r1 = r0 + kDgammaRows < b ? r0 + kDgammaRows : b;
+  // dOut of a row is read before the store of that row's dX, which may be the same memory; a group's stores
+  // never precede the reads of its own rows.  No branch around the loads (see above).
+  auto fetch = [&](int64_t row0, Rows& w) {
 #pragma unroll
-    for (int k = 0; k < ITERS; ++k) {
-      const int i = k * 256 + t;
-      if (i < nv) {
-        aa[k] = *(const Vec<T, VEC>*)(dU + row * lddu + i * VEC);
-        xx[k] = *(const Vec<T, VEC>*)(H + row * ldh + i * VEC);
-        rr[k] = *(const Vec<T, VEC>*)(dOut + row * lddo + i * VEC);
+    for (int q = 0; q < RB; ++q) {
+      const int64_t row = row0 + q < r1 ? row0 + q : r1 - 1;
+      w.rs[q] = rstd[row];
+#pragma unroll
+      for (int k = 0; k < ITERS; ++k) {
+        const int i = k * 256 + t < nv ? k * 256 + t : 0;
+        w.a[q][k] = *(const Vec<T, VEC>*)(dU + row * lddu + i * VEC);
+        w.x[q][k] = *(const Vec<T, VEC>*)(H + row * ldh + i * VEC);
+        w.r[q][k] = *(const Vec<T, VEC>*)(dOut + row * lddo + i * VEC);
+      }
+    }
+  };
+  auto finish = [&](int64_t row0, int slot, const Rows& w) {
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+      float dot = 0.f;
+#pragma unroll
+      for (int k = 0; k < ITERS; ++k) {
+        float s = 0.f;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) s += (float)w.a[q][k].e[e] * (float)g[k].e[e] * ((float)w.x[q][k].e[e] * w.rs[q]);
+        dot += k * 256 + t < nv ? s : 0.f;
+      }
+      dot = wave_sum(dot);
+      if (lane == 0) red[slot][q][wave] = dot;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+      if (row0 + q >= r1) break;
+      const float c = ((red[slot][q][0] + red[slot][q][1]) + (red[slot][q][2] + red[slot][q][3])) / (float)d;
+      T* dx = dX + (row0 + q) * lddx;
+#pragma unroll
+      for (int k = 0; k < ITERS; ++k) {
+        const int i = k * 256 + t;
+        if (i < nv) {
+          Vec<T, VEC> o;
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) {
+            const float n = (float)w.x[q][k].e[e] * w.rs[q];
+            o.e[e] = (T)((float)w.r[q][k].e[e] + w.rs[q] * ((float)w.a[q][k].e[e] * (float)g[k].e[e] - n * c));
+            acc[k][e] += (float)w.a[q][k].e[e] * n;
+          }
+          *(Vec<T, VEC>*)(dx + i * VEC) = o;
+        }
       }
     }
   };
   // Two register sets take turns (no copies between them: a copy would have to wait for the loads
-  // it moves): one row is finished from the first while the second receives the row after it.
-  Vec<T, VEC> a2[ITERS], x2[ITERS], r2[ITERS];
-  float rs = 0.f, rs2 = 0.f;
-  auto finish_row = [&](int64_t row, int slot, const Vec<T, VEC> (&aa)[ITERS], const Vec<T, VEC> (&xx)[ITERS],
-                        const Vec<T, VEC> (&rr)[ITERS], float rsv) {
-    float dot = 0.f;
-#pragma unroll
-    for (int k = 0; k < ITERS; ++k)
-      if (k * 256 + t < nv) {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) dot += (float)aa[k].e[e] * (float)g[k].e[e] * ((float)xx[k].e[e] * rsv);
-      }
-    dot = wave_sum(dot);
-    if (lane == 0) red[slot][wave] = dot;
-    __syncthreads();
-    const float c = ((red[slot][0] + red[slot][1]) + (red[slot][2] + red[slot][3])) / (float)d;
-    T* dx = dX + row * lddx;
-#pragma unroll
-    for (int k = 0; k < ITERS; ++k) {
-      const int i = k * 256 + t;
-      if (i < nv) {
-        Vec<T, VEC> o;
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          const float n = (float)xx[k].e[e] * rsv;
-          o.e[e] = (T)((float)rr[k].e[e] + rsv * ((float)aa[k].e[e] * (float)g[k].e[e] - n * c));
-          acc[k][e] += (float)aa[k].e[e] * n;
-        }
-        *(Vec<T, VEC>*)(dx + i * VEC) = o;
-      }
-    }
-  };
-  if (r0 < r1) { fetch(r0, a, x, r); rs = rstd[r0]; }
-  for (int64_t row = r0; row < r1; row += 2) {      // bounds are the same for the whole workgroup
-    if (row + 1 < r1) { fetch(row + 1, a2, x2, r2); rs2 = rstd[row + 1]; }
-    finish_row(row, 0, a, x, r, rs);
-    if (row + 1 < r1) {
-      if (row + 2 < r1) { fetch(row + 2, a, x, r); rs = rstd[row + 2]; }
-      finish_row(row + 1, 1, a2, x2, r2, rs2);
-    }
+  // it moves): one group is finished from the first while the second receives the group after it.
+  Rows w0, w1;
+  fetch(r0, w0);
+#pragma unroll 1
+  for (int64_t row = r0; row < r1; row += 2 * RB) {      // bounds are the same for the whole workgroup
+    fetch(row + RB, w1);
+    finish(row, 0, w0);
+    fetch(row + 2 * RB, w0);
+    if (row + RB < r1) finish(row + RB, 1, w1);
   }
   if (!partial) return;
 #pragma unroll
@@ -449,7 +469,6 @@ __global__ __launch_bounds__(256) void swiglu_bwd_kernel(const T* __restrict__ G
 }
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
-constexpr int kDgammaRows = 16;
 
 // The register-resident row kernels (bf16, eight elements per lane and step) cover rows of up to
 // 8 * 64 * 8 = 4096 elements whose strides keep every 16-byte vector aligned.
@@ -491,16 +510,15 @@ hipError_t launch_rmsnorm_bwd(bool bf16, const void* dU, int64_t lddu, const voi
   if (bf16 && d % 8 == 0 && d <= 8192 && lddu % 8 == 0 && ldh % 8 == 0 && lddo % 8 == 0 && lddx % 8 == 0) {
     const int nv = d / 8;
     const dim3 grid((unsigned)rmsnorm_bwd_blocks(b));
-#define MECEFO_NORM_BWD(KERNEL, ITERS, LDS)                                                                          \
-  hipLaunchKernelGGL((KERNEL<__bf16, 8, ITERS>), grid, dim3(256), LDS, s, (const __bf16*)dU, lddu,                 \
-                     (const __bf16*)H, ldh, rstd, (const __bf16*)gamma, (const __bf16*)dOut, lddo, (__bf16*)dX, lddx, \
-                     dg_partial, b, d, kDgammaRows)
+#define MECEFO_NORM_BWD(LDS, ...)                                                                                    \
+  hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(256), LDS, s, (const __bf16*)dU, lddu, (const __bf16*)H, ldh, rstd,   \
+                     (const __bf16*)gamma, (const __bf16*)dOut, lddo, (__bf16*)dX, lddx, dg_partial, b, d)
     const size_t comb = (size_t)3 * d * 4;
-    if (nv <= 64) MECEFO_NORM_BWD(rmsnorm_bwd_fused_kernel, 1, comb);         // a wave per row
-    else if (nv <= 128) MECEFO_NORM_BWD(rmsnorm_bwd_fused_kernel, 2, comb);
-    else if (nv <= 256) MECEFO_NORM_BWD(rmsnorm_bwd_block_kernel, 1, 0);      // the workgroup per row
-    else if (nv <= 512) MECEFO_NORM_BWD(rmsnorm_bwd_block_kernel, 2, 0);
-    else MECEFO_NORM_BWD(rmsnorm_bwd_block_kernel, 4, 0);
+    if (nv <= 64) MECEFO_NORM_BWD(comb, rmsnorm_bwd_fused_kernel<__bf16, 8, 1>);         // a wave per row
+    else if (nv <= 128) MECEFO_NORM_BWD(comb, rmsnorm_bwd_fused_kernel<__bf16, 8, 2>);
+    else if (nv <= 256) MECEFO_NORM_BWD(0, rmsnorm_bwd_block_kernel<__bf16, 8, 1, 4>);   // the workgroup per row
+    else if (nv <= 512) MECEFO_NORM_BWD(0, rmsnorm_bwd_block_kernel<__bf16, 8, 2, 2>);
+    else MECEFO_NORM_BWD(0, rmsnorm_bwd_block_kernel<__bf16, 8, 4, 1>);
 #undef MECEFO_NORM_BWD
     return hipGetLastError();
   }
