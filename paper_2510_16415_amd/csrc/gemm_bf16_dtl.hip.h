@@ -222,34 +222,39 @@ struct FragKS {
 template <int BK, int NB, int ROWS, bool KC> struct FragSel { using type = FragKC<BK, NB, ROWS>; };
 template <int BK, int NB, int ROWS> struct FragSel<BK, NB, ROWS, false> { using type = FragKS<BK, NB, ROWS>; };
 
-// Pipeline shape of the direct-to-LDS kernel for a tile: 64 K elements per stage, NS LDS buffers.
-template <class Cfg, int NS_> struct DtlPipe {
-  static constexpr int BK = 64, NS = NS_;
+// Pipeline shape of the direct-to-LDS kernel for a tile: 64 K elements per stage, KG groups of Cfg::NT threads
+// that take the stages in turn (each with NS LDS buffers of its own) and add up their tiles at the end.
+template <class Cfg, int NS_, int KG_ = 1> struct DtlPipe {
+  static constexpr int BK = 64, NS = NS_, KG = KG_, THREADS = Cfg::NT * KG;
   static constexpr int A_BYTES = Cfg::BM * BK * 2, B_BYTES = Cfg::BN * BK * 2, STAGE_BYTES = A_BYTES + B_BYTES;
   static constexpr int NW = Cfg::NT / 64;
   static constexpr int FPS = STAGE_BYTES / 1024 / NW;      // fill instructions per wave and stage
   // per-wave LDS slice of the staged epilogue: 32 rows x (WN + 4) floats, or 2 x 32 x (WN / 2 + 4)
   static constexpr int EP_WAVE_BYTES = 32 * (Cfg::WN + 8) * 4;
-  static constexpr int LDS_BYTES = NS * STAGE_BYTES > NW * EP_WAVE_BYTES ? NS * STAGE_BYTES : NW * EP_WAVE_BYTES;
+  static constexpr int SUM_BYTES = (KG - 1) * Cfg::BM * Cfg::BN * 4;      // the other groups' tiles, behind the epilogue slices
+  static constexpr int EP_BYTES = NW * EP_WAVE_BYTES + SUM_BYTES;
+  static constexpr int LDS_BYTES = KG * NS * STAGE_BYTES > EP_BYTES ? KG * NS * STAGE_BYTES : EP_BYTES;
   static_assert(NS >= 2 && NS <= 4 && LDS_BYTES <= 160 * 1024 && (NS - 1) * FPS <= 63, "bad pipeline");
 };
 
 // RAGGED: K may end inside a 16-byte chunk (the instantiation without it keeps the large tile's loop free of the
 // test: 0.5 % of the 7B-shaped layer).
 template <class Cfg, class Pipe, bool AKC, bool BKC, int EPI, bool RAGGED>
-__global__ __launch_bounds__(Cfg::NT, 2) void gemm_bf16_dtl_kernel(const KArgs args) {
+__global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const KArgs args) {
   constexpr bool DUAL = epi_is_dual(EPI);
   constexpr int BM = Cfg::BM, BN = Cfg::BN, NT = Cfg::NT;
   constexpr int TM = Cfg::WM / 16, TN = Cfg::WN / 16;     // 16x16 MFMA blocks per wave
   constexpr int BK = Pipe::BK, NS = Pipe::NS, KS = BK / 32, FPS = Pipe::FPS;
-  constexpr int A_BYTES = Pipe::A_BYTES, STAGE = Pipe::STAGE_BYTES;
+  constexpr int A_BYTES = Pipe::A_BYTES, STAGE = Pipe::STAGE_BYTES, KG = Pipe::KG;
   static_assert(TM % 2 == 0 && TN % (DUAL ? 2 : 1) == 0, "the epilogue takes 32 rows at a time");
   constexpr int BN_OUT = DUAL ? BN / 2 : BN;
-  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem_all[];
 
-  const int t = threadIdx.x;
+  const int group = KG > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NT) : 0;
+  const int t = threadIdx.x - group * NT;      // thread, wave and LDS buffers within the group
   const int lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  uint8_t* smem = smem_all + group * NS * STAGE;
   const int wm = wave / Cfg::WAVES_N, wn = wave % Cfg::WAVES_N;
 
   const int nblocks = args.total_tiles * args.splits;
@@ -305,9 +310,10 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_bf16_dtl_kernel(const KArgs a
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
 
-  auto issue = [&](int kt, uint32_t stage) {
+  auto issue = [&](int kt, uint32_t stage) {     // kt < 0: no stage left for this group, all zeros
     const int seg = (kt >= kt_per_seg ? 1 : 0) + (kt >= 2 * kt_per_seg ? 1 : 0);
-    const int k0 = (kt - seg * kt_per_seg) * BK;
+    const int k0 = KG > 1 && kt < 0 ? 0 : (kt - seg * kt_per_seg) * BK;
+    const int K = KG > 1 && kt < 0 ? 0 : p.K;
     const bool tail = k0 + BK > K;
     if (DUAL) {
       da.issue(ra0, ra0, stage, k0, K, tail);
@@ -344,6 +350,7 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_bf16_dtl_kernel(const KArgs a
   // while the other waits on LDS.
   if (NT == 512 && wave >= 4) __builtin_amdgcn_s_setprio(1);
   const int nst = kt_end - kt_begin;
+  const int turns = KG > 1 ? (nst + KG - 1) / KG : nst;      // stages of the group with the most
   // The (up to eight) tiles of a tile column run at the same time on one XCD and share their B panel.
   // Each starts its K loop at a different stage (rotation by the tile row, wrapping around), so that
   // they do not all ask L2 for the same lines at the same moment: the first request of a line then
@@ -352,7 +359,9 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_bf16_dtl_kernel(const KArgs a
   // strides measured slower).  Measured on the 7B-shaped layer: recompute launch -3.5 %, the others
   // -1 % to 0.  The summation order over K depends on the tile row only, so reruns stay bit-equal.
   const int rot = args.krot > 0 && nst > 0 ? __builtin_amdgcn_readfirstlane((tc.tm % args.krot) % nst) : 0;
-  auto kmap = [&](int i) {
+  auto kmap = [&](int turn) {
+    const int i = KG > 1 ? turn * KG + group : turn;
+    if (KG > 1 && i >= nst) return -1;
     int k = kt_begin + i + rot;
     return k >= kt_end ? k - nst : k;
   };
@@ -361,17 +370,21 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_bf16_dtl_kernel(const KArgs a
   const bool ragged = RAGGED && (AKC || BKC) && (K & 7) && !p.kpad_ok;
   auto clear_ragged = [&](int kt, uint8_t* stage) {
     const int seg = (kt >= kt_per_seg ? 1 : 0) + (kt >= 2 * kt_per_seg ? 1 : 0);
-    if (!ragged || kt != (seg + 1) * kt_per_seg - 1) return;
-    DmaA::clear_tail(stage, t, K % BK);
-    DmaB::clear_tail(stage + A_BYTES, t, K % BK);
+    if (!ragged) return;
+    const bool last = kt == (seg + 1) * kt_per_seg - 1;
+    if (KG == 1 && !last) return;      // several groups: every one of them meets the barrier in every turn
+    if (last) {
+      DmaA::clear_tail(stage, t, K % BK);
+      DmaB::clear_tail(stage + A_BYTES, t, K % BK);
+    }
     __syncthreads();
   };
   if (nst > 0) {
     // Fill every buffer of the ring, wait for the first stage only.
 #pragma unroll
     for (int s = 0; s < NS; ++s)
-      if (s < nst) issue(kmap(s), smem_addr + s * STAGE);
-    wait_fills_leave<FPS>(min(NS, nst) - 1);
+      if (s < turns) issue(kmap(s), smem_addr + s * STAGE);
+    wait_fills_leave<FPS>(min(NS, turns) - 1);
     __syncthreads();
     clear_ragged(kmap(0), smem);
 #pragma unroll
@@ -380,19 +393,40 @@ __global__ __launch_bounds__(Cfg::NT, 2) void gemm_bf16_dtl_kernel(const KArgs a
     for (int j = 0; j < TN; ++j) bfr[j] = fb.fetch_one(j, smem + A_BYTES, 0);
     int buf = 0;
     static_assert(KS == 2, "two 32-K steps per stage");
-    for (int kt = kt_begin; kt < kt_end; ++kt) {
+    for (int turn = 0; turn < turns; ++turn) {
       const uint8_t* sc = smem + buf * STAGE;
       const int nbuf = buf + 1 == NS ? 0 : buf + 1;
       step(0, sc, 1);
       // Every fragment of this stage is in registers or on its way.  Wait for the next stage only
       // (younger fills stay in flight), meet the other waves, then refill this buffer NS stages ahead.
-      wait_fills_leave<FPS>(min(NS - 2, kt_end - kt - 2));
+      wait_fills_leave<FPS>(min(NS - 2, turns - turn - 2));
       __syncthreads();
-      if (kt + NS < kt_end) issue(kmap(kt - kt_begin + NS), smem_addr + buf * STAGE);
-      if (ragged && kt + 1 < kt_end) clear_ragged(kmap(kt - kt_begin + 1), smem + nbuf * STAGE);
+      if (turn + NS < turns) issue(kmap(turn + NS), smem_addr + buf * STAGE);
+      if (ragged && turn + 1 < turns) clear_ragged(kmap(turn + 1), smem + nbuf * STAGE);
       step(1, smem + nbuf * STAGE, 0);
       buf = nbuf;
     }
+  }
+
+  // The groups' tiles are added in a fixed order, lane by lane (the buffers are free: the last barrier followed
+  // every fragment fetch that is used); the first group goes on to the epilogue.
+  if constexpr (KG > 1) {
+    f32x4_t* part = (f32x4_t*)(smem_all + Pipe::NW * Pipe::EP_WAVE_BYTES);
+    __syncthreads();
+    if (group > 0) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) part[(((group - 1) * TM + i) * TN + j) * NT + t] = acc[i][j];
+    }
+    __syncthreads();
+    if (group > 0) return;
+#pragma unroll
+    for (int g = 1; g < KG; ++g)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] += part[(((g - 1) * TM + i) * TN + j) * NT + t];
   }
 
   // Epilogue, staged through LDS so that global accesses are 16 bytes per lane and cover whole

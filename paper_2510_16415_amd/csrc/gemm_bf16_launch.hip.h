@@ -25,13 +25,14 @@ using PipeL = DtlPipe<CfgL8, 2>;
 using PipeM2 = DtlPipe<CfgM, 2>;   // 64 KiB: two workgroups per CU cover each other's waits
 using PipeM4 = DtlPipe<CfgM8, 4>;   // 128 KiB: one workgroup per CU, three stages in flight
 using PipeT = DtlPipe<CfgT, 3>;    // 48 KiB
+using PipeT2 = DtlPipe<CfgT, 3, 2>;   // 96 KiB: one workgroup per CU, two groups of waves share out K
 
 // ---- choice of the tile ------------------------------------------------------------------------
 // What bounds a launch depends on how many workgroups it gives a CU.  One 256 x 256 workgroup per CU has
 // the best rate (fewest operand bytes per multiply-add), but a K stage takes it 1.4 to 1.8 us however few
 // of them there are, so a launch that fills a quarter of the chip pays the full length of K at that pace:
 // smaller tiles walk K two to four times faster and give the idle CUs work.  The choice is the smallest
-// modelled time over the four configurations,
+// modelled time over the configurations,
 //     fixed + per_round * n + stages * max(stage_alone, stage_shared * n),   n = workgroups per CU,
 // with constants fitted to a sweep of 50 launches over every operand layout (K 32 to 11008, 2 to 2752
 // workgroups; the model is within 15 % of nearly all of them).  Sides measured, in us (256^2 / 128^2
@@ -40,14 +41,18 @@ using PipeT = DtlPipe<CfgT, 3>;    // 48 KiB
 // 101; [2048 x 512], K 1376: 33 / 16 / 17 / 11; SwiGLU recompute of 2048 tokens, d 2048, f 5461: 119 / 111 /
 // 138 / 156; [4096 x 4096], K 8192: 248 / 310 / 383 / 456.  The register-staged 128 x 128 kernel that the
 // small launches ran on before took 51, 81, 51, 99, 23, 143 and 624 us.
-enum TileConfig : int { TILE_L = 0, TILE_M2 = 1, TILE_M4 = 2, TILE_T = 3, TILE_COUNT = 4 };
+// The 64 x 64 workgroup is a chain of short stages (LDS reads, four MFMAs, barrier, fill addresses: 0.35 to 0.44 us);
+// two groups of waves halve it where the CU would hold no second workgroup and K has sixteen stages to share:
+// [2048 x 512], two segments of K 1376: 20.3 -> 16.5 us, [512 x 512], K 2048: 15.1 -> 12.0, K 512: 6.8 both.
+enum TileConfig : int { TILE_L = 0, TILE_M2 = 1, TILE_M4 = 2, TILE_T = 3, TILE_T2 = 4, TILE_COUNT = 5 };
 
 struct TileModel { int bm, bn, slots; float fixed, per_round, stage_alone, stage_shared; };
 inline const TileModel& tile_model(int c) {
   static const TileModel m[TILE_COUNT] = {{256, 256, 1, 3.5f, 2.5f, 1.45f, 1.75f},
                                           {128, 128, 2, 3.0f, 1.2f, 0.88f, 0.62f},
                                           {128, 128, 1, 4.5f, 1.2f, 0.70f, 0.72f},
-                                          {64, 64, 3, 2.5f, 0.5f, 0.44f, 0.28f}};
+                                          {64, 64, 3, 2.5f, 0.5f, 0.40f, 0.28f},
+                                          {64, 64, 1, 4.5f, 0.5f, 0.26f, 0.45f}};
   return m[c];
 }
 
@@ -68,6 +73,13 @@ inline int bf16_stages(const GemmLaunch& g) {
   return st;
 }
 
+// A K that is no multiple of 8 and not padded with zeros behind a K-contiguous operand.
+inline bool bf16_ragged(const GemmLaunch& g) {
+  for (int i = 0; i < g.nprob; ++i)
+    if ((g.a_kcontig || g.b_kcontig) && (g.p[i].K % 8) && !g.p[i].kpad_ok) return true;
+  return false;
+}
+
 // Modelled time in us of the launch cut along K into `splits` parts, on configuration c.
 inline float bf16_tile_cost(const GemmLaunch& g, int c, int splits) {
   const TileModel& m = tile_model(c);
@@ -80,8 +92,10 @@ inline float bf16_tile_cost(const GemmLaunch& g, int c, int splits) {
 inline int bf16_best_tile(const GemmLaunch& g, int splits, float* cost = nullptr) {
   int best = TILE_L;
   float t = bf16_tile_cost(g, TILE_L, splits);
+  const bool ragged = bf16_ragged(g);
   for (int c = 1; c < TILE_COUNT; ++c) {
-    const float x = bf16_tile_cost(g, c, splits);
+    // with a ragged K the groups of waves meet one more barrier per stage: a third of what they save
+    const float x = bf16_tile_cost(g, c, splits) + (c == TILE_T2 && ragged ? 0.05f * cdiv(bf16_stages(g), splits) : 0.f);
     if (x < t) { t = x; best = c; }
   }
   if (cost) *cost = t;
@@ -107,7 +121,7 @@ inline int bf16_plan_splits(const GemmLaunch& g, int most) {
   return best;
 }
 
-struct NoPipe { static constexpr int LDS_BYTES = 0; };
+struct NoPipe { static constexpr int LDS_BYTES = 0, THREADS = 0; };
 
 // One kernel instantiation: its entry point, its dynamic LDS size and the once-per-device limit raise.
 template <class Cfg, bool AKC, bool BKC, int EPI, class Pipe, bool RAGGED>
@@ -123,13 +137,6 @@ struct Bf16Kernel {
     return limit.ensure((const void*)entry(), LDS);
   }
 };
-
-// A K that is no multiple of 8 and not padded with zeros behind a K-contiguous operand.
-inline bool bf16_ragged(const GemmLaunch& g) {
-  for (int i = 0; i < g.nprob; ++i)
-    if ((g.a_kcontig || g.b_kcontig) && (g.p[i].K % 8) && !g.p[i].kpad_ok) return true;
-  return false;
-}
 
 template <class Cfg, bool AKC, bool BKC, int EPI, class Pipe = NoPipe, bool RAGGED = true>
 hipError_t run_bf16(GemmLaunch& g, hipStream_t stream) {
@@ -162,7 +169,7 @@ hipError_t run_bf16(GemmLaunch& g, hipStream_t stream) {
   if (tiles == 0) return hipSuccess;
   const hipError_t e = Kern::prepare();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(Kern::entry(), dim3(tiles * a.splits), dim3(Cfg::NT), LDS, stream, a);
+  hipLaunchKernelGGL(Kern::entry(), dim3(tiles * a.splits), dim3(Kern::DTL ? Pipe::THREADS : Cfg::NT), LDS, stream, a);
   return hipGetLastError();
 }
 
@@ -174,6 +181,7 @@ hipError_t prepare_bf16() {
   if (e == hipSuccess) e = Bf16Kernel<CfgM, AKC, BKC, EPI, PipeM2, true>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgM8, AKC, BKC, EPI, PipeM4, true>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgT, AKC, BKC, EPI, PipeT, true>::prepare();
+  if (e == hipSuccess) e = Bf16Kernel<CfgT, AKC, BKC, EPI, PipeT2, true>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgL4, AKC, BKC, EPI, NoPipe, true>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgL8, AKC, BKC, EPI, NoPipe, true>::prepare();
   return e;
@@ -203,6 +211,7 @@ hipError_t run_bf16_auto(GemmLaunch& g, hipStream_t stream) {
     case TILE_M2: return run_bf16<CfgM, AKC, BKC, EPI, PipeM2>(g, stream);
     case TILE_M4: return run_bf16<CfgM8, AKC, BKC, EPI, PipeM4>(g, stream);
     case TILE_T: return run_bf16<CfgT, AKC, BKC, EPI, PipeT>(g, stream);
+    case TILE_T2: return run_bf16<CfgT, AKC, BKC, EPI, PipeT2>(g, stream);
     default:
       if (bf16_ragged(g)) return run_bf16<CfgL8, AKC, BKC, EPI, PipeL, AKC || BKC>(g, stream);
       return run_bf16<CfgL8, AKC, BKC, EPI, PipeL, false>(g, stream);

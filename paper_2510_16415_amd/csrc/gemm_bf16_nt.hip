@@ -7,7 +7,7 @@ namespace mecefo {
 // of a 256 x 256 tile's wave and the 64 of a 128 x 128 one do for head dimensions 64 and 128 or 64.
 bool gemm_bf16_rope_ok(const GemmLaunch& g, int dh) {
   const int c = bf16_tile_choice(g);
-  return (dh == 64 && c >= 0 && c != TILE_T) || (dh == 128 && c == TILE_L);
+  return (dh == 64 && c >= 0 && c != TILE_T && c != TILE_T2) || (dh == 128 && c == TILE_L);
 }
 static hipError_t run_rope(GemmLaunch& g, hipStream_t s) {
   switch (bf16_tile_choice(g)) {
