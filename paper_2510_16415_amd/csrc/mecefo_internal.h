@@ -52,9 +52,10 @@ struct GemmProblem {
   const float* rowvec;   // attention epilogues: fp32 per output row, product z starts at z * M
   float scale;           // attention epilogues, EPI_POLY
   const float* addend;   // EPI_POLY, EPI_HILO: fp32 [M x ldc], may be NULL (zero); may be C0 of EPI_HILO itself
-  float poly_a, poly_b;  // EPI_POLY
-  int rope_half, rope_seq;   // EPI_ROPE: half the head dimension (0: plain store) and the sequence length; rowvec and
-                             // addend are the cosine and sine tables [rope_seq][rope_half]
+  union {                // one epilogue uses one pair: kernel arguments are read by every workgroup before it can start
+    struct { float poly_a, poly_b; };      // EPI_POLY
+    struct { int rope_half, rope_seq; };   // EPI_ROPE: half the head dimension (0: plain store) and the sequence length;
+  };                                       // rowvec and addend are the cosine and sine tables [rope_seq][rope_half]
   int causal;            // CausalK
 };
 
