@@ -250,6 +250,7 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const K
   constexpr int BN_OUT = DUAL ? BN / 2 : BN;
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem_all[];
 
+  touch_args(args);
   const int group = KG > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NT) : 0;
   const int t = threadIdx.x - group * NT;      // thread, wave and LDS buffers within the group
   const int lane = t & 63;

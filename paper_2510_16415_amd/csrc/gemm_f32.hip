@@ -92,6 +92,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const KArgs args) {
   constexpr int KG = Cfg::KSPLIT ? FK / 64 : FK / 16;       // groups of 16 K per wave and stage
   __shared__ __attribute__((aligned(16))) float lds[2][MATS][FT * FS];
   static_assert(!Cfg::KSPLIT || 4 * NB * FT * (FT + 1) <= 2 * MATS * FT * FS, "the partial tiles reuse the operand buffers");
+  touch_args(args);
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int nblocks = args.total_tiles * args.splits;
