@@ -166,8 +166,9 @@ struct Workspace {
   int64_t c_elems[3];
 };
 
-// Split count for the token contraction of Eq. (2): the outputs ([f x r], [d x r]) are small, so
-// the long token dimension is cut to get enough workgroups for 256 CUs.
+// Most parts the token contraction of Eq. (2) may be cut into (what the workspace holds partials for): the outputs
+// ([f x r], [d x r]) are small, so the long token dimension gives workgroups for 256 CUs.  The launch takes as many of
+// them as its cost model finds worth their summation.
 int choose_splits(const Ctx& c, const int64_t c_rows[3], const int r[3]) {
   int tiles_l = 0, tiles_s = 0, tiles_f = 0;
   for (int i = 0; i < 3; ++i) {
@@ -180,9 +181,8 @@ int choose_splits(const Ctx& c, const int64_t c_rows[3], const int r[3]) {
   if (!c.bf16) { tiles = tiles_f; ktiles = cdiv((int)c.b, 16); target = 512; }
   else if (tiles_l >= 160) { tiles = tiles_l; ktiles = cdiv((int)c.b, 64); target = 256; }
   else {
-    // Mid-size layers: 256 x 256 tiles on the direct-to-LDS kernel, cut along the tokens into just
-    // enough parts for half the chip, beat 128 x 128 tiles as long as every part keeps eight K
-    // stages (the launcher applies the same rule when it picks the tile configuration).
+    // Mid-size layers: 256 x 256 tiles cut along the tokens into just enough parts for half the chip, as long
+    // as every part keeps eight K stages.
     ktiles = cdiv((int)c.b, 64);
     const int s_l = tiles_l > 0 ? cdiv(128, tiles_l) : 0;
     if (s_l >= 1 && s_l <= 16 && ktiles / s_l >= 8) return s_l;
@@ -196,9 +196,9 @@ int choose_splits(const Ctx& c, const int64_t c_rows[3], const int r[3]) {
   return s < 1 ? 1 : s;
 }
 
-// K splits for a launch that stores activation-dtype outputs but has too few 256 x 256 tiles to fill
-// the chip (mid-size layers: dU = dG Wg + dZ Wu with a small d, the projections with a small r):
-// the long contraction is cut so that about 256 workgroups exist, fp32 partials are summed in order.
+// Most K splits of a launch that stores activation-dtype outputs but has too few 256 x 256 tiles to fill
+// the chip (mid-size layers: dU = dG Wg + dZ Wu with a small d, the projections with a small r): the long
+// contraction may be cut until about 256 workgroups exist, fp32 partials are summed in order.
 constexpr int kMaxStoreSplits = 4;
 int store_splits(bool bf16, int tiles_large, int min_stages) {
   if (!bf16 || tiles_large <= 0 || tiles_large >= 128 || min_stages < 32) return 1;
