@@ -398,7 +398,7 @@ mecefo_status_t mecefo_profile_clock_mhz(double* mhz_by_stage);
 mecefo_status_t mecefo_init(void);
 
 /* Process-wide switches for tests and measurements (not needed for normal use; the library chooses
- * by shape).  name "tile": bf16 GEMM configuration, value "auto" | "S" (128x128) | "L4" | "L8R" (256x256,
+ * by shape).  name "tile": bf16 GEMM configuration, value "auto" | "S" (128x128, direct-to-LDS) | "L4" | "L8R" (256x256,
  * register-staged) | "L8" (256x256, direct-to-LDS).  name "attention": "auto" | "gemm" (batched GEMM
  * launches instead of the fused attention kernels).  Affects calls made after it returns. */
 mecefo_status_t mecefo_set_option(const char* name, const char* value);
