@@ -9,7 +9,7 @@
 // tiles are added through LDS in a fixed order.  Launches with 64 x 64 tiles for every CU take those, each wave
 // a 32 x 32 quarter, K stages of 32: half the operand bytes per multiply-add.
 // Measured against the kernel before (64 x 64 tiles of plain FMAs, K slices of 16, loads in front of their use):
-// one layer's skip backward at the sizes above 574 -> 71.5 us, the exact FFN backward of 1024 tokens, d = 512,
+// one layer's skip backward at the sizes above 574 -> 69 us, the exact FFN backward of 1024 tokens, d = 512,
 // f = 1536 937 -> 217 us and of 2048 tokens, d = 2048, f = 5461 8258 -> 4001 us; errors against fp64 are the same
 // (64 x 64 tiles) or half (the split sums) of what they were.
 #include "gemm_common.hip.h"
@@ -38,24 +38,28 @@ template <class Cfg, bool kc>
 struct TileF32 {
   static constexpr int NV = Cfg::NV, FT = Cfg::FT, FK = Cfg::FK;
   f32x4_t v[NV];
-  uint32_t voff[NV], step;      // byte offsets at K = 0, bytes per K
-  int bytes;                    // range of the buffer
+  uint32_t voff[NV];            // byte offsets within the tile's rows (K-contiguous) or the stage's K rows
+  int64_t total, first, ld4;    // bytes of the matrix, bytes in front of the tile's first row, bytes per row
   __device__ inline int row(int t, int i) const { const int c = t + 256 * i; return kc ? c / (FK / 4) : c % (FT / 4) * 4; }
   __device__ inline int kk(int t, int i) const { const int c = t + 256 * i; return kc ? c % (FK / 4) * 4 : c / (FT / 4); }
   __device__ inline void init(int t, int64_t ld, int row0, int rows, int K) {
-    const int64_t span = kc ? (int64_t)(rows - 1) * ld + K : (int64_t)(K - 1) * ld + rows;
-    bytes = __builtin_amdgcn_readfirstlane(K > 0 ? (int)(span * 4) : 0);
-    step = (uint32_t)(kc ? 4 : ld * 4);
+    ld4 = ld * 4;
+    total = K > 0 ? (kc ? (rows - 1) * ld4 + K * (int64_t)4 : (K - 1) * ld4 + rows * (int64_t)4) : 0;
+    first = kc ? row0 * ld4 : 0;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int r = row0 + row(t, i), k = kk(t, i);
-      voff[i] = r < rows ? (uint32_t)((kc ? (int64_t)r * ld + k : (int64_t)k * ld + r) * 4) : 0x80000000u;
+      voff[i] = r < rows ? (uint32_t)((kc ? (int64_t)(r - row0) * ld + k : (int64_t)k * ld + r) * 4) : 0x80000000u;
     }
   }
   __device__ inline void load(const void* base, int t, int k0, int K) {
     const bool tail = k0 + FK > K;              // wave-uniform
-    const uint32_t soff = (uint32_t)k0 * step;
-    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+    // rows are addressed from the tile (or stage): a projection's row stride is not bounded, so the matrix may be
+    // longer than the 2 GiB a buffer spans
+    const int64_t at = kc ? first : k0 * ld4, left = total - at;
+    const uint32_t soff = kc ? (uint32_t)k0 * 4 : 0;
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<void*>(base) + at, 0,
+                                                                       (int)(left < 0x7FFFFFFF ? left : 0x7FFFFFFF), 0x00020000);
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const uint32_t off = tail && k0 + kk(t, i) >= K ? 0x80000000u : voff[i];

@@ -99,3 +99,25 @@ def test_exact_backward_products_f32(b, d, f):
     for got, n, want in ((dU, d, dg @ wg + dz @ wu), (dWg, d, dg.T @ u), (dWu, d, dz.T @ u), (dWd, f, dy.T @ a)):
         assert relerr(got[:, :n], want) <= 1e-5
         assert bool(got[:, n:].isnan().all())
+
+
+def test_f32_projection_with_a_row_stride_beyond_the_buffer_range():
+    """A projection whose rows lie so far apart that the matrix spans more than 2 GiB is read like a dense one."""
+    b, d, f, r = 70, 96, 130, 8
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda")   # noqa: E731
+    U, dY, Wg, Wu, Wd = rnd(b, d), rnd(b, d), rnd(f, d) * 0.1, rnd(f, d) * 0.1, rnd(d, f) * 0.1
+    dense = [rnd(n, r) for n in (d, d, f)]
+    far = torch.empty(f, 4400000, device="cuda")          # 130 rows of 17.6 MB: 2.29 GB
+    far[:, :r] = dense[2]
+    desc = B.make_desc(b, d, f, B.F32, B.F32, d, f, d, f, 1e-6)
+    ws = torch.empty(B.mecefo_workspace_bytes(desc, r, r, r), dtype=torch.uint8, device="cuda")
+    out = []
+    for last in (dense[2], far):
+        g = [torch.zeros(*s, device="cuda") for s in ((b, d), (f, d), (f, d), (d, f))]
+        B.mecefo_ffn_bwd_lowrank(desc, U, dY, Wg, Wu, Wd, B.proj(dense[0], r), B.proj(dense[1], r), B.proj(last, r),
+                                 B.SIDE_INPUT, g[0], g[1], g[2], g[3], 0, ws)
+        torch.cuda.synchronize()
+        out.append(g)
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
