@@ -20,30 +20,37 @@ namespace {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4f_t;
 
-// FT x FT output tile, K stages of FK; KSPLIT: the four waves share out K, else the tile.
-template <int FT_, int FK_, bool KSPLIT_> struct F32Cfg {
+// FT x FT output tile, K stages of FK; KSPLIT: the four waves share out K, else the tile; FAR: rows addressed in 64 bits.
+template <int FT_, int FK_, bool KSPLIT_, bool FAR_ = false> struct F32Cfg {
   static constexpr int FT = FT_, FK = FK_;
-  static constexpr bool KSPLIT = KSPLIT_;
+  static constexpr bool KSPLIT = KSPLIT_, FAR = FAR_;
   static constexpr int FS = FK + 4;           // LDS row stride (floats): the 16 rows of an operand read fall on different banks
   static constexpr int NV = FT * FK / 1024;   // four-element loads per thread, operand and stage
 };
 using CfgSmall = F32Cfg<32, 64, true>;
 using CfgWide = F32Cfg<64, 32, false>;
+using CfgFar = F32Cfg<32, 64, true, true>;
 
 // One operand tile, [FT rows][FK] in LDS.  A load takes four consecutive elements of the source's rows (dword
 // alignment is enough): K-contiguous four K of a row, K-strided four rows of one K.  The buffer range is the
 // matrix itself, so what lies behind its last element reads as zero; rows and K outside the matrix are pointed
-// behind the range.
+// behind the range.  The offsets from the first row of a tile (or K row of a stage) are 32 bits wide, which every
+// tensor below 2 GiB allows.  A projection's row stride is not bounded: rows that lie further apart are read element
+// by element through 64-bit addresses (FAR).
 template <class Cfg, bool kc>
 struct TileF32 {
   static constexpr int NV = Cfg::NV, FT = Cfg::FT, FK = Cfg::FK;
   f32x4_t v[NV];
   uint32_t voff[NV];            // byte offsets within the tile's rows (K-contiguous) or the stage's K rows
   int64_t total, first, ld4;    // bytes of the matrix, bytes in front of the tile's first row, bytes per row
+  int row0, rows;               // FAR
   __device__ inline int row(int t, int i) const { const int c = t + 256 * i; return kc ? c / (FK / 4) : c % (FT / 4) * 4; }
   __device__ inline int kk(int t, int i) const { const int c = t + 256 * i; return kc ? c % (FK / 4) * 4 : c / (FT / 4); }
-  __device__ inline void init(int t, int64_t ld, int row0, int rows, int K) {
+  __device__ inline void init(int t, int64_t ld, int first_row, int n_rows, int K) {
+    row0 = first_row;
+    rows = n_rows;
     ld4 = ld * 4;
+    if constexpr (Cfg::FAR) return;
     total = K > 0 ? (kc ? (rows - 1) * ld4 + K * (int64_t)4 : (K - 1) * ld4 + rows * (int64_t)4) : 0;
     first = kc ? row0 * ld4 : 0;
 #pragma unroll
@@ -53,9 +60,18 @@ struct TileF32 {
     }
   }
   __device__ inline void load(const void* base, int t, int k0, int K) {
+    if constexpr (Cfg::FAR) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int r = row0 + row(t, i), k = k0 + kk(t, i);
+        const float* q = (const float*)((const char*)base + (kc ? (int64_t)r * ld4 + k * (int64_t)4 : (int64_t)k * ld4 + r * (int64_t)4));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[i][e] = (kc ? r < rows && k + e < K : k < K && r + e < rows) ? q[e] : 0.f;
+      }
+      return;
+    }
     const bool tail = k0 + FK > K;              // wave-uniform
-    // rows are addressed from the tile (or stage): a projection's row stride is not bounded, so the matrix may be
-    // longer than the 2 GiB a buffer spans
+    // the base moves with the tile (or stage): the matrix may be longer than the 2 GiB a buffer spans
     const int64_t at = kc ? first : k0 * ld4, left = total - at;
     const uint32_t soff = kc ? (uint32_t)k0 * 4 : 0;
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<void*>(base) + at, 0,
@@ -248,9 +264,24 @@ hipError_t run_f32_cfg(GemmLaunch& g, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Whether the rows of one tile (K-contiguous operand) or the K rows of one stage span 2 GiB or more.  Only a
+// projection can: it is B of the project products and A or B of the expand products.
+inline bool f32_far(const GemmLaunch& g) {
+  auto span = [](int64_t ld, int rows) { return ld * 4 * (rows < 64 ? rows : 64); };
+  for (int i = 0; i < g.nprob; ++i) {
+    const GemmProblem& p = g.p[i];
+    if (span(p.lda, g.a_kcontig ? p.M : p.K) >= (int64_t)1 << 31 || span(p.ldb, g.b_kcontig ? p.N : p.K) >= (int64_t)1 << 31) return true;
+  }
+  return false;
+}
+
 // 64 x 64 tiles once they give every CU two workgroups.
 template <int EPI>
 hipError_t run_f32(GemmLaunch& g, hipStream_t stream) {
+  if (f32_far(g)) {
+    if constexpr (EPI == EPI_STORE || EPI == EPI_GRAD) return run_f32_cfg<CfgFar, EPI>(g, stream);
+    else return hipErrorInvalidValue;
+  }
   const int splits = EPI == EPI_SPLIT_F32 && g.splits > 1 ? g.splits : 1;
   return f32_tiles(g, 64) * splits >= 512 ? run_f32_cfg<CfgWide, EPI>(g, stream) : run_f32_cfg<CfgSmall, EPI>(g, stream);
 }

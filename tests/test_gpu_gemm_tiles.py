@@ -121,3 +121,31 @@ def test_f32_projection_with_a_row_stride_beyond_the_buffer_range():
         out.append(g)
     for x, y in zip(*out):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("side", [B.SIDE_INPUT, B.SIDE_OUTPUT])
+@pytest.mark.parametrize("ld", [8_388_607, 9_000_001, 18_000_000])
+def test_f32_projection_whose_tile_rows_span_more_than_32_bits(ld, side):
+    """Rows 36 MB apart put the last of a stage's 64 K rows (project) behind 2 GiB, rows of 72 MB those of a
+    32-row tile (expand) as well, and the 64 K rows behind 4 GiB.  8388607 is the last stride in reach of 32-bit
+    offsets.  Both sides read a projection in both products; the results are those of the dense matrix."""
+    b, d, f, r = 70, 96, 130, 8
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda")   # noqa: E731
+    U, dY, Wg, Wu, Wd = rnd(b, d), rnd(b, d), rnd(f, d) * 0.1, rnd(f, d) * 0.1, rnd(d, f) * 0.1
+    rows = (d, d, f) if side == B.SIDE_INPUT else (f, f, d)
+    dense = [rnd(n, r) for n in rows]
+    which = rows.index(f)
+    far = torch.empty(f, ld, device="cuda")
+    far[:, :r] = dense[which]
+    desc = B.make_desc(b, d, f, B.F32, B.F32, d, f, d, f, 1e-6)
+    ws = torch.empty(B.mecefo_workspace_bytes(desc, r, r, r), dtype=torch.uint8, device="cuda")
+    out = []
+    for last in (dense[which], far):
+        P = [last if i == which else t for i, t in enumerate(dense)]
+        g = [torch.zeros(*s, device="cuda") for s in ((b, d), (f, d), (f, d), (d, f))]
+        B.mecefo_ffn_bwd_lowrank(desc, U, dY, Wg, Wu, Wd, *(B.proj(p, r) for p in P), side, *g, 0, ws)
+        torch.cuda.synchronize()
+        out.append(g)
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
