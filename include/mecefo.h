@@ -38,7 +38,8 @@
  * be 16-byte aligned and all row strides multiples of 8 elements (so an odd d_ff such
  * as 5461 needs ld >= 5464); columns between the logical width and the stride are
  * never read as data.  dtype MECEFO_F32: no alignment rule beyond 4 bytes.
- * Every tensor must be smaller than 2 GiB.  With tokens == 0 the [b x *] pointers may be NULL.
+ * Every tensor must be smaller than 2 GiB, counted from its first element to its last (an fp32
+ * projection may span more).  With tokens == 0 the [b x *] pointers may be NULL.
  *
  * Errors: argument checks happen on the host before anything is enqueued; on a
  * non-OK status nothing was launched by that call (MECEFO_ERR_LAUNCH excepted) and

@@ -119,6 +119,9 @@ mecefo_status_t check_proj(const Ctx& c, const mecefo_proj_t& P, int dim, const 
   if (P.ld < P.r) return fail(MECEFO_ERR_INVALID_ARG, "projection %s: ld %lld < r %d", name, (long long)P.ld, P.r);
   if (c.bf16 && (P.ld % 8 || ((uintptr_t)P.P) % 16))
     return fail(MECEFO_ERR_INVALID_ARG, "projection %s: bf16 path needs ld %% 8 == 0 and a 16-byte aligned pointer", name);
+  // the bf16 kernels address a whole operand with 32-bit offsets: rows behind 2 GiB would read as zeros
+  if (c.bf16 && dim > 1 && P.ld > (0x7FFFFFFF / 2 - P.r) / (dim - 1))
+    return fail(MECEFO_ERR_UNSUPPORTED, "projection %s: %d rows of stride %lld reach 2 GiB", name, dim, (long long)P.ld);
   return MECEFO_OK;
 }
 

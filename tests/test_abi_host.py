@@ -78,6 +78,25 @@ def test_null_and_rank_validation_happens_before_any_launch():
     assert st == B.ERR_INVALID_ARG and "side" in B.mecefo_last_error()
 
 
+@pytest.mark.parametrize("side", [B.SIDE_INPUT, B.SIDE_OUTPUT])
+def test_bf16_projection_beyond_the_buffer_range_is_rejected(side):
+    """bf16 operands are addressed with 32-bit offsets: the projection with the most rows (f = 104) may end at the
+    last byte below 2 GiB, not behind it.  fp32 ones are not bounded."""
+    lib = B.lib()
+    f = 104
+    fake = C.c_void_p(0x10000)
+    last = ((2**31 - 1) // 2 - 8) // (f - 1) // 8 * 8          # (f - 1) ld + r elements of two bytes below 2 GiB
+    for dtype, ld, want in ((B.BF16, last, B.ERR_WORKSPACE_TOO_SMALL), (B.BF16, last + 8, B.ERR_UNSUPPORTED),
+                            (B.BF16, 1 << 40, B.ERR_UNSUPPORTED), (B.F32, 1 << 40, B.ERR_WORKSPACE_TOO_SMALL)):
+        d = B.make_desc(16, 64, f, dtype)
+        P = [B.Proj(0x1000, 8, 8) for _ in range(3)]
+        P[2 if side == B.SIDE_INPUT else 1] = B.Proj(0x1000, 8, ld)
+        st = lib.mecefo_block_bwd_skip(C.byref(d), fake, fake, fake, fake, fake, fake, *P, side,
+                                       fake, fake, fake, fake, fake, 0, fake, 16, None)
+        assert st == want, (dtype, ld, B.mecefo_last_error())
+        assert st != B.ERR_UNSUPPORTED or "reach 2 GiB" in B.mecefo_last_error()
+
+
 def test_partially_overlapping_dx_is_rejected():
     """dX may be dOut or H themselves (in-place) or lie apart from them; a partial overlap would let the
     Eq. (2) launches read rows of dOut that the norm backward has already overwritten."""
