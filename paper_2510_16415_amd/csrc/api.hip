@@ -1144,7 +1144,8 @@ mecefo_status_t block_fwd(const mecefo_ffn_desc_t* desc, const mecefo_attn_desc_
     void* dst[3] = {Q, K, V};
     const void* wt[3] = {in->Wq, in->Wk, in->Wv};
     for (int i = 0; i < 3; ++i) g.p[i] = prob(Xn, nullptr, dm, wt[i], nullptr, a.ld_w_dd, dst[i], nullptr, nullptr, ldq, b, dm, dm, 1);
-    const bool rotate = c.bf16 && gemm_bf16_rope_ok(g, dh);
+    g.tile = c.bf16 ? gemm_bf16_rope_tile(g, dh) : -1;
+    const bool rotate = g.tile >= 0;
     if (rotate) {
       g.epi = EPI_ROPE;
       for (int i = 0; i < 2; ++i) { g.p[i].rope_half = dh / 2; g.p[i].rope_seq = S; g.p[i].rowvec = cs; g.p[i].addend = sn; }

@@ -44,7 +44,8 @@ using PipeT2 = DtlPipe<CfgT, 3, 2>;   // 96 KiB: one workgroup per CU, two group
 // The 64 x 64 workgroup is a chain of short stages (LDS reads, four MFMAs, barrier, fill addresses: 0.35 to 0.44 us);
 // two groups of waves halve it where the CU would hold no second workgroup and K has sixteen stages to share:
 // [2048 x 512], two segments of K 1376: 20.3 -> 16.5 us, [512 x 512], K 2048: 15.1 -> 12.0, K 512: 6.8 both.
-enum TileConfig : int { TILE_L = 0, TILE_M2 = 1, TILE_M4 = 2, TILE_T = 3, TILE_T2 = 4, TILE_COUNT = 5 };
+enum TileConfig : int { TILE_L = 0, TILE_M2 = 1, TILE_M4 = 2, TILE_T = 3, TILE_T2 = 4, TILE_COUNT = 5,
+                        TILE_R4 = 5, TILE_R8 = 6 };   // register-staged with four or eight waves: forced only
 
 struct TileModel { int bm, bn, slots; float fixed, per_round, stage_alone, stage_shared; };
 inline const TileModel& tile_model(int c) {
@@ -187,27 +188,20 @@ hipError_t prepare_bf16() {
   return e;
 }
 
-// The configuration of a launch that may be forced to a direct-to-LDS one (1: 128 x 128, 4: 256 x 256); -1 for the
-// register-staged ones.
-inline int bf16_tile_choice(const GemmLaunch& g) {
-  switch (options().tile.load(std::memory_order_relaxed)) {
-    case 1: return TILE_M2;
-    case 2: case 3: return -1;
-    case 4: return TILE_L;
-    default: return bf16_best_tile(g, g.epi == EPI_SPLIT_F32 && g.splits > 1 ? g.splits : 1);
-  }
+// The configuration mecefo_set_option("tile", ...) forces, -1 when the model decides.  Another host thread may change
+// the option at any time: whoever needs the answer twice for one launch keeps it.
+inline int bf16_forced_tile() {
+  static const int tile[5] = {-1, TILE_M2, TILE_R4, TILE_R8, TILE_L};
+  return tile[options().tile.load(std::memory_order_relaxed)];
 }
 
-// mecefo_set_option("tile", ...) forces 1: 128 x 128, 2 and 3: 256 x 256 register-staged with four or
-// eight waves, 4: 256 x 256 direct-to-LDS; otherwise the model decides.
 template <bool AKC, bool BKC, int EPI>
 hipError_t run_bf16_auto(GemmLaunch& g, hipStream_t stream) {
-  const int c = bf16_tile_choice(g);
-  if (c < 0) {
-    return options().tile.load(std::memory_order_relaxed) == 2 ? run_bf16<CfgL4, AKC, BKC, EPI>(g, stream)
-                                                               : run_bf16<CfgL8, AKC, BKC, EPI>(g, stream);
-  }
+  int c = bf16_forced_tile();
+  if (c < 0) c = bf16_best_tile(g, g.epi == EPI_SPLIT_F32 && g.splits > 1 ? g.splits : 1);
   switch (c) {
+    case TILE_R4: return run_bf16<CfgL4, AKC, BKC, EPI>(g, stream);
+    case TILE_R8: return run_bf16<CfgL8, AKC, BKC, EPI>(g, stream);
     case TILE_M2: return run_bf16<CfgM, AKC, BKC, EPI, PipeM2>(g, stream);
     case TILE_M4: return run_bf16<CfgM8, AKC, BKC, EPI, PipeM4>(g, stream);
     case TILE_T: return run_bf16<CfgT, AKC, BKC, EPI, PipeT>(g, stream);

@@ -7,19 +7,20 @@ namespace mecefo {
 // of a 256 x 256 tile's wave and the 64 of a 128 x 128 one do for head dimensions 64 and 128 or 64.
 // The two rotations as launches cost about 7 us in all on small calls (3.4 us each and the gap), more on large
 // ones: a tile that can rotate is taken when the model puts it within 6 us of the best one (an 8-layer stack of
-// d = 512, 2048 tokens, whose 64 x 64 and 128 x 128 tiles are a tie: 1201 -> 1183 us).  -1: none.
-static int rope_tile(const GemmLaunch& g, int dh) {
-  const int forced = bf16_tile_choice(g);
-  if (options().tile.load(std::memory_order_relaxed)) return (forced == TILE_L && (dh == 64 || dh == 128)) || (dh == 64 && forced == TILE_M2) ? forced : -1;
+// d = 512, 2048 tokens, whose 64 x 64 and 128 x 128 tiles are a tie: 1201 -> 1183 us).
+int gemm_bf16_rope_tile(const GemmLaunch& g, int dh) {
+  const int forced = bf16_forced_tile();
+  if (forced >= 0) return (forced == TILE_L && (dh == 64 || dh == 128)) || (dh == 64 && forced == TILE_M2) ? forced : -1;
   if (dh != 64 && dh != 128) return -1;
   int best = TILE_L;
   for (int c : {TILE_M2, TILE_M4})
     if (dh == 64 && bf16_tile_cost(g, c, 1) < bf16_tile_cost(g, best, 1)) best = c;
-  return bf16_tile_cost(g, best, 1) <= bf16_tile_cost(g, forced, 1) + 6.f ? best : -1;
+  float least;
+  bf16_best_tile(g, 1, &least);
+  return bf16_tile_cost(g, best, 1) <= least + 6.f ? best : -1;
 }
-bool gemm_bf16_rope_ok(const GemmLaunch& g, int dh) { return rope_tile(g, dh) >= 0; }
 static hipError_t run_rope(GemmLaunch& g, hipStream_t s) {
-  switch (rope_tile(g, 2 * g.p[0].rope_half)) {
+  switch (g.tile) {
     case TILE_L: return run_bf16<CfgL8, true, true, EPI_ROPE, PipeL, false>(g, s);
     case TILE_M2: return run_bf16<CfgM, true, true, EPI_ROPE, PipeM2>(g, s);
     case TILE_M4: return run_bf16<CfgM8, true, true, EPI_ROPE, PipeM4>(g, s);

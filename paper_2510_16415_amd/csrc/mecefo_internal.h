@@ -67,6 +67,7 @@ struct GemmLaunch {
   bool bf16;        // operand dtype (bf16 MFMA path) or fp32
   bool out_f32;     // EPI_GRAD: gradient buffer dtype is fp32 (else same as operands)
   int accumulate;   // EPI_GRAD
+  int tile;         // EPI_ROPE: the configuration that gemm_bf16_rope_tile found for this launch
   int splits;       // EPI_SPLIT_F32: number of K splits (partials laid out [split][M x ldc] per problem)
   float* partial;   // EPI_SPLIT_F32: base of the partial buffer; problem i starts at partial_off[i]
   int64_t partial_off[3];
@@ -106,8 +107,8 @@ Options& options();
 hipError_t prepare_gemm_bf16_nt();
 hipError_t prepare_gemm_bf16_nn();
 hipError_t prepare_gemm_bf16_tn();
-// Whether the bf16 launch (NT layout) may carry EPI_ROPE for heads of dimension dh.
-bool gemm_bf16_rope_ok(const GemmLaunch& g, int dh);
+// The configuration with which the bf16 launch (NT layout) carries EPI_ROPE for heads of dimension dh; -1: none.
+int gemm_bf16_rope_tile(const GemmLaunch& g, int dh);
 hipError_t prepare_attention_fwd();
 hipError_t prepare_attention_bwd();
 

@@ -155,3 +155,44 @@ def test_config_c5_block_fwd_whole_batch():
     fwd = Forward(blk, heads, batch, seq)
     got = fwd.run()
     print("C5 fwd, whole batch", assert_close(got, want, TOL["bf16"], label="C5 fwd: "))
+
+
+def test_tile_option_changed_by_another_thread_during_a_forward():
+    """The switch may change between any two launches of a call: whether Q and K are rotated in the product's
+    epilogue is one decision, whatever the switch says when the product is launched (one head of dimension 128:
+    "auto" rotates in the epilogue, "S" in a launch of its own).  Every call succeeds with the usual error."""
+    import threading
+    b, S, heads, d, f = 1, 64, 1, 128, 344
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    rnd = lambda n, k, s=1.0: (torch.randn(n, k, generator=gen, device="cuda") * s).to(torch.bfloat16)   # noqa: E731
+    inp = dict(X=rnd(S, d), g_attn=torch.ones(d, dtype=torch.bfloat16, device="cuda"),
+               g_ffn=torch.ones(d, dtype=torch.bfloat16, device="cuda"),
+               **{k: rnd(d, d, d ** -0.5) for k in ("Wq", "Wk", "Wv", "Wo")},
+               Wg=rnd(f, d, d ** -0.5), Wu=rnd(f, d, d ** -0.5), Wd=rnd(d, f, f ** -0.5))
+    desc, attn = B.make_desc(b * S, d, f, B.BF16), B.make_attn_desc(b, S, heads, d)
+    ws = torch.empty(B.mecefo_block_fwd_workspace_bytes(desc, attn), dtype=torch.uint8, device="cuda")
+    mk = lambda: dict(Out=torch.empty(S, d, dtype=torch.bfloat16, device="cuda"),   # noqa: E731
+                      H=torch.empty(S, d, dtype=torch.bfloat16, device="cuda"))
+    ref = mk()
+    B.mecefo_block_fwd(desc, attn, inp, ref, ws)
+    stop = threading.Event()
+
+    def toggle():
+        while not stop.is_set():
+            B.mecefo_set_option("tile", "S")
+            B.mecefo_set_option("tile", "auto")
+    thread = threading.Thread(target=toggle)
+    thread.start()
+    try:
+        for i in range(20):
+            out = mk()
+            for _ in range(200):
+                B.mecefo_block_fwd(desc, attn, inp, out, ws)
+            torch.cuda.synchronize()
+            for k in ("Out", "H"):
+                err = (out[k].double() - ref[k].double()).norm() / ref[k].double().norm()
+                assert float(err) <= TOL["bf16"], (i, k, float(err))
+    finally:
+        stop.set()
+        thread.join()
+        B.mecefo_set_option("tile", "auto")
