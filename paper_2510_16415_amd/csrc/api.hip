@@ -539,11 +539,13 @@ struct FwdWs {
   size_t Xn, rstd, Q, K, V, O, L, A, S32, P, cs, sn, total;
   int64_t ldp;
   int hc;        // heads per attention chunk
+  bool fused;    // the attention kernel without scores; read from the switch once per public call
 };
 
 // The block forward takes the fused attention kernel (no score or probability buffer) whenever it is
 // built for the shape; mecefo_set_option("attention", "gemm") keeps the materialised-score form for testing.  The
-// workspace query and the call consult the same predicate.
+// workspace query and the call consult the same predicate.  The layout carries its answer: another host thread may
+// change the switch during the call, and the regions behind the scores lie elsewhere in the other form.
 bool fwd_attention_fused(const Ctx& c, const mecefo_attn_desc_t& a) {
   if (options().attn_gemm.load(std::memory_order_relaxed)) return false;
   // bf16 descriptors have row strides that are multiples of 8 (checked with the descriptor)
@@ -568,20 +570,20 @@ FwdWs fwd_layout(const Ctx& c, const mecefo_attn_desc_t& a) {
   if (hc < 1) hc = 1;
   if (hc > a.heads) hc = a.heads;
   w.hc = (int)hc;
-  const bool fused = fwd_attention_fused(c, a);
-  w.S32 = take(fused ? 0 : (size_t)hc * per_head);
-  w.P = take(fused ? 0 : (size_t)hc * a.seq * w.ldp * c.esz);
+  w.fused = fwd_attention_fused(c, a);
+  w.S32 = take(w.fused ? 0 : (size_t)hc * per_head);
+  w.P = take(w.fused ? 0 : (size_t)hc * a.seq * w.ldp * c.esz);
   w.cs = take((size_t)a.seq * (dh / 2) * 4);
   w.sn = take((size_t)a.seq * (dh / 2) * 4);
   w.total = off + 256;
   return w;
 }
 
-// The block forward behind mecefo_block_fwd; tables_ready: the workspace holds the rotary tables of a previous
-// layer of the same public call.
+// The block forward behind mecefo_block_fwd.  plan: the layout that every layer of one public call shares, NULL to
+// make it here; tables_ready: the workspace holds the rotary tables of a previous layer of the same plan.
 mecefo_status_t block_fwd(const mecefo_ffn_desc_t* desc, const mecefo_attn_desc_t* attn,
-                          const mecefo_block_fwd_inputs_t* in, const mecefo_block_fwd_outputs_t* out, void* ws,
-                          size_t ws_bytes, void* hip_stream, bool tables_ready);
+                          const mecefo_block_fwd_inputs_t* in, const mecefo_block_fwd_outputs_t* out,
+                          const FwdWs* plan, void* ws, size_t ws_bytes, void* hip_stream, bool tables_ready);
 
 mecefo_status_t check_lowrank_args(const Ctx& c, const mecefo_proj_t P[3], mecefo_side_t side, int exact_mask = 0) {
   if (side != MECEFO_SIDE_INPUT && side != MECEFO_SIDE_OUTPUT) return fail(MECEFO_ERR_INVALID_ARG, "side must be MECEFO_SIDE_INPUT or MECEFO_SIDE_OUTPUT");
@@ -1093,15 +1095,15 @@ mecefo_status_t mecefo_block_fwd_workspace_bytes(const mecefo_ffn_desc_t* desc, 
 mecefo_status_t mecefo_block_fwd(const mecefo_ffn_desc_t* desc, const mecefo_attn_desc_t* attn,
                                  const mecefo_block_fwd_inputs_t* in, const mecefo_block_fwd_outputs_t* out,
                                  void* ws, size_t ws_bytes, void* hip_stream) {
-  return block_fwd(desc, attn, in, out, ws, ws_bytes, hip_stream, false);
+  return block_fwd(desc, attn, in, out, nullptr, ws, ws_bytes, hip_stream, false);
 }
 
 }  // extern "C"
 
 namespace {
 mecefo_status_t block_fwd(const mecefo_ffn_desc_t* desc, const mecefo_attn_desc_t* attn,
-                          const mecefo_block_fwd_inputs_t* in, const mecefo_block_fwd_outputs_t* out, void* ws,
-                          size_t ws_bytes, void* hip_stream, bool tables_ready) {
+                          const mecefo_block_fwd_inputs_t* in, const mecefo_block_fwd_outputs_t* out,
+                          const FwdWs* plan, void* ws, size_t ws_bytes, void* hip_stream, bool tables_ready) {
   Ctx c;
   TRY(check_desc(desc, &c));
   TRY(check_attn(c, attn));
@@ -1116,7 +1118,7 @@ mecefo_status_t block_fwd(const mecefo_ffn_desc_t* desc, const mecefo_attn_desc_
   if (given != 0 && given != 5) return fail(MECEFO_ERR_INVALID_ARG, "Q, K, V, O, L must all be given (standard mode) or all be NULL (neighbor mode)");
   TRY(check_ptr(c, out->Q, "Q", false)); TRY(check_ptr(c, out->K, "K", false)); TRY(check_ptr(c, out->V, "V", false)); TRY(check_ptr(c, out->O, "O", false));
   if (any && out->Out == in->X) return fail(MECEFO_ERR_INVALID_ARG, "Out must not alias X");
-  const FwdWs w = fwd_layout(c, *attn);
+  const FwdWs w = plan ? *plan : fwd_layout(c, *attn);
   if (w.total > ws_bytes) return fail(MECEFO_ERR_WORKSPACE_TOO_SMALL, "workspace has %zu bytes, %zu needed", ws_bytes, w.total);
   if (!ws) return fail(MECEFO_ERR_INVALID_ARG, "workspace is NULL");
   if (!any) return MECEFO_OK;
@@ -1157,9 +1159,8 @@ mecefo_status_t block_fwd(const mecefo_ffn_desc_t* desc, const mecefo_attn_desc_
     }
   }
   const float scale = 1.0f / sqrtf((float)dh);
-  const bool fused = fwd_attention_fused(c, a);
-  if (fused) HIP_TRY(launch_attn_fwd(Q, K, V, O, ldq, L, a.batch, S, a.heads, dh, scale, s));
-  for (int bi = 0; bi < (fused ? 0 : a.batch); ++bi)
+  if (w.fused) HIP_TRY(launch_attn_fwd(Q, K, V, O, ldq, L, a.batch, S, a.heads, dh, scale, s));
+  for (int bi = 0; bi < (w.fused ? 0 : a.batch); ++bi)
     for (int h0 = 0; h0 < a.heads; h0 += w.hc) {
       const int hc = a.heads - h0 < w.hc ? a.heads - h0 : w.hc;
       const int64_t tok = ((int64_t)bi * S * ldq + (int64_t)h0 * dh) * c.esz;
@@ -1238,8 +1239,8 @@ mecefo_status_t mecefo_stack_fwd_neighbor(const mecefo_ffn_desc_t* desc, const m
   if (n_layers < 1) return fail(MECEFO_ERR_INVALID_ARG, "n_layers must be >= 1");
   if (!layers || !H) return fail(MECEFO_ERR_INVALID_ARG, "layers and H are required");
   if (c.b > 0 && X_out == X0) return fail(MECEFO_ERR_INVALID_ARG, "X_out must not alias X0");
-  size_t inner = 0;
-  TRY(mecefo_block_fwd_workspace_bytes(desc, attn, &inner));
+  const FwdWs plan = fwd_layout(c, *attn);
+  const size_t inner = plan.total;
   const size_t act = (size_t)up(c.b * desc->ld_act_d * c.esz, 256);
   if (!ws) return fail(MECEFO_ERR_INVALID_ARG, "workspace is NULL");
   char* base = (char*)up((int64_t)(uintptr_t)ws, 256);
@@ -1253,8 +1254,8 @@ mecefo_status_t mecefo_stack_fwd_neighbor(const mecefo_ffn_desc_t* desc, const m
     mecefo_block_fwd_inputs_t in = {x, w.g_attn, w.g_ffn, w.Wq, w.Wk, w.Wv, w.Wo, w.Wg, w.Wu, w.Wd};
     void* y = l == n_layers - 1 ? X_out : pp[l & 1];
     mecefo_block_fwd_outputs_t out = {y, H[l], nullptr, nullptr, nullptr, nullptr, nullptr};
-    // every layer of the call uses the same workspace: the angle tables of the first one serve them all
-    mecefo_status_t st = block_fwd(desc, attn, &in, &out, inner_ws, ws_bytes - lead - 2 * act, hip_stream, l > 0);
+    // every layer of the call uses the same workspace and layout: the angle tables of the first one serve them all
+    mecefo_status_t st = block_fwd(desc, attn, &in, &out, &plan, inner_ws, ws_bytes - lead - 2 * act, hip_stream, l > 0);
     if (st != MECEFO_OK) return st;
     x = y;
   }

@@ -222,6 +222,40 @@ def test_stack_calls_equal_the_per_layer_calls_bit_for_bit():
             assert np.array_equal(a["grads"][l][k], b["grads"][l][k]), (l, k)
 
 
+def test_attention_option_changed_by_another_thread_during_a_stack_forward():
+    """The two attention forms lay out the workspace differently, and the layers of one call share the angle tables
+    that the first one made: the form is decided once per call.  The workspace has the larger form's size and starts
+    at 0xFF in every call.  Whatever form a call takes, it is within the gate of the fused one: a layer's forms differ
+    by the bf16 rounding of the probabilities."""
+    import threading
+    st = Stack(3, 2, 96, 128, 344, 2, 16, "bf16", 3)
+    st.forward()
+    torch.cuda.synchronize()
+    ref = [t.clone() for t in [*st.H, st.Xout]]
+    stop = threading.Event()
+    try:
+        B.mecefo_set_option("attention", "gemm")
+        st.ws = poisoned_ws(B.mecefo_stack_workspace_bytes(st.desc, st.attn, st.r, st.r, st.r))
+
+        def toggle():
+            while not stop.is_set():
+                B.mecefo_set_option("attention", "auto")
+                B.mecefo_set_option("attention", "gemm")
+        thread = threading.Thread(target=toggle)
+        thread.start()
+        for i in range(300):
+            st.ws.fill_(255)
+            st.forward()
+            torch.cuda.synchronize()
+            for got, want in zip([*st.H, st.Xout], ref):
+                err = float((got.double() - want.double()).norm() / want.double().norm())
+                assert err <= TOL["bf16"], (i, err)
+    finally:
+        stop.set()
+        thread.join()
+        B.mecefo_set_option("attention", "auto")
+
+
 def _mixed_setup(seed, modes):
     """A small bf16 stack whose layers are forwarded one by one in standard mode (everything a
     standard-mode backward needs is kept), plus gradient buffers filled with NaN canaries."""
