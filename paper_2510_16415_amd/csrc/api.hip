@@ -640,10 +640,9 @@ mecefo_status_t mecefo_init(void) {
 mecefo_status_t mecefo_set_option(const char* name, const char* value) {
   if (!name || !value) return fail(MECEFO_ERR_INVALID_ARG, "option name and value are required");
   if (!strcmp(name, "tile")) {
-    static const char* const names[5] = {"auto", "S", "L4", "L8R", "L8"};
-    for (int i = 0; i < 5; ++i)
-      if (!strcmp(value, names[i])) { options().tile.store(i, std::memory_order_relaxed); return MECEFO_OK; }
-    return fail(MECEFO_ERR_INVALID_ARG, "option tile: value must be auto, S, L4, L8R or L8 (got %s)", value);
+    for (int i = 0; i < kTileOptions; ++i)
+      if (!strcmp(value, kTileOptionName[i])) { options().tile.store(i, std::memory_order_relaxed); return MECEFO_OK; }
+    return fail(MECEFO_ERR_INVALID_ARG, "option tile: value must be auto, S, S4, T, T2, L4, L8R or L8 (got %s)", value);
   }
   if (!strcmp(name, "attention")) {
     if (!strcmp(value, "auto")) { options().attn_gemm.store(0, std::memory_order_relaxed); return MECEFO_OK; }

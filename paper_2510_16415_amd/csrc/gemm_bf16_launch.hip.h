@@ -191,7 +191,7 @@ hipError_t prepare_bf16() {
 // The configuration mecefo_set_option("tile", ...) forces, -1 when the model decides.  Another host thread may change
 // the option at any time: whoever needs the answer twice for one launch keeps it.
 inline int bf16_forced_tile() {
-  static const int tile[5] = {-1, TILE_M2, TILE_R4, TILE_R8, TILE_L};
+  static const int tile[kTileOptions] = {-1, TILE_M2, TILE_R4, TILE_R8, TILE_L, TILE_M4, TILE_T, TILE_T2};
   return tile[options().tile.load(std::memory_order_relaxed)];
 }
 

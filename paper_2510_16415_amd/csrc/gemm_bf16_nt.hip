@@ -10,7 +10,8 @@ namespace mecefo {
 // d = 512, 2048 tokens, whose 64 x 64 and 128 x 128 tiles are a tie: 1201 -> 1183 us).
 int gemm_bf16_rope_tile(const GemmLaunch& g, int dh) {
   const int forced = bf16_forced_tile();
-  if (forced >= 0) return (forced == TILE_L && (dh == 64 || dh == 128)) || (dh == 64 && forced == TILE_M2) ? forced : -1;
+  if (forced >= 0)
+    return (forced == TILE_L && (dh == 64 || dh == 128)) || (dh == 64 && (forced == TILE_M2 || forced == TILE_M4)) ? forced : -1;
   if (dh != 64 && dh != 128) return -1;
   int best = TILE_L;
   for (int c : {TILE_M2, TILE_M4})

@@ -181,8 +181,8 @@ def test_refresh_schedule_of_alg3_and_counter_reset_of_alg1():
 
 
 def test_set_option_validates_names_and_values():
-    B.mecefo_set_option("tile", "L8")
-    B.mecefo_set_option("tile", "auto")
+    for tile in ("S", "S4", "T", "T2", "L4", "L8R", "L8", "auto"):
+        B.mecefo_set_option("tile", tile)
     B.mecefo_set_option("attention", "gemm")
     B.mecefo_set_option("attention", "auto")
     for name, value in (("tile", "L"), ("tile", "L9"), ("attention", "fast"), ("speed", "max")):

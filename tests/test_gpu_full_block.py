@@ -109,7 +109,7 @@ def test_full_block_bf16_ragged(batch, seq, d, f, heads):
     print(errs)
 
 
-@pytest.mark.parametrize("tile", ["S", "L4", "L8R", "L8"])
+@pytest.mark.parametrize("tile", ["S", "S4", "T", "T2", "L4", "L8R", "L8"])
 def test_full_block_bf16_forced_tiles_cross_the_diagonal(tile, mecefo_option):
     """Sequences longer than two tiles of every configuration, so that the causal clipping of the
     K loops and the skipped tiles above the diagonal are exercised; seq is not a multiple of 8."""
@@ -132,6 +132,16 @@ def test_full_block_bf16_five_product_attention_path(batch, seq, d, heads, mecef
     mecefo_option("attention", "gemm")
     _, _, errs = run_case(9, batch, seq, d, 344, heads, "bf16")
     print(errs)
+
+
+@pytest.mark.parametrize("tile", ["S", "S4", "T", "T2", "L8"])
+def test_full_block_bf16_five_product_attention_on_every_tile(tile, mecefo_option):
+    """The softmax products, whose epilogues and causal clipping know the tile: seq ends inside every tile and, odd,
+    inside a 16-byte chunk of the contraction."""
+    mecefo_option("attention", "gemm")
+    mecefo_option("tile", tile)
+    _, _, errs = run_case(10, 2, 523, 256, 344, 2, "bf16")
+    print(tile, errs)
 
 
 def test_full_block_accumulate_alias_and_bf16_grads():

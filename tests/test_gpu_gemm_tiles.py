@@ -1,6 +1,6 @@
-"""The tile configurations of the bf16 GEMM core behind its size rule, through the public FFN calls: sizes for
-which the rule takes 64 x 64, 128 x 128 (two and four LDS stages) and 256 x 256 tiles, with rows, columns and
-contractions that end inside a tile, inside a 16-byte chunk of K (with NaN behind it), or just past an edge."""
+"""The tile configurations of the bf16 GEMM core through the public FFN calls, forced one by one and as the size rule
+picks them, with rows, columns and contractions that end inside a tile, inside a 16-byte chunk of K (with NaN
+behind it), or just past an edge."""
 import pytest
 import torch
 
@@ -20,16 +20,29 @@ def relerr(got, want):
     return float((got.double() - want.double()).norm() / want.double().norm())
 
 
-# (tokens, d, f): edges of the 64, 128 and 256 tiles and one past them; then one larger size per configuration
+# (tokens, d, f): edges of the 64, 128 and 256 tiles and one past them; long ragged contractions with few output
+# tiles; larger sizes, whose launches the rule spreads over all configurations
 SIZES = [(1, 8, 1), (63, 64, 65), (64, 72, 7), (129, 128, 63), (255, 136, 257), (257, 264, 129),
-         (700, 1000, 1111),      # 64 x 64, several workgroups per CU
-         (3000, 2504, 1107),     # 128 x 128, two per CU
-         (2048, 1536, 2741),     # 128 x 128, long K, one per CU
-         (4100, 4096, 1037)]     # 256 x 256
+         (129, 512, 2741), (2048, 512, 1999),
+         (700, 1000, 1111), (3000, 2504, 1107), (2048, 1536, 2741), (4100, 4096, 1037)]
+# what every configuration is forced onto: a single stage, stages that the wave groups of "T2" share out unevenly, and
+# several workgroups per dimension of the largest tile
+FORCED = [(t, *s) for t in ("S", "S4", "T", "T2", "L8") for s in
+          ((1, 8, 1), (63, 64, 65), (129, 128, 63), (257, 264, 129), (129, 512, 2741), (600, 520, 1111))]
 
 
 @pytest.mark.parametrize("b,d,f", SIZES)
 def test_forward_products_with_a_ragged_contraction(b, d, f):
+    check_forward_products(b, d, f)
+
+
+@pytest.mark.parametrize("tile,b,d,f", FORCED)
+def test_forward_products_on_every_tile(tile, b, d, f, mecefo_option):
+    mecefo_option("tile", tile)
+    check_forward_products(b, d, f)
+
+
+def check_forward_products(b, d, f):
     """A = silu(U Wg^T) * (U Wu^T) and Y = A Wd^T: both operands K-contiguous, K = f ends anywhere.  Error: one
     bf16 rounding of A, one of Y (2^-9 each) and the fp32 sums: the gate of 1e-2 leaves a factor of two."""
     gen = torch.Generator(device="cuda").manual_seed(b * 7 + f)
@@ -50,6 +63,16 @@ def test_forward_products_with_a_ragged_contraction(b, d, f):
 
 @pytest.mark.parametrize("b,d,f", SIZES)
 def test_exact_backward_products(b, d, f):
+    check_exact_backward(b, d, f)
+
+
+@pytest.mark.parametrize("tile,b,d,f", FORCED)
+def test_exact_backward_products_on_every_tile(tile, b, d, f, mecefo_option):
+    mecefo_option("tile", tile)
+    check_exact_backward(b, d, f)
+
+
+def check_exact_backward(b, d, f):
     """dA (K-strided B), the fused SwiGLU backward, dU (two K segments) and the three weight gradients (both
     operands K-strided) against the same steps in fp32 torch.  The library keeps dA, dG, dZ and A in bf16: 2^-9
     per rounding, at most three in a row, below 1e-2 in the norm."""

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
-@pytest.mark.parametrize("tile", ["auto", "L8", "S"])
+@pytest.mark.parametrize("tile", ["auto", "L8", "S", "S4", "T", "T2"])
 def test_first_call_of_a_fresh_process_under_graph_capture(tile):
     child = os.path.join(HERE, "graph_after_init_child.py")
     res = subprocess.run([sys.executable, "-u", child, tile], capture_output=True, text=True, timeout=110)

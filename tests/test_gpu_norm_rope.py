@@ -65,12 +65,24 @@ def rotate(x, seq, heads, dh):
 
 
 @pytest.mark.parametrize("batch,seq,heads,dh,pad", [
-    (1, 5, 1, 64, 0), (2, 33, 2, 128, 8),      # 64 x 64 tiles: rotation as a launch
-    (3, 131, 13, 64, 16),                      # 128 x 128 tiles, ragged rows and columns
-    (4, 1000, 10, 64, 0),                      # 128 x 128 tiles, several workgroups per CU
-    (8, 256, 8, 64, 0),                        # 128 x 128 tiles, one per CU
-    (3, 700, 16, 128, 8), (2, 1100, 30, 64, 0)])   # 256 x 256 tiles
+    (1, 5, 1, 64, 0), (2, 33, 2, 128, 8), (3, 131, 13, 64, 16), (4, 1000, 10, 64, 0), (8, 256, 8, 64, 0),
+    (3, 700, 16, 128, 8), (2, 1100, 30, 64, 0)])
 def test_forward_with_rotation_and_residual_epilogues(batch, seq, heads, dh, pad):
+    """The tile, and whether the rotation is an epilogue, as the size rule has it."""
+    check_forward(batch, seq, heads, dh, pad)
+
+
+@pytest.mark.parametrize("tile,dh", [
+    ("S", 64), ("S4", 64), ("L8", 64), ("L8", 128),                      # rotation in the epilogue
+    ("S", 128), ("S4", 128), ("T", 64), ("T", 128), ("T2", 64)])         # rotation as a launch
+@pytest.mark.parametrize("batch,seq,heads,pad", [(1, 5, 1, 0), (3, 131, 5, 16)])
+def test_forward_with_rotation_on_every_tile(batch, seq, heads, pad, tile, dh, mecefo_option):
+    """One head in one corner of a tile; rows and heads that end inside a tile, positions that wrap inside one."""
+    mecefo_option("tile", tile)
+    check_forward(batch, seq, heads, dh, pad)
+
+
+def check_forward(batch, seq, heads, dh, pad):
     """Q, K (rotated), V and the residual sums H, Out.  bf16 products of a bf16 norm output, one rounding on
     storing: 2^-9 each, below 1e-2; H and Out add a bf16 attention output and FFN of the library's own."""
     b, d, f = batch * seq, heads * dh, 72

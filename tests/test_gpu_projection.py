@@ -79,6 +79,20 @@ def test_refresh_bf16_planted_gap(m, n, r, left, pad):
     assert orth_defect(P) < 1e-2
 
 
+@pytest.mark.parametrize("tile", ["S", "S4", "T", "T2", "L8"])
+@pytest.mark.parametrize("m,n,r,left", [(344, 128, 33, 0), (200, 333, 40, 1)])
+def test_refresh_bf16_on_every_tile(m, n, r, left, tile, mecefo_option):
+    """The polynomial and the hi + lo halves as epilogues of every tile, with ranks, rows and contractions that end
+    inside the tile; gates as above."""
+    mecefo_option("tile", tile)
+    rng = np.random.default_rng([6, m, n, r])
+    W, _, _ = I.planted_spectrum_matrix(rng, m, n, I.spectrum_with_gap(min(m, n), r), "bf16")
+    want = O.projection_from_svd(W.astype(np.float64), r, O.SIDE_OUTPUT if left else O.SIDE_INPUT)
+    P = refresh(W, gaussian_start(6, m if left else n, r), r, "bf16", left=left, iters=8)
+    assert max_principal_sine(P, want) < 1e-2
+    assert orth_defect(P) < 1e-2
+
+
 def test_light_settings_reach_the_bf16_floor():
     """Eight conditioning steps per round (s_1/s_r = 13 here: log(13^2)/log(3.44) + 3 = 7.2) and three
     polishing steps: the settings bench.py times."""
