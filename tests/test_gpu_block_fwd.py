@@ -113,6 +113,53 @@ def test_fused_attention_random_shapes_forward_then_backward():
         print(label, max(errs.values()), max(berrs.values()))
 
 
+@pytest.mark.parametrize("dh", [64, 128])
+def test_fused_attention_with_rising_maxima_and_infinite_scores(dh):
+    """The fused forward rescales only when a query's maximum rises by more than 8 (log2 units) above its reference:
+    scores whose maximum rises from key block to key block by 6 to 10, by little, by a lot and not at all.  Then keys
+    whose scores overflow: -inf is no probability at all, +inf makes the query (and no other) not a number.
+    One head; rotary base 1e30 leaves head dimensions from dh/4 on unrotated, where the scores are made:
+    rows (a, c, e, 0 ...) of rms 1, q = c in two dimensions, k = 14 a in one and 1e38 e in the other."""
+    rng = np.random.default_rng([37, dh])
+    steps = [0, 7.5, 8.5, 6, 10, 0.5, -20, 16.5, 7.8, 8.2, 30, -3, 9]
+    seq, d, f = 64 * len(steps) + 5, dh, 72
+    top = np.cumsum(steps)[np.minimum(np.arange(seq) // 64, len(steps) - 1)]
+    a = (top - 10 * rng.random(seq)) / (1.4427 * 14)                 # scores below the block's maximum ...
+    a[::64] = top[::64] / (1.4427 * 14)                              # ... which its first key has
+    X = np.zeros((seq, d), dtype=np.float32)
+    X[:, 0], X[:, 1] = a, np.sqrt(d - a * a)
+    eye = lambda: np.zeros((d, d), dtype=np.float32)                 # noqa: E731
+    Wq, Wk, Wv, Wo = eye(), eye(), rng.standard_normal((d, d)).astype(np.float32) * d ** -0.5, eye()
+    i, j = dh // 4, dh // 4 + 1
+    Wq[i, 1] = Wq[j, 1] = 1
+    Wk[i, 0], Wk[j, 2] = 14, 1e38
+    g = np.ones(d, dtype=np.float32)
+    W = dict(Wq=Wq, Wk=Wk, Wv=Wv, Wo=Wo, Wg=np.zeros((f, d), np.float32), Wu=np.zeros((f, d), np.float32),
+             Wd=np.zeros((d, f), np.float32), g_attn=g, g_ffn=g)
+    desc, attn = B.make_desc(seq, d, f, B.BF16), B.make_attn_desc(1, seq, 1, d, rope_theta=1e30)
+    for special in ({}, {70: -4.0, 300: -3.0, seq - 20: 4.0}):       # key -> e
+        Xs = X.copy()
+        for key, e in special.items():
+            Xs[key, 2], Xs[key, 1] = e, np.sqrt(d - a[key] ** 2 - e * e)
+        inp = {k: dev(v, "bf16") for k, v in dict(W, X=Xs).items()}
+        out = {k: torch.full((seq, d), float("nan"), dtype=torch.bfloat16, device="cuda") for k in ("Out", "H", "Q", "K", "V", "O")}
+        out["L"] = torch.full((seq,), float("nan"), device="cuda")
+        B.mecefo_block_fwd(desc, attn, inp, out, poisoned_ws(B.mecefo_block_fwd_workspace_bytes(desc, attn)))
+        torch.cuda.synchronize()
+        q, k, v, o = (out[n].float().cpu() for n in ("Q", "K", "V", "O"))
+        # fp32 products, which overflow where the kernel's do
+        s = (q @ k.T * dh ** -0.5).masked_fill(torch.triu(torch.ones(seq, seq, dtype=torch.bool), 1), -float("inf"))
+        assert int(torch.isinf(torch.tril(s)).sum()) == sum(seq - key for key in special)
+        bad = (s == float("inf")).any(1)
+        assert int(bad.sum()) == (20 if special else 0)
+        assert bool(o[bad].isnan().all()) and not bool(out["L"].cpu()[bad].isfinite().any())
+        want = torch.softmax(s.double(), 1)[~bad] @ v.double()
+        err = (o[~bad].double() - want).norm(dim=1) / want.norm(dim=1)
+        assert float(err.max()) <= 1e-2, int(err.argmax())           # bf16 probabilities and output: 2^-9 each
+        # scores up to 90 in fp32 with an FMA on top: 90 x 2^-22 and the rounding of exp2 and log2
+        assert float((out["L"].cpu()[~bad].double() - torch.logsumexp(s[~bad].double(), 1)).abs().max()) <= 1e-3
+
+
 def test_neighbor_mode_forward_keeps_only_h_and_matches_standard_mode():
     p, X, dOut, blk, fwd, std, want, _ = run_fwd(25, 2, 200, 128, 344, 4, "bf16")
     nb = fwd.run(neighbor=True)
