@@ -307,9 +307,9 @@ GemmProblem prob(const void* A0, const void* A1, int64_t lda, const void* B0, co
 }
 
 // A store launch into the library's own buffers (row stride == ldc of every problem), cut along K
-// into up to `most` parts (what the workspace holds partials for) when that fills the chip better.
+// into up to `most` parts (what the workspace holds partials for; 1 for fp32) when that fills the chip better.
 mecefo_status_t launch_store_split(const Ctx& c, const Bufs& bf, GemmLaunch& g, int most, hipStream_t s) {
-  const int splits = most <= 1 ? 1 : c.bf16 ? bf16_plan_splits(g, most) : f32_plan_splits(g, most);
+  const int splits = most > 1 ? bf16_plan_splits(g, most) : 1;
   if (splits <= 1) {
     HIP_TRY(launch_gemm(g, s));
     return MECEFO_OK;

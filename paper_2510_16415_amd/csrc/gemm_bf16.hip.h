@@ -319,28 +319,25 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_bf16_kernel(const KArgs args) {
           const float v2 = DUAL ? acc[i][DUAL ? j + TN / 2 : j][e] : 0.f;
           epilogue_elem<EPI, __bf16>(p, args, tc.prob, tc.split, row, col, v, v2);
         }
-    return;
-  }
-  // Swapped operands: the B fragment was the MFMA's row operand, so a lane holds, for
-  // block (i, j), output row lane%32 and the four consecutive columns 8*g + 4*(lane/32) + 0..3
-  // in accumulator elements 4g..4g+3 (g = 0..3): stores are 8 or 16 bytes wide.
-  const int row_w = m0 + wm * Cfg::WM + lrow;
-  constexpr int TNO = DUAL ? TN / 2 : TN;
-  const int col_w = n0 + wn * (DUAL ? Cfg::WN / 2 : Cfg::WN) + 4 * (lane >> 5);
+  } else {
+    // Swapped operands: the B fragment was the MFMA's row operand, so a lane holds, for
+    // block (i, j), output row lane%32 and the four consecutive columns 8*g + 4*(lane/32) + 0..3
+    // in accumulator elements 4g..4g+3 (g = 0..3): stores are 8 or 16 bytes wide.
+    static_assert(!DUAL, "swapped operands: single products");
+    const int row_w = m0 + wm * Cfg::WM + lrow;
+    const int col_w = n0 + wn * Cfg::WN + 4 * (lane >> 5);
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TNO; ++j)
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        float v[4], v2[4];
+        for (int g4 = 0; g4 < 4; ++g4) {
+          float v[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          v[e] = acc[i][j][4 * g4 + e];
-          v2[e] = DUAL ? acc[i][DUAL ? j + TN / 2 : j][4 * g4 + e] : 0.f;
+          for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * g4 + e];
+          epilogue_vec4<EPI>(p, args, tc.prob, tc.split, row_w + i * 32, col_w + j * 32 + 8 * g4, v);
         }
-        epilogue_vec4<EPI>(p, args, tc.prob, tc.split, row_w + i * 32, col_w + j * 32 + 8 * g4, v, v2);
-      }
+  }
 }
 
 }  // namespace mecefo

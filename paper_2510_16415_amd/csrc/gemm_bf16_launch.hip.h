@@ -47,13 +47,13 @@ using PipeT2 = DtlPipe<CfgT, 3, 2>;   // 96 KiB: one workgroup per CU, two group
 enum TileConfig : int { TILE_L = 0, TILE_M2 = 1, TILE_M4 = 2, TILE_T = 3, TILE_T2 = 4, TILE_COUNT = 5,
                         TILE_R4 = 5, TILE_R8 = 6 };   // register-staged with four or eight waves: forced only
 
-struct TileModel { int bm, bn, slots; float fixed, per_round, stage_alone, stage_shared; };
+struct TileModel { int bm, bn; float fixed, per_round, stage_alone, stage_shared; };
 inline const TileModel& tile_model(int c) {
-  static const TileModel m[TILE_COUNT] = {{256, 256, 1, 3.5f, 2.5f, 1.45f, 1.75f},
-                                          {128, 128, 2, 3.0f, 1.2f, 0.88f, 0.62f},
-                                          {128, 128, 1, 4.5f, 1.2f, 0.70f, 0.72f},
-                                          {64, 64, 3, 2.5f, 0.5f, 0.40f, 0.28f},
-                                          {64, 64, 1, 4.5f, 0.5f, 0.26f, 0.45f}};
+  static const TileModel m[TILE_COUNT] = {{256, 256, 3.5f, 2.5f, 1.45f, 1.75f},
+                                          {128, 128, 3.0f, 1.2f, 0.88f, 0.62f},
+                                          {128, 128, 4.5f, 1.2f, 0.70f, 0.72f},
+                                          {64, 64, 2.5f, 0.5f, 0.40f, 0.28f},
+                                          {64, 64, 4.5f, 0.5f, 0.26f, 0.45f}};
   return m[c];
 }
 

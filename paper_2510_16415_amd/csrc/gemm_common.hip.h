@@ -1,6 +1,8 @@
 // Device-side pieces shared by the bf16 MFMA GEMM and the fp32 GEMM: kernel argument
 // block, block-id -> tile mapping, and the per-element epilogues.
 #pragma once
+#include <stddef.h>
+
 #include "mecefo_internal.h"
 
 namespace mecefo {
@@ -58,6 +60,8 @@ __device__ inline int xcd_remap(int bid, int nblocks) {
 // and the setup behind it fetch them piece by piece, each piece behind the previous one's use, and every first
 // touch of a line is a miss of the scalar cache; after this the pieces are hits.  Six dependent launches of
 // an expert's backward (129 tokens, d 512, f 200): 35.1 -> 32.6 us.
+static_assert(sizeof(KArgs) == 976 && offsetof(KArgs, p[1]) == 232 && offsetof(KArgs, nprob) == 696,
+              "touch_args names a word of every line of this layout");
 __device__ inline void touch_args(const KArgs& a) {
   asm volatile("" :: "s"(a.p[0].A[0]), "s"(a.p[0].ldb), "s"(a.p[0].batch), "s"(a.p[0].c_bo), "s"(a.p[1].A[0]),
                "s"(a.p[1].ldb), "s"(a.p[1].batch), "s"(a.p[1].c_bo), "s"(a.p[2].A[0]), "s"(a.p[2].ldb), "s"(a.p[2].batch),
@@ -170,6 +174,8 @@ template <bool PRECISE> __device__ inline float sigmoid_f(float g) {
   }
 }
 
+template <int EPI> constexpr bool kUnhandledEpilogue = false;
+
 // One output element (single products) or one (gate, up) pair (dual products).
 template <int EPI, typename T>
 __device__ inline void epilogue_elem(const GemmProblem& p, const KArgs& a, int prob, int split,
@@ -264,14 +270,13 @@ __device__ inline void epilogue_elem(const GemmProblem& p, const KArgs& a, int p
       dz[idx] = from_f32<T>(0.f);
       dg[idx] = from_f32<T>(0.f);
     }
+  } else {
+    static_assert(kUnhandledEpilogue<EPI>, "no single-element form of this epilogue");
   }
 }
 
 constexpr bool epi_is_dual(int epi) { return epi == EPI_SWIGLU_FWD || epi == EPI_SWIGLU_BWD; }
 
-// Four consecutive output columns of one row (bf16 storage path): 8-byte stores of bf16 and
-// 16-byte stores of fp32 when the group lies inside the matrix, else element by element.
-// Row strides are multiples of 8 elements and col0 of 4, so the vector accesses are aligned.
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
 
 __device__ inline bf16x4_t pack_bf16x4(float a, float b, float c, float d) {
@@ -280,8 +285,6 @@ __device__ inline bf16x4_t pack_bf16x4(float a, float b, float c, float d) {
   return o;
 }
 
-// Eight consecutive output columns of one row (bf16 outputs, 16-byte accesses), used by the
-// LDS-staged epilogue; falls back to single elements at the ragged right edge.
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8s_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
@@ -292,13 +295,17 @@ __device__ inline bf16x8s_t pack_bf16x8(const float (&v)[8]) {
   return o;
 }
 
+// Eight consecutive output columns of one row (bf16 outputs, 16-byte accesses), used by the
+// LDS-staged epilogue; falls back to single elements at the ragged right edge.
 template <int EPI>
 __device__ inline void epilogue_vec8(const GemmProblem& p, const KArgs& a, int prob, int split, int row,
                                      int col0, const float (&v)[8], const float (&v2)[8]) {
   if (row >= p.M) return;
   if (col0 + 8 > p.N) {
+    if constexpr (EPI != EPI_ROPE) {      // whole heads: never ragged
 #pragma unroll
-    for (int e = 0; e < 8; ++e) epilogue_elem<EPI, __bf16>(p, a, prob, split, row, col0 + e, v[e], v2[e]);
+      for (int e = 0; e < 8; ++e) epilogue_elem<EPI, __bf16>(p, a, prob, split, row, col0 + e, v[e], v2[e]);
+    }
     return;
   }
   const int64_t idx = (int64_t)row * p.ldc + col0;
@@ -319,30 +326,17 @@ __device__ inline void epilogue_vec8(const GemmProblem& p, const KArgs& a, int p
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] = (float)pr[e] * (v[e] - dsum) * p.scale;
     *c = pack_bf16x8(o);
-  } else if constexpr (EPI == EPI_SPLIT_F32) {
-    float* base = a.partial + a.partial_off[prob] + (int64_t)split * p.M * p.ldc + idx;
-    const f32x4_t o0 = {v[0], v[1], v[2], v[3]}, o1 = {v[4], v[5], v[6], v[7]};
-    *(f32x4_t*)base = o0;
-    *(f32x4_t*)(base + 4) = o1;
-  } else if constexpr (EPI == EPI_GRAD) {
-    if (a.out_f32) {
-      float* c = (float*)p.C[0] + idx;
-      f32x4_t o0 = {v[0], v[1], v[2], v[3]}, o1 = {v[4], v[5], v[6], v[7]};
-      if (a.accumulate) { o0 += *(const f32x4_t*)c; o1 += *(const f32x4_t*)(c + 4); }
-      *(f32x4_t*)c = o0;
-      *(f32x4_t*)(c + 4) = o1;
-    } else {
-      bf16x8s_t* c = (bf16x8s_t*)((__bf16*)p.C[0] + idx);
-      float o[8];
+  } else if constexpr (EPI == EPI_GRAD) {      // bf16 gradients; fp32 ones take epilogue_vec4
+    bf16x8s_t* c = (bf16x8s_t*)((__bf16*)p.C[0] + idx);
+    float o[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] = v[e];
-      if (a.accumulate) {
-        const bf16x8s_t old = *c;
+    for (int e = 0; e < 8; ++e) o[e] = v[e];
+    if (a.accumulate) {
+      const bf16x8s_t old = *c;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] += (float)old[e];
-      }
-      *c = pack_bf16x8(o);
+      for (int e = 0; e < 8; ++e) o[e] += (float)old[e];
     }
+    *c = pack_bf16x8(o);
   } else if constexpr (EPI == EPI_RESID) {
     const bf16x8s_t r = *(const bf16x8s_t*)((const __bf16*)p.C[1] + idx);
     float o[8];
@@ -406,22 +400,25 @@ __device__ inline void epilogue_vec8(const GemmProblem& p, const KArgs& a, int p
     *(bf16x8s_t*)((__bf16*)p.C[2] + idx) = pack_bf16x8(oa);
     *(bf16x8s_t*)((__bf16*)p.C[1] + idx) = pack_bf16x8(oz);
     *dg = pack_bf16x8(og);
+  } else {
+    static_assert(kUnhandledEpilogue<EPI>, "no eight-column form of this epilogue");
   }
 }
 
+// Four consecutive output columns of one row (fp32 outputs, 16-byte stores; bf16 gradients of the register-staged
+// kernel) when the group lies inside the matrix, else element by element.  Row strides are multiples of 8
+// elements and col0 of 4, so the vector accesses are aligned.
 template <int EPI>
 __device__ inline void epilogue_vec4(const GemmProblem& p, const KArgs& a, int prob, int split, int row,
-                                     int col0, const float (&v)[4], const float (&v2)[4]) {
+                                     int col0, const float (&v)[4]) {
   if (row >= p.M) return;
   if (col0 + 4 > p.N) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) epilogue_elem<EPI, __bf16>(p, a, prob, split, row, col0 + e, v[e], v2[e]);
+    for (int e = 0; e < 4; ++e) epilogue_elem<EPI, __bf16>(p, a, prob, split, row, col0 + e, v[e], 0.f);
     return;
   }
   const int64_t idx = (int64_t)row * p.ldc + col0;
-  if constexpr (EPI == EPI_STORE) {
-    *(bf16x4_t*)((__bf16*)p.C[0] + idx) = pack_bf16x4(v[0], v[1], v[2], v[3]);
-  } else if constexpr (EPI == EPI_SPLIT_F32) {
+  if constexpr (EPI == EPI_SPLIT_F32) {
     float* base = a.partial + a.partial_off[prob] + (int64_t)split * p.M * p.ldc;
     f32x4_t o = {v[0], v[1], v[2], v[3]};
     *(f32x4_t*)(base + idx) = o;
@@ -448,29 +445,8 @@ __device__ inline void epilogue_vec4(const GemmProblem& p, const KArgs& a, int p
     *(bf16x4_t*)((__bf16*)p.C[1] + idx) = h;
     *(bf16x4_t*)((__bf16*)p.C[2] + idx) =
         pack_bf16x4(x[0] - (float)h[0], x[1] - (float)h[1], x[2] - (float)h[2], x[3] - (float)h[3]);
-  } else if constexpr (EPI == EPI_SWIGLU_FWD) {
-    float av[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) av[e] = v[e] * sigmoid_f<false>(v[e]) * v2[e];
-    if (p.C[0]) *(bf16x4_t*)((__bf16*)p.C[0] + idx) = pack_bf16x4(v[0], v[1], v[2], v[3]);
-    if (p.C[1]) *(bf16x4_t*)((__bf16*)p.C[1] + idx) = pack_bf16x4(v2[0], v2[1], v2[2], v2[3]);
-    *(bf16x4_t*)((__bf16*)p.C[2] + idx) = pack_bf16x4(av[0], av[1], av[2], av[3]);
-  } else if constexpr (EPI == EPI_SWIGLU_BWD) {
-    bf16x4_t* dg = (bf16x4_t*)((__bf16*)p.C[0] + idx);
-    const bf16x4_t da4 = *dg;
-    float oa[4], oz[4], og[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float da = (float)da4[e];
-      const float sg = sigmoid_f<false>(v[e]);
-      const float s = v[e] * sg;
-      oa[e] = s * v2[e];
-      oz[e] = da * s;
-      og[e] = da * v2[e] * (sg * (1.0f + v[e] * (1.0f - sg)));
-    }
-    *(bf16x4_t*)((__bf16*)p.C[2] + idx) = pack_bf16x4(oa[0], oa[1], oa[2], oa[3]);
-    *(bf16x4_t*)((__bf16*)p.C[1] + idx) = pack_bf16x4(oz[0], oz[1], oz[2], oz[3]);
-    *dg = pack_bf16x4(og[0], og[1], og[2], og[3]);
+  } else {
+    static_assert(kUnhandledEpilogue<EPI>, "no four-column form of this epilogue");
   }
 }
 
