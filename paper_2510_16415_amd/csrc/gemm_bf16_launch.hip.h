@@ -6,7 +6,7 @@
 
 namespace mecefo {
 
-using CfgL4 = TileCfg<256, 256, 2, 2>;   // register staging, forced by the "tile" option only
+using CfgL4 = TileCfg<256, 256, 2, 2>;   // register staging, which only the "tile" option reaches
 using CfgL8 = TileCfg<256, 256, 4, 2>;   // 8 waves x (64 x 128): two waves per SIMD hide latency
 using CfgM = TileCfg<128, 128, 2, 2>;    // 4 waves x (64 x 64): two workgroups per CU
 using CfgM8 = TileCfg<128, 128, 4, 2>;   // 8 waves x (32 x 64): one workgroup per CU
@@ -174,6 +174,11 @@ hipError_t run_bf16(GemmLaunch& g, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// The register-staged kernels serve as a second implementation in tests only; the epilogues of the projection refresh,
+// the residual adds and the rotation are not built for them, and such launches take the 256 x 256 direct-to-LDS tile
+// where a register-staged one is forced.
+constexpr bool register_staged(int epi) { return epi != EPI_POLY && epi != EPI_HILO && epi != EPI_RESID && epi != EPI_ROPE; }
+
 // Limit raise for the configurations of one (layout, epilogue) pair.
 template <bool AKC, bool BKC, int EPI>
 hipError_t prepare_bf16() {
@@ -183,8 +188,10 @@ hipError_t prepare_bf16() {
   if (e == hipSuccess) e = Bf16Kernel<CfgM8, AKC, BKC, EPI, PipeM4, true>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgT, AKC, BKC, EPI, PipeT, true>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgT, AKC, BKC, EPI, PipeT2, true>::prepare();
-  if (e == hipSuccess) e = Bf16Kernel<CfgL4, AKC, BKC, EPI, NoPipe, true>::prepare();
-  if (e == hipSuccess) e = Bf16Kernel<CfgL8, AKC, BKC, EPI, NoPipe, true>::prepare();
+  if constexpr (register_staged(EPI)) {
+    if (e == hipSuccess) e = Bf16Kernel<CfgL4, AKC, BKC, EPI, NoPipe, true>::prepare();
+    if (e == hipSuccess) e = Bf16Kernel<CfgL8, AKC, BKC, EPI, NoPipe, true>::prepare();
+  }
   return e;
 }
 
@@ -199,9 +206,11 @@ template <bool AKC, bool BKC, int EPI>
 hipError_t run_bf16_auto(GemmLaunch& g, hipStream_t stream) {
   int c = bf16_forced_tile();
   if (c < 0) c = bf16_best_tile(g, g.epi == EPI_SPLIT_F32 && g.splits > 1 ? g.splits : 1);
+  if constexpr (register_staged(EPI)) {
+    if (c == TILE_R4) return run_bf16<CfgL4, AKC, BKC, EPI>(g, stream);
+    if (c == TILE_R8) return run_bf16<CfgL8, AKC, BKC, EPI>(g, stream);
+  }
   switch (c) {
-    case TILE_R4: return run_bf16<CfgL4, AKC, BKC, EPI>(g, stream);
-    case TILE_R8: return run_bf16<CfgL8, AKC, BKC, EPI>(g, stream);
     case TILE_M2: return run_bf16<CfgM, AKC, BKC, EPI, PipeM2>(g, stream);
     case TILE_M4: return run_bf16<CfgM8, AKC, BKC, EPI, PipeM4>(g, stream);
     case TILE_T: return run_bf16<CfgT, AKC, BKC, EPI, PipeT>(g, stream);
