@@ -737,7 +737,7 @@ def per_config_lines(B, torch, I, names=("C1", "C2", "C3", "C4")):
         ms = ts[len(ts) // 2]
         flops = b * (10 * d * f + 6 * r * (d + f)) + 6 * r * d * f
         peak = PEAK_BF16_TFLOPS if bf16 else PEAK_F32_VECTOR_TFLOPS
-        out[name] = {"layer": f"tokens={b}, d={d}, f={f}, r={r}, {cfg.dtype}" + (" (plain FMA path, untuned)" if not bf16 else ""),
+        out[name] = {"layer": f"tokens={b}, d={d}, f={f}, r={r}, {cfg.dtype}" + (" (fp32 MFMA path)" if not bf16 else ""),
                      "ms_per_layer_median": round(ms, 4), "ms_per_layer_min": round(ts[0], 4),
                      "tokens_per_s": round(b / (ms * 1e-3), 1),
                      "tflops_per_layer": round(flops / (ms * 1e-3) / 1e12, 2),

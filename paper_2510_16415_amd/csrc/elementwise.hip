@@ -237,8 +237,8 @@ __global__ __launch_bounds__(256, 2) void rmsnorm_bwd_fused_kernel(const T* __re
 // The same for long rows: the whole workgroup works on RB rows at a time (thread t owns vectors
 // t, t + 256, ...), the row dot products are combined across the four waves through LDS (one barrier
 // per group of rows, alternating slots), and the next group's rows are fetched while the current one is
-// finished.  RB keeps about four vectors of each operand per thread in flight and a barrier per 8 to 24 KB
-// (one row at a time: 21 us for [2048 x 2048]; the skip call around it went from 465 to 458 us, the standard
+// finished.  RB keeps about four vectors of each operand per thread in flight and a barrier per RB rows, 8 to 16 KB
+// of each operand (one row at a time: 21 us for [2048 x 2048]; the skip call around it went from 465 to 458 us, the standard
 // one with two of them from 757 to 739).  Every thread owns its columns for all rows
 // of the block, so its sums go straight to partial[block][col].
 template <typename T, int VEC, int ITERS, int RB>

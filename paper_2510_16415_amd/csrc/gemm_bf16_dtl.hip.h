@@ -1,10 +1,11 @@
 // bf16 MFMA GEMM for gfx950 with direct-to-LDS operand staging.
 //
-// One workgroup computes a 256 x 256 (eight wavefronts of 64 x 128), 128 x 128 (eight of 32 x 64) or
-// 64 x 64 (four of 32 x 32) output tile.  Two differences to gemm_bf16.hip.h.  The products run on v_mfma_f32_16x16x32_bf16: on Gaussian operands the matrix cores
-// are power-limited, and this shape moves half the accumulator bytes per multiply-add of the 32x32x16
-// one -- a bare MFMA loop on random operands sustains 2100 TFLOP/s at 2.1 GHz with it against 1860 at
-// 1.83 GHz.  And the operand tiles never pass through registers:
+// One workgroup computes a 256 x 256 (eight wavefronts of 64 x 128), 128 x 128 (four of 64 x 64 with two LDS
+// stages, or eight of 32 x 64 with four) or 64 x 64 output tile (four of 32 x 32, or two groups of four that share out
+// K).  Two differences to gemm_bf16.hip.h.  The products run on v_mfma_f32_16x16x32_bf16: on Gaussian operands a
+// loop of nothing but MFMAs is power-limited, and this shape moves half the accumulator bytes per multiply-add
+// of the 32x32x16 one -- 2100 TFLOP/s at 2.1 GHz on random operands against 1860 at 1.83 GHz.  And the operand
+// tiles never pass through registers:
 // `buffer_load_dwordx4 ... lds` writes 1 KiB per wavefront instruction straight into LDS
 // (lane i lands at base + 16 i).  K is cut into stages of BK (32 or 64) held in a ring of NS
 // LDS buffers; a buffer is refilled as soon as the barrier that ends its last use has passed,
@@ -13,7 +14,7 @@
 //   * K-contiguous operands keep the XOR-swizzled [rows][64] layout: the swizzle is applied by
 //     choosing which 16-byte chunk of the row each lane fetches.
 //   * K-strided operands ([K x rows] in memory: weights used as [K x N], activations in the
-//     token contraction) stay in their memory order [64 k][256 rows] in LDS and are transposed
+//     token contraction) stay in their memory order [64 k][tile rows] in LDS and are transposed
 //     on the way to the MFMA registers by ds_read_b64_tr_b16 (each 16-lane group turns four
 //     k-rows of 16 elements into four K-consecutive values per lane); their 16-byte chunks are
 //     XOR-swizzled by k so that the eight k-rows of a 32-lane pass fall into different banks.

@@ -19,10 +19,15 @@ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 // A3+B2; a second barrier that lets two fills overlap; one operand staged through registers two
 // stages ahead; line-touch prefetch of later stages (+8 %).  Fill latency is not what bounds the
 // loop (a fills-only loop runs a stage in 0.9-1.3 us, the full loop gives it 1.4): LDS traffic of
-// fills plus fragment reads and MFMA issue are both near a stage's length, and on Gaussian operands
-// the matrix cores are power-limited.
+// fills plus fragment reads and MFMA issue are both near a stage's length.  The power limit comes on top: the 7B-shaped
+// layer takes 7 % longer on Gaussian than on all-zero operands.
 using PipeL = DtlPipe<CfgL8, 2>;
-using PipeM2 = DtlPipe<CfgM, 2>;   // 64 KiB: two workgroups per CU cover each other's waits
+// 64 KiB: two workgroups per CU cover each other's waits.  Four waves of 64 x 64 against eight of 32 x 64 (fewer LDS bytes
+// per multiply-add, fewer waves to cover latency): a draw.  Calls with four waves, on two boxes: [4096 x 1024] skip
+// backward of two micro-batches 0.3 % slower and 1.5 % faster, [2048 x 2048] skip 1.8 and 1.1 % slower, 8-layer stack
+// of [2048 x 512] 2.4 % slower on both, [4096 x 1024] forward equal and 1.4 % faster; mean of 16 and of 23 cases
+// 0.6 and 0.3 % slower.
+using PipeM2 = DtlPipe<CfgM, 2>;
 using PipeM4 = DtlPipe<CfgM8, 4>;   // 128 KiB: one workgroup per CU, three stages in flight
 using PipeT = DtlPipe<CfgT, 3>;    // 48 KiB
 using PipeT2 = DtlPipe<CfgT, 3, 2>;   // 96 KiB: one workgroup per CU, two groups of waves share out K
@@ -35,7 +40,9 @@ using PipeT2 = DtlPipe<CfgT, 3, 2>;   // 96 KiB: one workgroup per CU, two group
 // modelled time over the configurations,
 //     fixed + per_round * n + stages * max(stage_alone, stage_shared * n),   n = workgroups per CU,
 // with constants fitted to a sweep of 50 launches over every operand layout (K 32 to 11008, 2 to 2752
-// workgroups; the model is within 15 % of nearly all of them).  Sides measured, in us (256^2 / 128^2
+// workgroups; the model is within 15 % of nearly all of them).  Every launch of the sweep had one K: a grouped launch
+// is costed as if each of its problems had the longest one, which overstates it (the projections of Eq. (2): K = d, d
+// and f).  Sides measured, in us (256^2 / 128^2
 // two-stage / 128^2 four-stage / 64^2): [2048 x 2048], K 2048: 49 / 27 / 27 / 35; the same three in one
 // launch: 54 / 60 / 73 / 84; [512 x 512], K 2048: 47 / 23 / 25 / 15; [2048 x 2048], K 5461: 135 / 80 / 61 /
 // 101; [2048 x 512], K 1376: 33 / 16 / 17 / 11; SwiGLU recompute of 2048 tokens, d 2048, f 5461: 119 / 111 /
@@ -47,6 +54,7 @@ using PipeT2 = DtlPipe<CfgT, 3, 2>;   // 96 KiB: one workgroup per CU, two group
 enum TileConfig : int { TILE_L = 0, TILE_M2 = 1, TILE_M4 = 2, TILE_T = 3, TILE_T2 = 4, TILE_COUNT = 5,
                         TILE_R4 = 5, TILE_R8 = 6 };   // register-staged with four or eight waves: forced only
 
+// No bound on the workgroups that share a CU: the rates of larger n are those of the fullest CU measured.
 struct TileModel { int bm, bn; float fixed, per_round, stage_alone, stage_shared; };
 inline const TileModel& tile_model(int c) {
   static const TileModel m[TILE_COUNT] = {{256, 256, 3.5f, 2.5f, 1.45f, 1.75f},

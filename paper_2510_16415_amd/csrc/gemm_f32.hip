@@ -275,7 +275,10 @@ inline bool f32_far(const GemmLaunch& g) {
   return false;
 }
 
-// 64 x 64 tiles once they give every CU two workgroups.
+// 64 x 64 tiles once they give every CU two workgroups.  Skip backwards with the line at 256 / 1024 / 2048 tiles against
+// 512, us: [1024 x 512], f 1376: 185 / 178 / 178 against 175; [1024 x 1024], f 2752 (688 tiles): 536 / 484 / 484 against
+// 516; [2048 x 512], f 1376 (704): 290 / 272 / 271 against 282; [4096 x 512], f 1376: 451 / 464 / 473 against 452;
+// [4096 x 1024], f 2752: 1515 / 1490 / 1539 against 1487.
 template <int EPI>
 hipError_t run_f32(GemmLaunch& g, hipStream_t stream) {
   if (f32_far(g)) {
@@ -288,7 +291,10 @@ hipError_t run_f32(GemmLaunch& g, hipStream_t stream) {
 }  // namespace
 
 // K splits of a launch that may be cut into up to `most` parts: a stage takes about 0.5 us while every CU has at
-// most two workgroups, the sum of the parts one more launch of 5 us per problem.
+// most two workgroups, the sum of the parts one more launch of 5 us per problem.  Skip backwards never cut / always cut
+// as far as the workspace holds, against this rule, us: [8192 x 128], f 344, rank 16: 189 / 133 against 133; [4096 x 256],
+// f 688, rank 32: 198 / 182 against 182; [2048 x 128], f 344, rank 32: 79.0 / 78.0 against 79.0; [256 x 256], f 688: 69.5 / 74.8
+// against 69.5; [1024 x 512], f 1376: 175 / 189 against 175; [4096 x 1024], f 2752: 1492 / 1501 against 1487.
 int f32_plan_splits(const GemmLaunch& g, int most) {
   const int tiles = f32_tiles(g, CfgSmall::FT);
   int stages = 0;

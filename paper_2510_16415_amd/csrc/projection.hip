@@ -24,11 +24,12 @@ constexpr int kMaxSplits = 8;
 // directions, whose share of X after one application of W^T W is (s_r/s_1)^2.  The halves are written by
 // whatever produces the iterate: the product's epilogue, the sum of its K splits, the normalisation.
 //
-// A refresh is a chain of some 100 dependent products of a few microseconds each, so launches count: with
+// A refresh is a chain of some 60 dependent products of a few microseconds each, so launches count: with
 // the polynomial and the halves in the epilogues a Newton-Schulz step is three products (four launches where
 // the Gram matrix is cut along K) instead of three products, two or three elementwise kernels and a copy.
-// Three matrices of [5461 x 2048], rank 512, two rounds of eight steps and three polishing steps: 438 launches
-// and 3390 us before, 261 and 2650 us now.
+// Three matrices of [5461 x 2048], rank 512, two rounds of eight steps and three polishing steps: 406 launches and
+// 6760 us on the register-staged kernels with separate elementwise launches, 219 and 2380 us now (3390 -> 2650 us by the
+// epilogues alone).
 
 // Sum of the K splits of a product, finished like its epilogue would (EPI_POLY or EPI_HILO; fixed order).
 struct SplitSum {
