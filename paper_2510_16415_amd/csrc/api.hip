@@ -627,6 +627,12 @@ const char* mecefo_last_error(void) { return g_err; }
 const char* mecefo_version(void) { return "mecefo-gfx950 0.2"; }
 
 mecefo_status_t mecefo_init(void) {
+  // bit i: prepared on device i (devices above 63 are prepared every time, kernel by kernel)
+  static std::atomic<uint64_t> done{0};
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
+  if (done.load(std::memory_order_acquire) & bit) return MECEFO_OK;
   HIP_TRY(prepare_gemm_bf16_nt());
   HIP_TRY(prepare_gemm_bf16_nn());
   HIP_TRY(prepare_gemm_bf16_tn());
@@ -634,6 +640,7 @@ mecefo_status_t mecefo_init(void) {
   HIP_TRY(prepare_attention_bwd());
   void* p = nullptr;
   TRY(scratch_on_current_device(&p));
+  done.fetch_or(bit, std::memory_order_release);
   return MECEFO_OK;
 }
 
