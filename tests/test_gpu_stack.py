@@ -233,16 +233,16 @@ def test_attention_option_changed_by_another_thread_during_a_stack_forward():
     torch.cuda.synchronize()
     ref = [t.clone() for t in [*st.H, st.Xout]]
     stop = threading.Event()
-    try:
-        B.mecefo_set_option("attention", "gemm")
-        st.ws = poisoned_ws(B.mecefo_stack_workspace_bytes(st.desc, st.attn, st.r, st.r, st.r))
 
-        def toggle():
-            while not stop.is_set():
-                B.mecefo_set_option("attention", "auto")
-                B.mecefo_set_option("attention", "gemm")
-        thread = threading.Thread(target=toggle)
-        thread.start()
+    def toggle():
+        while not stop.is_set():
+            B.mecefo_set_option("attention", "auto")
+            B.mecefo_set_option("attention", "gemm")
+    thread = threading.Thread(target=toggle)
+    B.mecefo_set_option("attention", "gemm")
+    st.ws = poisoned_ws(B.mecefo_stack_workspace_bytes(st.desc, st.attn, st.r, st.r, st.r))
+    thread.start()
+    try:
         for i in range(300):
             st.ws.fill_(255)
             st.forward()
