@@ -289,7 +289,6 @@ GemmLaunch new_launch(const Ctx& c, bool akc, bool bkc, int epi) {
   g.epi = epi;
   g.bf16 = c.bf16;
   g.out_f32 = c.grad_f32;
-  g.splits = 1;
   g.clk = g_prof.cur_clk;
   return g;
 }
@@ -306,6 +305,23 @@ GemmProblem prob(const void* A0, const void* A1, int64_t lda, const void* B0, co
   return p;
 }
 
+// Makes a store launch write `splits` fp32 parts of every problem into `partial`, one problem's behind the other's;
+// C receives the outputs they belong to.
+void cut_along_k(GemmLaunch& g, int splits, float* partial, void** C) {
+  for (int i = 0; i < g.nprob; ++i) {
+    GemmProblem& p = g.p[i];
+    C[i] = p.C[0];
+    p.C[0] = partial;
+    p.splits = splits;
+    partial += (int64_t)splits * p.M * p.ldc;
+  }
+}
+mecefo_status_t sum_parts(const Ctx& c, const GemmLaunch& g, void* const* C, hipStream_t s) {
+  for (int i = 0; i < g.nprob; ++i)
+    HIP_TRY(launch_splitk_reduce(c.bf16, (const float*)g.p[i].C[0], g.p[i].splits, (int64_t)g.p[i].M * g.p[i].ldc, C[i], s));
+  return MECEFO_OK;
+}
+
 // A store launch into the library's own buffers (row stride == ldc of every problem), cut along K
 // into up to `most` parts (what the workspace holds partials for; 1 for fp32) when that fills the chip better.
 mecefo_status_t launch_store_split(const Ctx& c, const Bufs& bf, GemmLaunch& g, int most, hipStream_t s) {
@@ -314,20 +330,10 @@ mecefo_status_t launch_store_split(const Ctx& c, const Bufs& bf, GemmLaunch& g, 
     HIP_TRY(launch_gemm(g, s));
     return MECEFO_OK;
   }
-  g.epi = EPI_SPLIT_F32;
-  g.splits = splits;
-  g.partial = (float*)(bf.base + bf.w.partial);
-  void* C[3];
-  int64_t poff = 0;
-  for (int i = 0; i < g.nprob; ++i) {
-    C[i] = g.p[i].C[0];
-    g.partial_off[i] = poff;
-    poff += (int64_t)splits * g.p[i].M * g.p[i].ldc;
-  }
+  void* C[kMaxProblems];
+  cut_along_k(g, splits, (float*)(bf.base + bf.w.partial), C);
   HIP_TRY(launch_gemm(g, s));
-  for (int i = 0; i < g.nprob; ++i)
-    HIP_TRY(launch_splitk_reduce(c.bf16, g.partial + g.partial_off[i], splits, (int64_t)g.p[i].M * g.p[i].ldc, C[i], s));
-  return MECEFO_OK;
+  return sum_parts(c, g, C, s);
 }
 
 // dA = dY Wd  ->  recompute G, Z from U and apply the SwiGLU backward in the epilogue
@@ -440,14 +446,8 @@ mecefo_status_t lowrank_wgrad(const Ctx& c, const Bufs& bf, const void* U, int64
     // the workspace holds partials for up to bf.w.splits parts
     const int most = b > 0 ? bf.w.splits : 1;
     const int splits = most <= 1 ? 1 : c.bf16 ? bf16_plan_splits(g, most) : f32_plan_splits(g, most);
-    if (splits > 1) g.epi = EPI_SPLIT_F32;
-    g.splits = splits;
-    g.partial = (float*)(base + bf.w.partial);
-    int64_t poff = 0;
-    for (int j = 0; j < n_lr; ++j) {
-      g.partial_off[j] = poff;
-      poff += (int64_t)splits * g.p[j].M * g.p[j].ldc;
-    }
+    void* dst[kMaxProblems];
+    if (splits > 1) cut_along_k(g, splits, (float*)(base + bf.w.partial), dst);
     {
       STAGE(MECEFO_STAGE_CONTRACT, s);
       g.clk = g_prof.cur_clk;
@@ -455,12 +455,7 @@ mecefo_status_t lowrank_wgrad(const Ctx& c, const Bufs& bf, const void* U, int64
     }
     if (splits > 1) {
       STAGE(MECEFO_STAGE_SPLITK_REDUCE, s);
-      // partial of problem j is [split][rows x ldt]; the reduction keeps that row stride
-      for (int j = 0; j < n_lr; ++j) {
-        const int i = lr[j];
-        const int rows = in ? m_out[i] : n_in[i];
-        HIP_TRY(launch_splitk_reduce(c.bf16, g.partial + g.partial_off[j], splits, (int64_t)rows * ldt[i], C[i], s));
-      }
+      TRY(sum_parts(c, g, dst, s));
     }
   }
   {  // expand: dW = C P^T (SIDE_INPUT) or P C^T (SIDE_OUTPUT), K = r, into the gradient buffers

@@ -178,25 +178,28 @@ template <int R, int NT, bool DUAL> struct LoaderSel<R, NT, false, DUAL> {
 };
 
 template <class Cfg, bool AKC, bool BKC, int EPI>
-__global__ __launch_bounds__(Cfg::NT) void gemm_bf16_kernel(const KArgs args) {
+__global__ __launch_bounds__(Cfg::NT) void gemm_bf16_kernel(const KArgs) {
   constexpr bool DUAL = epi_is_dual(EPI);
-  // fp32 outputs (gradients, split-K partials): issue the MFMA with swapped operands so that a
+  // gradients (fp32 mostly): issue the MFMA with swapped operands so that a
   // lane holds four consecutive columns and stores 16 bytes; bf16 outputs keep the layout in
   // which a half-wave writes 32 consecutive columns of one row.
-  constexpr bool SWAP = EPI == EPI_GRAD || EPI == EPI_SPLIT_F32;
+  constexpr bool SWAP = EPI == EPI_GRAD;
   constexpr int BM = Cfg::BM, BN = Cfg::BN, TM = Cfg::TM, TN = Cfg::TN, NT = Cfg::NT;
   constexpr int BN_OUT = DUAL ? BN / 2 : BN;       // output columns covered per tile
   static_assert(!DUAL || (TN % 2 == 0), "dual tiles pair MFMA blocks");
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
 
+  const KHead head = load_head();
   const int t = threadIdx.x;
   const int lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wave / Cfg::WAVES_N, wn = wave % Cfg::WAVES_N;
 
-  const int nblocks = args.total_tiles * args.splits;
-  const TileCoord tc = map_tile(args, xcd_remap(blockIdx.x, nblocks));
-  const GemmProblem p = product_view<2>(args.p[tc.prob], tc.z);
+  int index;
+  const int prob = map_problem(head, blockIdx.x, &index);
+  const KProblem kp = load_problem(prob);
+  const TileCoord tc = map_tile<BM, BN_OUT>(head, kp, prob, index);
+  const GemmProblem p = product_view<2>(head, kp, tc.z);
   const int m0 = tc.tm * BM, n0 = tc.tn * BN_OUT;
   if (causal_tile_unused(p, m0, n0, BM)) return;
 
@@ -205,9 +208,8 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_bf16_kernel(const KArgs args) {
   const int K = p.K;
   const int kt_per_seg = (K + kBK - 1) / kBK;
   const int kt_total = kt_per_seg * nseg;
-  const int kt_chunk = __builtin_amdgcn_readfirstlane((kt_total + args.splits - 1) / args.splits);
-  int kt_begin = tc.split * kt_chunk;
-  int kt_end = min(kt_total, kt_begin + kt_chunk);
+  int kt_begin = tc.split * p.chunk;
+  int kt_end = min(kt_total, kt_begin + p.chunk);
   causal_clip(p, m0, n0, BM, kBK, kt_begin, kt_end);
 
   typename LoaderSel<BM, NT, AKC, false>::type la;
@@ -317,7 +319,7 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_bf16_kernel(const KArgs args) {
           const int col = col_w + j * 32;
           const float v = acc[i][j][e];
           const float v2 = DUAL ? acc[i][DUAL ? j + TN / 2 : j][e] : 0.f;
-          epilogue_elem<EPI, __bf16>(p, args, tc.prob, tc.split, row, col, v, v2);
+          epilogue_elem<EPI, __bf16>(p, head, tc.split, row, col, v, v2);
         }
   } else {
     // Swapped operands: the B fragment was the MFMA's row operand, so a lane holds, for
@@ -335,7 +337,7 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_bf16_kernel(const KArgs args) {
           float v[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * g4 + e];
-          epilogue_vec4<EPI>(p, args, tc.prob, tc.split, row_w + i * 32, col_w + j * 32 + 8 * g4, v);
+          epilogue_vec4<EPI>(p, head, tc.split, row_w + i * 32, col_w + j * 32 + 8 * g4, v);
         }
   }
 }

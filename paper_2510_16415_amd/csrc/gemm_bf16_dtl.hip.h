@@ -98,7 +98,7 @@ struct DmaKC {   // K-contiguous source; one wave instruction covers RPI consecu
     for (int q = 0; q < NI; ++q) {
       const int row = (q * NW + w) * RPI + rsub;
       const int gr = row_base + (DUAL ? (row & (ROWS / 2 - 1)) : row);
-      voff[q] = gr < rows_total ? (uint32_t)(((int64_t)gr * ld + c * 8) * 2) : kOOB;
+      voff[q] = gr < rows_total ? ((uint32_t)gr * (uint32_t)ld + c * 8) * 2 : kOOB;      // operands lie below 2 GiB
     }
   }
   __device__ inline void issue(u32x4_t r0, u32x4_t r1, uint32_t tile, int k0, int K, bool tail) const {
@@ -152,7 +152,7 @@ struct DmaKS {   // K-strided source; one wave instruction covers KPI k rows of 
     const int cm = KsMap<ROWS>::logical(lane % CH, krow0);     // the swizzle sees k % 16 only: the same for every q
     const int m = row_base + cm * 8;
     ld2 = (uint32_t)(ld * 2);
-    voff = m < rows_total ? (uint32_t)(((int64_t)krow0 * ld + m) * 2) : kOOB;
+    voff = m < rows_total ? ((uint32_t)krow0 * (uint32_t)ld + m) * 2 : kOOB;
   }
   __device__ inline void issue(u32x4_t r0, u32x4_t, uint32_t tile, int k0, int K, bool tail) const {
     const uint32_t soff = (uint32_t)k0 * ld2;
@@ -241,7 +241,7 @@ template <class Cfg, int NS_, int KG_ = 1> struct DtlPipe {
 // RAGGED: K may end inside a 16-byte chunk (the instantiation without it keeps the large tile's loop free of the
 // test: 0.5 % of the 7B-shaped layer).
 template <class Cfg, class Pipe, bool AKC, bool BKC, int EPI, bool RAGGED>
-__global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const KArgs args) {
+__global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const KArgs) {
   constexpr bool DUAL = epi_is_dual(EPI);
   constexpr int BM = Cfg::BM, BN = Cfg::BN, NT = Cfg::NT;
   constexpr int TM = Cfg::WM / 16, TN = Cfg::WN / 16;     // 16x16 MFMA blocks per wave
@@ -251,7 +251,7 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const K
   constexpr int BN_OUT = DUAL ? BN / 2 : BN;
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem_all[];
 
-  touch_args(args);
+  const KHead head = load_head();
   const int group = KG > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NT) : 0;
   const int t = threadIdx.x - group * NT;      // thread, wave and LDS buffers within the group
   const int lane = t & 63;
@@ -259,22 +259,23 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const K
   uint8_t* smem = smem_all + group * NS * STAGE;
   const int wm = wave / Cfg::WAVES_N, wn = wave % Cfg::WAVES_N;
 
-  const int nblocks = args.total_tiles * args.splits;
   // Measurement only: shader-clock cycles and constant-rate (100 MHz) ticks this workgroup takes.
   uint64_t clk_c0 = 0, clk_w0 = 0;
-  if (args.clk) { clk_c0 = clock64(); clk_w0 = wall_clock64(); }
-  const TileCoord tc = map_tile(args, xcd_remap(blockIdx.x, nblocks));
-  const GemmProblem p = product_view<2>(args.p[tc.prob], tc.z);
+  if (head.clk) { clk_c0 = clock64(); clk_w0 = wall_clock64(); }
+  int index;
+  const int prob = map_problem(head, blockIdx.x, &index);
+  const KProblem kp = load_problem(prob);
+  const TileCoord tc = map_tile<BM, BN_OUT>(head, kp, prob, index);
+  const GemmProblem p = product_view<2>(head, kp, tc.z);
   const int m0 = tc.tm * BM, n0 = tc.tn * BN_OUT;
   if (causal_tile_unused(p, m0, n0, BM)) return;
 
   const int nseg = DUAL ? 1 : p.nseg;
   const int K = p.K;
-  const int kt_per_seg = (K + BK - 1) / BK;
+  const int kt_per_seg = (uint32_t)(K + BK - 1) / BK;
   const int kt_total = kt_per_seg * nseg;
-  const int kt_chunk = __builtin_amdgcn_readfirstlane((kt_total + args.splits - 1) / args.splits);
-  int kt_begin = tc.split * kt_chunk;
-  int kt_end = min(kt_total, kt_begin + kt_chunk);
+  int kt_begin = tc.split * p.chunk;
+  int kt_end = min(kt_total, kt_begin + p.chunk);
   causal_clip(p, m0, n0, BM, BK, kt_begin, kt_end);
 
   using DmaA = typename DmaSel<BK, NT, BM, AKC, false>::type;
@@ -329,7 +330,6 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const K
   // Fragments: A double-buffered by K step, B single-buffered -- a B block is reloaded for the next
   // step right behind the MFMAs of its column, the last use of its present contents.
   bf16x8_t af[2][TM], bfr[TN];
-  static_assert(TM <= TN, "the A reloads ride on the first columns of the step");
   // One 32-K step: MFMAs column by column; behind column j the loads of the next step's B block j and
   // (for j < TM) A block j from `next`, step `ns`.  (Behind the very last step of the K loop these
   // loads fetch fragments nobody uses: cheaper than a branch per column.)
@@ -340,7 +340,12 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const K
       for (int i = 0; i < TM; ++i)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[cur][i], bfr[j], acc[i][j], 0, 0, 0);
       bfr[j] = fb.fetch_one(j, next + A_BYTES, ns);
-      if (j < TM) af[cur ^ 1][j] = fa.fetch_one(j, next, ns);
+      if constexpr (TM <= TN) {
+        if (j < TM) af[cur ^ 1][j] = fa.fetch_one(j, next, ns);
+      } else {                 // taller than wide: the A blocks are shared out over the columns
+#pragma unroll
+        for (int i = j * TM / TN; i < (j + 1) * TM / TN; ++i) af[cur ^ 1][i] = fa.fetch_one(i, next, ns);
+      }
     }
     // The scheduler's built-in pattern that alternates single MFMAs with single LDS reads.  Measured
     // against its other pattern, none, and an order pinned column by column (same box, alternating
@@ -360,7 +365,8 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const K
   // row keeps every shared line in use for at most eight stages, well inside the 4 MB L2 (larger
   // strides measured slower).  Measured on the 7B-shaped layer: recompute launch -3.5 %, the others
   // -1 % to 0.  The summation order over K depends on the tile row only, so reruns stay bit-equal.
-  const int rot = args.krot > 0 && nst > 0 ? __builtin_amdgcn_readfirstlane((tc.tm % args.krot) % nst) : 0;
+  int rot = head.krot > 0 ? tc.tm & (head.krot - 1) : 0;      // krot: a power of two
+  while (rot >= nst && rot > 0) rot = nst > 0 ? rot - nst : 0;
   auto kmap = [&](int turn) {
     const int i = KG > 1 ? turn * KG + group : turn;
     if (KG > 1 && i >= nst) return -1;
@@ -464,9 +470,9 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const K
       // fp32 outputs: four columns per lane, so that one store instruction covers whole 512-byte row
       // pieces (with eight columns per lane each of the two 16-byte stores would fill every other
       // 16 bytes of its lines)
-      constexpr bool F32_OUT = EPI == EPI_SPLIT_F32 || EPI == EPI_HILO;
-      if constexpr (F32_OUT || EPI == EPI_GRAD) {
-        if (F32_OUT || args.out_f32) {
+      constexpr bool F32_OUT = EPI == EPI_HILO;
+      if constexpr (F32_OUT || EPI == EPI_GRAD || EPI == EPI_STORE) {
+        if (F32_OUT || (EPI == EPI_GRAD ? head.out_f32 != 0 : p.splits > 1)) {
           constexpr int LPR4 = W / 4, RPI4 = 64 / LPR4;
           const int r4 = lane / LPR4, c4 = (lane % LPR4) * 4;
 #pragma unroll
@@ -474,7 +480,7 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const K
             const int rl = it * RPI4 + r4;
             const f32x4_t g = *(const f32x4_t*)(ep + rl * RS + c4);
             const float v4[4] = {g[0], g[1], g[2], g[3]};
-            epilogue_vec4<EPI>(p, args, tc.prob, tc.split, row_w + i * 32 + rl, col_w - rd_c8 + c4, v4);
+            epilogue_vec4<EPI>(p, head, tc.split, row_w + i * 32 + rl, col_w - rd_c8 + c4, v4);
           }
           continue;
         }
@@ -500,12 +506,12 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const K
             for (int e = 0; e < 4; ++e) { v2[e] = z0[e]; v2[4 + e] = z1[e]; }
           }
         }
-        if constexpr (!F32_OUT) epilogue_vec8<EPI>(p, args, tc.prob, tc.split, row_w + i * 32 + rl, col_w, v, v2);
+        if constexpr (!F32_OUT) epilogue_vec8<EPI>(p, head, tc.split, row_w + i * 32 + rl, col_w, v, v2);
       }
     }
   }
-  if (args.clk && (blockIdx.x & 63) == 0 && t == 0) {
-    uint32_t* o = args.clk + 2 * ((blockIdx.x >> 6) & 63);
+  if (head.clk && (blockIdx.x & 63) == 0 && t == 0) {
+    uint32_t* o = head.clk + 2 * ((blockIdx.x >> 6) & 63);
     o[0] = (uint32_t)(clock64() - clk_c0);
     o[1] = (uint32_t)(wall_clock64() - clk_w0);
   }

@@ -153,32 +153,11 @@ hipError_t run_bf16(GemmLaunch& g, hipStream_t stream) {
   constexpr int LDS = Kern::LDS;
   constexpr bool DUAL = epi_is_dual(EPI);
   KArgs a;
-  a.nprob = g.nprob;
-  int tiles = 0;
-  for (int i = 0; i < 3; ++i) {
-    a.p[i] = g.p[i < g.nprob ? i : 0];
-    a.partial_off[i] = g.partial_off[i];
-    if (i >= g.nprob) continue;
-    GemmProblem& p = a.p[i];
-    p.tiles_m = cdiv(p.M, Cfg::BM);
-    p.tiles_n = cdiv(p.N, DUAL ? Cfg::BN / 2 : Cfg::BN);
-    p.tile_begin = tiles;
-    tiles += p.tiles_m * p.tiles_n * (p.batch > 1 ? p.batch : 1);
-    if (p.nseg < 2) { p.A[1] = p.A[0]; if (!DUAL) p.B[1] = p.B[0]; }
-    if (p.nseg < 3) { p.A[2] = p.A[0]; p.B[2] = p.B[0]; }
-  }
-  a.total_tiles = tiles;
-  fill_schedule(a);
-  a.splits = (EPI == EPI_SPLIT_F32 && g.splits > 1) ? g.splits : 1;
-  a.accumulate = g.accumulate;
-  a.out_f32 = g.out_f32;
-  a.partial = g.partial;
-  a.krot = 8;
-  a.clk = g.clk;
-  if (tiles == 0) return hipSuccess;
+  fill_kargs(a, g, Cfg::BM, DUAL ? Cfg::BN / 2 : Cfg::BN, kBK, 8);
+  if (a.h.total == 0) return hipSuccess;
   const hipError_t e = Kern::prepare();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(Kern::entry(), dim3(tiles * a.splits), dim3(Kern::DTL ? Pipe::THREADS : Cfg::NT), LDS, stream, a);
+  hipLaunchKernelGGL(Kern::entry(), dim3(a.h.total), dim3(Kern::DTL ? Pipe::THREADS : Cfg::NT), LDS, stream, a);
   return hipGetLastError();
 }
 
@@ -213,7 +192,7 @@ inline int bf16_forced_tile() {
 template <bool AKC, bool BKC, int EPI>
 hipError_t run_bf16_auto(GemmLaunch& g, hipStream_t stream) {
   int c = bf16_forced_tile();
-  if (c < 0) c = bf16_best_tile(g, g.epi == EPI_SPLIT_F32 && g.splits > 1 ? g.splits : 1);
+  if (c < 0) c = bf16_best_tile(g, g.p[0].splits > 1 ? g.p[0].splits : 1);
   if constexpr (register_staged(EPI)) {
     if (c == TILE_R4) return run_bf16<CfgL4, AKC, BKC, EPI>(g, stream);
     if (c == TILE_R8) return run_bf16<CfgL8, AKC, BKC, EPI>(g, stream);

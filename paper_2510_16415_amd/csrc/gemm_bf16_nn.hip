@@ -6,7 +6,6 @@ hipError_t launch_gemm_bf16_nn(GemmLaunch& g, hipStream_t s) {
   switch (g.epi) {
     case EPI_STORE: return run_bf16_auto<true, false, EPI_STORE>(g, s);
     case EPI_GRAD: return run_bf16_auto<true, false, EPI_GRAD>(g, s);
-    case EPI_SPLIT_F32: return run_bf16_auto<true, false, EPI_SPLIT_F32>(g, s);
     case EPI_HILO: return run_bf16_auto<true, false, EPI_HILO>(g, s);
     default: return hipErrorInvalidValue;
   }
@@ -15,7 +14,6 @@ hipError_t prepare_gemm_bf16_nn() {
   hipError_t e = hipSuccess;
   if (e == hipSuccess) e = prepare_bf16<true, false, EPI_STORE>();
   if (e == hipSuccess) e = prepare_bf16<true, false, EPI_GRAD>();
-  if (e == hipSuccess) e = prepare_bf16<true, false, EPI_SPLIT_F32>();
   if (e == hipSuccess) e = prepare_bf16<true, false, EPI_HILO>();
   return e;
 }

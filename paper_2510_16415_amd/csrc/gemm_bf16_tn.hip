@@ -5,7 +5,6 @@ namespace mecefo {
 hipError_t launch_gemm_bf16_tn(GemmLaunch& g, hipStream_t s) {
   switch (g.epi) {
     case EPI_STORE: return run_bf16_auto<false, false, EPI_STORE>(g, s);
-    case EPI_SPLIT_F32: return run_bf16_auto<false, false, EPI_SPLIT_F32>(g, s);
     case EPI_GRAD: return run_bf16_auto<false, false, EPI_GRAD>(g, s);
     case EPI_POLY: return run_bf16_auto<false, false, EPI_POLY>(g, s);
     case EPI_HILO: return run_bf16_auto<false, false, EPI_HILO>(g, s);
@@ -15,7 +14,6 @@ hipError_t launch_gemm_bf16_tn(GemmLaunch& g, hipStream_t s) {
 hipError_t prepare_gemm_bf16_tn() {
   hipError_t e = hipSuccess;
   if (e == hipSuccess) e = prepare_bf16<false, false, EPI_STORE>();
-  if (e == hipSuccess) e = prepare_bf16<false, false, EPI_SPLIT_F32>();
   if (e == hipSuccess) e = prepare_bf16<false, false, EPI_GRAD>();
   if (e == hipSuccess) e = prepare_bf16<false, false, EPI_POLY>();
   if (e == hipSuccess) e = prepare_bf16<false, false, EPI_HILO>();

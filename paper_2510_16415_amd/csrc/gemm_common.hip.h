@@ -7,44 +7,108 @@
 
 namespace mecefo {
 
-struct KArgs {
-  GemmProblem p[3];
-  int nprob;
-  int total_tiles;   // sum over problems of tiles_m * tiles_n
-  int splits;        // >= 1; block count = total_tiles * splits
-  int accumulate;
-  int out_f32;
-  float* partial;
-  int64_t partial_off[3];
-  int krot;          // direct-to-LDS kernel: tile row tm starts its K loop at stage tm % krot (0: off)
-  uint32_t* clk;     // measurement (NULL otherwise): every 64th workgroup stores its shader-clock cycles and
-                     // its 100 MHz wall ticks, pair number (workgroup / 64) % 64
-  // Schedule (filled by fill_schedule): the logical tile order is eight consecutive segments, one
-  // per XCD; segment x lists, heaviest problem first, the x-th eighth of every problem's tiles.
-  int order[3];         // problem indices, most work per tile first
-  int lstart[8][3];     // logical index at which (segment x, slot s) starts
-  int tstart[8][3];     // first tile (within its problem) of that chunk
+// One problem as the kernels read it: two lines of 64 bytes.
+struct KProblem {
+  const void* A[3];
+  const void* B[3];
+  void* C[3];
+  int64_t lda, ldb, ldc;
+  int M, N, K;
+  int chunk_nseg;          // 4 * (K stages of a workgroup) + nseg
+  int aux;                 // EPI_ROPE: rope_half, else pad_cols
+  int splits_kpad;         // 2 * splits + kpad_ok
+  uint32_t by_tiles, by_group;   // div_magic of the tiles of one part or product, and of the tiles of eight tile rows
 };
 
-// Host side: tile_begin / tiles_m / tiles_n must be set.  Longest-processing-time-first inside each
-// XCD segment keeps the tail of a grouped launch short when the problems differ in K.
-inline void fill_schedule(KArgs& a) {
-  int idx[3] = {0, 1, 2};
-  auto work = [&](int i) { return i < a.nprob ? (int64_t)a.p[i].K * (a.p[i].nseg > 1 ? a.p[i].nseg : 1) : (int64_t)-1; };
-  for (int i = 0; i < 3; ++i)
-    for (int j = i + 1; j < 3; ++j)
-      if (work(idx[j]) > work(idx[i])) { int t = idx[i]; idx[i] = idx[j]; idx[j] = t; }
-  int l = 0;
-  for (int s = 0; s < 3; ++s) a.order[s] = idx[s];
-  for (int x = 0; x < 8; ++x)
+// Division by a number that the host knows: one multiplication and a correction, where the compiler's sequence is
+// 30 instructions.
+inline uint32_t div_magic(uint32_t n) { return n > 1 ? (uint32_t)(((uint64_t)1 << 32) / n + 1) : 0xFFFFFFFFu; }
+__host__ __device__ inline int div_by(int x, int n, uint32_t magic) {
+  // n > 1: magic - 2^32 / n lies in (0, 1], so the product is x / n plus less than 1; n = 1: x - 1 (0 for x = 0)
+  const int q = (int)(((uint64_t)(uint32_t)x * magic) >> 32), r = x - q * n;
+  return q + (r >= n ? 1 : 0) - (r < 0 ? 1 : 0);
+}
+
+// Kernel arguments.  A workgroup needs them before its first load, and what it does until then is much of a small
+// launch: a head that is fetched as a whole, the mapping to a tile from it, and the tile's problem, fetched as a whole.
+// Fetched field by field, each where it is used, with the compiler's divisions in the mapping, the way to the first
+// load of a 64 x 64 tile took 620 instructions and 14 waits.
+struct KHead {
+  int nprob, total;        // problems; workgroups: the sum over problems of tiles * splits (* batch)
+  int accumulate, out_f32;
+  int krot;                // direct-to-LDS kernel: tile row tm starts its K loop at stage tm % krot (0: off)
+  int order;               // problem indices, four bits each, most work per workgroup first
+  int units[kMaxProblems]; // workgroups of the problems in that order
+  int batch, batch_inner, causal, rope_seq;
+  float scale, poly_a, poly_b;
+  int unused;
+  uint32_t* clk;           // measurement (NULL otherwise): every 64th workgroup stores its shader-clock cycles and
+                           // its 100 MHz wall ticks, pair number (workgroup / 64) % 64
+  const float* rowvec;
+  const float* addend;
+  int64_t a_bi, b_bi, c_bi, a_bo;
+};
+struct KArgs {
+  KHead h;
+  KProblem p[kMaxProblems];
+  int64_t b_bo, c_bo;
+};
+static_assert(sizeof(KHead) == 128 && sizeof(KProblem) == 128 && offsetof(KArgs, p) == 128, "whole lines of 64 bytes");
+
+// Host side: the arguments of a launch whose workgroups compute bm x bn tiles of the outputs in K stages of bk.  The logical
+// order of the workgroups is eight consecutive segments, one per XCD; segment x lists, heaviest problem first, the
+// x-th eighth of every problem's workgroups.  Longest-processing-time-first inside each segment keeps the tail of a
+// grouped launch short when the problems differ in K.
+inline void fill_kargs(KArgs& args, const GemmLaunch& g, int bm, int bn, int bk, int krot) {
+  KHead& a = args.h;
+  a.nprob = g.nprob;
+  a.accumulate = g.accumulate;
+  a.out_f32 = g.out_f32;
+  a.krot = krot;
+  a.clk = g.clk;
+  const GemmProblem& f = g.p[0];      // what every problem of a launch shares
+  a.batch = f.batch; a.batch_inner = f.batch_inner; a.causal = f.causal; a.rope_seq = f.rope_seq;
+  a.scale = f.scale; a.poly_a = f.poly_a; a.poly_b = f.poly_b;
+  a.unused = 0;
+  a.rowvec = f.rowvec; a.addend = f.addend;
+  a.a_bo = f.a_bo; a.a_bi = f.a_bi; a.b_bi = f.b_bi; a.c_bi = f.c_bi;
+  args.b_bo = f.b_bo; args.c_bo = f.c_bo;
+  int idx[kMaxProblems], units[kMaxProblems];
+  double work[kMaxProblems];
+  a.total = 0;
+  for (int i = 0; i < kMaxProblems; ++i) {
+    const GemmProblem& p = g.p[i < g.nprob ? i : 0];
+    KProblem& k = args.p[i];
+    // dual products keep B[1] as the up matrix; unused segments repeat the first
+    const bool dual = g.epi == EPI_SWIGLU_FWD || g.epi == EPI_SWIGLU_BWD;
+    const int nseg = dual || p.nseg < 1 ? 1 : p.nseg, splits = p.splits > 1 ? p.splits : 1;
     for (int s = 0; s < 3; ++s) {
-      const int pi = idx[s];
-      const int T = pi < a.nprob ? a.p[pi].tiles_m * a.p[pi].tiles_n * (a.p[pi].batch > 1 ? a.p[pi].batch : 1) : 0;
-      const int b0 = (int)((int64_t)x * T / 8), b1 = (int)((int64_t)(x + 1) * T / 8);
-      a.lstart[x][s] = l;
-      a.tstart[x][s] = b0;
-      l += b1 - b0;
+      k.A[s] = p.A[s < nseg ? s : 0];
+      k.B[s] = p.B[s < (dual ? 2 : nseg) ? s : 0];
+      k.C[s] = p.C[s];
     }
+    k.lda = p.lda; k.ldb = p.ldb; k.ldc = p.ldc;
+    k.M = p.M; k.N = p.N; k.K = p.K;
+    const int stages = (p.K + bk - 1) / bk * nseg;
+    k.chunk_nseg = 4 * ((stages + splits - 1) / splits) + nseg;
+    k.aux = g.epi == EPI_ROPE ? p.rope_half : p.pad_cols;
+    k.splits_kpad = 2 * splits + (p.kpad_ok ? 1 : 0);
+    const int tiles_m = (p.M + bm - 1) / bm, tiles_n = (p.N + bn - 1) / bn;
+    k.by_tiles = div_magic(tiles_m * tiles_n);
+    k.by_group = div_magic(8 * tiles_n);
+    idx[i] = i;
+    units[i] = i < g.nprob ? tiles_m * tiles_n * splits * (p.batch > 1 ? p.batch : 1) : 0;
+    work[i] = i < g.nprob ? (double)p.K * nseg / splits : -1.0;
+    a.total += units[i];
+  }
+  for (int i = 0; i < kMaxProblems; ++i)      // stable: equal problems keep their order
+    for (int j = kMaxProblems - 1; j > i; --j)
+      if (work[idx[j]] > work[idx[j - 1]]) { const int t = idx[j]; idx[j] = idx[j - 1]; idx[j - 1] = t; }
+  a.order = 0;
+  for (int s = 0; s < kMaxProblems; ++s) {
+    a.order |= idx[s] << (4 * s);
+    a.units[s] = units[idx[s]];
+  }
 }
 
 // The hardware hands consecutive workgroup ids to the 8 XCDs round-robin.  Renumber so
@@ -56,79 +120,107 @@ __device__ inline int xcd_remap(int bid, int nblocks) {
   return xcd * q + (xcd < rem ? xcd : rem) + local;
 }
 
-// Reads one word of every 64-byte line of the kernel arguments at once.  The mapping of a workgroup to its tile
-// and the setup behind it fetch them piece by piece, each piece behind the previous one's use, and every first
-// touch of a line is a miss of the scalar cache; after this the pieces are hits.  Six dependent launches of
-// an expert's backward (129 tokens, d 512, f 200): 35.1 -> 32.6 us.
-static_assert(sizeof(KArgs) == 976 && offsetof(KArgs, p[1]) == 232 && offsetof(KArgs, nprob) == 696,
-              "touch_args names a word of every line of this layout");
-__device__ inline void touch_args(const KArgs& a) {
-  asm volatile("" :: "s"(a.p[0].A[0]), "s"(a.p[0].ldb), "s"(a.p[0].batch), "s"(a.p[0].c_bo), "s"(a.p[1].A[0]),
-               "s"(a.p[1].ldb), "s"(a.p[1].batch), "s"(a.p[1].c_bo), "s"(a.p[2].A[0]), "s"(a.p[2].ldb), "s"(a.p[2].batch),
-               "s"(a.p[2].c_bo));
-  asm volatile("" :: "s"(a.nprob), "s"(a.krot), "s"(a.lstart[0][0]), "s"(a.lstart[5][0]), "s"(a.tstart[2][0]), "s"(a.tstart[7][2]));
+// 64 bytes of kernel arguments in scalar registers.
+typedef __attribute__((ext_vector_type(16))) uint32_t u32x16_t;
+typedef const __attribute__((address_space(4))) u32x16_t* KernargPtr;
+struct KWords { u32x16_t lo, hi; };
+
+// The head, and a touch of the first problem's lines behind the same wait: the only problem, as often as not, is then a
+// hit of the scalar cache.
+__device__ inline KHead load_head() {
+  KernargPtr k = (KernargPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  KWords w = {k[0], k[1]};
+  asm volatile("" : "+s"(w.lo), "+s"(w.hi) : "s"(k[2][0]), "s"(k[3][0]));
+  return __builtin_bit_cast(KHead, w);
+}
+__device__ inline KProblem load_problem(int prob) {
+  KernargPtr k = (KernargPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  KWords w = {k[2 + 2 * prob], k[3 + 2 * prob]};
+  asm volatile("" : "+s"(w.lo), "+s"(w.hi));
+  return __builtin_bit_cast(KProblem, w);
 }
 
 struct TileCoord { int prob, tm, tn, split, z; };
 
+// The problem of workgroup `bid` and its index there.
+__device__ inline int map_problem(const KHead& a, int bid, int* index) {
+  const int l = xcd_remap(bid, a.total);
+  *index = l;
+  if (a.nprob < 2) return 0;      // a single problem: the segments are consecutive eighths of its workgroups
+  // Segment x starts at the sum over problems of (x * units) / 8, no later than the first index that xcd_remap gives
+  // XCD x: the search for the segment of l goes upward from there.
+  auto first = [&](int x) {
+    int b = 0;
+#pragma unroll
+    for (int s = 0; s < kMaxProblems; ++s) b += (x * a.units[s]) >> 3;
+    return b;
+  };
+  int x = bid & 7;
+  while (x < 7 && first(x + 1) <= l) ++x;
+  int left = l - first(x), prob = 0, t = 0;
+#pragma unroll
+  for (int s = 0; s < kMaxProblems; ++s) {
+    const int b0 = (x * a.units[s]) >> 3, n = (((x + 1) * a.units[s]) >> 3) - b0;
+    if (left >= 0 && left < n) { prob = a.order >> (4 * s); t = b0 + left; }
+    left -= n;
+  }
+  *index = __builtin_amdgcn_readfirstlane(t);
+  return __builtin_amdgcn_readfirstlane(prob & 15);
+}
+
 // Grouped ordering inside one problem: walk GROUP tile-rows together so that concurrently
 // running blocks reuse both A panels (same tile-row) and B panels (same tile-column).
-__device__ inline TileCoord map_tile(const KArgs& a, int bid) {
+template <int BM, int BN>
+__device__ inline TileCoord map_tile(const KHead& a, const KProblem& p, int prob, int t) {
   TileCoord tc;
-  tc.split = a.splits > 1 ? __builtin_amdgcn_readfirstlane(bid / a.total_tiles) : 0;
-  const int l = __builtin_amdgcn_readfirstlane(bid - tc.split * a.total_tiles);
-  // A single problem: the segments are consecutive eighths of its tiles.  Without the schedule its arguments lie at
-  // fixed offsets and are fetched at once, where schedule, order and problem are three fetches that wait for each
-  // other: 0.5 to 0.7 us less per launch (refresh of three matrices, 150 of them: 2638 -> 2469 us).
-  int pi = 0, t = l;
-  if (a.nprob > 1) {
-    // find the (segment, slot) chunk that holds logical index l: the last one starting at or before l
-    int x = 0, sl = 0;
-#pragma unroll
-    for (int xi = 0; xi < 8; ++xi)
-#pragma unroll
-      for (int si = 0; si < 3; ++si)
-        if (a.lstart[xi][si] <= l) { x = xi; sl = si; }
-    pi = a.order[sl];
-    t = l - a.lstart[x][sl] + a.tstart[x][sl];
-  }
-  tc.prob = pi;
-  const int tiles_m = a.p[pi].tiles_m, tiles_n = a.p[pi].tiles_n;
-  tc.z = 0;
-  if (a.p[pi].batch > 1) {   // batched products: all tiles of one product are consecutive
-    const int per = tiles_m * tiles_n;
-    tc.z = __builtin_amdgcn_readfirstlane(t / per);
-    t -= tc.z * per;
-  }
+  tc.prob = prob;
+  const int tiles_m = (uint32_t)(p.M + BM - 1) / BM, tiles_n = (uint32_t)(p.N + BN - 1) / BN, per = tiles_m * tiles_n;
+  const int part = p.splits_kpad >= 4 || a.batch > 1 ? div_by(t, per, p.by_tiles) : 0;
+  t -= part * per;
+  tc.split = p.splits_kpad >= 4 ? part : 0;    // cut along K: all tiles of one part are consecutive
+  tc.z = p.splits_kpad >= 4 ? 0 : part;        // batched products: all tiles of one product are consecutive
   constexpr int GROUP = 8;
   const int gsize = GROUP * tiles_n;
-  const int g = t / gsize;
-  const int first_m = g * GROUP;
+  const int g = div_by(t, gsize, p.by_group);
+  const int first_m = g * GROUP, tt = t - g * gsize;
   const int gm = min(tiles_m - first_m, GROUP);
-  const int tt = t - g * gsize;
-  // Integer division runs on the vector ALU; tell the compiler the results are wave-uniform so
-  // that everything derived from them (buffer offsets, loop bounds) stays in scalar registers.
-  tc.tm = __builtin_amdgcn_readfirstlane(first_m + tt % gm);
-  tc.tn = __builtin_amdgcn_readfirstlane(tt / gm);
-  tc.prob = __builtin_amdgcn_readfirstlane(tc.prob);
-  tc.split = __builtin_amdgcn_readfirstlane(tc.split);
+  tc.tn = tt >> 3;
+  if (gm < GROUP) {            // the last group, of 1 to 7 tile rows: 65536 / gm rounded up, then corrected
+    constexpr uint64_t lo = 0x3334400055568000ull, hi = 0x24932AABull;      // gm = 2 to 5, 6 and 7
+    const int m = gm == 1 ? 65536 : (int)((gm < 6 ? lo >> (16 * (gm - 2)) : hi >> (16 * (gm - 6))) & 0xFFFF);
+    int q = (int)(((uint64_t)(uint32_t)tt * m) >> 16);
+    while (q * gm > tt) --q;
+    while ((q + 1) * gm <= tt) ++q;
+    tc.tn = q;
+  }
+  // wave-uniform by construction; told to the compiler so that everything derived from them (buffer offsets, loop
+  // bounds) stays in scalar registers
+  tc.tn = __builtin_amdgcn_readfirstlane(tc.tn);
+  tc.tm = __builtin_amdgcn_readfirstlane(first_m + tt - tc.tn * gm);
   return tc;
 }
 
-// The problem as seen by one product of a batch: operand, output and row-vector pointers moved to
-// product z.  ESZ = bytes per operand / output element.
+// A problem as one product of a batch sees it: operand, output and row-vector pointers moved to product z.
+// ESZ = bytes per operand / output element.
 template <int ESZ>
-__device__ inline GemmProblem product_view(const GemmProblem& p, int z) {
-  GemmProblem q = p;
-  if (p.batch > 1) {
-    const int zo = __builtin_amdgcn_readfirstlane(z / p.batch_inner), zi = z - zo * p.batch_inner;
-    const int64_t ao = ((int64_t)zo * p.a_bo + (int64_t)zi * p.a_bi) * ESZ;
-    const int64_t bo = ((int64_t)zo * p.b_bo + (int64_t)zi * p.b_bi) * ESZ;
-    const int64_t co = ((int64_t)zo * p.c_bo + (int64_t)zi * p.c_bi) * ESZ;
-    q.A[0] = (const char*)p.A[0] + ao;
-    q.B[0] = (const char*)p.B[0] + bo;
-    q.C[0] = (char*)p.C[0] + co;
-    if (p.rowvec) q.rowvec = p.rowvec + (int64_t)z * p.M;
+__device__ inline GemmProblem product_view(const KHead& a, const KProblem& p, int z) {
+  GemmProblem q;
+#pragma unroll
+  for (int s = 0; s < 3; ++s) { q.A[s] = p.A[s]; q.B[s] = p.B[s]; q.C[s] = p.C[s]; }
+  q.lda = p.lda; q.ldb = p.ldb; q.ldc = p.ldc;
+  q.M = p.M; q.N = p.N; q.K = p.K; q.nseg = p.chunk_nseg & 3; q.chunk = p.chunk_nseg >> 2;
+  q.pad_cols = p.aux; q.rope_half = p.aux;
+  q.splits = p.splits_kpad >> 1; q.kpad_ok = p.splits_kpad & 1;
+  q.rowvec = a.rowvec; q.addend = a.addend; q.scale = a.scale; q.causal = a.causal;
+  q.poly_a = a.poly_a; q.poly_b = a.poly_b; q.rope_seq = a.rope_seq;
+  if (a.batch > 1) {
+    const __attribute__((address_space(4))) int64_t* outer =
+        (const __attribute__((address_space(4))) int64_t*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(KArgs, b_bo) / 8;
+    const int zo = __builtin_amdgcn_readfirstlane(z / a.batch_inner), zi = z - zo * a.batch_inner;
+    q.A[0] = (const char*)p.A[0] + ((int64_t)zo * a.a_bo + (int64_t)zi * a.a_bi) * ESZ;
+    q.B[0] = (const char*)p.B[0] + ((int64_t)zo * outer[0] + (int64_t)zi * a.b_bi) * ESZ;
+    q.C[0] = (char*)p.C[0] + ((int64_t)zo * outer[1] + (int64_t)zi * a.c_bi) * ESZ;
+    if (a.rowvec) q.rowvec = a.rowvec + (int64_t)z * p.M;
   }
   return q;
 }
@@ -154,6 +246,7 @@ __device__ inline bool causal_tile_unused(const GemmProblem& p, int m0, int n0, 
 
 // Causal attention products only touch part of K (or nothing): clip the stage range [lo, hi).
 __device__ inline void causal_clip(const GemmProblem& p, int m0, int n0, int bm, int bk, int& lo, int& hi) {
+  if (p.causal == CAUSAL_NONE) return;
   if (p.causal == CAUSAL_K_FROM_M) lo = max(lo, m0 / bk);
   else if (p.causal == CAUSAL_K_UPTO_M) hi = min(hi, (m0 + bm + bk - 1) / bk);
   else if (p.causal == CAUSAL_TILE && n0 > m0 + bm - 1) hi = lo;
@@ -178,15 +271,14 @@ template <int EPI> constexpr bool kUnhandledEpilogue = false;
 
 // One output element (single products) or one (gate, up) pair (dual products).
 template <int EPI, typename T>
-__device__ inline void epilogue_elem(const GemmProblem& p, const KArgs& a, int prob, int split,
+__device__ inline void epilogue_elem(const GemmProblem& p, const KHead& a, int split,
                                      int row, int col, float v, float v2) {
   if (row >= p.M) return;
   if constexpr (EPI == EPI_STORE) {
-    if (col < p.N) ((T*)p.C[0])[(int64_t)row * p.ldc + col] = from_f32<T>(v);
-  } else if constexpr (EPI == EPI_SPLIT_F32) {
     if (col < p.N) {
-      float* base = a.partial + a.partial_off[prob] + (int64_t)split * p.M * p.ldc;
-      base[(int64_t)row * p.ldc + col] = v;
+      const int64_t idx = (int64_t)row * p.ldc + col;
+      if (sizeof(T) == 4 || p.splits > 1) ((float*)p.C[0])[(int64_t)split * p.M * p.ldc + idx] = v;
+      else ((T*)p.C[0])[idx] = from_f32<T>(v);
     }
   } else if constexpr (EPI == EPI_GRAD) {
     if (col < p.N) {
@@ -298,13 +390,13 @@ __device__ inline bf16x8s_t pack_bf16x8(const float (&v)[8]) {
 // Eight consecutive output columns of one row (bf16 outputs, 16-byte accesses), used by the
 // LDS-staged epilogue; falls back to single elements at the ragged right edge.
 template <int EPI>
-__device__ inline void epilogue_vec8(const GemmProblem& p, const KArgs& a, int prob, int split, int row,
-                                     int col0, const float (&v)[8], const float (&v2)[8]) {
+__device__ inline void epilogue_vec8(const GemmProblem& p, const KHead& a, int split, int row, int col0,
+                                     const float (&v)[8], const float (&v2)[8]) {
   if (row >= p.M) return;
   if (col0 + 8 > p.N) {
     if constexpr (EPI != EPI_ROPE) {      // whole heads: never ragged
 #pragma unroll
-      for (int e = 0; e < 8; ++e) epilogue_elem<EPI, __bf16>(p, a, prob, split, row, col0 + e, v[e], v2[e]);
+      for (int e = 0; e < 8; ++e) epilogue_elem<EPI, __bf16>(p, a, split, row, col0 + e, v[e], v2[e]);
     }
     return;
   }
@@ -409,19 +501,18 @@ __device__ inline void epilogue_vec8(const GemmProblem& p, const KArgs& a, int p
 // kernel) when the group lies inside the matrix, else element by element.  Row strides are multiples of 8
 // elements and col0 of 4, so the vector accesses are aligned.
 template <int EPI>
-__device__ inline void epilogue_vec4(const GemmProblem& p, const KArgs& a, int prob, int split, int row,
-                                     int col0, const float (&v)[4]) {
+__device__ inline void epilogue_vec4(const GemmProblem& p, const KHead& a, int split, int row, int col0,
+                                     const float (&v)[4]) {
   if (row >= p.M) return;
   if (col0 + 4 > p.N) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) epilogue_elem<EPI, __bf16>(p, a, prob, split, row, col0 + e, v[e], 0.f);
+    for (int e = 0; e < 4; ++e) epilogue_elem<EPI, __bf16>(p, a, split, row, col0 + e, v[e], 0.f);
     return;
   }
   const int64_t idx = (int64_t)row * p.ldc + col0;
-  if constexpr (EPI == EPI_SPLIT_F32) {
-    float* base = a.partial + a.partial_off[prob] + (int64_t)split * p.M * p.ldc;
+  if constexpr (EPI == EPI_STORE) {            // a part of a product that is cut along K
     f32x4_t o = {v[0], v[1], v[2], v[3]};
-    *(f32x4_t*)(base + idx) = o;
+    *(f32x4_t*)((float*)p.C[0] + (int64_t)split * p.M * p.ldc + idx) = o;
   } else if constexpr (EPI == EPI_GRAD) {
     if (a.out_f32) {
       f32x4_t* c = (f32x4_t*)((float*)p.C[0] + idx);

@@ -105,27 +105,28 @@ struct TileF32 {
 };
 
 template <class Cfg, int EPI, bool AKC, bool BKC>
-__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const KArgs args) {
+__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const KArgs) {
   constexpr bool DUAL = epi_is_dual(EPI);
   constexpr int FT = Cfg::FT, FK = Cfg::FK, FS = Cfg::FS;
   constexpr int NB = DUAL ? 2 : 1, MATS = 1 + NB;
   constexpr int KG = Cfg::KSPLIT ? FK / 64 : FK / 16;       // groups of 16 K per wave and stage
   __shared__ __attribute__((aligned(16))) float lds[2][MATS][FT * FS];
   static_assert(!Cfg::KSPLIT || 4 * NB * FT * (FT + 1) <= 2 * MATS * FT * FS, "the partial tiles reuse the operand buffers");
-  touch_args(args);
+  const KHead head = load_head();
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int nblocks = args.total_tiles * args.splits;
-  const TileCoord tc = map_tile(args, xcd_remap(blockIdx.x, nblocks));
-  const GemmProblem p = product_view<4>(args.p[tc.prob], tc.z);
+  int index;
+  const int prob = map_problem(head, blockIdx.x, &index);
+  const KProblem kp = load_problem(prob);
+  const TileCoord tc = map_tile<FT, FT>(head, kp, prob, index);
+  const GemmProblem p = product_view<4>(head, kp, tc.z);
   const int m0 = tc.tm * FT, n0 = tc.tn * FT;
   if (causal_tile_unused(p, m0, n0, FT)) return;
   const int nseg = DUAL ? 1 : p.nseg;
-  const int kt_per_seg = (p.K + FK - 1) / FK;
+  const int kt_per_seg = (uint32_t)(p.K + FK - 1) / FK;
   const int kt_total = kt_per_seg * nseg;
-  const int kt_chunk = __builtin_amdgcn_readfirstlane((kt_total + args.splits - 1) / args.splits);
-  int kt_begin = tc.split * kt_chunk;
-  int kt_end = min(kt_total, kt_begin + kt_chunk);
+  int kt_begin = tc.split * p.chunk;
+  int kt_end = min(kt_total, kt_begin + p.chunk);
   causal_clip(p, m0, n0, FT, FK, kt_begin, kt_end);
 
   f32x4_t acc[NB][2][2];
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const KArgs args) {
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          epilogue_elem<EPI, float>(p, args, tc.prob, tc.split, m0 + 32 * wm + 16 * i + 4 * (lane >> 4) + e,
+          epilogue_elem<EPI, float>(p, head, tc.split, m0 + 32 * wm + 16 * i + 4 * (lane >> 4) + e,
                                     n0 + 32 * wn + 16 * j + (lane & 15), acc[0][i][j][e], acc[NB - 1][i][j][e]);
     return;
   }
@@ -218,44 +219,27 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const KArgs args) {
       constexpr int W = NB * FT * (FT + 1);      // one wave's partial tiles
       s[w] = (q[0] + q[W]) + (q[2 * W] + q[3 * W]);
     }
-    epilogue_elem<EPI, float>(p, args, tc.prob, tc.split, m0 + r, n0 + c, s[0], s[1]);
+    epilogue_elem<EPI, float>(p, head, tc.split, m0 + r, n0 + c, s[0], s[1]);
   }
 }
 
+// Workgroups of a launch with ft x ft tiles.
 inline int f32_tiles(const GemmLaunch& g, int ft) {
   int tiles = 0;
   for (int i = 0; i < g.nprob; ++i)
-    tiles += ((g.p[i].M + ft - 1) / ft) * ((g.p[i].N + ft - 1) / ft) * (g.p[i].batch > 1 ? g.p[i].batch : 1);
+    tiles += ((g.p[i].M + ft - 1) / ft) * ((g.p[i].N + ft - 1) / ft) * (g.p[i].batch > 1 ? g.p[i].batch : 1) *
+             (g.p[i].splits > 1 ? g.p[i].splits : 1);
   return tiles;
 }
 
 template <class Cfg, int EPI>
 hipError_t run_f32_cfg(GemmLaunch& g, hipStream_t stream) {
-  constexpr int FT = Cfg::FT;
   KArgs a;
-  a.clk = nullptr;
-  a.nprob = g.nprob;
-  int tiles = 0;
-  for (int i = 0; i < 3; ++i) {
-    a.p[i] = g.p[i < g.nprob ? i : 0];
-    a.partial_off[i] = g.partial_off[i];
-    if (i >= g.nprob) continue;
-    GemmProblem& p = a.p[i];
-    p.tiles_m = (p.M + FT - 1) / FT;
-    p.tiles_n = (p.N + FT - 1) / FT;
-    p.tile_begin = tiles;
-    tiles += p.tiles_m * p.tiles_n * (p.batch > 1 ? p.batch : 1);
-    if (p.nseg < 2) { p.A[1] = p.A[0]; if (!epi_is_dual(EPI)) p.B[1] = p.B[0]; }
-    if (p.nseg < 3) { p.A[2] = p.A[0]; p.B[2] = p.B[0]; }
-  }
-  a.total_tiles = tiles;
-  fill_schedule(a);
-  a.splits = (EPI == EPI_SPLIT_F32 && g.splits > 1) ? g.splits : 1;
-  a.accumulate = g.accumulate;
-  a.out_f32 = 1;
-  a.partial = g.partial;
-  if (tiles == 0) return hipSuccess;
-  const dim3 grid(tiles * a.splits);
+  fill_kargs(a, g, Cfg::FT, Cfg::FT, Cfg::FK, 0);
+  a.h.out_f32 = 1;
+  a.h.clk = nullptr;
+  if (a.h.total == 0) return hipSuccess;
+  const dim3 grid(a.h.total);
   if (g.a_kcontig && g.b_kcontig) hipLaunchKernelGGL((gemm_f32_kernel<Cfg, EPI, true, true>), grid, dim3(256), 0, stream, a);
   else if constexpr (epi_is_dual(EPI) || EPI == EPI_ATTN_P || EPI == EPI_ATTN_DS) return hipErrorInvalidValue;
   else if (g.a_kcontig) hipLaunchKernelGGL((gemm_f32_kernel<Cfg, EPI, true, false>), grid, dim3(256), 0, stream, a);
@@ -285,8 +269,7 @@ hipError_t run_f32(GemmLaunch& g, hipStream_t stream) {
     if constexpr (EPI == EPI_STORE || EPI == EPI_GRAD) return run_f32_cfg<CfgFar, EPI>(g, stream);
     else return hipErrorInvalidValue;
   }
-  const int splits = EPI == EPI_SPLIT_F32 && g.splits > 1 ? g.splits : 1;
-  return f32_tiles(g, 64) * splits >= 512 ? run_f32_cfg<CfgWide, EPI>(g, stream) : run_f32_cfg<CfgSmall, EPI>(g, stream);
+  return f32_tiles(g, 64) >= 512 ? run_f32_cfg<CfgWide, EPI>(g, stream) : run_f32_cfg<CfgSmall, EPI>(g, stream);
 }
 }  // namespace
 
@@ -315,7 +298,6 @@ int f32_plan_splits(const GemmLaunch& g, int most) {
 hipError_t launch_gemm_f32(GemmLaunch& g, hipStream_t s) {
   switch (g.epi) {
     case EPI_STORE: return run_f32<EPI_STORE>(g, s);
-    case EPI_SPLIT_F32: return run_f32<EPI_SPLIT_F32>(g, s);
     case EPI_GRAD: return run_f32<EPI_GRAD>(g, s);
     case EPI_SWIGLU_FWD: return run_f32<EPI_SWIGLU_FWD>(g, s);
     case EPI_SWIGLU_BWD: return run_f32<EPI_SWIGLU_BWD>(g, s);

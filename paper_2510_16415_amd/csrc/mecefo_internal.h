@@ -8,8 +8,7 @@
 namespace mecefo {
 
 enum Epilogue : int {
-  EPI_STORE = 0,       // C0[row, col] = acc                          (activation dtype)
-  EPI_SPLIT_F32 = 1,   // partial[split][row, col] = acc   (fp32 split-K partial, row stride ldc)
+  EPI_STORE = 0,       // C0[row, col] = acc (activation dtype); a problem cut along K: C0 is fp32 [split][M x ldc]
   EPI_GRAD = 2,        // C0[row, col] (+)= acc                       (gradient dtype, optional accumulate)
   EPI_SWIGLU_FWD = 3,  // dual: G=C0, Z=C1, A=C2 = silu(g)*z
   EPI_SWIGLU_BWD = 4,  // dual: dA read from C0; C0=dG, C1=dZ, C2=A
@@ -20,6 +19,8 @@ enum Epilogue : int {
   EPI_RESID = 9,       // C0[row, col] = acc + C1[row, col]   (activation dtype; C1 may be C0)
   EPI_ROPE = 10,       // C0 = acc rotated: pairs (j, j + rope_half) of every head by the angle of position row % rope_seq
 };
+
+constexpr int kMaxProblems = 4;   // of one launch
 
 enum CausalK : int {
   CAUSAL_NONE = 0,
@@ -42,8 +43,8 @@ struct GemmProblem {
   int nseg;        // 1 to 3 K segments (ignored for dual products)
   int pad_cols;    // SwiGLU epilogues: columns [N, pad_cols) of the outputs are set to zero
   int kpad_ok;     // K-contiguous operands: bytes between K and the next multiple of 8 are known to be zero
-  int tile_begin;  // filled by the launcher
-  int tiles_m, tiles_n;
+  int splits;      // EPI_STORE: parts the contraction is cut into (0, 1: whole)
+  int chunk;       // device side: K stages of a workgroup
   // Batched products (attention: one product per (sequence, head)): `batch` independent products of
   // identical size; product z = zo * batch_inner + zi reads A + zo*a_bo + zi*a_bi, etc.; all six
   // offsets are counted in operand elements (an fp32 output behind bf16 operands counts two per element).
@@ -52,15 +53,14 @@ struct GemmProblem {
   const float* rowvec;   // attention epilogues: fp32 per output row, product z starts at z * M
   float scale;           // attention epilogues, EPI_POLY
   const float* addend;   // EPI_POLY, EPI_HILO: fp32 [M x ldc], may be NULL (zero); may be C0 of EPI_HILO itself
-  union {                // one epilogue uses one pair: kernel arguments are read by every workgroup before it can start
-    struct { float poly_a, poly_b; };      // EPI_POLY
-    struct { int rope_half, rope_seq; };   // EPI_ROPE: half the head dimension (0: plain store) and the sequence length;
-  };                                       // rowvec and addend are the cosine and sine tables [rope_seq][rope_half]
+  float poly_a, poly_b;  // EPI_POLY
+  int rope_half, rope_seq;   // EPI_ROPE: half the head dimension (0: plain store) and the sequence length; rowvec and
+                             // addend are the cosine and sine tables [rope_seq][rope_half]
   int causal;            // CausalK
 };
 
 struct GemmLaunch {
-  GemmProblem p[3];
+  GemmProblem p[kMaxProblems];   // batch, causal and the epilogues' scalars and vectors: those of p[0] hold for all
   int nprob;
   bool a_kcontig, b_kcontig;
   int epi;          // Epilogue
@@ -68,9 +68,6 @@ struct GemmLaunch {
   bool out_f32;     // EPI_GRAD: gradient buffer dtype is fp32 (else same as operands)
   int accumulate;   // EPI_GRAD
   int tile;         // EPI_ROPE: the configuration that gemm_bf16_rope_tile found for this launch
-  int splits;       // EPI_SPLIT_F32: number of K splits (partials laid out [split][M x ldc] per problem)
-  float* partial;   // EPI_SPLIT_F32: base of the partial buffer; problem i starts at partial_off[i]
-  int64_t partial_off[3];
   uint32_t* clk;    // measurement: 64 (cycles, wall ticks) pairs written by the direct-to-LDS kernel, or NULL
 };
 

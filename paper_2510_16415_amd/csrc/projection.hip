@@ -201,7 +201,7 @@ GemmLaunch product(const Plan& pl, bool akc, bool bkc, const void* A_hi, const v
   GemmLaunch g;
   memset(&g, 0, sizeof(g));
   g.a_kcontig = akc; g.b_kcontig = bkc; g.epi = EPI_GRAD; g.bf16 = pl.bf16; g.out_f32 = true;
-  g.splits = 1; g.nprob = 1;
+  g.nprob = 1;
   GemmProblem& p = g.p[0];
   const bool two = A_lo != nullptr || B_lo != nullptr;
   p.A[0] = A_hi; p.A[1] = A_lo ? A_lo : A_hi; p.A[2] = A_hi;
@@ -222,16 +222,17 @@ hipError_t run_product(const Plan& pl, char* base, GemmLaunch& g, hipStream_t s)
   }
   if (splits <= 1) return launch_gemm(g, s);
   const int epi = g.epi;
-  g.epi = EPI_SPLIT_F32;
-  g.splits = splits;
-  g.partial = (float*)(base + pl.partial);
-  g.partial_off[0] = 0;
-  hipError_t e = launch_gemm(g, s);
+  GemmLaunch cut = g;
+  float* const partial = (float*)(base + pl.partial);
+  cut.epi = EPI_STORE;
+  cut.p[0].splits = splits;
+  cut.p[0].C[0] = partial;
+  hipError_t e = launch_gemm(cut, s);
   if (e != hipSuccess) return e;
   const int64_t mn = (int64_t)p.M * p.ldc;
-  if (epi == EPI_GRAD) return launch_splitk_reduce(false, g.partial, splits, mn, p.C[0], s);
+  if (epi == EPI_GRAD) return launch_splitk_reduce(false, partial, splits, mn, p.C[0], s);
   const dim3 grid((unsigned)((mn + 1023) / 1024));
-  SplitSum q{g.partial, splits, mn, p.ldc, nullptr, nullptr, nullptr, p.addend, p.poly_a, p.poly_b, p.scale};
+  SplitSum q{partial, splits, mn, p.ldc, nullptr, nullptr, nullptr, p.addend, p.poly_a, p.poly_b, p.scale};
   if (epi == EPI_POLY) {
     q.raw = (float*)p.C[1]; q.hi = (__bf16*)p.C[0];
     hipLaunchKernelGGL(split_sum_kernel<EPI_POLY>, grid, dim3(256), 0, s, q);
