@@ -165,6 +165,7 @@ struct StageTimer {
 struct Workspace {
   // offsets in bytes from the (256-byte aligned) workspace base
   size_t U, rstd, DG, DZ, AA, dU, T[3], C[3], partial, dgp, total;
+  int64_t room;      // fp32 elements of the partial buffer
   int splits;
   int64_t c_elems[3];
 };
@@ -263,6 +264,7 @@ Workspace layout(const Ctx& c, const int r[3], mecefo_side_t side, int force_spl
     if ((size_t)spr * t > partial) partial = (size_t)spr * t;
   }
   w.partial = take(partial);
+  w.room = (int64_t)(partial / 4);
   w.dgp = take((size_t)rmsnorm_bwd_blocks(c.b) * c.dm * 4);
   w.total = off + 256;   // slack for aligning the caller's base pointer
   return w;
@@ -305,43 +307,29 @@ GemmProblem prob(const void* A0, const void* A1, int64_t lda, const void* B0, co
   return p;
 }
 
-// Makes a store launch write `splits` fp32 parts of every problem into `partial`, one problem's behind the other's;
-// C receives the outputs they belong to.
-void cut_along_k(GemmLaunch& g, int splits, float* partial, void** C) {
+// A store launch into the library's own buffers, its problems cut along K as their `splits` say (bf16_plan_splits):
+// those write fp32 parts into `partial`, one problem's behind the other's, which one more launch sums.
+mecefo_status_t launch_store(const Ctx& c, const Bufs& bf, GemmLaunch& g, hipStream_t s) {
+  SumJob jobs[kMaxProblems];
+  int n = 0;
+  float* partial = (float*)(bf.base + bf.w.partial);
   for (int i = 0; i < g.nprob; ++i) {
     GemmProblem& p = g.p[i];
-    C[i] = p.C[0];
+    if (p.splits <= 1) continue;
+    jobs[n++] = SumJob{partial, p.C[0], (int64_t)p.M * p.ldc, p.splits};
     p.C[0] = partial;
-    p.splits = splits;
-    partial += (int64_t)splits * p.M * p.ldc;
+    partial += (int64_t)p.splits * p.M * p.ldc;
   }
-}
-mecefo_status_t sum_parts(const Ctx& c, const GemmLaunch& g, void* const* C, hipStream_t s) {
-  for (int i = 0; i < g.nprob; ++i)
-    HIP_TRY(launch_splitk_reduce(c.bf16, (const float*)g.p[i].C[0], g.p[i].splits, (int64_t)g.p[i].M * g.p[i].ldc, C[i], s));
+  HIP_TRY(launch_gemm(g, s));
+  if (n > 0) HIP_TRY(launch_sum_parts(c.bf16, jobs, n, s));
   return MECEFO_OK;
 }
 
-// A store launch into the library's own buffers (row stride == ldc of every problem), cut along K
-// into up to `most` parts (what the workspace holds partials for; 1 for fp32) when that fills the chip better.
-mecefo_status_t launch_store_split(const Ctx& c, const Bufs& bf, GemmLaunch& g, int most, hipStream_t s) {
-  const int splits = most > 1 ? bf16_plan_splits(g, most) : 1;
-  if (splits <= 1) {
-    HIP_TRY(launch_gemm(g, s));
-    return MECEFO_OK;
-  }
-  void* C[kMaxProblems];
-  cut_along_k(g, splits, (float*)(bf.base + bf.w.partial), C);
-  HIP_TRY(launch_gemm(g, s));
-  return sum_parts(c, g, C, s);
-}
-
 // dA = dY Wd  ->  recompute G, Z from U and apply the SwiGLU backward in the epilogue
-// (DG = dG, DZ = dZ, AA = A)  ->  dU = dG Wg + dZ Wu.   Sec. 3.3 (Rcomp) + exact Dgrad.
-mecefo_status_t recompute_and_dgrad(const Ctx& c, const Bufs& bf, const void* U, int64_t ldu, const void* dY,
+// (DG = dG, DZ = dZ, AA = A).   Sec. 3.3 (Rcomp).
+mecefo_status_t recompute(const Ctx& c, const Bufs& bf, const void* U, int64_t ldu, const void* dY,
                                     int64_t lddy, const void* Wg, const void* Wu, const void* Wd,
-                                    const void* Gsaved, const void* Zsaved, void* dU, int64_t lddu,
-                                    hipStream_t s) {
+                                    const void* Gsaved, const void* Zsaved, hipStream_t s) {
   const mecefo_ffn_desc_t& d = *c.d;
   char* base = bf.base;
   void* DG = base + bf.w.DG; void* DZ = base + bf.w.DZ; void* AA = base + bf.w.AA;
@@ -364,111 +352,133 @@ mecefo_status_t recompute_and_dgrad(const Ctx& c, const Bufs& bf, const void* U,
     g.p[0] = prob(U, nullptr, ldu, Wg, Wu, d.ld_w_fd, DG, DZ, AA, c.ldf, b, c.ff, c.dm, 1, (int)c.ldf);
     HIP_TRY(launch_gemm(g, s));
   }
-  if (dU) {  // dU = dG Wg + dZ Wu   [b x d], two K segments of length f
-    STAGE(MECEFO_STAGE_DGRAD_GATE_UP, s);
-    GemmLaunch g = new_launch(c, true, false, EPI_STORE);
-    g.nprob = 1;
-    g.p[0] = prob(DG, DZ, c.ldf, Wg, Wu, d.ld_w_fd, dU, nullptr, nullptr, lddu, b, c.dm, c.ff, 2);
-    g.p[0].kpad_ok = 1;   // DG / DZ padding columns were written as zeros; the weight rows are predicated exactly
-    // K is only cut when dU is the workspace's own [b x d] buffer (the reduction writes whole rows)
-    TRY(launch_store_split(c, bf, g, dU == base + bf.w.dU ? store_splits_du(c) : 1, s));
-  }
   return MECEFO_OK;
 }
 
-// Eq. (2) for the three FFN matrices, each as project -> contract over tokens -> expand.
-//   SIDE_INPUT : T = X P [b x r];  C = Gy^T T [m x r];  dW [m x n] = C P^T.
-//   SIDE_OUTPUT: T = Gy P [b x r]; C = X^T T [n x r];   dW [m x n] = P C^T.
-// gate: (Gy, X) = (dG, U); up: (dZ, U); down: (dY, A).
-mecefo_status_t lowrank_wgrad(const Ctx& c, const Bufs& bf, const void* U, int64_t ldu, const void* dY,
-                              int64_t lddy, const mecefo_proj_t P[3], mecefo_side_t side, void* dW[3],
-                              int accumulate, hipStream_t s, int exact_mask = 0) {
+// dU = dG Wg + dZ Wu   [b x d], two K segments of length f
+GemmProblem dgrad_problem(const Ctx& c, const Bufs& bf, const void* Wg, const void* Wu, void* dU, int64_t lddu) {
+  GemmProblem p = prob(bf.base + bf.w.DG, bf.base + bf.w.DZ, c.ldf, Wg, Wu, c.d->ld_w_fd, dU, nullptr, nullptr, lddu,
+                       (int)c.b, c.dm, c.ff, 2);
+  p.kpad_ok = 1;   // DG / DZ padding columns were written as zeros; the weight rows are predicated exactly
+  p.whole = dU != bf.base + bf.w.dU;
+  return p;
+}
+mecefo_status_t dgrad(const Ctx& c, const Bufs& bf, const void* Wg, const void* Wu, void* dU, int64_t lddu, hipStream_t s) {
+  if (!dU || c.b == 0) return MECEFO_OK;
+  STAGE(MECEFO_STAGE_DGRAD_GATE_UP, s);
+  GemmLaunch g = new_launch(c, true, false, EPI_STORE);
+  g.nprob = 1;
+  g.p[0] = dgrad_problem(c, bf, Wg, Wu, dU, lddu);
+  if (c.bf16) bf16_plan_splits(g, bf.w.room);
+  return launch_store(c, bf, g, s);
+}
+
+// The three products of Eq. (2) for the FFN matrices that take it, T = X P, C = Gy^T T, dW = C P^T (SIDE_INPUT) or
+// T = Gy P, C = X^T T, dW = P C^T (SIDE_OUTPUT), with (Gy, X) = (dG, U) for gate, (dZ, U) for up, (dY, A) for down.
+struct LowRank {
+  const void* Gy[3]; const void* X[3];
+  int64_t ldgy[3], ldx[3], ldt[3], lddw[3];
+  int m_out[3], n_in[3];      // rows and columns of dW
+  void* T[3]; void* C[3];
+  const mecefo_proj_t* P;
+  bool in;                    // SIDE_INPUT
+  int lr[3], ex[3], n_lr, n_ex;      // matrices that take Eq. (2), and those that take the exact weight gradient
+};
+LowRank low_rank(const Ctx& c, const Bufs& bf, const void* U, int64_t ldu, const void* dY, int64_t lddy,
+                 const mecefo_proj_t P[3], mecefo_side_t side, int exact_mask) {
   const mecefo_ffn_desc_t& d = *c.d;
   char* base = bf.base;
-  const int b = (int)c.b;
-  const void* Gy[3] = {base + bf.w.DG, base + bf.w.DZ, dY};
-  const int64_t ldgy[3] = {c.ldf, c.ldf, lddy};
-  const void* X[3] = {U, U, base + bf.w.AA};
-  const int64_t ldx[3] = {ldu, ldu, c.ldf};
-  const int m_out[3] = {c.ff, c.ff, c.dm};   // rows of dW
-  const int n_in[3] = {c.dm, c.dm, c.ff};    // cols of dW
-  const int64_t lddw[3] = {d.ld_w_fd, d.ld_w_fd, d.ld_w_df};
-  const bool in = side == MECEFO_SIDE_INPUT;
-  int64_t ldt[3];
-  void* T[3];
-  void* C[3];
-  for (int i = 0; i < 3; ++i) { ldt[i] = up(P[i].r, 8); T[i] = base + bf.w.T[i]; C[i] = base + bf.w.C[i]; }
-  // matrices that take Eq. (2) and matrices that take the exact weight gradient
-  int lr[3], ex[3], n_lr = 0, n_ex = 0;
+  LowRank q = {{base + bf.w.DG, base + bf.w.DZ, dY}, {U, U, base + bf.w.AA}, {c.ldf, c.ldf, lddy}, {ldu, ldu, c.ldf}, {},
+               {d.ld_w_fd, d.ld_w_fd, d.ld_w_df}, {c.ff, c.ff, c.dm}, {c.dm, c.dm, c.ff}, {}, {}, P,
+               side == MECEFO_SIDE_INPUT, {}, {}, 0, 0};
   for (int i = 0; i < 3; ++i) {
-    if (exact_mask & (1 << i)) ex[n_ex++] = i;
-    else lr[n_lr++] = i;
+    q.ldt[i] = up(P[i].r, 8); q.T[i] = base + bf.w.T[i]; q.C[i] = base + bf.w.C[i];
+    if (exact_mask & (1 << i)) q.ex[q.n_ex++] = i;
+    else q.lr[q.n_lr++] = i;
   }
+  return q;
+}
+// T of matrix i: contraction over the projected dimension
+GemmProblem project_problem(const Ctx& c, const Bufs& bf, const LowRank& q, int i) {
+  const void* a_op = q.in ? q.X[i] : q.Gy[i];
+  GemmProblem p = prob(a_op, nullptr, q.in ? q.ldx[i] : q.ldgy[i], q.P[i].P, nullptr, q.P[i].ld, q.T[i], nullptr, nullptr,
+                       q.ldt[i], (int)c.b, q.P[i].r, q.in ? q.n_in[i] : q.m_out[i], 1);
+  // the K-contiguous operand is one of the library's own zero-padded [b x f] buffers (A, dG, dZ)
+  p.kpad_ok = (a_op == bf.base + bf.w.AA || a_op == bf.base + bf.w.DG || a_op == bf.base + bf.w.DZ) ? 1 : 0;
+  return p;
+}
 
-  if (n_ex > 0) {  // exact Wgrad: dW = Gy^T X, contraction over tokens
+// dU and the projections of Eq. (2), in one launch where that is shorter than two.  Both are few long products: dU
+// [b x d] walks 2 f, the down projection's T [b x r] walks f (SIDE_INPUT) on a fraction of the chip, the others d.
+mecefo_status_t dgrad_and_project(const Ctx& c, const Bufs& bf, const LowRank& q, const void* Wg, const void* Wu,
+                                  void* dU, int64_t lddu, hipStream_t s) {
+  if (c.b == 0) return MECEFO_OK;
+  GemmLaunch project = new_launch(c, true, false, EPI_STORE);
+  for (int j = 0; j < q.n_lr; ++j) project.p[project.nprob++] = project_problem(c, bf, q, q.lr[j]);
+  if (dU && q.n_lr > 0) {
+    GemmLaunch both = project, alone = project;
+    both.p[both.nprob++] = alone.p[0] = dgrad_problem(c, bf, Wg, Wu, dU, lddu);
+    alone.nprob = 1;
+    const bool merge = c.bf16 ? bf16_plan_splits(both, bf.w.room) < bf16_plan_splits(alone, bf.w.room) + bf16_plan_splits(project, bf.w.room)
+                              : !f32_far(both);
+    if (merge) {
+      STAGE(MECEFO_STAGE_DGRAD_GATE_UP, s);
+      both.clk = g_prof.cur_clk;
+      return launch_store(c, bf, both, s);
+    }
+  }
+  TRY(dgrad(c, bf, Wg, Wu, dU, lddu, s));
+  if (q.n_lr == 0) return MECEFO_OK;
+  STAGE(MECEFO_STAGE_PROJECT, s);
+  project.clk = g_prof.cur_clk;
+  if (c.bf16) bf16_plan_splits(project, bf.w.room);
+  return launch_store(c, bf, project, s);
+}
+
+// The weight gradients: exact ones, and Eq. (2) from the projections on.
+mecefo_status_t lowrank_wgrad(const Ctx& c, const Bufs& bf, const LowRank& q, void* dW[3], int accumulate, hipStream_t s) {
+  const int b = (int)c.b;
+  if (q.n_ex > 0) {  // exact Wgrad: dW = Gy^T X, contraction over tokens
     STAGE(MECEFO_STAGE_WGRAD_EXACT, s);
     GemmLaunch g = new_launch(c, false, false, EPI_GRAD);
-    g.nprob = n_ex;
+    g.nprob = q.n_ex;
     g.accumulate = accumulate;
-    for (int j = 0; j < n_ex; ++j) {
-      const int i = ex[j];
-      g.p[j] = prob(Gy[i], nullptr, ldgy[i], X[i], nullptr, ldx[i], dW[i], nullptr, nullptr, lddw[i], m_out[i], n_in[i], b, 1);
+    for (int j = 0; j < q.n_ex; ++j) {
+      const int i = q.ex[j];
+      g.p[j] = prob(q.Gy[i], nullptr, q.ldgy[i], q.X[i], nullptr, q.ldx[i], dW[i], nullptr, nullptr, q.lddw[i], q.m_out[i],
+                    q.n_in[i], b, 1);
     }
     HIP_TRY(launch_gemm(g, s));
   }
-  if (n_lr == 0) return MECEFO_OK;
-
-  if (b > 0) {  // project: T = (X or Gy) P, contraction over the projected dimension
-    STAGE(MECEFO_STAGE_PROJECT, s);
-    GemmLaunch g = new_launch(c, true, false, EPI_STORE);
-    g.nprob = n_lr;
-    for (int j = 0; j < n_lr; ++j) {
-      const int i = lr[j];
-      g.p[j] = prob(in ? X[i] : Gy[i], nullptr, in ? ldx[i] : ldgy[i], P[i].P, nullptr, P[i].ld, T[i], nullptr,
-                    nullptr, ldt[i], b, P[i].r, in ? n_in[i] : m_out[i], 1);
-      // the K-contiguous operand is one of the library's own zero-padded [b x f] buffers (A, dG, dZ)
-      const void* a_op = in ? X[i] : Gy[i];
-      g.p[j].kpad_ok = (a_op == base + bf.w.AA || a_op == base + bf.w.DG || a_op == base + bf.w.DZ) ? 1 : 0;
-    }
-    int rr[3] = {0, 0, 0};
-    for (int j = 0; j < n_lr; ++j) rr[lr[j]] = P[lr[j]].r;
-    TRY(launch_store_split(c, bf, g, store_splits_project(c, rr, side), s));
-  }
+  if (q.n_lr == 0) return MECEFO_OK;
   {  // contract over tokens: C = (Gy or X)^T T   [rows x r], K = b
+    STAGE(MECEFO_STAGE_CONTRACT, s);
     GemmLaunch g = new_launch(c, false, false, EPI_STORE);
-    g.nprob = n_lr;
-    for (int j = 0; j < n_lr; ++j) {
-      const int i = lr[j];
-      const int rows = in ? m_out[i] : n_in[i];
-      g.p[j] = prob(in ? Gy[i] : X[i], nullptr, in ? ldgy[i] : ldx[i], T[i], nullptr, ldt[i], C[i], nullptr,
-                    nullptr, ldt[i], rows, P[i].r, b, 1);
+    g.nprob = q.n_lr;
+    for (int j = 0; j < q.n_lr; ++j) {
+      const int i = q.lr[j];
+      g.p[j] = prob(q.in ? q.Gy[i] : q.X[i], nullptr, q.in ? q.ldgy[i] : q.ldx[i], q.T[i], nullptr, q.ldt[i], q.C[i],
+                    nullptr, nullptr, q.ldt[i], q.in ? q.m_out[i] : q.n_in[i], q.P[i].r, b, 1);
     }
-    // the workspace holds partials for up to bf.w.splits parts
-    const int most = b > 0 ? bf.w.splits : 1;
-    const int splits = most <= 1 ? 1 : c.bf16 ? bf16_plan_splits(g, most) : f32_plan_splits(g, most);
-    void* dst[kMaxProblems];
-    if (splits > 1) cut_along_k(g, splits, (float*)(base + bf.w.partial), dst);
-    {
-      STAGE(MECEFO_STAGE_CONTRACT, s);
-      g.clk = g_prof.cur_clk;
-      HIP_TRY(launch_gemm(g, s));
+    // no more parts than the workspace holds
+    if (b > 0) {
+      if (c.bf16) bf16_plan_splits(g, bf.w.room);
+      else f32_plan_splits(g, bf.w.splits);
     }
-    if (splits > 1) {
-      STAGE(MECEFO_STAGE_SPLITK_REDUCE, s);
-      TRY(sum_parts(c, g, dst, s));
-    }
+    TRY(launch_store(c, bf, g, s));
   }
   {  // expand: dW = C P^T (SIDE_INPUT) or P C^T (SIDE_OUTPUT), K = r, into the gradient buffers
     STAGE(MECEFO_STAGE_EXPAND, s);
     GemmLaunch g = new_launch(c, true, true, EPI_GRAD);
-    g.nprob = n_lr;
+    g.nprob = q.n_lr;
     g.accumulate = accumulate;
-    for (int j = 0; j < n_lr; ++j) {
-      const int i = lr[j];
-      g.p[j] = in ? prob(C[i], nullptr, ldt[i], P[i].P, nullptr, P[i].ld, dW[i], nullptr, nullptr, lddw[i],
-                         m_out[i], n_in[i], P[i].r, 1)
-                  : prob(P[i].P, nullptr, P[i].ld, C[i], nullptr, ldt[i], dW[i], nullptr, nullptr, lddw[i],
-                         m_out[i], n_in[i], P[i].r, 1);
+    for (int j = 0; j < q.n_lr; ++j) {
+      const int i = q.lr[j];
+      const mecefo_proj_t& P = q.P[i];
+      g.p[j] = q.in ? prob(q.C[i], nullptr, q.ldt[i], P.P, nullptr, P.ld, dW[i], nullptr, nullptr, q.lddw[i], q.m_out[i],
+                           q.n_in[i], P.r, 1)
+                    : prob(P.P, nullptr, P.ld, q.C[i], nullptr, q.ldt[i], dW[i], nullptr, nullptr, q.lddw[i], q.m_out[i],
+                           q.n_in[i], P.r, 1);
     }
     HIP_TRY(launch_gemm(g, s));
   }
@@ -766,7 +776,8 @@ mecefo_status_t mecefo_ffn_bwd_exact(const mecefo_ffn_desc_t* desc, const void* 
   Bufs bf;
   TRY(carve(c, r0, MECEFO_SIDE_INPUT, ws, ws_bytes, &bf));
   hipStream_t s = (hipStream_t)hip_stream;
-  TRY(recompute_and_dgrad(c, bf, U, desc->ld_act_d, dY, desc->ld_act_d, Wg, Wu, Wd, G, Z, dU, desc->ld_act_d, s));
+  TRY(recompute(c, bf, U, desc->ld_act_d, dY, desc->ld_act_d, Wg, Wu, Wd, G, Z, s));
+  TRY(dgrad(c, bf, Wg, Wu, dU, desc->ld_act_d, s));
   // exact Wgrad: dWg = dG^T U, dWu = dZ^T U [f x d]; dWd = dY^T A [d x f]; contraction over tokens
   STAGE(MECEFO_STAGE_WGRAD_EXACT, s);
   GemmLaunch g = new_launch(c, false, false, EPI_GRAD);
@@ -799,9 +810,11 @@ mecefo_status_t mecefo_ffn_bwd_lowrank(const mecefo_ffn_desc_t* desc, const void
   Bufs bf;
   TRY(carve(c, r, side, ws, ws_bytes, &bf));
   hipStream_t s = (hipStream_t)hip_stream;
-  TRY(recompute_and_dgrad(c, bf, U, desc->ld_act_d, dY, desc->ld_act_d, Wg, Wu, Wd, nullptr, nullptr, dU, desc->ld_act_d, s));
+  const LowRank q = low_rank(c, bf, U, desc->ld_act_d, dY, desc->ld_act_d, P, side, 0);
+  TRY(recompute(c, bf, U, desc->ld_act_d, dY, desc->ld_act_d, Wg, Wu, Wd, nullptr, nullptr, s));
+  TRY(dgrad_and_project(c, bf, q, Wg, Wu, dU, desc->ld_act_d, s));
   void* dW[3] = {dWg, dWu, dWd};
-  return lowrank_wgrad(c, bf, U, desc->ld_act_d, dY, desc->ld_act_d, P, side, dW, accumulate, s);
+  return lowrank_wgrad(c, bf, q, dW, accumulate, s);
 }
 
 mecefo_status_t mecefo_block_bwd_skip_ex(const mecefo_ffn_desc_t* desc, const void* H, const void* dOut,
@@ -843,7 +856,9 @@ mecefo_status_t mecefo_block_bwd_skip_ex(const mecefo_ffn_desc_t* desc, const vo
     ldu = c.dm;
   }
   void* dUb = base + bf.w.dU;
-  TRY(recompute_and_dgrad(c, bf, U, ldu, dOut, desc->ld_act_d, Wg, Wu, Wd, Gs, Zs, dUb, c.dm, s));
+  const LowRank q = low_rank(c, bf, U, ldu, dOut, desc->ld_act_d, P, side, exact_mask);
+  TRY(recompute(c, bf, U, ldu, dOut, desc->ld_act_d, Wg, Wu, Wd, Gs, Zs, s));
+  TRY(dgrad_and_project(c, bf, q, Wg, Wu, dUb, c.dm, s));
   // Skip the MHA connection: the gradient handed to the previous layer is dH = dOut + normbwd(dU).
   auto norm_backward = [&]() -> mecefo_status_t {
     STAGE(MECEFO_STAGE_NORM_BWD, s);
@@ -865,7 +880,7 @@ mecefo_status_t mecefo_block_bwd_skip_ex(const mecefo_ffn_desc_t* desc, const vo
   const bool dx_first = dX != dOut && dX != H;
   if (dx_first) TRY(norm_backward());
   void* dW[3] = {dWg, dWu, dWd};
-  TRY(lowrank_wgrad(c, bf, U, ldu, dOut, desc->ld_act_d, P, side, dW, accumulate, s, exact_mask));
+  TRY(lowrank_wgrad(c, bf, q, dW, accumulate, s));
   if (!dx_first) TRY(norm_backward());
   return MECEFO_OK;
 }
@@ -939,7 +954,8 @@ mecefo_status_t mecefo_block_bwd_full(const mecefo_ffn_desc_t* desc, const mecef
     STAGE(MECEFO_STAGE_NORM_FWD, s);
     HIP_TRY(launch_rmsnorm_fwd(c.bf16, in->H, d.ld_act_d, in->g_ffn, d.rms_eps, Ub, dm, rstd, c.b, dm, s));
   }
-  TRY(recompute_and_dgrad(c, bf, Ub, dm, in->dOut, d.ld_act_d, in->Wg, in->Wu, in->Wd, nullptr, nullptr, dUb, dm, s));
+  TRY(recompute(c, bf, Ub, dm, in->dOut, d.ld_act_d, in->Wg, in->Wu, in->Wd, nullptr, nullptr, s));
+  TRY(dgrad(c, bf, in->Wg, in->Wu, dUb, dm, s));
   {
     STAGE(MECEFO_STAGE_WGRAD_EXACT, s);
     GemmLaunch g = new_launch(c, false, false, EPI_GRAD);

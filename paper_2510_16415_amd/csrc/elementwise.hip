@@ -406,23 +406,32 @@ __global__ __launch_bounds__(256) void add_kernel(const T* a, int64_t lda, const
   *(Vec<T, VEC>*)(out + r * ldo + cv * VEC) = o;
 }
 
-// C[i] = sum_s partial[s][i], fixed summation order (bit-reproducible).
+// out[i] = sum over the parts of part[k][i] for up to four products, fixed summation order (bit-reproducible).  One
+// launch for all of them: a launch of its own for each of three small products is 5 us each.
+struct SumJobs { SumJob j[kMaxProblems]; unsigned first[kMaxProblems]; };      // first[k]: first block of job k
 template <typename T>
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ partial, int splits,
-                                                            int64_t mn, T* __restrict__ C) {
-  const int64_t i4 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+__global__ __launch_bounds__(256) void sum_parts_kernel(const SumJobs a) {
+  int k = 0;
+#pragma unroll
+  for (int i = 1; i < kMaxProblems; ++i) k = blockIdx.x >= a.first[i] ? i : k;
+  const SumJob job = a.j[k];
+  T* C = (T*)job.out;
+  const int64_t i4 = ((int64_t)(blockIdx.x - a.first[k]) * 256 + threadIdx.x) * 4, mn = job.n;
   if (i4 >= mn) return;
-  if (i4 + 4 <= mn) {
-    float4 s = *(const float4*)(partial + i4);
-    for (int k = 1; k < splits; ++k) {
-      const float4 v = *(const float4*)(partial + (int64_t)k * mn + i4);
+  if (i4 + 4 <= mn && mn % 4 == 0) {
+    float4 s = *(const float4*)(job.part + i4);
+#pragma unroll 4
+    for (int q = 1; q < job.parts; ++q) {
+      const float4 v = *(const float4*)(job.part + (int64_t)q * mn + i4);
       s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
     }
-    C[i4] = (T)s.x; C[i4 + 1] = (T)s.y; C[i4 + 2] = (T)s.z; C[i4 + 3] = (T)s.w;
+    Vec<T, 4> o;
+    o.e[0] = (T)s.x; o.e[1] = (T)s.y; o.e[2] = (T)s.z; o.e[3] = (T)s.w;
+    *(Vec<T, 4>*)(C + i4) = o;
   } else {
-    for (int64_t i = i4; i < mn; ++i) {
+    for (int64_t i = i4; i < mn && i < i4 + 4; ++i) {
       float s = 0.f;
-      for (int k = 0; k < splits; ++k) s += partial[(int64_t)k * mn + i];
+      for (int q = 0; q < job.parts; ++q) s += job.part[(int64_t)q * mn + i];
       C[i] = (T)s;
     }
   }
@@ -567,15 +576,17 @@ hipError_t launch_add(bool bf16, const void* a, int64_t lda, const void* bsrc, i
   return hipGetLastError();
 }
 
-hipError_t launch_splitk_reduce(bool bf16, const float* partial, int splits, int64_t mn, void* C,
-                                hipStream_t s) {
-  const unsigned grid = blocks_for((mn + 3) / 4);
-  if (bf16)
-    hipLaunchKernelGGL(splitk_reduce_kernel<__bf16>, dim3(grid), dim3(256), 0, s, partial, splits, mn,
-                       (__bf16*)C);
-  else
-    hipLaunchKernelGGL(splitk_reduce_kernel<float>, dim3(grid), dim3(256), 0, s, partial, splits, mn,
-                       (float*)C);
+hipError_t launch_sum_parts(bool bf16, const SumJob* jobs, int n, hipStream_t s) {
+  SumJobs a;
+  unsigned grid = 0;
+  for (int i = 0; i < kMaxProblems; ++i) {
+    a.j[i] = jobs[i < n ? i : 0];
+    a.first[i] = i < n ? grid : 0xFFFFFFFFu;
+    if (i < n) grid += blocks_for((jobs[i].n + 3) / 4);
+  }
+  if (grid == 0) return hipSuccess;
+  if (bf16) hipLaunchKernelGGL(sum_parts_kernel<__bf16>, dim3(grid), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(sum_parts_kernel<float>, dim3(grid), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -13,6 +13,7 @@ using CfgM8 = TileCfg<128, 128, 4, 2>;   // 8 waves x (32 x 64): one workgroup p
 using CfgT = TileCfg<64, 64, 2, 2>;      // 4 waves x (32 x 32): three workgroups per CU
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
+constexpr int kMaxSplits = 16;   // parts a product may be cut into along K
 
 // Two 64 KiB stages, refilled one stage ahead.  Measured alternatives that lost: four 32-K stages
 // (64-byte row pieces double the L2 request count); rings of three buffers, symmetric or A2+B3 /
@@ -40,9 +41,8 @@ using PipeT2 = DtlPipe<CfgT, 3, 2>;   // 96 KiB: one workgroup per CU, two group
 // modelled time over the configurations,
 //     fixed + per_round * n + stages * max(stage_alone, stage_shared * n),   n = workgroups per CU,
 // with constants fitted to a sweep of 50 launches over every operand layout (K 32 to 11008, 2 to 2752
-// workgroups; the model is within 15 % of nearly all of them).  Every launch of the sweep had one K: a grouped launch
-// is costed as if each of its problems had the longest one, which overstates it (the projections of Eq. (2): K = d, d
-// and f).  Sides measured, in us (256^2 / 128^2
+// workgroups; the model is within 15 % of nearly all of them).  Every launch of the sweep had one K; problems of
+// different length are laid out over the CUs, the longest first.  Sides measured, in us (256^2 / 128^2
 // two-stage / 128^2 four-stage / 64^2): [2048 x 2048], K 2048: 49 / 27 / 27 / 35; the same three in one
 // launch: 54 / 60 / 73 / 84; [512 x 512], K 2048: 47 / 23 / 25 / 15; [2048 x 2048], K 5461: 135 / 80 / 61 /
 // 101; [2048 x 512], K 1376: 33 / 16 / 17 / 11; SwiGLU recompute of 2048 tokens, d 2048, f 5461: 119 / 111 /
@@ -65,21 +65,15 @@ inline const TileModel& tile_model(int c) {
   return m[c];
 }
 
-// Output tiles of a launch, and the K stages of its longest problem.
-inline int bf16_tiles(const GemmLaunch& g, int bm, int bn) {
-  const bool dual = epi_is_dual(g.epi);
-  int t = 0;
-  for (int i = 0; i < g.nprob; ++i)
-    t += cdiv(g.p[i].M, bm) * cdiv(g.p[i].N, dual ? bn / 2 : bn) * (g.p[i].batch > 1 ? g.p[i].batch : 1);
-  return t;
+// K stages of a workgroup of problem i, and the workgroups of the problem on bm x bn tiles.
+inline int bf16_parts(const GemmProblem& p) { return p.splits > 1 ? p.splits : 1; }
+inline int bf16_stages(const GemmLaunch& g, int i) {
+  const GemmProblem& p = g.p[i];
+  return cdiv(cdiv(p.K, kBK) * (p.nseg > 1 && !epi_is_dual(g.epi) ? p.nseg : 1), bf16_parts(p));
 }
-inline int bf16_stages(const GemmLaunch& g) {
-  int st = 0;
-  for (int i = 0; i < g.nprob; ++i) {
-    const int s = cdiv(g.p[i].K, kBK) * (g.p[i].nseg > 1 && !epi_is_dual(g.epi) ? g.p[i].nseg : 1);
-    if (s > st) st = s;
-  }
-  return st;
+inline int bf16_units(const GemmLaunch& g, int i, int bm, int bn) {
+  const GemmProblem& p = g.p[i];
+  return cdiv(p.M, bm) * cdiv(p.N, epi_is_dual(g.epi) ? bn / 2 : bn) * (p.batch > 1 ? p.batch : 1) * bf16_parts(p);
 }
 
 // A K that is no multiple of 8 and not padded with zeros behind a K-contiguous operand.
@@ -89,45 +83,107 @@ inline bool bf16_ragged(const GemmLaunch& g) {
   return false;
 }
 
-// Modelled time in us of the launch cut along K into `splits` parts, on configuration c.
-inline float bf16_tile_cost(const GemmLaunch& g, int c, int splits) {
+// Modelled time in us of the launch on configuration c.
+inline float bf16_tile_cost(const GemmLaunch& g, int c) {
   const TileModel& m = tile_model(c);
-  const float blocks = (float)bf16_tiles(g, m.bm, m.bn) * splits;
-  float n = blocks / 256.f;
-  if (n < 4.f) n = (float)(int)(n + 0.999f);   // few workgroups per CU: the fullest CU sets the time
-  const float stage = n <= 1.f ? m.stage_alone : fmaxf(m.stage_alone, m.stage_shared * n);
-  return m.fixed + m.per_round * n + (float)cdiv(bf16_stages(g), splits) * stage;
+  int units[kMaxProblems], stages[kMaxProblems], total = 0, longest = 0;
+  bool equal = true;
+  for (int i = 0; i < g.nprob; ++i) {
+    units[i] = bf16_units(g, i, m.bm, m.bn);
+    stages[i] = bf16_stages(g, i);
+    total += units[i];
+    if (stages[i] > longest) longest = stages[i];
+    equal &= stages[i] == stages[0];
+  }
+  float n = total / 256.f, load;               // workgroups and K stages of the fullest CU
+  if (equal || n >= 4.f) {
+    if (n < 4.f) n = (float)(int)(n + 0.999f);   // few workgroups per CU: the fullest CU sets the time
+    load = 0.f;
+    for (int i = 0; i < g.nprob; ++i) load += (float)units[i] * stages[i];
+    load *= n / total;
+  } else {
+    // Problems of different length, the longest first, each workgroup to the CU with the least to do.  At most
+    // 2 * kMaxProblems * 4 groups of equally loaded CUs come about: a problem fills whole groups, and splits one.
+    struct { int load, cus, wgs; } q[64] = {{0, 256, 0}};
+    int nq = 1;
+    bool done[kMaxProblems] = {};
+    for (int k = 0; k < g.nprob; ++k) {
+      int i = -1;
+      for (int j = 0; j < g.nprob; ++j)
+        if (!done[j] && (i < 0 || stages[j] > stages[i])) i = j;
+      done[i] = true;
+      for (int left = units[i]; left > 0 && nq < 64;) {
+        int at = 0;
+        for (int j = 1; j < nq; ++j)
+          if (q[j].load < q[at].load) at = j;
+        const int take = left < q[at].cus ? left : q[at].cus;
+        if (take < q[at].cus) {
+          q[nq] = q[at];
+          q[nq++].cus -= take;
+          q[at].cus = take;
+        }
+        q[at].load += stages[i];
+        q[at].wgs += 1;
+        left -= take;
+      }
+    }
+    int at = 0;
+    for (int j = 1; j < nq; ++j)
+      if (q[j].load > q[at].load) at = j;
+    load = (float)q[at].load;
+    n = (float)q[at].wgs;
+  }
+  const float time = total <= 256 ? load * m.stage_alone : fmaxf(longest * m.stage_alone, load * m.stage_shared);
+  return m.fixed + m.per_round * n + time;
 }
-inline int bf16_best_tile(const GemmLaunch& g, int splits, float* cost = nullptr) {
+inline int bf16_best_tile(const GemmLaunch& g, float* cost = nullptr) {
   int best = TILE_L;
-  float t = bf16_tile_cost(g, TILE_L, splits);
+  float t = bf16_tile_cost(g, TILE_L);
   const bool ragged = bf16_ragged(g);
+  int longest = 0;
+  for (int i = 0; i < g.nprob; ++i) longest = bf16_stages(g, i) > longest ? bf16_stages(g, i) : longest;
   for (int c = 1; c < TILE_COUNT; ++c) {
     // with a ragged K the groups of waves meet one more barrier per stage: a third of what they save
-    const float x = bf16_tile_cost(g, c, splits) + (c == TILE_T2 && ragged ? 0.05f * cdiv(bf16_stages(g), splits) : 0.f);
+    const float x = bf16_tile_cost(g, c) + (c == TILE_T2 && ragged ? 0.05f * longest : 0.f);
     if (x < t) { t = x; best = c; }
   }
   if (cost) *cost = t;
   return best;
 }
 
-// K splits of a launch that may be cut into up to `most` parts: every part keeps four or more stages, and
-// the fp32 partials (written, read back and summed by one more launch: about 5 us and their bytes at
-// 3 TB/s) have to be paid for by a shorter K loop.
-inline int bf16_plan_splits(const GemmLaunch& g, int most) {
-  double out = 0;
-  for (int i = 0; i < g.nprob; ++i) out += (double)g.p[i].M * g.p[i].ldc * 4;
-  const int stages = bf16_stages(g);
-  int best = 1;
-  float t;
-  bf16_best_tile(g, 1, &t);
-  for (int s = 2; s <= most && stages / s >= 4; ++s) {
-    float x;
-    bf16_best_tile(g, s, &x);
-    x += 5.f + (float)(out * s * 2 / 3e6);
-    if (x < t) { t = x; best = s; }
+// Cuts the problems of a store launch along K (their `splits`) where that makes the launch shorter, into parts of about
+// equal length with four or more stages each, of which `room` fp32 elements can be held.  The parts are written, read
+// back and summed by one more launch: about 5 us and their bytes at 3 TB/s.  Returns the modelled time of it all.
+inline float bf16_plan_splits(GemmLaunch& g, int64_t room) {
+  int longest = 0;
+  for (int i = 0; i < g.nprob; ++i) {
+    g.p[i].splits = 1;
+    longest = bf16_stages(g, i) > longest ? bf16_stages(g, i) : longest;
   }
-  return best;
+  float t;
+  bf16_best_tile(g, &t);
+  int best[kMaxProblems];
+  for (int i = 0; i < g.nprob; ++i) best[i] = 1;
+  for (int s = 2; s <= kMaxSplits && longest / s >= 4; ++s) {
+    const int len = cdiv(longest, s);
+    int64_t out = 0;
+    for (int i = 0; i < g.nprob; ++i) {
+      g.p[i].splits = 1;
+      const int whole = bf16_stages(g, i);
+      g.p[i].splits = !g.p[i].whole && whole > len + len / 8 ? cdiv(whole, len) : 1;
+      if (g.p[i].splits > 1) out += (int64_t)g.p[i].splits * g.p[i].M * g.p[i].ldc;
+    }
+    if (out > room) break;
+    float x;
+    bf16_best_tile(g, &x);
+    x += 5.f + (float)((double)out * 8 / 3e6);
+    if (x < t) {
+      t = x;
+      for (int i = 0; i < g.nprob; ++i) best[i] = g.p[i].splits;
+    }
+  }
+  for (int i = 0; i < g.nprob; ++i) g.p[i].splits = best[i];
+  return t;
 }
 
 struct NoPipe { static constexpr int LDS_BYTES = 0, THREADS = 0; };
@@ -192,7 +248,7 @@ inline int bf16_forced_tile() {
 template <bool AKC, bool BKC, int EPI>
 hipError_t run_bf16_auto(GemmLaunch& g, hipStream_t stream) {
   int c = bf16_forced_tile();
-  if (c < 0) c = bf16_best_tile(g, g.p[0].splits > 1 ? g.p[0].splits : 1);
+  if (c < 0) c = bf16_best_tile(g);
   if constexpr (register_staged(EPI)) {
     if (c == TILE_R4) return run_bf16<CfgL4, AKC, BKC, EPI>(g, stream);
     if (c == TILE_R8) return run_bf16<CfgL8, AKC, BKC, EPI>(g, stream);

@@ -18,10 +18,10 @@ int gemm_bf16_rope_tile(const GemmLaunch& g, int dh) {
   if (dh != 64 && dh != 128) return -1;
   int best = TILE_L;
   for (int c : {TILE_M2, TILE_M4})
-    if (dh == 64 && bf16_tile_cost(g, c, 1) < bf16_tile_cost(g, best, 1)) best = c;
+    if (dh == 64 && bf16_tile_cost(g, c) < bf16_tile_cost(g, best)) best = c;
   float least;
-  bf16_best_tile(g, 1, &least);
-  return bf16_tile_cost(g, best, 1) <= least + 6.f ? best : -1;
+  bf16_best_tile(g, &least);
+  return bf16_tile_cost(g, best) <= least + 6.f ? best : -1;
 }
 static hipError_t run_rope(GemmLaunch& g, hipStream_t s) {
   switch (g.tile) {

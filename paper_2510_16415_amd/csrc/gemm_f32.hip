@@ -248,17 +248,6 @@ hipError_t run_f32_cfg(GemmLaunch& g, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Whether the rows of one tile (K-contiguous operand) or the K rows of one stage span 2 GiB or more.  Only a
-// projection can: it is B of the project products and A or B of the expand products.
-inline bool f32_far(const GemmLaunch& g) {
-  auto span = [](int64_t ld, int rows) { return ld * 4 * (rows < 64 ? rows : 64); };
-  for (int i = 0; i < g.nprob; ++i) {
-    const GemmProblem& p = g.p[i];
-    if (span(p.lda, g.a_kcontig ? p.M : p.K) >= (int64_t)1 << 31 || span(p.ldb, g.b_kcontig ? p.N : p.K) >= (int64_t)1 << 31) return true;
-  }
-  return false;
-}
-
 // 64 x 64 tiles once they give every CU two workgroups.  Skip backwards with the line at 256 / 1024 / 2048 tiles against
 // 512, us: [1024 x 512], f 1376: 185 / 178 / 178 against 175; [1024 x 1024], f 2752 (688 tiles): 536 / 484 / 484 against
 // 516; [2048 x 512], f 1376 (704): 290 / 272 / 271 against 282; [4096 x 512], f 1376: 451 / 464 / 473 against 452;
@@ -273,12 +262,23 @@ hipError_t run_f32(GemmLaunch& g, hipStream_t stream) {
 }
 }  // namespace
 
+// Whether the rows of one tile (K-contiguous operand) or the K rows of one stage span 2 GiB or more.  Only a
+// projection can: it is B of the project products and A or B of the expand products.
+bool f32_far(const GemmLaunch& g) {
+  auto span = [](int64_t ld, int rows) { return ld * 4 * (rows < 64 ? rows : 64); };
+  for (int i = 0; i < g.nprob; ++i) {
+    const GemmProblem& p = g.p[i];
+    if (span(p.lda, g.a_kcontig ? p.M : p.K) >= (int64_t)1 << 31 || span(p.ldb, g.b_kcontig ? p.N : p.K) >= (int64_t)1 << 31) return true;
+  }
+  return false;
+}
+
 // K splits of a launch that may be cut into up to `most` parts: a stage takes about 0.5 us while every CU has at
 // most two workgroups, the sum of the parts one more launch of 5 us per problem.  Skip backwards never cut / always cut
 // as far as the workspace holds, against this rule, us: [8192 x 128], f 344, rank 16: 189 / 133 against 133; [4096 x 256],
 // f 688, rank 32: 198 / 182 against 182; [2048 x 128], f 344, rank 32: 79.0 / 78.0 against 79.0; [256 x 256], f 688: 69.5 / 74.8
 // against 69.5; [1024 x 512], f 1376: 175 / 189 against 175; [4096 x 1024], f 2752: 1492 / 1501 against 1487.
-int f32_plan_splits(const GemmLaunch& g, int most) {
+void f32_plan_splits(GemmLaunch& g, int most) {
   const int tiles = f32_tiles(g, CfgSmall::FT);
   int stages = 0;
   for (int i = 0; i < g.nprob; ++i) {
@@ -292,7 +292,7 @@ int f32_plan_splits(const GemmLaunch& g, int most) {
     const float x = (float)((stages + s - 1) / s) * 0.5f * (n > 1.f ? n : 1.f) + (s > 1 ? 5.f * g.nprob : 0.f);
     if (s == 1 || x < t) { t = x; best = s; }
   }
-  return best;
+  for (int i = 0; i < g.nprob; ++i) g.p[i].splits = best;
 }
 
 hipError_t launch_gemm_f32(GemmLaunch& g, hipStream_t s) {

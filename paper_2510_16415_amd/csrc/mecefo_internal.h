@@ -44,6 +44,7 @@ struct GemmProblem {
   int pad_cols;    // SwiGLU epilogues: columns [N, pad_cols) of the outputs are set to zero
   int kpad_ok;     // K-contiguous operands: bytes between K and the next multiple of 8 are known to be zero
   int splits;      // EPI_STORE: parts the contraction is cut into (0, 1: whole)
+  bool whole;      // host side: never cut (the sum of the parts writes rows of ldc elements, padding included)
   int chunk;       // device side: K stages of a workgroup
   // Batched products (attention: one product per (sequence, head)): `batch` independent products of
   // identical size; product z = zo * batch_inner + zi reads A + zo*a_bo + zi*a_bi, etc.; all six
@@ -114,7 +115,8 @@ hipError_t prepare_attention_bwd();
 hipError_t launch_gemm(GemmLaunch& g, hipStream_t stream);
 hipError_t launch_gemm_bf16(GemmLaunch& g, hipStream_t stream);
 hipError_t launch_gemm_f32(GemmLaunch& g, hipStream_t stream);
-int f32_plan_splits(const GemmLaunch& g, int most);
+void f32_plan_splits(GemmLaunch& g, int most);   // cuts every problem of the launch into the same number of parts
+bool f32_far(const GemmLaunch& g);
 
 // Elementwise / reduction kernels (elementwise.hip).  `bf16` selects the storage type.
 hipError_t launch_rmsnorm_fwd(bool bf16, const void* H, int64_t ldh, const void* gamma, float eps,
@@ -130,9 +132,9 @@ hipError_t launch_dgamma_reduce(const float* dg_partial, int nblk, int d, void* 
 // dX = dOut + dU  (no-norm variant)
 hipError_t launch_add(bool bf16, const void* a, int64_t lda, const void* bsrc, int64_t ldb, void* out,
                       int64_t ldo, int64_t rows, int cols, hipStream_t s);
-// C[M x N] (activation dtype) = sum over splits of partial[split][M*N]
-hipError_t launch_splitk_reduce(bool bf16, const float* partial, int splits, int64_t mn, void* C,
-                                hipStream_t s);
+// out[0 .. n) (activation dtype, 16-byte aligned) = sum over the parts of part[k][0 .. n), for up to kMaxProblems jobs
+struct SumJob { const float* part; void* out; int64_t n; int parts; };
+hipError_t launch_sum_parts(bool bf16, const SumJob* jobs, int n, hipStream_t s);
 // Standalone SwiGLU backward from saved G, Z: reads dA (in DG), writes DG=dG, DZ=dZ, AA=A; pads zeroed.
 hipError_t launch_swiglu_bwd(bool bf16, const void* G, const void* Z, int64_t ldgz, void* DG, void* DZ,
                              void* AA, int64_t ldf, int64_t b, int f, int pad_cols, hipStream_t s);

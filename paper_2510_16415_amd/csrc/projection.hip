@@ -16,7 +16,7 @@ namespace mecefo {
 namespace {
 
 constexpr int kNormBlocks = 256;
-constexpr int kMaxSplits = 8;
+constexpr int kHeldSplits = 8;
 
 // The iterate is kept as an fp32 master copy.  For bf16 weights it enters the MFMA products as the
 // sum of two bf16 matrices (hi = bf16(x), lo = bf16(x - hi): 16 mantissa bits), contracted as two K
@@ -186,7 +186,7 @@ Plan make_plan(bool bf16, int m, int n, int r, int left) {
   p.part = take(kNormBlocks * 4);
   // split-K partials of the products with few output tiles and a long contraction
   const int64_t big = (p.dim > p.other ? p.dim : p.other);
-  p.partial = take(bf16 ? (size_t)kMaxSplits * big * p.ldx * 4 : 0);
+  p.partial = take(bf16 ? (size_t)kHeldSplits * big * p.ldx * 4 : 0);
   p.total = off + 256;
   return p;
 }
@@ -217,8 +217,9 @@ hipError_t run_product(const Plan& pl, char* base, GemmLaunch& g, hipStream_t s)
   GemmProblem& p = g.p[0];
   int splits = 1;
   if (pl.bf16) {
-    const int64_t most = (int64_t)kMaxSplits * (pl.dim > pl.other ? pl.dim : pl.other) * pl.ldx / ((int64_t)p.M * p.ldc);
-    splits = bf16_plan_splits(g, most < 16 ? (int)most : 16);
+    bf16_plan_splits(g, (int64_t)kHeldSplits * (pl.dim > pl.other ? pl.dim : pl.other) * pl.ldx);
+    splits = p.splits;
+    p.splits = 1;
   }
   if (splits <= 1) return launch_gemm(g, s);
   const int epi = g.epi;
@@ -230,7 +231,10 @@ hipError_t run_product(const Plan& pl, char* base, GemmLaunch& g, hipStream_t s)
   hipError_t e = launch_gemm(cut, s);
   if (e != hipSuccess) return e;
   const int64_t mn = (int64_t)p.M * p.ldc;
-  if (epi == EPI_GRAD) return launch_splitk_reduce(false, partial, splits, mn, p.C[0], s);
+  if (epi == EPI_GRAD) {
+    const SumJob job{partial, p.C[0], mn, splits};
+    return launch_sum_parts(false, &job, 1, s);
+  }
   const dim3 grid((unsigned)((mn + 1023) / 1024));
   SplitSum q{partial, splits, mn, p.ldc, nullptr, nullptr, nullptr, p.addend, p.poly_a, p.poly_b, p.scale};
   if (epi == EPI_POLY) {
