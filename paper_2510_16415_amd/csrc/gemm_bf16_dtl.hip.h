@@ -240,18 +240,15 @@ template <class Cfg, int NS_, int KG_ = 1> struct DtlPipe {
 
 // RAGGED: K may end inside a 16-byte chunk (the instantiation without it keeps the large tile's loop free of the
 // test: 0.5 % of the 7B-shaped layer).
-template <class Cfg, class Pipe, bool AKC, bool BKC, int EPI, bool RAGGED>
-__global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const KArgs) {
+// SEGS: products may have several K segments.
+template <class Cfg, class Pipe, bool AKC, bool BKC, int EPI, bool RAGGED, bool SEGS>
+__device__ __forceinline__ void dtl_tile(const KHead& head, const GemmProblem& p, int m0, int n0, int split, uint8_t* smem_all) {
   constexpr bool DUAL = epi_is_dual(EPI);
   constexpr int BM = Cfg::BM, BN = Cfg::BN, NT = Cfg::NT;
   constexpr int TM = Cfg::WM / 16, TN = Cfg::WN / 16;     // 16x16 MFMA blocks per wave
   constexpr int BK = Pipe::BK, NS = Pipe::NS, KS = BK / 32, FPS = Pipe::FPS;
   constexpr int A_BYTES = Pipe::A_BYTES, STAGE = Pipe::STAGE_BYTES, KG = Pipe::KG;
   static_assert(TM % 2 == 0 && TN % (DUAL ? 2 : 1) == 0, "the epilogue takes 32 rows at a time");
-  constexpr int BN_OUT = DUAL ? BN / 2 : BN;
-  extern __shared__ __attribute__((aligned(1024))) uint8_t smem_all[];
-
-  const KHead head = load_head();
   const int group = KG > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NT) : 0;
   const int t = threadIdx.x - group * NT;      // thread, wave and LDS buffers within the group
   const int lane = t & 63;
@@ -259,22 +256,11 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const K
   uint8_t* smem = smem_all + group * NS * STAGE;
   const int wm = wave / Cfg::WAVES_N, wn = wave % Cfg::WAVES_N;
 
-  // Measurement only: shader-clock cycles and constant-rate (100 MHz) ticks this workgroup takes.
-  uint64_t clk_c0 = 0, clk_w0 = 0;
-  if (head.clk) { clk_c0 = clock64(); clk_w0 = wall_clock64(); }
-  int index;
-  const int prob = map_problem(head, blockIdx.x, &index);
-  const KProblem kp = load_problem(prob);
-  const TileCoord tc = map_tile<BM, BN_OUT>(head, kp, prob, index);
-  const GemmProblem p = product_view<2>(head, kp, tc.z);
-  const int m0 = tc.tm * BM, n0 = tc.tn * BN_OUT;
-  if (causal_tile_unused(p, m0, n0, BM)) return;
-
-  const int nseg = DUAL ? 1 : p.nseg;
+  const int nseg = DUAL || !SEGS ? 1 : p.nseg;
   const int K = p.K;
   const int kt_per_seg = (uint32_t)(K + BK - 1) / BK;
   const int kt_total = kt_per_seg * nseg;
-  int kt_begin = tc.split * p.chunk;
+  int kt_begin = split * p.chunk;
   int kt_end = min(kt_total, kt_begin + p.chunk);
   causal_clip(p, m0, n0, BM, BK, kt_begin, kt_end);
 
@@ -314,11 +300,11 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const K
       for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
 
   auto issue = [&](int kt, uint32_t stage) {     // kt < 0: no stage left for this group, all zeros
-    const int seg = (kt >= kt_per_seg ? 1 : 0) + (kt >= 2 * kt_per_seg ? 1 : 0);
+    const int seg = SEGS ? (kt >= kt_per_seg ? 1 : 0) + (kt >= 2 * kt_per_seg ? 1 : 0) : 0;
     const int k0 = KG > 1 && kt < 0 ? 0 : (kt - seg * kt_per_seg) * BK;
     const int K = KG > 1 && kt < 0 ? 0 : p.K;
     const bool tail = k0 + BK > K;
-    if (DUAL) {
+    if (DUAL || !SEGS) {
       da.issue(ra0, ra0, stage, k0, K, tail);
       db.issue(rb0, rb1, stage + A_BYTES, k0, K, tail);
     } else {
@@ -365,7 +351,7 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const K
   // row keeps every shared line in use for at most eight stages, well inside the 4 MB L2 (larger
   // strides measured slower).  Measured on the 7B-shaped layer: recompute launch -3.5 %, the others
   // -1 % to 0.  The summation order over K depends on the tile row only, so reruns stay bit-equal.
-  int rot = head.krot > 0 ? tc.tm & (head.krot - 1) : 0;      // krot: a power of two
+  int rot = head.krot > 0 ? m0 / BM & (head.krot - 1) : 0;      // krot: a power of two
   while (rot >= nst && rot > 0) rot = nst > 0 ? rot - nst : 0;
   auto kmap = [&](int turn) {
     const int i = KG > 1 ? turn * KG + group : turn;
@@ -480,7 +466,7 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const K
             const int rl = it * RPI4 + r4;
             const f32x4_t g = *(const f32x4_t*)(ep + rl * RS + c4);
             const float v4[4] = {g[0], g[1], g[2], g[3]};
-            epilogue_vec4<EPI>(p, head, tc.split, row_w + i * 32 + rl, col_w - rd_c8 + c4, v4);
+            epilogue_vec4<EPI>(p, head, split, row_w + i * 32 + rl, col_w - rd_c8 + c4, v4);
           }
           continue;
         }
@@ -506,14 +492,86 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const K
             for (int e = 0; e < 4; ++e) { v2[e] = z0[e]; v2[4 + e] = z1[e]; }
           }
         }
-        if constexpr (!F32_OUT) epilogue_vec8<EPI>(p, head, tc.split, row_w + i * 32 + rl, col_w, v, v2);
+        if constexpr (!F32_OUT) epilogue_vec8<EPI>(p, head, split, row_w + i * 32 + rl, col_w, v, v2);
       }
     }
   }
-  if (head.clk && (blockIdx.x & 63) == 0 && t == 0) {
-    uint32_t* o = head.clk + 2 * ((blockIdx.x >> 6) & 63);
-    o[0] = (uint32_t)(clock64() - clk_c0);
-    o[1] = (uint32_t)(wall_clock64() - clk_w0);
+}
+
+// Measurement only: shader-clock cycles and constant-rate (100 MHz) ticks of a workgroup.
+struct WorkgroupClock {
+  uint64_t c0 = 0, w0 = 0;
+  __device__ inline void start(const KHead& head) {
+    if (head.clk) { c0 = clock64(); w0 = wall_clock64(); }
+  }
+  __device__ inline void stop(const KHead& head) const {
+    if (head.clk && (blockIdx.x & 63) == 0 && threadIdx.x == 0) {
+      uint32_t* o = head.clk + 2 * ((blockIdx.x >> 6) & 63);
+      o[0] = (uint32_t)(clock64() - c0);
+      o[1] = (uint32_t)(wall_clock64() - w0);
+    }
+  }
+};
+
+template <class Cfg, class Pipe, bool AKC, bool BKC, int EPI, bool RAGGED>
+__global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const KArgs) {
+  constexpr int BM = Cfg::BM, BN_OUT = epi_is_dual(EPI) ? Cfg::BN / 2 : Cfg::BN;
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+  const KHead head = load_head();
+  WorkgroupClock clock;
+  clock.start(head);
+  int index;
+  const int prob = map_problem(head, blockIdx.x, &index);
+  const KProblem kp = load_problem(prob);
+  const TileCoord tc = map_tile<BM, BN_OUT>(head, kp, prob, index);
+  const GemmProblem p = product_view<2>(head, kp, tc.z);
+  const int m0 = tc.tm * BM, n0 = tc.tn * BN_OUT;
+  if (causal_tile_unused(p, m0, n0, BM)) return;
+  dtl_tile<Cfg, Pipe, AKC, BKC, EPI, RAGGED, true>(head, p, m0, n0, tc.split, smem);
+  clock.stop(head);
+}
+
+// Launches whose 256 x 256 tiles leave a last round of at most 128: the workgroups of the full rounds compute such
+// tiles (Cfg), and the last round's tiles are shared out over the chip in halves, quarters or sixteenths (C2, C4, C16),
+// which walk K two to six times as fast.  head.total counts the workgroups of the full rounds, the tail's tiles are the
+// last of the problem with the most.
+template <class Cfg, class Pipe, class C2, class P2, class C4, class P4, class C16, class P16, bool AKC, bool BKC, int EPI>
+__global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_tail_kernel(const KArgs) {
+  static_assert(P2::THREADS == Pipe::THREADS && P4::THREADS == Pipe::THREADS && P16::THREADS == Pipe::THREADS, "one launch");
+  constexpr int BM = Cfg::BM, BN_OUT = epi_is_dual(EPI) ? Cfg::BN / 2 : Cfg::BN;
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+  const KHead head = load_head();
+  WorkgroupClock clock;
+  clock.start(head);
+  const int bid = blockIdx.x, extra = bid - head.total;
+  if (extra < 0) {
+    int index;
+    const int prob = map_problem(head, bid, &index);
+    const KProblem kp = load_problem(prob);
+    const TileCoord tc = map_tile<BM, BN_OUT>(head, kp, prob, index);
+    const GemmProblem p = product_view<2>(head, kp, 0);
+    dtl_tile<Cfg, Pipe, AKC, BKC, EPI, false, false>(head, p, tc.tm * BM, tc.tn * BN_OUT, 0, smem);
+    clock.stop(head);
+    return;
+  }
+  const int prob = head.tail >> 28, shift = head.tail >> 24 & 15, first = head.tail & 0xFFFFFF;
+  const int e = xcd_remap(extra, (int)gridDim.x - head.total);
+  const KProblem kp = load_problem(prob);
+  const TileCoord tc = map_tile<BM, BN_OUT>(head, kp, prob, first + (e >> shift));
+  const GemmProblem p = product_view<2>(head, kp, 0);
+  const int part = e & ((1 << shift) - 1);
+  int m0 = tc.tm * BM, n0 = tc.tn * BN_OUT;
+  if (shift == 1) {
+    m0 += part * C2::BM;
+    if (m0 < p.M) dtl_tile<C2, P2, AKC, BKC, EPI, false, false>(head, p, m0, n0, 0, smem);
+  } else if (shift == 2) {
+    m0 += (part >> 1) * C4::BM;
+    n0 += (part & 1) * (BN_OUT / 2);
+    if (m0 < p.M && n0 < p.N) dtl_tile<C4, P4, AKC, BKC, EPI, false, false>(head, p, m0, n0, 0, smem);
+  } else {
+    m0 += (part >> 2) * C16::BM;
+    n0 += (part & 3) * (BN_OUT / 4);
+    if (m0 < p.M && n0 < p.N) dtl_tile<C16, P16, AKC, BKC, EPI, false, false>(head, p, m0, n0, 0, smem);
   }
 }
 

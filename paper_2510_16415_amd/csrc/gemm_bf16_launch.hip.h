@@ -11,6 +11,8 @@ using CfgL8 = TileCfg<256, 256, 4, 2>;   // 8 waves x (64 x 128): two waves per 
 using CfgM = TileCfg<128, 128, 2, 2>;    // 4 waves x (64 x 64): two workgroups per CU
 using CfgM8 = TileCfg<128, 128, 4, 2>;   // 8 waves x (32 x 64): one workgroup per CU
 using CfgT = TileCfg<64, 64, 2, 2>;      // 4 waves x (32 x 32): three workgroups per CU
+using CfgH = TileCfg<128, 256, 2, 4>;    // 8 waves x (64 x 64): half a large tile, in the last round of a launch
+using CfgK = TileCfg<192, 256, 2, 4>;    // 8 waves x (96 x 64): three quarters of one
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 constexpr int kMaxSplits = 16;   // parts a product may be cut into along K
@@ -30,6 +32,8 @@ using PipeL = DtlPipe<CfgL8, 2>;
 // 0.6 and 0.3 % slower.
 using PipeM2 = DtlPipe<CfgM, 2>;
 using PipeM4 = DtlPipe<CfgM8, 4>;   // 128 KiB: one workgroup per CU, three stages in flight
+using PipeH = DtlPipe<CfgH, 3>;    // 144 KiB
+using PipeK = DtlPipe<CfgK, 2>;    // 112 KiB
 using PipeT = DtlPipe<CfgT, 3>;    // 48 KiB
 using PipeT2 = DtlPipe<CfgT, 3, 2>;   // 96 KiB: one workgroup per CU, two groups of waves share out K
 
@@ -39,7 +43,8 @@ using PipeT2 = DtlPipe<CfgT, 3, 2>;   // 96 KiB: one workgroup per CU, two group
 // of them there are, so a launch that fills a quarter of the chip pays the full length of K at that pace:
 // smaller tiles walk K two to four times faster and give the idle CUs work.  The choice is the smallest
 // modelled time over the configurations,
-//     fixed + per_round * n + stages * max(stage_alone, stage_shared * n),   n = workgroups per CU,
+//     fixed + per_round * n + stages * max(stage_alone, stage_shared * n),   n = workgroups per CU
+// (stage_alone .. stage_full between 96 and 256 workgroups on a CU each),
 // with constants fitted to a sweep of 50 launches over every operand layout (K 32 to 11008, 2 to 2752
 // workgroups; the model is within 15 % of nearly all of them).  Every launch of the sweep had one K; problems of
 // different length are laid out over the CUs, the longest first.  Sides measured, in us (256^2 / 128^2
@@ -51,18 +56,30 @@ using PipeT2 = DtlPipe<CfgT, 3, 2>;   // 96 KiB: one workgroup per CU, two group
 // The 64 x 64 workgroup is a chain of short stages (LDS reads, four MFMAs, barrier, fill addresses: 0.35 to 0.44 us);
 // two groups of waves halve it where the CU would hold no second workgroup and K has sixteen stages to share:
 // [2048 x 512], two segments of K 1376: 20.3 -> 16.5 us, [512 x 512], K 2048: 15.1 -> 12.0, K 512: 6.8 both.
-enum TileConfig : int { TILE_L = 0, TILE_M2 = 1, TILE_M4 = 2, TILE_T = 3, TILE_T2 = 4, TILE_COUNT = 5,
-                        TILE_R4 = 5, TILE_R8 = 6 };   // register-staged with four or eight waves: forced only
+enum TileConfig : int { TILE_L = 0, TILE_M2 = 1, TILE_M4 = 2, TILE_T = 3, TILE_T2 = 4, TILE_K = 5, TILE_COUNT = 6,
+                        TILE_R4 = 6, TILE_R8 = 7,      // register-staged with four or eight waves: forced only
+                        TILE_LT = 8 };                 // forced: TILE_L with its last round cut up where it can be
 
 // No bound on the workgroups that share a CU: the rates of larger n are those of the fullest CU measured.
-struct TileModel { int bm, bn; float fixed, per_round, stage_alone, stage_shared; };
+struct TileModel { int bm, bn; float fixed, per_round, stage_alone, stage_full, stage_shared; };
 inline const TileModel& tile_model(int c) {
-  static const TileModel m[TILE_COUNT] = {{256, 256, 3.5f, 2.5f, 1.45f, 1.75f},
-                                          {128, 128, 3.0f, 1.2f, 0.88f, 0.62f},
-                                          {128, 128, 4.5f, 1.2f, 0.70f, 0.72f},
-                                          {64, 64, 2.5f, 0.5f, 0.40f, 0.28f},
-                                          {64, 64, 4.5f, 0.5f, 0.26f, 0.45f}};
+  static const TileModel m[TILE_COUNT] = {{256, 256, 3.5f, 2.5f, 1.45f, 1.75f, 1.75f},
+                                          {128, 128, 3.0f, 1.2f, 0.88f, 0.88f, 0.62f},
+                                          {128, 128, 4.5f, 1.2f, 0.70f, 0.70f, 0.72f},
+                                          {64, 64, 2.5f, 0.5f, 0.40f, 0.40f, 0.28f},
+                                          {64, 64, 4.5f, 0.5f, 0.26f, 0.26f, 0.45f},
+                                          {192, 256, 3.5f, 2.2f, 1.20f, 1.45f, 1.47f}};
   return m[c];
+}
+constexpr int kCUs = 256;
+
+// What the 192-row tile and the cut-up last round are built for: operands whose rows can be cut anywhere, and the
+// epilogues of launches that can be large.
+constexpr bool has_tile_k(bool akc, bool bkc, int epi) {
+  return akc && (epi == EPI_STORE || (bkc && (epi == EPI_GRAD || epi == EPI_SWIGLU_FWD || epi == EPI_SWIGLU_BWD || epi == EPI_RESID)));
+}
+constexpr bool has_tail(bool akc, bool bkc, int epi) {
+  return has_tile_k(akc, bkc, epi) || (!akc && !bkc && (epi == EPI_GRAD || epi == EPI_STORE));
 }
 
 // K stages of a workgroup of problem i, and the workgroups of the problem on bm x bn tiles.
@@ -81,6 +98,32 @@ inline bool bf16_ragged(const GemmLaunch& g) {
   for (int i = 0; i < g.nprob; ++i)
     if ((g.a_kcontig || g.b_kcontig) && (g.p[i].K % 8) && !g.p[i].kpad_ok) return true;
   return false;
+}
+
+// The last round of a launch on 256 x 256 tiles, when it holds at most 128 of them: each takes a CU the length of K at
+// 1.75 us a stage while half the chip and more is idle.  Cut into halves, quarters or sixteenths the same tiles go to all
+// CUs, which walk K at 1.0, 0.72 or 0.45 us a stage; whatever takes the least time, `saved` us less than the whole ones.
+struct TailPlan { int tiles, shift, prob; float saved; };
+inline TailPlan bf16_tail(const GemmLaunch& g) {
+  TailPlan plan = {0, 0, 0, 0.f};
+  if (!has_tail(g.a_kcontig, g.b_kcontig, g.epi) || bf16_ragged(g)) return plan;
+  int total = 0, most = 0;
+  for (int i = 0; i < g.nprob; ++i) {
+    const GemmProblem& p = g.p[i];
+    if (p.batch > 1 || p.splits > 1 || (p.nseg > 1 && !epi_is_dual(g.epi)) || p.causal != CAUSAL_NONE || bf16_stages(g, i) != bf16_stages(g, 0)) return plan;
+    const int u = bf16_units(g, i, 256, 256);
+    total += u;
+    if (u > most) { most = u; plan.prob = i; }
+  }
+  const int rest = total % kCUs;
+  if (total < kCUs || rest == 0 || rest > kCUs / 2 || rest >= most || total >= 1 << 24) return plan;
+  const float st = (float)bf16_stages(g, 0), rate[3] = {1.0f, 0.72f, 0.45f};
+  const int shift[3] = {1, 2, 4};
+  for (int k = 0; k < 3; ++k) {
+    const float saved = 4.f + 1.75f * st - cdiv(rest << shift[k], kCUs) * (4.f + rate[k] * st);
+    if (saved > plan.saved) { plan.saved = saved; plan.shift = shift[k]; plan.tiles = rest; }
+  }
+  return plan;
 }
 
 // Modelled time in us of the launch on configuration c.
@@ -133,8 +176,11 @@ inline float bf16_tile_cost(const GemmLaunch& g, int c) {
     load = (float)q[at].load;
     n = (float)q[at].wgs;
   }
-  const float time = total <= 256 ? load * m.stage_alone : fmaxf(longest * m.stage_alone, load * m.stage_shared);
-  return m.fixed + m.per_round * n + time;
+  // up to a workgroup per CU: a stage takes longer the more of them there are (256 x 256: 1.45 us up to 96, 1.65 with 176)
+  const float full = fminf(fmaxf((total - 96) / 160.f, 0.f), 1.f);
+  const float alone = m.stage_alone + full * (m.stage_full - m.stage_alone);
+  const float time = total <= kCUs ? load * alone : fmaxf(longest * m.stage_alone, load * m.stage_shared);
+  return m.fixed + m.per_round * n + time - (c == TILE_L && n < 4.f ? bf16_tail(g).saved : 0.f);
 }
 inline int bf16_best_tile(const GemmLaunch& g, float* cost = nullptr) {
   int best = TILE_L;
@@ -143,6 +189,7 @@ inline int bf16_best_tile(const GemmLaunch& g, float* cost = nullptr) {
   int longest = 0;
   for (int i = 0; i < g.nprob; ++i) longest = bf16_stages(g, i) > longest ? bf16_stages(g, i) : longest;
   for (int c = 1; c < TILE_COUNT; ++c) {
+    if (c == TILE_K && (ragged || !has_tile_k(g.a_kcontig, g.b_kcontig, g.epi))) continue;
     // with a ragged K the groups of waves meet one more barrier per stage: a third of what they save
     const float x = bf16_tile_cost(g, c) + (c == TILE_T2 && ragged ? 0.05f * longest : 0.f);
     if (x < t) { t = x; best = c; }
@@ -153,7 +200,8 @@ inline int bf16_best_tile(const GemmLaunch& g, float* cost = nullptr) {
 
 // Cuts the problems of a store launch along K (their `splits`) where that makes the launch shorter, into parts of about
 // equal length with four or more stages each, of which `room` fp32 elements can be held.  The parts are written, read
-// back and summed by one more launch: about 5 us and their bytes at 3 TB/s.  Returns the modelled time of it all.
+// back and summed by one more launch: about 8 us and their bytes at 5 TB/s while the cache behind the L2s holds them
+// (59 MB: 11 us), at 3 beyond.  Returns the modelled time of it all.
 inline float bf16_plan_splits(GemmLaunch& g, int64_t room) {
   int longest = 0;
   for (int i = 0; i < g.nprob; ++i) {
@@ -176,7 +224,7 @@ inline float bf16_plan_splits(GemmLaunch& g, int64_t room) {
     if (out > room) break;
     float x;
     bf16_best_tile(g, &x);
-    x += 5.f + (float)((double)out * 8 / 3e6);
+    x += 8.f + (float)out * (out < 32 << 20 ? 0.8e-6f : 2.7e-6f);
     if (x < t) {
       t = x;
       for (int i = 0; i < g.nprob; ++i) best[i] = g.p[i].splits;
@@ -217,6 +265,37 @@ hipError_t run_bf16(GemmLaunch& g, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// The launch whose last round is cut up as `plan` says.
+template <bool AKC, bool BKC, int EPI>
+struct TailKernel {
+  static constexpr int LDS = PipeH::LDS_BYTES;
+  static_assert(LDS >= PipeL::LDS_BYTES && LDS >= PipeM4::LDS_BYTES && LDS >= PipeT2::LDS_BYTES, "the largest of them");
+  static auto entry() -> void (*)(const KArgs) {
+    return gemm_bf16_tail_kernel<CfgL8, PipeL, CfgH, PipeH, CfgM8, PipeM4, CfgT, PipeT2, AKC, BKC, EPI>;
+  }
+  static hipError_t prepare() {
+    static LdsLimitOnce limit;
+    return limit.ensure((const void*)entry(), LDS);
+  }
+};
+template <bool AKC, bool BKC, int EPI>
+hipError_t run_bf16_tail(GemmLaunch& g, const TailPlan& plan, hipStream_t stream) {
+  using Kern = TailKernel<AKC, BKC, EPI>;
+  KArgs a;
+  fill_kargs(a, g, CfgL8::BM, epi_is_dual(EPI) ? CfgL8::BN / 2 : CfgL8::BN, kBK, 8);
+  for (int s = 0; s < kMaxProblems; ++s)
+    if ((a.h.order >> (4 * s) & 15) == plan.prob) {
+      a.h.units[s] -= plan.tiles;
+      a.h.total -= plan.tiles;
+      a.h.tail = plan.prob << 28 | plan.shift << 24 | a.h.units[s];
+      break;
+    }
+  const hipError_t e = Kern::prepare();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(Kern::entry(), dim3(a.h.total + (plan.tiles << plan.shift)), dim3(PipeL::THREADS), Kern::LDS, stream, a);
+  return hipGetLastError();
+}
+
 // The register-staged kernels serve as a second implementation in tests only; the epilogues of the projection refresh,
 // the residual adds and the rotation are not built for them, and such launches take the 256 x 256 direct-to-LDS tile
 // where a register-staged one is forced.
@@ -231,6 +310,12 @@ hipError_t prepare_bf16() {
   if (e == hipSuccess) e = Bf16Kernel<CfgM8, AKC, BKC, EPI, PipeM4, true>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgT, AKC, BKC, EPI, PipeT, true>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgT, AKC, BKC, EPI, PipeT2, true>::prepare();
+  if constexpr (has_tile_k(AKC, BKC, EPI)) {
+    if (e == hipSuccess) e = Bf16Kernel<CfgK, AKC, BKC, EPI, PipeK, false>::prepare();
+  }
+  if constexpr (has_tail(AKC, BKC, EPI)) {
+    if (e == hipSuccess) e = TailKernel<AKC, BKC, EPI>::prepare();
+  }
   if constexpr (register_staged(EPI)) {
     if (e == hipSuccess) e = Bf16Kernel<CfgL4, AKC, BKC, EPI, NoPipe, true>::prepare();
     if (e == hipSuccess) e = Bf16Kernel<CfgL8, AKC, BKC, EPI, NoPipe, true>::prepare();
@@ -241,14 +326,13 @@ hipError_t prepare_bf16() {
 // The configuration mecefo_set_option("tile", ...) forces, -1 when the model decides.  Another host thread may change
 // the option at any time: whoever needs the answer twice for one launch keeps it.
 inline int bf16_forced_tile() {
-  static const int tile[kTileOptions] = {-1, TILE_M2, TILE_R4, TILE_R8, TILE_L, TILE_M4, TILE_T, TILE_T2};
+  static const int tile[kTileOptions] = {-1, TILE_M2, TILE_R4, TILE_R8, TILE_L, TILE_M4, TILE_T, TILE_T2, TILE_K, TILE_LT};
   return tile[options().tile.load(std::memory_order_relaxed)];
 }
 
 template <bool AKC, bool BKC, int EPI>
 hipError_t run_bf16_auto(GemmLaunch& g, hipStream_t stream) {
-  int c = bf16_forced_tile();
-  if (c < 0) c = bf16_best_tile(g);
+  const int forced = bf16_forced_tile(), c = forced < 0 ? bf16_best_tile(g) : forced;
   if constexpr (register_staged(EPI)) {
     if (c == TILE_R4) return run_bf16<CfgL4, AKC, BKC, EPI>(g, stream);
     if (c == TILE_R8) return run_bf16<CfgL8, AKC, BKC, EPI>(g, stream);
@@ -259,6 +343,13 @@ hipError_t run_bf16_auto(GemmLaunch& g, hipStream_t stream) {
     case TILE_T: return run_bf16<CfgT, AKC, BKC, EPI, PipeT>(g, stream);
     case TILE_T2: return run_bf16<CfgT, AKC, BKC, EPI, PipeT2>(g, stream);
     default:
+      if constexpr (has_tile_k(AKC, BKC, EPI)) {
+        if (c == TILE_K && !bf16_ragged(g)) return run_bf16<CfgK, AKC, BKC, EPI, PipeK, false>(g, stream);
+      }
+      if constexpr (has_tail(AKC, BKC, EPI)) {
+        const TailPlan plan = bf16_tail(g);
+        if (plan.saved > 0.f && (forced < 0 || forced == TILE_LT)) return run_bf16_tail<AKC, BKC, EPI>(g, plan, stream);
+      }
       if (bf16_ragged(g)) return run_bf16<CfgL8, AKC, BKC, EPI, PipeL, AKC || BKC>(g, stream);
       return run_bf16<CfgL8, AKC, BKC, EPI, PipeL, false>(g, stream);
   }

@@ -41,7 +41,7 @@ struct KHead {
   int units[kMaxProblems]; // workgroups of the problems in that order
   int batch, batch_inner, causal, rope_seq;
   float scale, poly_a, poly_b;
-  int unused;
+  int tail;                // launches that cut up their last round: problem, log2 of the parts of a tile, first tile
   uint32_t* clk;           // measurement (NULL otherwise): every 64th workgroup stores its shader-clock cycles and
                            // its 100 MHz wall ticks, pair number (workgroup / 64) % 64
   const float* rowvec;
@@ -69,7 +69,7 @@ inline void fill_kargs(KArgs& args, const GemmLaunch& g, int bm, int bn, int bk,
   const GemmProblem& f = g.p[0];      // what every problem of a launch shares
   a.batch = f.batch; a.batch_inner = f.batch_inner; a.causal = f.causal; a.rope_seq = f.rope_seq;
   a.scale = f.scale; a.poly_a = f.poly_a; a.poly_b = f.poly_b;
-  a.unused = 0;
+  a.tail = 0;
   a.rowvec = f.rowvec; a.addend = f.addend;
   a.a_bo = f.a_bo; a.a_bi = f.a_bi; a.b_bi = f.b_bi; a.c_bi = f.c_bi;
   args.b_bo = f.b_bo; args.c_bo = f.c_bo;
