@@ -400,7 +400,7 @@ mecefo_status_t mecefo_init(void);
 
 /* Process-wide switches for tests and measurements (not needed for normal use; the library chooses
  * by shape).  name "tile": bf16 GEMM configuration, value "auto", direct-to-LDS "S" (128x128 with two LDS stages),
- * "S4" (128x128 with four), "T" (64x64), "T2" (64x64, two groups of waves share out K), "K" (192x256, where it is
+ * "S4" (128x128 with four), "T" (64x64), "T2" (64x64, two groups of waves share out K), "X" (32x32, eight waves share out K), "K" (192x256, where it is
  * built for the launch), "L8" (256x256) and "LT" ("L8" with a short last round cut up), or register-staged "L4" and "L8R"
  * (256x256); launches that a value is not built for take "L8".  name "attention": "auto" | "gemm" (batched GEMM
  * launches instead of the fused attention kernels).  Affects calls made after it returns. */

@@ -657,7 +657,7 @@ mecefo_status_t mecefo_set_option(const char* name, const char* value) {
   if (!strcmp(name, "tile")) {
     for (int i = 0; i < kTileOptions; ++i)
       if (!strcmp(value, kTileOptionName[i])) { options().tile.store(i, std::memory_order_relaxed); return MECEFO_OK; }
-    return fail(MECEFO_ERR_INVALID_ARG, "option tile: value must be auto, S, S4, T, T2, K, L4, L8R, L8 or LT (got %s)", value);
+    return fail(MECEFO_ERR_INVALID_ARG, "option tile: value must be auto, S, S4, T, T2, X, K, L4, L8R, L8 or LT (got %s)", value);
   }
   if (!strcmp(name, "attention")) {
     if (!strcmp(value, "auto")) { options().attn_gemm.store(0, std::memory_order_relaxed); return MECEFO_OK; }

@@ -2,7 +2,7 @@
 //
 // One workgroup computes a 256 x 256 (eight wavefronts of 64 x 128), 128 x 128 (four of 64 x 64 with two LDS
 // stages, or eight of 32 x 64 with four) or 64 x 64 output tile (four of 32 x 32, or two groups of four that share out
-// K).  Two differences to gemm_bf16.hip.h.  The products run on v_mfma_f32_16x16x32_bf16: on Gaussian operands a
+// K), or 32 x 32 (eight waves that share out K, each with buffers of its own).  Two differences to gemm_bf16.hip.h.  The products run on v_mfma_f32_16x16x32_bf16: on Gaussian operands a
 // loop of nothing but MFMAs is power-limited, and this shape moves half the accumulator bytes per multiply-add
 // of the 32x32x16 one -- 2100 TFLOP/s at 2.1 GHz on random operands against 1860 at 1.83 GHz.  And the operand
 // tiles never pass through registers:
@@ -130,9 +130,11 @@ struct DmaKC {   // K-contiguous source; one wave instruction covers RPI consecu
 // The map is its own inverse.
 template <int ROWS> struct KsMap {
   static constexpr int CH = ROWS / 8;
-  static_assert(ROWS == 64 || ROWS == 128 || ROWS == 256, "unsupported tile width");
-  static __device__ inline int fold(int c) { return ROWS == 64 ? c : c ^ ((c & 2) << 2); }
-  static __device__ inline int swz(int k) { return ROWS == 64 ? (k & 2) | ((k & 8) >> 1) : ((k & 7) << 1) ^ (k & 8); }
+  static_assert(ROWS == 32 || ROWS == 64 || ROWS == 128 || ROWS == 256, "unsupported tile width");
+  static __device__ inline int fold(int c) { return ROWS <= 64 ? c : c ^ ((c & 2) << 2); }
+  static __device__ inline int swz(int k) {
+    return ROWS == 32 ? (k & 8) >> 2 : ROWS == 64 ? (k & 2) | ((k & 8) >> 1) : ((k & 7) << 1) ^ (k & 8);
+  }
   static __device__ inline int phys(int c, int k) { return (fold(c) ^ swz(k)) & (CH - 1); }
   static __device__ inline int logical(int pos, int k) { return fold((pos ^ swz(k)) & (CH - 1)); }
 };
@@ -141,25 +143,30 @@ template <int BK, int NT, int ROWS>
 struct DmaKS {   // K-strided source; one wave instruction covers KPI k rows of 2 * ROWS bytes
   static constexpr int ROWB = ROWS * 2, CH = ROWB / 16, KPI = 1024 / ROWB;
   static constexpr int NW = NT / 64, NI = (BK / KPI) / NW;
-  static_assert(NI >= 1 && (NI == 1 || (NW * KPI) % 16 == 0), "unsupported stage size");
-  uint32_t voff;      // lane offset for q = 0; instruction q adds NW * KPI * q rows
+  // the swizzle sees k % 16: one lane offset for all instructions, or two that take turns
+  static constexpr int NV = NI == 1 || (NW * KPI) % 16 == 0 ? 1 : 2;
+  static_assert(NI >= 1 && (NV == 1 || (NW * KPI) % 16 == 8), "unsupported stage size");
+  uint32_t voff[NV];  // lane offset of k row krow0; instruction q adds NW * KPI * q rows
   uint32_t ld2;
   int krow0;          // k row of this lane for q = 0
   int w;
   __device__ inline void init(int lane, int wave, int row_base, int rows_total, int64_t ld) {
     w = wave;
     krow0 = KPI * w + lane / CH;
-    const int cm = KsMap<ROWS>::logical(lane % CH, krow0);     // the swizzle sees k % 16 only: the same for every q
-    const int m = row_base + cm * 8;
     ld2 = (uint32_t)(ld * 2);
-    voff = m < rows_total ? ((uint32_t)krow0 * (uint32_t)ld + m) * 2 : kOOB;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      const int m = row_base + KsMap<ROWS>::logical(lane % CH, krow0 + v * NW * KPI) * 8;
+      voff[v] = m < rows_total ? ((uint32_t)krow0 * (uint32_t)ld + m) * 2 : kOOB;
+    }
   }
   __device__ inline void issue(u32x4_t r0, u32x4_t, uint32_t tile, int k0, int K, bool tail) const {
     const uint32_t soff = (uint32_t)k0 * ld2;
 #pragma unroll
     for (int q = 0; q < NI; ++q) {
       const bool kvalid = !tail || (k0 + krow0 + NW * KPI * q < K);
-      const uint32_t off = (kvalid && voff != kOOB) ? voff + (uint32_t)(NW * KPI * q) * ld2 : kOOB;
+      const uint32_t v = voff[q % NV];
+      const uint32_t off = (kvalid && v != kOOB) ? v + (uint32_t)(NW * KPI * q) * ld2 : kOOB;
       fill_lds_16B(r0, tile + (q * NW + w) * 1024, off, soff);
     }
   }
@@ -343,7 +350,14 @@ __device__ __forceinline__ void dtl_tile(const KHead& head, const GemmProblem& p
   // while the other waits on LDS.
   if (NT == 512 && wave >= 4) __builtin_amdgcn_s_setprio(1);
   const int nst = kt_end - kt_begin;
-  const int turns = KG > 1 ? (nst + KG - 1) / KG : nst;      // stages of the group with the most
+  // A group of one wave reads nothing but its own fills: it waits for itself only, and for no one within the K loop.
+  constexpr bool SOLO = Cfg::NT == 64;
+  auto meet = [&]() {
+    if constexpr (SOLO) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // reads of the buffer that is refilled next
+    else __syncthreads();
+  };
+  // stages of this group; of the one with the most where the groups meet in every turn
+  const int turns = SOLO ? (nst - group + KG - 1) / KG : KG > 1 ? (nst + KG - 1) / KG : nst;
   // The (up to eight) tiles of a tile column run at the same time on one XCD and share their B panel.
   // Each starts its K loop at a different stage (rotation by the tile row, wrapping around), so that
   // they do not all ask L2 for the same lines at the same moment: the first request of a line then
@@ -366,20 +380,20 @@ __device__ __forceinline__ void dtl_tile(const KHead& head, const GemmProblem& p
     const int seg = (kt >= kt_per_seg ? 1 : 0) + (kt >= 2 * kt_per_seg ? 1 : 0);
     if (!ragged) return;
     const bool last = kt == (seg + 1) * kt_per_seg - 1;
-    if (KG == 1 && !last) return;      // several groups: every one of them meets the barrier in every turn
+    if ((KG == 1 || SOLO) && !last) return;      // several groups: every one of them meets the barrier in every turn
     if (last) {
       DmaA::clear_tail(stage, t, K % BK);
       DmaB::clear_tail(stage + A_BYTES, t, K % BK);
     }
-    __syncthreads();
+    meet();
   };
-  if (nst > 0) {
+  if (turns > 0) {
     // Fill every buffer of the ring, wait for the first stage only.
 #pragma unroll
     for (int s = 0; s < NS; ++s)
       if (s < turns) issue(kmap(s), smem_addr + s * STAGE);
     wait_fills_leave<FPS>(min(NS, turns) - 1);
-    __syncthreads();
+    meet();
     clear_ragged(kmap(0), smem);
 #pragma unroll
     for (int i = 0; i < TM; ++i) af[0][i] = fa.fetch_one(i, smem, 0);
@@ -394,7 +408,7 @@ __device__ __forceinline__ void dtl_tile(const KHead& head, const GemmProblem& p
       // Every fragment of this stage is in registers or on its way.  Wait for the next stage only
       // (younger fills stay in flight), meet the other waves, then refill this buffer NS stages ahead.
       wait_fills_leave<FPS>(min(NS - 2, turns - turn - 2));
-      __syncthreads();
+      meet();
       if (turn + NS < turns) issue(kmap(turn + NS), smem_addr + buf * STAGE);
       if (ragged && turn + 1 < turns) clear_ragged(kmap(turn + 1), smem + nbuf * STAGE);
       step(1, smem + nbuf * STAGE, 0);

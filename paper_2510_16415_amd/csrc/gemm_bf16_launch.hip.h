@@ -11,6 +11,7 @@ using CfgL8 = TileCfg<256, 256, 4, 2>;   // 8 waves x (64 x 128): two waves per 
 using CfgM = TileCfg<128, 128, 2, 2>;    // 4 waves x (64 x 64): two workgroups per CU
 using CfgM8 = TileCfg<128, 128, 4, 2>;   // 8 waves x (32 x 64): one workgroup per CU
 using CfgT = TileCfg<64, 64, 2, 2>;      // 4 waves x (32 x 32): three workgroups per CU
+using CfgX = TileCfg<32, 32, 1, 1>;      // one wave, of eight that share out K
 using CfgH = TileCfg<128, 256, 2, 4>;    // 8 waves x (64 x 64): half a large tile, in the last round of a launch
 using CfgK = TileCfg<192, 256, 2, 4>;    // 8 waves x (96 x 64): three quarters of one
 
@@ -37,6 +38,8 @@ using PipeK = DtlPipe<CfgK, 2>;    // 112 KiB
 using PipeT = DtlPipe<CfgT, 3>;    // 48 KiB
 using PipeT2 = DtlPipe<CfgT, 3, 2>;   // 96 KiB: one workgroup per CU, two groups of waves share out K
 
+using PipeX = DtlPipe<CfgX, 2, 8>;    // 128 KiB: eight groups of one wave
+
 // ---- choice of the tile ------------------------------------------------------------------------
 // What bounds a launch depends on how many workgroups it gives a CU.  One 256 x 256 workgroup per CU has
 // the best rate (fewest operand bytes per multiply-add), but a K stage takes it 1.4 to 1.8 us however few
@@ -56,19 +59,24 @@ using PipeT2 = DtlPipe<CfgT, 3, 2>;   // 96 KiB: one workgroup per CU, two group
 // The 64 x 64 workgroup is a chain of short stages (LDS reads, four MFMAs, barrier, fill addresses: 0.35 to 0.44 us);
 // two groups of waves halve it where the CU would hold no second workgroup and K has sixteen stages to share:
 // [2048 x 512], two segments of K 1376: 20.3 -> 16.5 us, [512 x 512], K 2048: 15.1 -> 12.0, K 512: 6.8 both.
-enum TileConfig : int { TILE_L = 0, TILE_M2 = 1, TILE_M4 = 2, TILE_T = 3, TILE_T2 = 4, TILE_K = 5, TILE_COUNT = 6,
-                        TILE_R4 = 6, TILE_R8 = 7,      // register-staged with four or eight waves: forced only
-                        TILE_LT = 8 };                 // forced: TILE_L with its last round cut up where it can be
+// Launches of fewer 64 x 64 tiles than a quarter of the CUs take 32 x 32 ones: eight waves share out K, each fills and
+// reads LDS buffers of its own and meets the others only to add up the tile, so that a CU has 64 to 128 KiB in flight
+// and no barrier to wait at.  64 x 64 with two groups against 32 x 32, us: [512 x 512], K 512: 5.0 / 4.3, K 2048:
+// 10.6 / 7.6, K 5461: 23.3 / 15.3; [129 x 200], K 512: 5.1 / 4.1; but [2048 x 512], K 512: 5.3 / 12.7 (1024 workgroups).
+enum TileConfig : int { TILE_L = 0, TILE_M2 = 1, TILE_M4 = 2, TILE_T = 3, TILE_T2 = 4, TILE_K = 5, TILE_X = 6, TILE_COUNT = 7,
+                        TILE_R4 = 7, TILE_R8 = 8,      // register-staged with four or eight waves: forced only
+                        TILE_LT = 9 };                 // forced: TILE_L with its last round cut up where it can be
 
 // No bound on the workgroups that share a CU: the rates of larger n are those of the fullest CU measured.
 struct TileModel { int bm, bn; float fixed, per_round, stage_alone, stage_full, stage_shared; };
 inline const TileModel& tile_model(int c) {
   static const TileModel m[TILE_COUNT] = {{256, 256, 3.5f, 2.5f, 1.45f, 1.75f, 1.75f},
-                                          {128, 128, 3.0f, 1.2f, 0.88f, 0.88f, 0.62f},
-                                          {128, 128, 4.5f, 1.2f, 0.70f, 0.70f, 0.72f},
-                                          {64, 64, 2.5f, 0.5f, 0.40f, 0.40f, 0.28f},
-                                          {64, 64, 4.5f, 0.5f, 0.26f, 0.26f, 0.45f},
-                                          {192, 256, 3.5f, 2.2f, 1.20f, 1.45f, 1.47f}};
+                                          {128, 128, 2.0f, 1.0f, 0.86f, 0.86f, 0.62f},
+                                          {128, 128, 2.6f, 0.9f, 0.69f, 0.69f, 0.72f},
+                                          {64, 64, 2.0f, 0.5f, 0.33f, 0.36f, 0.28f},
+                                          {64, 64, 2.6f, 0.5f, 0.23f, 0.26f, 0.45f},
+                                          {192, 256, 3.5f, 2.2f, 1.20f, 1.45f, 1.47f},
+                                          {32, 32, 2.4f, 0.9f, 0.10f, 0.15f, 0.15f}};
   return m[c];
 }
 constexpr int kCUs = 256;
@@ -78,6 +86,7 @@ constexpr int kCUs = 256;
 constexpr bool has_tile_k(bool akc, bool bkc, int epi) {
   return akc && (epi == EPI_STORE || (bkc && (epi == EPI_GRAD || epi == EPI_SWIGLU_FWD || epi == EPI_SWIGLU_BWD || epi == EPI_RESID)));
 }
+constexpr bool has_tile_x(int epi) { return epi != EPI_ATTN_P && epi != EPI_ATTN_DS && epi != EPI_ROPE; }
 constexpr bool has_tail(bool akc, bool bkc, int epi) {
   return has_tile_k(akc, bkc, epi) || (!akc && !bkc && (epi == EPI_GRAD || epi == EPI_STORE));
 }
@@ -189,6 +198,7 @@ inline int bf16_best_tile(const GemmLaunch& g, float* cost = nullptr) {
   int longest = 0;
   for (int i = 0; i < g.nprob; ++i) longest = bf16_stages(g, i) > longest ? bf16_stages(g, i) : longest;
   for (int c = 1; c < TILE_COUNT; ++c) {
+    if (c == TILE_X && !has_tile_x(g.epi)) continue;
     if (c == TILE_K && (ragged || !has_tile_k(g.a_kcontig, g.b_kcontig, g.epi))) continue;
     // with a ragged K the groups of waves meet one more barrier per stage: a third of what they save
     const float x = bf16_tile_cost(g, c) + (c == TILE_T2 && ragged ? 0.05f * longest : 0.f);
@@ -200,8 +210,8 @@ inline int bf16_best_tile(const GemmLaunch& g, float* cost = nullptr) {
 
 // Cuts the problems of a store launch along K (their `splits`) where that makes the launch shorter, into parts of about
 // equal length with four or more stages each, of which `room` fp32 elements can be held.  The parts are written, read
-// back and summed by one more launch: about 8 us and their bytes at 5 TB/s while the cache behind the L2s holds them
-// (59 MB: 11 us), at 3 beyond.  Returns the modelled time of it all.
+// back and summed by one more launch: 4 us and their bytes, at about 5 TB/s each way while the cache behind the L2s holds
+// them (the sum of 59 MB takes 11 us, of 4 MB 5 us), at 3 beyond.  Returns the modelled time of it all.
 inline float bf16_plan_splits(GemmLaunch& g, int64_t room) {
   int longest = 0;
   for (int i = 0; i < g.nprob; ++i) {
@@ -224,7 +234,7 @@ inline float bf16_plan_splits(GemmLaunch& g, int64_t room) {
     if (out > room) break;
     float x;
     bf16_best_tile(g, &x);
-    x += 8.f + (float)out * (out < 32 << 20 ? 0.8e-6f : 2.7e-6f);
+    x += 4.f + (float)out * (out < 32 << 20 ? 1.0e-6f : 2.7e-6f);
     if (x < t) {
       t = x;
       for (int i = 0; i < g.nprob; ++i) best[i] = g.p[i].splits;
@@ -310,6 +320,9 @@ hipError_t prepare_bf16() {
   if (e == hipSuccess) e = Bf16Kernel<CfgM8, AKC, BKC, EPI, PipeM4, true>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgT, AKC, BKC, EPI, PipeT, true>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgT, AKC, BKC, EPI, PipeT2, true>::prepare();
+  if constexpr (has_tile_x(EPI)) {
+    if (e == hipSuccess) e = Bf16Kernel<CfgX, AKC, BKC, EPI, PipeX, true>::prepare();
+  }
   if constexpr (has_tile_k(AKC, BKC, EPI)) {
     if (e == hipSuccess) e = Bf16Kernel<CfgK, AKC, BKC, EPI, PipeK, false>::prepare();
   }
@@ -326,7 +339,7 @@ hipError_t prepare_bf16() {
 // The configuration mecefo_set_option("tile", ...) forces, -1 when the model decides.  Another host thread may change
 // the option at any time: whoever needs the answer twice for one launch keeps it.
 inline int bf16_forced_tile() {
-  static const int tile[kTileOptions] = {-1, TILE_M2, TILE_R4, TILE_R8, TILE_L, TILE_M4, TILE_T, TILE_T2, TILE_K, TILE_LT};
+  static const int tile[kTileOptions] = {-1, TILE_M2, TILE_R4, TILE_R8, TILE_L, TILE_M4, TILE_T, TILE_T2, TILE_K, TILE_LT, TILE_X};
   return tile[options().tile.load(std::memory_order_relaxed)];
 }
 
@@ -343,6 +356,9 @@ hipError_t run_bf16_auto(GemmLaunch& g, hipStream_t stream) {
     case TILE_T: return run_bf16<CfgT, AKC, BKC, EPI, PipeT>(g, stream);
     case TILE_T2: return run_bf16<CfgT, AKC, BKC, EPI, PipeT2>(g, stream);
     default:
+      if constexpr (has_tile_x(EPI)) {
+        if (c == TILE_X) return run_bf16<CfgX, AKC, BKC, EPI, PipeX>(g, stream);
+      }
       if constexpr (has_tile_k(AKC, BKC, EPI)) {
         if (c == TILE_K && !bf16_ragged(g)) return run_bf16<CfgK, AKC, BKC, EPI, PipeK, false>(g, stream);
       }

@@ -93,8 +93,8 @@ struct LdsLimitOnce {
 };
 
 // Process-wide switches behind mecefo_set_option (tests and measurements; 0 = the library decides).
-constexpr int kTileOptions = 10;
-inline const char* const kTileOptionName[kTileOptions] = {"auto", "S", "L4", "L8R", "L8", "S4", "T", "T2", "K", "LT"};
+constexpr int kTileOptions = 11;
+inline const char* const kTileOptionName[kTileOptions] = {"auto", "S", "L4", "L8R", "L8", "S4", "T", "T2", "K", "LT", "X"};
 struct Options {
   std::atomic<int> tile{0};        // bf16 GEMM configuration, index into kTileOptionName
   std::atomic<int> attn_gemm{0};   // 1: attention through batched GEMM launches instead of the fused kernels

@@ -1,4 +1,4 @@
-"""The 192 x 256 tile, and launches whose last round of 256 x 256 tiles is shared out in halves, quarters or sixteenths:
+"""The 32 x 32 and the 192 x 256 tile, and launches whose last round of 256 x 256 tiles is shared out in halves, quarters or sixteenths:
 sizes at which each of them is taken, with edges of the matrices inside the cut-up tiles."""
 import pytest
 import torch
@@ -12,6 +12,14 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("b,d,f", [(1, 8, 8), (191, 136, 264), (193, 128, 256), (385, 72, 520), (600, 520, 1112)])
 def test_products_on_192_row_tiles(b, d, f, mecefo_option):
     mecefo_option("tile", "K")
+    check_forward_products(b, d, f)
+    check_exact_backward(b, d, f)
+
+
+@pytest.mark.parametrize("b,d,f", [(1, 8, 1), (31, 32, 33), (33, 72, 31), (63, 64, 65), (97, 520, 264), (129, 512, 2741)])
+def test_products_on_32_row_tiles(b, d, f, mecefo_option):
+    """One stage (seven of eight waves have nothing to do), stages that do not divide by eight, a ragged K."""
+    mecefo_option("tile", "X")
     check_forward_products(b, d, f)
     check_exact_backward(b, d, f)
 
