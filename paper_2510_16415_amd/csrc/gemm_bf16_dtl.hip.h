@@ -249,7 +249,7 @@ template <class Cfg, int NS_, int KG_ = 1> struct DtlPipe {
 // test: 0.5 % of the 7B-shaped layer).
 // SEGS: products may have several K segments.
 template <class Cfg, class Pipe, bool AKC, bool BKC, int EPI, bool RAGGED, bool SEGS>
-__device__ __forceinline__ void dtl_tile(const KHead& head, const GemmProblem& p, int m0, int n0, int split, uint8_t* smem_all) {
+__device__ __forceinline__ void dtl_tile(const KHead& head, GemmProblem p, int m0, int n0, int split, uint8_t* smem_all) {
   constexpr bool DUAL = epi_is_dual(EPI);
   constexpr int BM = Cfg::BM, BN = Cfg::BN, NT = Cfg::NT;
   constexpr int TM = Cfg::WM / 16, TN = Cfg::WN / 16;     // 16x16 MFMA blocks per wave
@@ -437,6 +437,7 @@ __device__ __forceinline__ void dtl_tile(const KHead& head, const GemmProblem& p
         for (int j = 0; j < TN; ++j) acc[i][j] += part[(((g - 1) * TM + i) * TN + j) * NT + t];
   }
 
+  fold_norm<EPI>(p, lane);
   // Epilogue, staged through LDS so that global accesses are 16 bytes per lane and cover whole
   // rows (bf16: eight columns per access, fp32: two accesses of four).  Accumulator element e of a 16x16 block sits at row
   // 4*(lane/16) + e, column lane%16; each wave writes 32 rows of its sub-tile as fp32

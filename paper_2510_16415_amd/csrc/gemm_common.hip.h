@@ -41,7 +41,8 @@ struct KHead {
   int units[kMaxProblems]; // workgroups of the problems in that order
   int batch, batch_inner, causal, rope_seq;
   float scale, poly_a, poly_b;
-  int tail;                // launches that cut up their last round: problem, log2 of the parts of a tile, first tile
+  int tail;                // launches that cut up their last round: problem, log2 of the parts of a tile, first tile;
+                           // EPI_POLY, EPI_HILO: fold_norm
   uint32_t* clk;           // measurement (NULL otherwise): every 64th workgroup stores its shader-clock cycles and
                            // its 100 MHz wall ticks, pair number (workgroup / 64) % 64
   const float* rowvec;
@@ -69,7 +70,7 @@ inline void fill_kargs(KArgs& args, const GemmLaunch& g, int bm, int bn, int bk,
   const GemmProblem& f = g.p[0];      // what every problem of a launch shares
   a.batch = f.batch; a.batch_inner = f.batch_inner; a.causal = f.causal; a.rope_seq = f.rope_seq;
   a.scale = f.scale; a.poly_a = f.poly_a; a.poly_b = f.poly_b;
-  a.tail = 0;
+  a.tail = f.fold_norm;
   a.rowvec = f.rowvec; a.addend = f.addend;
   a.a_bo = f.a_bo; a.a_bi = f.a_bi; a.b_bi = f.b_bi; a.c_bi = f.c_bi;
   args.b_bo = f.b_bo; args.c_bo = f.c_bo;
@@ -213,6 +214,7 @@ __device__ inline GemmProblem product_view(const KHead& a, const KProblem& p, in
   q.splits = p.splits_kpad >> 1; q.kpad_ok = p.splits_kpad & 1;
   q.rowvec = a.rowvec; q.addend = a.addend; q.scale = a.scale; q.causal = a.causal;
   q.poly_a = a.poly_a; q.poly_b = a.poly_b; q.rope_seq = a.rope_seq;
+  q.fold_norm = a.tail != 0;
   if (a.batch > 1) {
     const __attribute__((address_space(4))) int64_t* outer =
         (const __attribute__((address_space(4))) int64_t*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(KArgs, b_bo) / 8;
@@ -269,6 +271,39 @@ template <bool PRECISE> __device__ inline float sigmoid_f(float g) {
 
 template <int EPI> constexpr bool kUnhandledEpilogue = false;
 
+// 1 / sqrt of a squared norm; a zero matrix is left unchanged.
+__device__ inline float inv_norm(float sq) { return sq > 0.f ? 1.0f / sqrtf(sq) : 1.0f; }
+__device__ inline float wave_total(float v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+// From the kNormBlocks partial sums of a squared norm, and from the trace of a Gram matrix; every wave for itself, in a
+// fixed order.
+__device__ inline float inv_norm_of_partials(const float* partial, int lane) {
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < kNormBlocks / 64; ++i) s += partial[64 * i + lane];
+  return inv_norm(wave_total(s));
+}
+__device__ inline float inv_norm_of_gram(const float* gram, int64_t ld, int n, int lane) {
+  float s = 0.f;
+#pragma unroll 8
+  for (int i = lane; i < n; i += 64) s += gram[i * (ld + 1)];
+  return inv_norm(wave_total(s));
+}
+// The norm that an epilogue folds into its coefficients (EPI_POLY) or its result (EPI_HILO, through poly_a).
+template <int EPI>
+__device__ inline void fold_norm(GemmProblem& p, int lane) {
+  if (EPI == EPI_POLY && p.fold_norm) {
+    const float k = inv_norm_of_gram(p.addend, p.ldc, p.N, lane), k2 = k * k;
+    p.poly_a *= k;
+    p.poly_b *= k * k2;
+    p.scale *= k * k2 * k2;
+  }
+  if (EPI == EPI_HILO) p.poly_a = p.fold_norm ? inv_norm_of_partials(p.rowvec, lane) : 1.f;
+}
+
 // One output element (single products) or one (gate, up) pair (dual products).
 template <int EPI, typename T>
 __device__ inline void epilogue_elem(const GemmProblem& p, const KHead& a, int split,
@@ -323,12 +358,13 @@ __device__ inline void epilogue_elem(const GemmProblem& p, const KHead& a, int s
   } else if constexpr (EPI == EPI_HILO) {
     if (col < p.N) {
       const int64_t idx = (int64_t)row * p.ldc + col;
-      const float x = p.addend ? v + p.addend[idx] : v;
+      const float y = sizeof(T) == 2 ? v * p.poly_a : v;
+      const float x = p.addend ? y + p.addend[idx] : y;
       if (p.C[0]) ((float*)p.C[0])[idx] = x;
       if constexpr (sizeof(T) == 2) {
         const T h = from_f32<T>(x);
         ((T*)p.C[1])[idx] = h;
-        ((T*)p.C[2])[idx] = from_f32<T>(x - to_f32<T>(h));
+        if (p.C[2]) ((T*)p.C[2])[idx] = from_f32<T>(x - to_f32<T>(h));
       }
     }
   } else if constexpr (EPI == EPI_SWIGLU_FWD) {
@@ -530,12 +566,14 @@ __device__ inline void epilogue_vec4(const GemmProblem& p, const KHead& a, int s
     }
   } else if constexpr (EPI == EPI_HILO) {
     f32x4_t x = {v[0], v[1], v[2], v[3]};
+    x *= p.poly_a;
     if (p.addend) x += *(const f32x4_t*)(p.addend + idx);
     if (p.C[0]) *(f32x4_t*)((float*)p.C[0] + idx) = x;
     const bf16x4_t h = pack_bf16x4(x[0], x[1], x[2], x[3]);
     *(bf16x4_t*)((__bf16*)p.C[1] + idx) = h;
-    *(bf16x4_t*)((__bf16*)p.C[2] + idx) =
-        pack_bf16x4(x[0] - (float)h[0], x[1] - (float)h[1], x[2] - (float)h[2], x[3] - (float)h[3]);
+    if (p.C[2])
+      *(bf16x4_t*)((__bf16*)p.C[2] + idx) =
+          pack_bf16x4(x[0] - (float)h[0], x[1] - (float)h[1], x[2] - (float)h[2], x[3] - (float)h[3]);
   } else {
     static_assert(kUnhandledEpilogue<EPI>, "no four-column form of this epilogue");
   }

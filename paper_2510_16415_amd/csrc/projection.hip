@@ -15,7 +15,6 @@
 namespace mecefo {
 namespace {
 
-constexpr int kNormBlocks = 256;
 constexpr int kHeldSplits = 8;
 
 // The iterate is kept as an fp32 master copy.  For bf16 weights it enters the MFMA products as the
@@ -40,16 +39,25 @@ struct SplitSum {
   __bf16 *hi, *lo;         // EPI_HILO: the two halves; EPI_POLY: hi is the polynomial
   const float* addend;
   float a, b, c;           // EPI_POLY
+  const float* norm;       // EPI_HILO: partial sums of the squared norm to divide by, or NULL
+  int fold, n;             // EPI_POLY: fold_norm and the order of the matrix
 };
 template <int EPI>
-__global__ __launch_bounds__(256) void split_sum_kernel(const SplitSum q) {
+__global__ __launch_bounds__(256) void split_sum_kernel(SplitSum q) {
+  const int lane = threadIdx.x & 63;
+  float k = 1.f;
+  if (EPI == EPI_HILO && q.norm) k = inv_norm_of_partials(q.norm, lane);
+  if (EPI == EPI_POLY && q.fold) {
+    k = inv_norm_of_gram(q.addend, q.ld, q.n, lane);
+    q.a *= k; q.b *= k * k * k; q.c *= k * (k * k) * (k * k);
+  }
   const int64_t i4 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;     // mn is a multiple of 8
   if (i4 >= q.mn) return;
   typedef __attribute__((ext_vector_type(4))) float f4;
   typedef __attribute__((ext_vector_type(4))) __bf16 h4;
   f4 s = *(const f4*)(q.partial + i4);
 #pragma unroll 4
-  for (int k = 1; k < q.splits; ++k) s += *(const f4*)(q.partial + (int64_t)k * q.mn + i4);
+  for (int j = 1; j < q.splits; ++j) s += *(const f4*)(q.partial + (int64_t)j * q.mn + i4);
   h4 h, l;
   if constexpr (EPI == EPI_POLY) {
     if (q.raw) *(f4*)(q.raw + i4) = s;
@@ -60,22 +68,24 @@ __global__ __launch_bounds__(256) void split_sum_kernel(const SplitSum q) {
     for (int e = 0; e < 4; ++e) h[e] = (__bf16)(col + e == row ? x[e] + q.a : x[e]);
     *(h4*)(q.hi + i4) = h;
   } else {
+    s *= k;
     if (q.addend) s += *(const f4*)(q.addend + i4);
     if (q.raw) *(f4*)(q.raw + i4) = s;
 #pragma unroll
     for (int e = 0; e < 4; ++e) { h[e] = (__bf16)s[e]; l[e] = (__bf16)(s[e] - (float)h[e]); }
     *(h4*)(q.hi + i4) = h;
-    *(h4*)(q.lo + i4) = l;
+    if (q.lo) *(h4*)(q.lo + i4) = l;
   }
 }
 
 // Block b sums rows b, b + gridDim.x, ... in a fixed order, thread t the groups of four columns t, t + 256, ...
 // and the rows four at a time, so that four loads are in flight (one scalar load after another: 8.5 us for
 // [5461 x 512]; the refresh with nine of them went from 2435 to 2377 us).
-__global__ __launch_bounds__(256) void sumsq_partial_kernel(const float* __restrict__ X, int64_t ld, int64_t rows,
+template <typename T>
+__global__ __launch_bounds__(256) void sumsq_partial_kernel(const T* __restrict__ X, int64_t ld, int64_t rows,
                                                             int cols, float* __restrict__ partial) {
   __shared__ float red[256];
-  typedef __attribute__((ext_vector_type(4))) float f4;
+  typedef __attribute__((ext_vector_type(4))) T t4;
   // columns [cols, ld) hold anything: groups of four that reach behind `cols` are cut off element by element
   const int groups = (cols + 3) / 4;
   // a block row is wide enough for `lanes` groups; the other threads take further rows of the block
@@ -86,17 +96,17 @@ __global__ __launch_bounds__(256) void sumsq_partial_kernel(const float* __restr
     const int64_t step = (int64_t)gridDim.x * per;
     for (int64_t row0 = (int64_t)blockIdx.x * per + sub; row0 < rows; row0 += 4 * step)
       for (int g = lane; g < groups; g += lanes) {
-        f4 v[4];
+        t4 v[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int64_t row = row0 + q * step < rows ? row0 + q * step : row0;
-          v[q] = *(const f4*)(X + row * ld + 4 * g);
+          v[q] = *(const t4*)(X + row * ld + 4 * g);
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
           if (row0 + q * step < rows) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc += 4 * g + e < cols ? v[q][e] * v[q][e] : 0.f;
+            for (int e = 0; e < 4; ++e) acc += 4 * g + e < cols ? (float)v[q][e] * (float)v[q][e] : 0.f;
           }
       }
   }
@@ -123,7 +133,7 @@ __global__ __launch_bounds__(256) void scale_by_inv_norm_kernel(float* __restric
     if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
     __syncthreads();
   }
-  const float s = red[0], k = s > 0.f ? 1.0f / sqrtf(s) : 1.0f;
+  const float k = inv_norm(red[0]);
   typedef __attribute__((ext_vector_type(4))) float f4;
   typedef __attribute__((ext_vector_type(4))) __bf16 h4;
   for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; i < n; i += (int64_t)gridDim.x * 1024) {
@@ -236,7 +246,8 @@ hipError_t run_product(const Plan& pl, char* base, GemmLaunch& g, hipStream_t s)
     return launch_sum_parts(false, &job, 1, s);
   }
   const dim3 grid((unsigned)((mn + 1023) / 1024));
-  SplitSum q{partial, splits, mn, p.ldc, nullptr, nullptr, nullptr, p.addend, p.poly_a, p.poly_b, p.scale};
+  SplitSum q{partial, splits, mn, p.ldc, nullptr, nullptr, nullptr, p.addend, p.poly_a, p.poly_b, p.scale,
+             p.fold_norm ? p.rowvec : nullptr, p.fold_norm, p.N};
   if (epi == EPI_POLY) {
     q.raw = (float*)p.C[1]; q.hi = (__bf16*)p.C[0];
     hipLaunchKernelGGL(split_sum_kernel<EPI_POLY>, grid, dim3(256), 0, s, q);
@@ -278,7 +289,7 @@ struct Refresh {
   hipError_t normalise() const {  // X /= ||X||_F, so that every singular value is <= 1
     float* part = (float*)(base + pl.part);
     const int64_t n = (int64_t)pl.dim * pl.ldx;
-    hipLaunchKernelGGL(sumsq_partial_kernel, dim3(kNormBlocks), dim3(256), 0, s, X32(), pl.ldx, (int64_t)pl.dim, pl.r, part);
+    hipLaunchKernelGGL(sumsq_partial_kernel<float>, dim3(kNormBlocks), dim3(256), 0, s, X32(), pl.ldx, (int64_t)pl.dim, pl.r, part);
     hipLaunchKernelGGL(scale_by_inv_norm_kernel, dim3((unsigned)(n < 1024 * 1024 ? (n + 1023) / 1024 : 1024)), dim3(256), 0, s, X32(), n, part,
                        (__bf16*)(pl.bf16 ? base + pl.Xh[cur] : nullptr), (__bf16*)(pl.bf16 ? base + pl.Xl[cur] : nullptr));
     return hipGetLastError();
@@ -286,8 +297,10 @@ struct Refresh {
 
   // One Newton-Schulz step X <- X (a I + b A + c A^2), A = X^T X; `additive` (c == 0): X <- X + X E
   // with E = (a - 1) I + b A.  A, A^2 and the polynomial only shape the conditioning and are taken
-  // in the storage type; the product with X keeps the split operand.
-  mecefo_status_t ns_step(float a, float b, float c, bool additive) {
+  // in the storage type; the product with X keeps the split operand.  The fp32 master copy of the result is written when
+  // it will be read (keep32); `fold`: X is not normalised yet, the polynomial takes A / tr A for A and is divided by
+  // sqrt(tr A), tr A = |X|_F^2.  out: where the bf16 half hi goes instead of the workspace (the result's last step).
+  mecefo_status_t ns_step(float a, float b, float c, bool additive, bool keep32, bool fold = false, void* out = nullptr) {
     const int r = pl.r, dim = pl.dim;
     float* A32 = (float*)(base + pl.A32);
     void* M16 = base + pl.M16;
@@ -302,11 +315,13 @@ struct Refresh {
     if (!additive) {  // a I + b A + c A^2, A^2 = A A^T (A is symmetric)
       GemmLaunch g = product(pl, true, true, A16, nullptr, pl.ldx, A16, nullptr, pl.ldx, nullptr, r, r, r);
       to_poly(g, M16, nullptr, A32, a, b, c);
+      g.p[0].fold_norm = fold;
       HIP_TRY(run_product(pl, base, g, s));
     }
     // the polynomial of the symmetric A is symmetric: X M = X M^T, so M is the K-contiguous operand
     GemmLaunch g = product(pl, true, true, x.hi, x.lo, pl.ldx, M16, nullptr, pl.ldx, nullptr, dim, r, r);
-    to_iterate(g, X32_next(), pl.Xh[cur ^ 1], pl.Xl[cur ^ 1], additive ? X32() : nullptr);
+    to_iterate(g, keep32 || !pl.bf16 ? X32_next() : nullptr, pl.Xh[cur ^ 1], pl.Xl[cur ^ 1], additive ? X32() : nullptr);
+    if (out) { g.p[0].C[1] = out; g.p[0].C[2] = nullptr; }
     HIP_TRY(run_product(pl, base, g, s));
     cur ^= 1;
     return MECEFO_OK;
@@ -315,28 +330,33 @@ struct Refresh {
   // Quintic steps with slope 3.4445 at zero: a small singular value grows by that factor per step,
   // values near 1 stay within about [0.7, 1.2] (the odd quintic used for low-precision
   // orthogonalisation; it does not converge to exactly 1, the cubic steps do).
-  mecefo_status_t condition(int steps) {
-    HIP_TRY(normalise());
+  mecefo_status_t condition(int steps, bool normalised, bool keep32, void* out) {
     for (int i = 0; i < steps; ++i) {
-      mecefo_status_t e = ns_step(3.4445f, -4.7750f, 2.0315f, false);
+      const bool last = i == steps - 1;
+      mecefo_status_t e = ns_step(3.4445f, -4.7750f, 2.0315f, false, last && keep32, i == 0 && !normalised, last ? out : nullptr);
       if (e != MECEFO_OK) return e;
     }
     return MECEFO_OK;
   }
 
-  mecefo_status_t power_round(const void* W, int64_t ldw, int left) {
+  // X <- W^T (W X).  start: the start basis in the caller's memory (bf16), which Y takes over 1 / its norm (`part` holds
+  // the partial sums), else NULL.  halves: the result goes out as bf16 halves, to be normalised by the first
+  // conditioning step; else as fp32, to be normalised next.
+  mecefo_status_t power_round(const void* W, int64_t ldw, int left, const void* start, int64_t ldstart, bool halves) {
     const int m = pl.m, n = pl.n, r = pl.r;
-    const Operand x = opX();
+    const Operand x = start ? Operand{start, nullptr} : opX();
+    const int64_t ldx = start ? ldstart : pl.ldx;
     // right vectors: Y = W X [m x r] (K = n), X' = W^T Y [n x r] (K = m, W read as [K x M]);
     // left vectors:  Y = W^T X [n x r] (K = m), X' = W Y [m x r] (K = n)
-    GemmLaunch g1 = left ? product(pl, false, false, W, nullptr, ldw, x.hi, x.lo, pl.ldx, nullptr, n, r, m)
-                         : product(pl, true, false, W, nullptr, ldw, x.hi, x.lo, pl.ldx, nullptr, m, r, n);
+    GemmLaunch g1 = left ? product(pl, false, false, W, nullptr, ldw, x.hi, x.lo, ldx, nullptr, n, r, m)
+                         : product(pl, true, false, W, nullptr, ldw, x.hi, x.lo, ldx, nullptr, m, r, n);
     to_iterate(g1, pl.bf16 ? nullptr : Y32(), pl.Yh, pl.Yl, nullptr);
+    if (start) { g1.p[0].fold_norm = true; g1.p[0].rowvec = (const float*)(base + pl.part); }
     HIP_TRY(run_product(pl, base, g1, s));
-    // X' is scaled next and split then: fp32 only
     const Operand y = opY();
     GemmLaunch g2 = left ? product(pl, true, false, W, nullptr, ldw, y.hi, y.lo, pl.ldx, X32_next(), m, r, n)
                          : product(pl, false, false, W, nullptr, ldw, y.hi, y.lo, pl.ldx, X32_next(), n, r, m);
+    if (halves) to_iterate(g2, nullptr, pl.Xh[cur ^ 1], pl.Xl[cur ^ 1], nullptr);
     HIP_TRY(run_product(pl, base, g2, s));
     cur ^= 1;
     return MECEFO_OK;
@@ -397,24 +417,42 @@ mecefo_status_t mecefo_projection_refresh(mecefo_dtype_t dtype, const void* W, i
   const int64_t ldx = pl.ldx;
   const unsigned gx = grid_for((int64_t)dim * ldx);
 
-  // start basis -> fp32 master copy (padding columns zeroed: they are contracted as K padding)
-  if (bf16) hipLaunchKernelGGL((convert2d_kernel<float, __bf16>), dim3(gx), dim3(256), 0, R.s, R.X32(), ldx, (const __bf16*)V0, ldv, (int64_t)dim, r, (int)ldx);
-  else hipLaunchKernelGGL((convert2d_kernel<float, float>), dim3(gx), dim3(256), 0, R.s, R.X32(), ldx, (const float*)V0, ldv, (int64_t)dim, r, (int)ldx);
-  HIP_TRY(hipGetLastError());
+  // bf16: the start basis is an operand of the first product where it lies (its rows keep 16-byte alignment), the norm of
+  // a power round's result is folded into the first conditioning step, and the last step writes P where its rows have no padding.  Three matrices of
+  // [5461 x 2048], rank 512: 18 launches and the second K segment of the first products fewer.
+  const bool direct = bf16 && power_iters > 0 && ldv % 8 == 0;
+  const bool fold = bf16 && cond_steps > 0;
+  void* const out = bf16 && ldp == ldx && r == ldx && (polish_steps > 0 || cond_steps > 0) ? P : nullptr;
+  if (direct) {
+    hipLaunchKernelGGL(sumsq_partial_kernel<__bf16>, dim3(kNormBlocks), dim3(256), 0, R.s, (const __bf16*)V0, ldv, (int64_t)dim, r, (float*)(R.base + pl.part));
+    HIP_TRY(hipGetLastError());
+  } else {
+    // start basis -> fp32 master copy (padding columns zeroed: they are contracted as K padding)
+    if (bf16) hipLaunchKernelGGL((convert2d_kernel<float, __bf16>), dim3(gx), dim3(256), 0, R.s, R.X32(), ldx, (const __bf16*)V0, ldv, (int64_t)dim, r, (int)ldx);
+    else hipLaunchKernelGGL((convert2d_kernel<float, float>), dim3(gx), dim3(256), 0, R.s, R.X32(), ldx, (const float*)V0, ldv, (int64_t)dim, r, (int)ldx);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(R.normalise());
+  }
   // The start basis is only normalised: a previous projection is orthonormal already and Gaussian
   // noise is well conditioned; without power rounds it is conditioned for the polishing steps.
-  st = R.condition(power_iters == 0 ? cond_steps : 0);
-  if (st != MECEFO_OK) return st;
-  for (int it = 0; it < power_iters; ++it) {
-    st = R.power_round(W, ldw, left);
+  if (power_iters == 0) {
+    st = R.condition(cond_steps, true, polish_steps > 0 || !out, polish_steps == 0 ? out : nullptr);
     if (st != MECEFO_OK) return st;
-    st = R.condition(cond_steps);
+  }
+  for (int it = 0; it < power_iters; ++it) {
+    const bool last = it == power_iters - 1;
+    st = R.power_round(W, ldw, left, direct && it == 0 ? V0 : nullptr, ldv, fold);
+    if (st != MECEFO_OK) return st;
+    if (!fold) HIP_TRY(R.normalise());
+    st = R.condition(cond_steps, !fold, last && (polish_steps > 0 || !out), last && polish_steps == 0 ? out : nullptr);
     if (st != MECEFO_OK) return st;
   }
   for (int i = 0; i < polish_steps; ++i) {  // cubic steps X <- X + X (I - X^T X) / 2
-    st = R.ns_step(1.5f, -0.5f, 0.f, true);
+    const bool last = i == polish_steps - 1;
+    st = R.ns_step(1.5f, -0.5f, 0.f, true, !last || !out, false, last ? out : nullptr);
     if (st != MECEFO_OK) return st;
   }
+  if (out) return MECEFO_OK;
   const unsigned gp = grid_for((int64_t)dim * r);
   if (bf16) hipLaunchKernelGGL((convert2d_kernel<__bf16, float>), dim3(gp), dim3(256), 0, R.s, (__bf16*)P, ldp, R.X32(), ldx, (int64_t)dim, r, r);
   else hipLaunchKernelGGL((convert2d_kernel<float, float>), dim3(gp), dim3(256), 0, R.s, (float*)P, ldp, R.X32(), ldx, (int64_t)dim, r, r);

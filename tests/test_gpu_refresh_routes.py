@@ -1,0 +1,71 @@
+"""The ways in and out of the projection refresh: a start basis read where it lies or converted first, results written by
+the last step or converted last, in place, with and without conditioning and polishing steps."""
+import pytest
+import torch
+
+from paper_2510_16415_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+M, N, R = 700, 384, 40
+
+
+def refresh(V0, ldv, ldp, r, left=0, iters=2, cond=8, polish=3, in_place=False, scale=1.0):
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    W = (torch.randn(M, N, generator=gen, device="cuda") * 0.02).to(torch.bfloat16)
+    dim = M if left else N
+    V = torch.full((dim, ldv), float("nan"), dtype=torch.bfloat16, device="cuda")
+    V[:, :r] = (V0[:dim, :r].float() * scale).to(torch.bfloat16)
+    P = V if in_place else torch.full((dim, ldp), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = torch.full((B.mecefo_projection_workspace_bytes(B.BF16, M, N, r, left),), 255, dtype=torch.uint8, device="cuda")
+    B.mecefo_projection_refresh(B.BF16, W, M, N, N, left, V, ldv, r, iters, cond, polish, P, ldp, ws)
+    torch.cuda.synchronize()
+    assert bool(P[:, :r].isfinite().all()) and bool(P[:, r:].isnan().all())      # columns behind r stay as they were
+    return P[:, :r].float()
+
+
+def start(r):
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    return (torch.randn(M, r, generator=gen, device="cuda") * N ** -0.5).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("left", [0, 1])
+@pytest.mark.parametrize("cond,polish", [(8, 3), (8, 0), (0, 0), (0, 3), (1, 1)])
+@pytest.mark.parametrize("r", [40, 33])
+def test_where_the_result_goes_does_not_change_it(r, cond, polish, left):
+    V0, up = start(r), (r + 7) // 8 * 8
+    want = refresh(V0, up, up, r, left, cond=cond, polish=polish)
+    assert torch.equal(refresh(V0, up, up + 16, r, left, cond=cond, polish=polish), want)
+    assert torch.equal(refresh(V0, up, up, r, left, cond=cond, polish=polish, in_place=True), want)
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -60, 2.0 ** 60])
+def test_the_scale_of_the_start_basis_does_not_matter(scale):
+    V0 = start(R)
+    assert torch.equal(refresh(V0, 40, 40, R, scale=scale), refresh(V0, 40, 40, R))
+
+
+@pytest.mark.parametrize("left", [0, 1])
+@pytest.mark.parametrize("cond,polish", [(8, 3), (8, 0), (0, 3)])
+def test_a_start_basis_that_has_to_be_converted(cond, polish, left):
+    """Rows of 43 elements are converted and normalised first: the same iteration from the start basis rounded to hi + lo
+    (2^-16 of it) instead of exactly.  The span is compared (a conditioning step multiplies a change of the singular values
+    by up to 3.4, so without polishing steps the bases differ): bf16 rounding of the halves and of P, 2^-9 of entries of
+    equal size, a few times that in the worst direction."""
+    V0 = start(R)
+    a, b = (torch.linalg.qr(refresh(V0, ld, ld, R, left, cond=cond, polish=polish).double())[0] for ld in (40, 43))
+    assert float((b - a @ (a.T @ b)).norm(2)) <= 2e-2
+
+
+@pytest.mark.parametrize("cond,polish", [(8, 3), (8, 0), (0, 3), (0, 0)])
+def test_without_power_rounds(cond, polish):
+    """Only conditions and polishes the start basis; its span stays: with V0 = Q diag, against torch's QR in 64 bits."""
+    V0 = start(R)
+    P = refresh(V0, 40, 40, R, iters=0, cond=cond, polish=polish).double()
+    q1, q0 = torch.linalg.qr(P)[0], torch.linalg.qr(V0[:N].double())[0]
+    # one bf16 rounding of P: 2^-9 of entries of equal size, a few times that in the worst direction of a conditioned basis
+    assert float((q1 - q0 @ (q0.T @ q1)).norm(2)) <= 2e-2
+
+
+def test_a_zero_matrix_gives_finite_results():
+    V0 = torch.zeros(M, R, dtype=torch.bfloat16, device="cuda")
+    assert bool((refresh(V0, 40, 40, R) == 0).all())
