@@ -644,6 +644,7 @@ mecefo_status_t mecefo_init(void) {
   HIP_TRY(prepare_gemm_bf16_nt());
   HIP_TRY(prepare_gemm_bf16_nn());
   HIP_TRY(prepare_gemm_bf16_tn());
+  HIP_TRY(prepare_gemm_f32());
   HIP_TRY(prepare_attention_fwd());
   HIP_TRY(prepare_attention_bwd());
   void* p = nullptr;

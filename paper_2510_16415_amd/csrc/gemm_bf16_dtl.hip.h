@@ -66,7 +66,9 @@ __device__ inline void wait_fills_leave(int stages_left) {
   if (stages_left <= 0) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(0) : "memory");
   else if (stages_left == 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(FPS) : "memory");
   else if (stages_left == 2) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * FPS) : "memory");
-  else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(3 * FPS) : "memory");
+  else if (stages_left == 3) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(3 * FPS) : "memory");
+  else if (stages_left == 4) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(4 * FPS) : "memory");
+  else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(5 * FPS) : "memory");
 }
 
 // ---- direct-to-LDS fill of one operand tile (ROWS rows x BK) -------------------------------

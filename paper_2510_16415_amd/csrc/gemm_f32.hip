@@ -12,7 +12,9 @@
 // one layer's skip backward at the sizes above 574 -> 69 us, the exact FFN backward of 1024 tokens, d = 512,
 // f = 1536 937 -> 217 us and of 2048 tokens, d = 2048, f = 5461 8258 -> 4001 us; errors against fp64 are the same
 // (64 x 64 tiles) or half (the split sums) of what they were.
-#include "gemm_common.hip.h"
+#include "gemm_bf16_dtl.hip.h"
+
+#include <type_traits>
 
 namespace mecefo {
 
@@ -103,6 +105,37 @@ struct TileF32 {
     }
   }
 };
+
+// Adds the four waves' partial 32 x 32 tiles through LDS in a fixed order ([wave][matrix][32][33]) and stores them.
+// Accumulator element e of a 16x16 block is row 4 (lane / 16) + e, column lane % 16.
+template <int EPI, int NB>
+__device__ inline void sum_quarters(const GemmProblem& p, const KHead& head, int split, int m0, int n0, int t,
+                                    const f32x4_t (&acc)[NB][2][2], float* part) {
+  constexpr int FT = 32;
+  const int lane = t & 63, wave = t >> 6;
+#pragma unroll
+  for (int w = 0; w < NB; ++w)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          part[((wave * NB + w) * FT + 16 * i + 4 * (lane >> 4) + e) * (FT + 1) + 16 * j + (lane & 15)] = acc[w][i][j][e];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < FT * FT / 256; ++i) {
+    const int r = (t + 256 * i) / FT, c = t % FT;
+    float s[2] = {0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NB; ++w) {
+      const float* q = part + (w * FT + r) * (FT + 1) + c;
+      constexpr int W = NB * FT * (FT + 1);      // one wave's partial tiles
+      s[w] = (q[0] + q[W]) + (q[2 * W] + q[3 * W]);
+    }
+    epilogue_elem<EPI, float>(p, head, split, m0 + r, n0 + c, s[0], s[1]);
+  }
+}
 
 template <class Cfg, int EPI, bool AKC, bool BKC>
 __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const KArgs) {
@@ -198,30 +231,185 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const KArgs) {
     return;
   }
   __syncthreads();
-  float* part = &lds[0][0][0];      // [wave][matrix][FT][FT + 1]
+  sum_quarters<EPI>(p, head, tc.split, m0, n0, t, acc, &lds[0][0][0]);
+}
+
+// The 32 x 32 tile with operands that go straight to LDS.  One stage ahead in registers, as above, a K stage takes the
+// latency of its loads, 0.75 us; a ring of six stages of 16 KiB (five of 24 for dual products) filled by
+// `buffer_load_dwordx4 ... lds` has 80 KiB and more in flight, and the matrix cores set the pace (16 MFMAs of 32 clocks
+// per wave and stage, 0.21 us).  Same tiles, same K order, so the sums are those of the kernel above bit for bit.
+// Needs rows that start on 16 bytes and whole pieces along a contiguous K (f32_direct); a piece that reaches behind the
+// end of K-strided rows brings elements that only outputs outside the matrix see.  256 tokens, d = 256, f = 688, skip
+// backward: 57.1 -> 51.9 us.
+// K-contiguous operands: [32 rows][64 K], the 16-byte chunks of a row XOR-swizzled by it.  K-strided ones: [64 K][32 rows]
+// in memory order; a lane reads single elements, 16 rows of four K rows at once, and neither the K row's parity nor its
+// half of the 32 rows may be the same for two of them: K bit 2 is folded into bit 0, K bit 3 into the chunk.
+template <bool kc>
+struct DmaF32 {
+  uint32_t voff[2];
+  int at;            // K-contiguous: first K of the chunk; K-strided: K row of instruction 0
+  int w;
+  __device__ inline void init(int lane, int wave, int64_t ld, int row0, int rows) {
+    w = wave;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int i = 4 * q + w;
+      if constexpr (kc) {
+        const int r = 4 * i + (lane >> 4);
+        at = 4 * ((lane & 15) ^ (r & 15));                    // the same for both: 16 rows apart
+        voff[q] = row0 + r < rows ? ((uint32_t)(row0 + r) * (uint32_t)ld + at) * 4 : kOOB;
+      } else {
+        const int pk = 8 * w + (lane >> 3), c = (lane & 7) ^ (4 * (w & 1));
+        at = pk ^ (pk >> 2 & 1);
+        voff[q] = row0 + 4 * c < rows ? ((uint32_t)(at + 32 * q) * (uint32_t)ld + row0 + 4 * c) * 4 : kOOB;
+      }
+    }
+  }
+  // soff: bytes to the stage; left: K from its start on (wave-uniform)
+  __device__ inline void issue(u32x4_t r, uint32_t tile, uint32_t soff, int left) const {
+    if (left >= 64) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) fill_lds_16B(r, tile + (4 * q + w) * 1024, voff[q], soff);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        fill_lds_16B(r, tile + (4 * q + w) * 1024, at + (kc ? 0 : 32 * q) < left ? voff[q] : kOOB, soff);
+    }
+  }
+  // Block i of 16 rows for this wave's 16 K of a stage: element e of lane l is row l % 16, K 4 (l / 16) + e.
+  static __device__ inline f32x4_t fetch(const uint8_t* tile, int lane, int wave, int i) {
+    const int row = 16 * i + (lane & 15), g = lane >> 4;
+    if constexpr (kc) return *(const f32x4_t*)(tile + row * 256 + (((4 * wave + g) ^ (row & 15)) << 4));
+    f32x4_t v;
+    const int col = (((row >> 2) ^ (4 * (g >> 1))) << 4) + (row & 3) * 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = *(const float*)(tile + (16 * wave + 4 * g + (e ^ (g & 1))) * 128 + col);
+    return v;
+  }
+};
+
+// Bytes of a matrix from its first to its last element.
+inline int64_t f32_span(bool kc, int64_t ld, int rows, int K) {
+  return K < 1 || rows < 1 ? 0 : kc ? ((rows - 1) * ld + K) * 4 : ((K - 1) * ld + rows) * 4;
+}
+
+template <int EPI> struct DirectF32 {
+  static constexpr int NB = epi_is_dual(EPI) ? 2 : 1, NS = NB == 2 ? 5 : 6, TILE = 8192, STAGE = TILE * (1 + NB);
+  static constexpr int LDS_BYTES = NS * STAGE;
+  static_assert(4 * NB * 32 * 33 * 4 <= LDS_BYTES, "the partial tiles reuse the operand buffers");
+};
+
+template <int EPI, bool AKC, bool BKC>
+__global__ __launch_bounds__(256, 2) void gemm_f32_direct_kernel(const KArgs) {
+  using D = DirectF32<EPI>;
+  constexpr bool DUAL = epi_is_dual(EPI);
+  constexpr int NB = D::NB, NS = D::NS, FT = 32, FK = 64, FPS = 2 * (1 + NB);
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+  const KHead head = load_head();
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  int index;
+  const int prob = map_problem(head, blockIdx.x, &index);
+  const KProblem kp = load_problem(prob);
+  const TileCoord tc = map_tile<FT, FT>(head, kp, prob, index);
+  const GemmProblem p = product_view<4>(head, kp, tc.z);
+  const int m0 = tc.tm * FT, n0 = tc.tn * FT;
+  if (causal_tile_unused(p, m0, n0, FT)) return;
+  const int nseg = DUAL ? 1 : p.nseg;
+  const int kt_per_seg = (uint32_t)(p.K + FK - 1) / FK;
+  int kt_begin = tc.split * p.chunk;
+  int kt_end = min(kt_per_seg * nseg, kt_begin + p.chunk);
+  causal_clip(p, m0, n0, FT, FK, kt_begin, kt_end);
+
+  DmaF32<AKC> da;
+  DmaF32<BKC> db;
+  da.init(lane, wave, p.lda, m0, p.M);
+  db.init(lane, wave, p.ldb, n0, p.N);
+  // The next stage to be filled: a wave issues one instruction at a time, MFMAs included, and with one wave per SIMD
+  // whatever it computes per stage adds to the stage, so the position is carried along.
+  const uint32_t smem_addr = lds_address(smem);
+  const uint32_t a_step = AKC ? 256u : 64u * (uint32_t)p.lda * 4, b_step = BKC ? 256u : 64u * (uint32_t)p.ldb * 4;
+  int seg = (kt_begin >= kt_per_seg ? 1 : 0) + (kt_begin >= 2 * kt_per_seg ? 1 : 0);
+  uint32_t at = (uint32_t)(kt_begin - seg * kt_per_seg);      // stage within the segment
+  u32x4_t ra = make_rsrc_words(select_base(DUAL ? 0 : seg, p.A[0], p.A[1], p.A[2]));
+  u32x4_t rb = make_rsrc_words(select_base(DUAL ? 0 : seg, p.B[0], p.B[1], p.B[2]));
+  const u32x4_t rb1 = make_rsrc_words(p.B[1]);
+  auto issue = [&](int slot) {
+    const uint32_t stage = smem_addr + slot * D::STAGE;
+    const int left = p.K - (int)at * FK;
+    da.issue(ra, stage, at * a_step, left);
+    db.issue(rb, stage + D::TILE, at * b_step, left);
+    if constexpr (DUAL) db.issue(rb1, stage + 2 * D::TILE, at * b_step, left);
+    if ((int)++at == kt_per_seg && !DUAL) {
+      at = 0;
+      ++seg;
+      ra = make_rsrc_words(select_base(seg, p.A[0], p.A[1], p.A[2]));
+      rb = make_rsrc_words(select_base(seg, p.B[0], p.B[1], p.B[2]));
+    }
+  };
+
+  f32x4_t acc[NB][2][2];
 #pragma unroll
   for (int w = 0; w < NB; ++w)
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < 2; ++j) acc[w][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int nst = kt_end - kt_begin;
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          part[((wave * NB + w) * FT + 16 * i + 4 * (lane >> 4) + e) * (FT + 1) + 16 * j + (lane & 15)] = acc[w][i][j][e];
-  __syncthreads();
+  for (int s = 0; s < NS; ++s)
+    if (s < nst) issue(s);
+  // Operands of two stages: while the MFMAs run on one, the reads of the next are under way.
+  struct Frags { f32x4_t a[2], b[NB][2]; } cur, next;
+  auto fetch = [&](Frags& f, int slot) {
+    const uint8_t* stage = smem + slot * D::STAGE;
 #pragma unroll
-  for (int i = 0; i < FT * FT / 256; ++i) {
-    const int r = (t + 256 * i) / FT, c = t % FT;
-    float s[2] = {0.f, 0.f};
+    for (int i = 0; i < 2; ++i) {
+      f.a[i] = DmaF32<AKC>::fetch(stage, lane, wave, i);
 #pragma unroll
-    for (int w = 0; w < NB; ++w) {
-      const float* q = part + (w * FT + r) * (FT + 1) + c;
-      constexpr int W = NB * FT * (FT + 1);      // one wave's partial tiles
-      s[w] = (q[0] + q[W]) + (q[2 * W] + q[3 * W]);
+      for (int w = 0; w < NB; ++w) f.b[w][i] = DmaF32<BKC>::fetch(stage + (1 + w) * D::TILE, lane, wave, i);
     }
-    epilogue_elem<EPI, float>(p, head, tc.split, m0 + r, n0 + c, s[0], s[1]);
+  };
+  auto multiply = [&](const Frags& f) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int w = 0; w < NB; ++w)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[w][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.a[i][e], f.b[w][j][e], acc[w][i][j], 0, 0, 0);
+  };
+  // Behind this, stage k is in every wave's registers, its buffer is refilled NS stages ahead, and stage k + 1 has
+  // landed; the younger ones stay in flight.
+  int slot = 0;
+  auto turn = [&](int k) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (nst - k >= NS) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NS - 2) * FPS) : "memory");
+    else wait_fills_leave<FPS>(nst - k - 2);
+    __syncthreads();
+    if (k + NS < nst) issue(slot);
+    slot = slot + 1 == NS ? 0 : slot + 1;
+  };
+  if (nst > 0) {
+    wait_fills_leave<FPS>(min(NS, nst) - 1);
+    __syncthreads();
+    fetch(cur, 0);
+    for (int k = 0; k < nst; k += 2) {
+      turn(k);
+      if (k + 1 < nst) fetch(next, slot);
+      multiply(cur);
+      if (k + 1 == nst) break;
+      turn(k + 1);
+      if (k + 2 < nst) fetch(cur, slot);
+      multiply(next);
+    }
   }
+  sum_quarters<EPI>(p, head, tc.split, m0, n0, t, acc, (float*)smem);
 }
+
+constexpr bool f32_nt_only(int epi) { return epi_is_dual(epi) || epi == EPI_ATTN_P || epi == EPI_ATTN_DS; }
 
 // Workgroups of a launch with ft x ft tiles.
 inline int f32_tiles(const GemmLaunch& g, int ft) {
@@ -241,7 +429,7 @@ hipError_t run_f32_cfg(GemmLaunch& g, hipStream_t stream) {
   if (a.h.total == 0) return hipSuccess;
   const dim3 grid(a.h.total);
   if (g.a_kcontig && g.b_kcontig) hipLaunchKernelGGL((gemm_f32_kernel<Cfg, EPI, true, true>), grid, dim3(256), 0, stream, a);
-  else if constexpr (epi_is_dual(EPI) || EPI == EPI_ATTN_P || EPI == EPI_ATTN_DS) return hipErrorInvalidValue;
+  else if constexpr (f32_nt_only(EPI)) return hipErrorInvalidValue;
   else if (g.a_kcontig) hipLaunchKernelGGL((gemm_f32_kernel<Cfg, EPI, true, false>), grid, dim3(256), 0, stream, a);
   else if (!g.b_kcontig) hipLaunchKernelGGL((gemm_f32_kernel<Cfg, EPI, false, false>), grid, dim3(256), 0, stream, a);
   else return hipErrorInvalidValue;
@@ -252,13 +440,77 @@ hipError_t run_f32_cfg(GemmLaunch& g, hipStream_t stream) {
 // 512, us: [1024 x 512], f 1376: 185 / 178 / 178 against 175; [1024 x 1024], f 2752 (688 tiles): 536 / 484 / 484 against
 // 516; [2048 x 512], f 1376 (704): 290 / 272 / 271 against 282; [4096 x 512], f 1376: 451 / 464 / 473 against 452;
 // [4096 x 1024], f 2752: 1515 / 1490 / 1539 against 1487.
+// Whether every operand of the launch can go to LDS in 16-byte pieces: rows (and the products of a batch) that start on
+// 16 bytes, whole pieces along a contiguous K, and less than 2 GiB.
+inline bool f32_direct(const GemmLaunch& g) {
+  const GemmProblem& f = g.p[0];
+  if (f.batch > 1 && (f.a_bo | f.a_bi | f.b_bo | f.b_bi) % 4) return false;
+  for (int i = 0; i < g.nprob; ++i) {
+    const GemmProblem& p = g.p[i];
+    const int segs = epi_is_dual(g.epi) ? 2 : p.nseg > 1 ? p.nseg : 1;
+    uintptr_t bits = 0;
+    for (int s = 0; s < segs; ++s) bits |= (uintptr_t)p.B[s] | (uintptr_t)p.A[epi_is_dual(g.epi) ? 0 : s];
+    if (bits % 16 || p.lda % 4 || p.ldb % 4 || ((g.a_kcontig || g.b_kcontig) && p.K % 4)) return false;
+    if (f32_span(g.a_kcontig, p.lda, p.M, p.K) >= (int64_t)1 << 31 || f32_span(g.b_kcontig, p.ldb, p.N, p.K) >= (int64_t)1 << 31) return false;
+  }
+  return true;
+}
+
+template <int EPI, bool AKC, bool BKC>
+struct DirectKernelF32 {
+  static hipError_t prepare() {
+    static LdsLimitOnce limit;
+    return limit.ensure((const void*)gemm_f32_direct_kernel<EPI, AKC, BKC>, DirectF32<EPI>::LDS_BYTES);
+  }
+  static hipError_t run(GemmLaunch& g, hipStream_t stream) {
+    KArgs a;
+    fill_kargs(a, g, 32, 32, 64, 0);
+    a.h.out_f32 = 1;
+    a.h.clk = nullptr;
+    if (a.h.total == 0) return hipSuccess;
+    const hipError_t e = prepare();
+    if (e != hipSuccess) return e;
+    // a ring no longer than K needs, so that a CU takes more workgroups of a short one
+    using D = DirectF32<EPI>;
+    int stages = 1;
+    for (int i = 0; i < g.nprob; ++i) stages = (a.p[i].chunk_nseg >> 2) > stages ? a.p[i].chunk_nseg >> 2 : stages;
+    const int ring = (stages < D::NS ? stages : D::NS) * D::STAGE, sum = 4 * D::NB * 32 * 33 * 4;
+    hipLaunchKernelGGL((gemm_f32_direct_kernel<EPI, AKC, BKC>), dim3(a.h.total), dim3(256), ring > sum ? ring : sum, stream, a);
+    return hipGetLastError();
+  }
+};
+template <int EPI>
+hipError_t run_f32_direct(GemmLaunch& g, hipStream_t stream) {
+  if (g.a_kcontig && g.b_kcontig) return DirectKernelF32<EPI, true, true>::run(g, stream);
+  if constexpr (!f32_nt_only(EPI)) {
+    if (g.a_kcontig) return DirectKernelF32<EPI, true, false>::run(g, stream);
+    if (!g.b_kcontig) return DirectKernelF32<EPI, false, false>::run(g, stream);
+  }
+  return hipErrorInvalidValue;
+}
+template <int... EPIS>
+hipError_t prepare_f32() {
+  hipError_t e = hipSuccess;
+  auto one = [&](auto epi) {
+    constexpr int E = decltype(epi)::value;
+    if (e == hipSuccess) e = DirectKernelF32<E, true, true>::prepare();
+    if constexpr (!f32_nt_only(E)) {
+      if (e == hipSuccess) e = DirectKernelF32<E, true, false>::prepare();
+      if (e == hipSuccess) e = DirectKernelF32<E, false, false>::prepare();
+    }
+  };
+  (one(std::integral_constant<int, EPIS>{}), ...);
+  return e;
+}
+
 template <int EPI>
 hipError_t run_f32(GemmLaunch& g, hipStream_t stream) {
   if (f32_far(g)) {
     if constexpr (EPI == EPI_STORE || EPI == EPI_GRAD) return run_f32_cfg<CfgFar, EPI>(g, stream);
     else return hipErrorInvalidValue;
   }
-  return f32_tiles(g, 64) >= 512 ? run_f32_cfg<CfgWide, EPI>(g, stream) : run_f32_cfg<CfgSmall, EPI>(g, stream);
+  if (f32_tiles(g, 64) >= 512) return run_f32_cfg<CfgWide, EPI>(g, stream);
+  return f32_direct(g) ? run_f32_direct<EPI>(g, stream) : run_f32_cfg<CfgSmall, EPI>(g, stream);
 }
 }  // namespace
 
@@ -293,6 +545,10 @@ void f32_plan_splits(GemmLaunch& g, int most) {
     if (s == 1 || x < t) { t = x; best = s; }
   }
   for (int i = 0; i < g.nprob; ++i) g.p[i].splits = best;
+}
+
+hipError_t prepare_gemm_f32() {
+  return prepare_f32<EPI_STORE, EPI_GRAD, EPI_SWIGLU_FWD, EPI_SWIGLU_BWD, EPI_ATTN_P, EPI_ATTN_DS, EPI_POLY, EPI_HILO, EPI_RESID>();
 }
 
 hipError_t launch_gemm_f32(GemmLaunch& g, hipStream_t s) {

@@ -110,6 +110,7 @@ Options& options();
 hipError_t prepare_gemm_bf16_nt();
 hipError_t prepare_gemm_bf16_nn();
 hipError_t prepare_gemm_bf16_tn();
+hipError_t prepare_gemm_f32();
 // The configuration with which the bf16 launch (NT layout) carries EPI_ROPE for heads of dimension dh; -1: none.
 int gemm_bf16_rope_tile(const GemmLaunch& g, int dh);
 hipError_t prepare_attention_fwd();
