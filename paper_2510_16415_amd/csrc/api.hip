@@ -309,14 +309,17 @@ GemmProblem prob(const void* A0, const void* A1, int64_t lda, const void* B0, co
 
 // A store launch into the library's own buffers, its problems cut along K as their `splits` say (bf16_plan_splits):
 // those write fp32 parts into `partial`, one problem's behind the other's, which one more launch sums.
-mecefo_status_t launch_store(const Ctx& c, const Bufs& bf, GemmLaunch& g, hipStream_t s) {
+// A problem with read_parts keeps them: `kept` says where they are.
+struct Parts { const float* p = nullptr; int n = 0; };
+mecefo_status_t launch_store(const Ctx& c, const Bufs& bf, GemmLaunch& g, hipStream_t s, Parts* kept = nullptr) {
   SumJob jobs[kMaxProblems];
   int n = 0;
   float* partial = (float*)(bf.base + bf.w.partial);
   for (int i = 0; i < g.nprob; ++i) {
     GemmProblem& p = g.p[i];
     if (p.splits <= 1) continue;
-    jobs[n++] = SumJob{partial, p.C[0], (int64_t)p.M * p.ldc, p.splits};
+    if (p.read_parts && kept) *kept = Parts{partial, p.splits};
+    else jobs[n++] = SumJob{partial, p.C[0], (int64_t)p.M * p.ldc, p.splits};
     p.C[0] = partial;
     partial += (int64_t)p.splits * p.M * p.ldc;
   }
@@ -363,14 +366,54 @@ GemmProblem dgrad_problem(const Ctx& c, const Bufs& bf, const void* Wg, const vo
   p.whole = dU != bf.base + bf.w.dU;
   return p;
 }
-mecefo_status_t dgrad(const Ctx& c, const Bufs& bf, const void* Wg, const void* Wu, void* dU, int64_t lddu, hipStream_t s) {
+// kept: not NULL where the norm backward behind it takes the parts of dU (norm_bwd_reads_parts).
+mecefo_status_t dgrad(const Ctx& c, const Bufs& bf, const void* Wg, const void* Wu, void* dU, int64_t lddu, hipStream_t s,
+                      Parts* kept = nullptr) {
   if (!dU || c.b == 0) return MECEFO_OK;
   STAGE(MECEFO_STAGE_DGRAD_GATE_UP, s);
   GemmLaunch g = new_launch(c, true, false, EPI_STORE);
   g.nprob = 1;
   g.p[0] = dgrad_problem(c, bf, Wg, Wu, dU, lddu);
+  g.p[0].read_parts = kept != nullptr;
   if (c.bf16) bf16_plan_splits(g, bf.w.room);
-  return launch_store(c, bf, g, s);
+  else if (kept) f32_plan_parts(g, bf.w.room);
+  return launch_store(c, bf, g, s, kept);
+}
+
+// ---- norm backward ----
+// dX = dOut + normbwd(dU) and the gain gradient.  dU is the workspace's own [b x d] buffer, or parts of it in the partial
+// buffer.  Where it is in parts, its buffer takes the sums of the gain gradient; the partial buffer does where it is free.
+NormBwd norm_bwd_args(const Ctx& c, const Bufs& bf, const Workspace& w, const Parts& parts, const void* H, int64_t ldh,
+                      const void* gamma, const void* dOut, int64_t lddo, void* dX, int64_t lddx, bool want_dgamma) {
+  char* base = bf.base;
+  NormBwd n = {base + w.dU, c.dm, 0, 0, H, ldh, (const float*)(base + w.rstd), gamma, dOut, lddo, dX, lddx,
+               (float*)(base + w.dgp), (int64_t)rmsnorm_bwd_blocks(c.b) * c.dm, c.b, c.dm};
+  if (parts.n > 1) {
+    n.dU = parts.p; n.parts = parts.n; n.part_stride = c.b * c.dm;
+    if ((c.b + 3) / 4 * c.dm <= c.b * c.dm * c.esz / 4) {
+      n.dg_partial = (float*)(base + w.dU);
+      n.dg_room = c.b * c.dm * c.esz / 4;
+    }
+  } else if (w.room > n.dg_room) {
+    n.dg_partial = (float*)(base + w.partial);
+    n.dg_room = w.room;
+  }
+  if (!want_dgamma) n.dg_partial = nullptr;
+  return n;
+}
+mecefo_status_t norm_backward(const Ctx& c, const NormBwd& n, void* dgamma, int accumulate, hipStream_t s) {
+  STAGE(MECEFO_STAGE_NORM_BWD, s);
+  int nblk = 0;
+  if (c.b > 0) HIP_TRY(launch_rmsnorm_bwd(c.bf16, n, &nblk, s));
+  if (dgamma) HIP_TRY(launch_dgamma_reduce(n.dg_partial, nblk, c.dm, dgamma, c.grad_f32, c.bf16, accumulate, s));
+  return MECEFO_OK;
+}
+// Whether these arguments suit the kernel that adds up parts.
+bool norm_bwd_reads_parts(const Ctx& c, const Bufs& bf, NormBwd n) {
+  n.dU = bf.base + bf.w.partial;
+  n.parts = 2;
+  n.part_stride = c.b * c.dm;
+  return rmsnorm_bwd_takes_parts(c.bf16, n);
 }
 
 // The three products of Eq. (2) for the FFN matrices that take it, T = X P, C = Gy^T T, dW = C P^T (SIDE_INPUT) or
@@ -411,13 +454,15 @@ GemmProblem project_problem(const Ctx& c, const Bufs& bf, const LowRank& q, int 
 // dU and the projections of Eq. (2), in one launch where that is shorter than two.  Both are few long products: dU
 // [b x d] walks 2 f, the down projection's T [b x r] walks f (SIDE_INPUT) on a fraction of the chip, the others d.
 mecefo_status_t dgrad_and_project(const Ctx& c, const Bufs& bf, const LowRank& q, const void* Wg, const void* Wu,
-                                  void* dU, int64_t lddu, hipStream_t s) {
+                                  void* dU, int64_t lddu, hipStream_t s, Parts* kept = nullptr) {
   if (c.b == 0) return MECEFO_OK;
   GemmLaunch project = new_launch(c, true, false, EPI_STORE);
   for (int j = 0; j < q.n_lr; ++j) project.p[project.nprob++] = project_problem(c, bf, q, q.lr[j]);
   if (dU && q.n_lr > 0) {
     GemmLaunch both = project, alone = project;
-    both.p[both.nprob++] = alone.p[0] = dgrad_problem(c, bf, Wg, Wu, dU, lddu);
+    alone.p[0] = dgrad_problem(c, bf, Wg, Wu, dU, lddu);
+    alone.p[0].read_parts = kept != nullptr;
+    both.p[both.nprob++] = alone.p[0];
     alone.nprob = 1;
     // large layers, where the two launches fill the chip by themselves, keep them (1456 us against 1474 for 8192 tokens,
     // d 4096, f 11008)
@@ -427,10 +472,12 @@ mecefo_status_t dgrad_and_project(const Ctx& c, const Bufs& bf, const LowRank& q
     if (merge) {
       STAGE(MECEFO_STAGE_DGRAD_GATE_UP, s);
       both.clk = g_prof.cur_clk;
-      return launch_store(c, bf, both, s);
+      if (!c.bf16 && kept) f32_plan_parts(both, bf.w.room);
+      return launch_store(c, bf, both, s, kept);
     }
   }
-  TRY(dgrad(c, bf, Wg, Wu, dU, lddu, s));
+  if (kept && q.n_lr > 0) kept = nullptr;      // the projections may need the partial buffer next
+  TRY(dgrad(c, bf, Wg, Wu, dU, lddu, s, kept));
   if (q.n_lr == 0) return MECEFO_OK;
   STAGE(MECEFO_STAGE_PROJECT, s);
   project.clk = g_prof.cur_clk;
@@ -862,30 +909,28 @@ mecefo_status_t mecefo_block_bwd_skip_ex(const mecefo_ffn_desc_t* desc, const vo
   void* dUb = base + bf.w.dU;
   const LowRank q = low_rank(c, bf, U, ldu, dOut, desc->ld_act_d, P, side, exact_mask);
   TRY(recompute(c, bf, U, ldu, dOut, desc->ld_act_d, Wg, Wu, Wd, Gs, Zs, s));
-  TRY(dgrad_and_project(c, bf, q, Wg, Wu, dUb, c.dm, s));
-  // Skip the MHA connection: the gradient handed to the previous layer is dH = dOut + normbwd(dU).
-  auto norm_backward = [&]() -> mecefo_status_t {
-    STAGE(MECEFO_STAGE_NORM_BWD, s);
-    if (gamma) {
-      const int nblk = rmsnorm_bwd_blocks(c.b);
-      float* dgp = dgamma ? (float*)(base + bf.w.dgp) : nullptr;
-      if (c.b > 0)
-        HIP_TRY(launch_rmsnorm_bwd(c.bf16, dUb, c.dm, H, desc->ld_act_d, rstd, gamma, dOut, desc->ld_act_d, dX,
-                                   desc->ld_act_d, dgp, nblk, c.b, c.dm, s));
-      if (dgamma) HIP_TRY(launch_dgamma_reduce(dgp, c.b > 0 ? nblk : 0, c.dm, dgamma, c.grad_f32, c.bf16, accumulate, s));
-    } else if (c.b > 0) {
-      HIP_TRY(launch_add(c.bf16, dOut, desc->ld_act_d, dUb, c.dm, dX, desc->ld_act_d, c.b, c.dm, s));
-    }
-    return MECEFO_OK;
-  };
   // Eq. (2) reads dOut (the down projection's output gradient) and, without a norm, H itself: when dX
   // is a buffer of its own the norm backward goes first, while dU is still in the caches and before
-  // the weight gradients flood them; when dX overwrites dOut (or H) it has to wait for Eq. (2).
+  // the weight gradients flood them; when dX overwrites dOut (or H) it has to wait for Eq. (2), which needs the
+  // partial buffer.
   const bool dx_first = dX != dOut && dX != H;
-  if (dx_first) TRY(norm_backward());
+  Parts parts;
+  auto norm_args = [&]() {
+    return norm_bwd_args(c, bf, bf.w, parts, H, desc->ld_act_d, gamma, dOut, desc->ld_act_d, dX, desc->ld_act_d, dgamma != nullptr);
+  };
+  const bool read_parts = gamma && dx_first && c.b > 0 && norm_bwd_reads_parts(c, bf, norm_args());
+  TRY(dgrad_and_project(c, bf, q, Wg, Wu, dUb, c.dm, s, read_parts ? &parts : nullptr));
+  // Skip the MHA connection: the gradient handed to the previous layer is dH = dOut + normbwd(dU).
+  auto norm_bwd = [&]() -> mecefo_status_t {
+    if (gamma) return norm_backward(c, norm_args(), dgamma, accumulate, s);
+    STAGE(MECEFO_STAGE_NORM_BWD, s);
+    if (c.b > 0) HIP_TRY(launch_add(c.bf16, dOut, desc->ld_act_d, dUb, c.dm, dX, desc->ld_act_d, c.b, c.dm, s));
+    return MECEFO_OK;
+  };
+  if (dx_first) TRY(norm_bwd());
   void* dW[3] = {dWg, dWu, dWd};
   TRY(lowrank_wgrad(c, bf, q, dW, accumulate, s));
-  if (!dx_first) TRY(norm_backward());
+  if (!dx_first) TRY(norm_bwd());
   return MECEFO_OK;
 }
 
@@ -942,9 +987,7 @@ mecefo_status_t mecefo_block_bwd_full(const mecefo_ffn_desc_t* desc, const mecef
   const mecefo_ffn_desc_t& d = *desc;
   const mecefo_attn_desc_t& a = *attn;
   const int b = (int)c.b, dm = c.dm, dh = dm / a.heads, S = a.seq;
-  const int nblk = rmsnorm_bwd_blocks(c.b);
   float* rstd = (float*)(base + fw.rstd);
-  float* dgp = (float*)(base + fw.dgp);
   void* Ub = base + fw.U;       // norm(H), later norm(X)
   void* dUb = base + fw.dU;     // dU, later dO, later dXn
   void* dH = base + w.dH;
@@ -959,7 +1002,11 @@ mecefo_status_t mecefo_block_bwd_full(const mecefo_ffn_desc_t* desc, const mecef
     HIP_TRY(launch_rmsnorm_fwd(c.bf16, in->H, d.ld_act_d, in->g_ffn, d.rms_eps, Ub, dm, rstd, c.b, dm, s));
   }
   TRY(recompute(c, bf, Ub, dm, in->dOut, d.ld_act_d, in->Wg, in->Wu, in->Wd, nullptr, nullptr, s));
-  TRY(dgrad(c, bf, in->Wg, in->Wu, dUb, dm, s));
+  Parts parts;
+  auto ffn_norm = [&]() {
+    return norm_bwd_args(c, bf, fw, parts, in->H, d.ld_act_d, in->g_ffn, in->dOut, d.ld_act_d, dH, dm, true);
+  };
+  TRY(dgrad(c, bf, in->Wg, in->Wu, dUb, dm, s, any && norm_bwd_reads_parts(c, bf, ffn_norm()) ? &parts : nullptr));
   {
     STAGE(MECEFO_STAGE_WGRAD_EXACT, s);
     GemmLaunch g = new_launch(c, false, false, EPI_GRAD);
@@ -970,13 +1017,7 @@ mecefo_status_t mecefo_block_bwd_full(const mecefo_ffn_desc_t* desc, const mecef
     g.p[2] = prob(in->dOut, nullptr, d.ld_act_d, base + fw.AA, nullptr, c.ldf, out->dWd, nullptr, nullptr, d.ld_w_df, dm, c.ff, b, 1);
     HIP_TRY(launch_gemm(g, s));
   }
-  {
-    STAGE(MECEFO_STAGE_NORM_BWD, s);
-    if (any)
-      HIP_TRY(launch_rmsnorm_bwd(c.bf16, dUb, dm, in->H, d.ld_act_d, rstd, in->g_ffn, in->dOut, d.ld_act_d, dH, dm,
-                                 dgp, nblk, c.b, dm, s));
-    HIP_TRY(launch_dgamma_reduce(dgp, any ? nblk : 0, dm, out->dg_ffn, c.grad_f32, c.bf16, accumulate, s));
-  }
+  TRY(norm_backward(c, ffn_norm(), out->dg_ffn, accumulate, s));
 
   // ---- attention module
   if (any) {
@@ -1085,22 +1126,25 @@ mecefo_status_t mecefo_block_bwd_full(const mecefo_ffn_desc_t* desc, const mecef
       g.p[i] = prob(src[i], nullptr, dm, Ub, nullptr, dm, dst[i], nullptr, nullptr, a.ld_w_dd, dm, dm, b, 1);
     HIP_TRY(launch_gemm(g, s));
   }
+  parts = Parts();
+  auto attn_norm = [&]() {
+    return norm_bwd_args(c, bf, fw, parts, in->X, d.ld_act_d, in->g_attn, dH, dm, out->dX, d.ld_act_d, true);
+  };
   if (any) {  // dXn = dQ Wq + dK Wk + dV Wv   [b x d], three K segments of length d
     STAGE(MECEFO_STAGE_QKV_DGRAD, s);
     GemmLaunch g = new_launch(c, true, false, EPI_STORE);
     g.nprob = 1;
     g.p[0] = prob(dQ, dK, dm, in->Wq, in->Wk, a.ld_w_dd, dUb, nullptr, nullptr, dm, b, dm, dm, 3);
     g.p[0].A[2] = dV; g.p[0].B[2] = in->Wv;
-    HIP_TRY(launch_gemm(g, s));
+    if (norm_bwd_reads_parts(c, bf, attn_norm())) {
+      g.p[0].read_parts = true;
+      if (c.bf16) bf16_plan_splits(g, fw.room);
+      else f32_plan_parts(g, fw.room);
+    }
+    TRY(launch_store(c, bf, g, s, &parts));
   }
-  {  // dX = dH + normbwd(dXn), dg_attn
-    STAGE(MECEFO_STAGE_NORM_BWD, s);
-    if (any)
-      HIP_TRY(launch_rmsnorm_bwd(c.bf16, dUb, dm, in->X, d.ld_act_d, rstd, in->g_attn, dH, dm, out->dX, d.ld_act_d,
-                                 dgp, nblk, c.b, dm, s));
-    HIP_TRY(launch_dgamma_reduce(dgp, any ? nblk : 0, dm, out->dg_attn, c.grad_f32, c.bf16, accumulate, s));
-  }
-  return MECEFO_OK;
+  // dX = dH + normbwd(dXn), dg_attn
+  return norm_backward(c, attn_norm(), out->dg_attn, accumulate, s);
 }
 
 mecefo_status_t mecefo_block_fwd_workspace_bytes(const mecefo_ffn_desc_t* desc, const mecefo_attn_desc_t* attn,

@@ -337,6 +337,113 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_block_kernel(const T* __restr
   }
 }
 
+// The same with a wave per row and as few rows per workgroup as it takes to fill the chip (rpw rows per wave, one after
+// the other); dU comes in the storage type (NP = 0), or as the NP fp32 parts of a product that was cut along K, added up
+// here in their order: a launch that sums them, and a bf16 rounding, are saved.  [2048 x 2048] from three parts: 11.5 us for the
+// sum and 14.5 behind it before, 17.7 now (76 MB); fp32 [256 x 256]: two launches of 9 us in all before, 5.0 now.
+template <typename T, int VEC, int ITERS, int NP>
+__global__ __launch_bounds__(256) void rmsnorm_bwd_rows_kernel(const void* __restrict__ dU, int64_t lddu, int64_t part,
+                                                               const T* __restrict__ H, int64_t ldh,
+                                                               const float* __restrict__ rstd,
+                                                               const T* __restrict__ gamma,
+                                                               const T* dOut, int64_t lddo, T* dX, int64_t lddx,
+                                                               float* __restrict__ partial, int64_t b, int d, int rpw) {
+  extern __shared__ float comb[];      // [3][d]: the column sums of waves 1-3
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int nv = d / VEC;
+  Vec<T, VEC> g[ITERS];
+  float acc[ITERS][VEC];
+#pragma unroll
+  for (int k = 0; k < ITERS; ++k) {
+    g[k] = *(const Vec<T, VEC>*)(gamma + (k * 64 + lane < nv ? k * 64 + lane : 0) * VEC);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) acc[k][e] = 0.f;
+  }
+#pragma unroll 1
+  for (int q = 0; q < rpw; ++q) {
+    const int64_t row = (int64_t)blockIdx.x * 4 * rpw + 4 * q + wave;
+    if (row >= b) break;               // the same for the whole wave
+    // no branch around the loads (see above); all of a row are read before it is written (dX may be dOut)
+    float a[ITERS][VEC];
+    Vec<T, VEC> x[ITERS], r[ITERS];
+#pragma unroll
+    for (int k = 0; k < ITERS; ++k) {
+      const int i = k * 64 + lane < nv ? k * 64 + lane : 0;
+      x[k] = *(const Vec<T, VEC>*)(H + row * ldh + i * VEC);
+      r[k] = *(const Vec<T, VEC>*)(dOut + row * lddo + i * VEC);
+      if constexpr (NP == 0) {
+        const Vec<T, VEC> v = *(const Vec<T, VEC>*)((const T*)dU + row * lddu + i * VEC);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) a[k][e] = (float)v.e[e];
+      } else {
+        constexpr int V4 = VEC < 4 ? VEC : 4;
+        Vec<float, V4> v[NP][VEC / V4];
+#pragma unroll
+        for (int n = 0; n < NP; ++n)
+#pragma unroll
+          for (int h = 0; h < VEC / V4; ++h)
+            v[n][h] = *(const Vec<float, V4>*)((const float*)dU + n * part + row * lddu + i * VEC + h * V4);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          a[k][e] = v[0][e / V4].e[e % V4];
+#pragma unroll
+          for (int n = 1; n < NP; ++n) a[k][e] += v[n][e / V4].e[e % V4];
+        }
+      }
+    }
+    const float rs = rstd[row];
+    float dot = 0.f;
+#pragma unroll
+    for (int k = 0; k < ITERS; ++k) {
+      float s = 0.f;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) s += a[k][e] * (float)g[k].e[e] * ((float)x[k].e[e] * rs);
+      dot += k * 64 + lane < nv ? s : 0.f;
+    }
+    const float c = wave_sum(dot) / (float)d;
+    T* dx = dX + row * lddx;
+#pragma unroll
+    for (int k = 0; k < ITERS; ++k) {
+      const int i = k * 64 + lane;
+      if (i < nv) {
+        Vec<T, VEC> o;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          const float n = (float)x[k].e[e] * rs;
+          o.e[e] = (T)((float)r[k].e[e] + rs * (a[k][e] * (float)g[k].e[e] - n * c));
+          acc[k][e] += a[k][e] * n;
+        }
+        *(Vec<T, VEC>*)(dx + i * VEC) = o;
+      }
+    }
+  }
+  if (!partial) return;      // kernel argument: the whole workgroup takes the same branch
+  if (wave > 0) {
+#pragma unroll
+    for (int k = 0; k < ITERS; ++k) {
+      const int i = k * 64 + lane;
+      if (i < nv) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) comb[(wave - 1) * d + i * VEC + e] = acc[k][e];
+      }
+    }
+  }
+  __syncthreads();
+  if (wave == 0) {
+#pragma unroll
+    for (int k = 0; k < ITERS; ++k) {
+      const int i = k * 64 + lane;
+      if (i < nv) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          const int col = i * VEC + e;
+          partial[(int64_t)blockIdx.x * d + col] = ((acc[k][e] + comb[col]) + comb[d + col]) + comb[2 * d + col];
+        }
+      }
+    }
+  }
+}
+
 // Partial column sums of dU * N over a chunk of rows: partial[chunk][col].
 template <typename T, int VEC>
 __global__ __launch_bounds__(256) void dgamma_partial_kernel(const T* __restrict__ dU, int64_t lddu,
@@ -513,15 +620,64 @@ hipError_t launch_rmsnorm_fwd(bool bf16, const void* H, int64_t ldh, const void*
 
 int rmsnorm_bwd_blocks(int64_t b) { return (int)((b + kDgammaRows - 1) / kDgammaRows); }
 
-hipError_t launch_rmsnorm_bwd(bool bf16, const void* dU, int64_t lddu, const void* H, int64_t ldh,
-                              const float* rstd, const void* gamma, const void* dOut, int64_t lddo, void* dX,
-                              int64_t lddx, float* dg_partial, int nblk, int64_t b, int d, hipStream_t s) {
-  if (bf16 && d % 8 == 0 && d <= 8192 && lddu % 8 == 0 && ldh % 8 == 0 && lddo % 8 == 0 && lddx % 8 == 0) {
+namespace {
+// What the kernel with a wave per row reads: vectors of 16 bytes where everything is aligned to them, single fp32
+// elements of short rows where not; 0 where it is not built.
+int rows_kernel_vec(bool bf16, const NormBwd& n) {
+  const int v = bf16 ? 8 : 4;
+  const uintptr_t bits = (uintptr_t)n.dU | (uintptr_t)n.H | (uintptr_t)n.gamma | (uintptr_t)n.dOut | (uintptr_t)n.dX;
+  const bool aligned = n.d % v == 0 && n.lddu % v == 0 && n.ldh % v == 0 && n.lddo % v == 0 && n.lddx % v == 0 && bits % 16 == 0;
+  if (aligned && n.d <= 2048) return v;
+  return !bf16 && n.parts == 0 && n.d <= 512 ? 1 : 0;
+}
+// Rows per wave: few enough for 512 workgroups, as far as there is room for a row of gain-gradient sums from each.
+int rows_kernel_rpw(const NormBwd& n) {
+  int rpw = 1;
+  while (rpw < 4 && (n.b + 4 * rpw - 1) / (4 * rpw) > 512) rpw *= 2;
+  while (rpw < 4 && n.dg_partial && (n.b + 4 * rpw - 1) / (4 * rpw) * n.d > n.dg_room) rpw *= 2;
+  return rpw;
+}
+}  // namespace
+
+bool rmsnorm_bwd_takes_parts(bool bf16, const NormBwd& n) {
+  return n.parts >= 2 && n.parts <= kMaxNormParts && rows_kernel_vec(bf16, n) > 1;
+}
+
+hipError_t launch_rmsnorm_bwd(bool bf16, const NormBwd& n, int* nblk, hipStream_t s) {
+  const int64_t b = n.b;
+  const int d = n.d;
+  const int vec = rows_kernel_vec(bf16, n);
+  // bf16 without parts: more rows per wave go to the kernels that have several of them in flight
+  const int rpw = rows_kernel_rpw(n);
+  if (vec > 0 && (n.parts > 0 || !bf16 || rpw <= 2)) {
+    *nblk = (int)((b + 4 * rpw - 1) / (4 * rpw));
+    auto go = [&](auto type, auto v, auto iters, auto np) {
+      using T = decltype(type);
+      hipLaunchKernelGGL((rmsnorm_bwd_rows_kernel<T, decltype(v)::value, decltype(iters)::value, decltype(np)::value>),
+                         dim3((unsigned)*nblk), dim3(256), (size_t)3 * d * 4, s, n.dU, n.lddu, n.part_stride, (const T*)n.H, n.ldh,
+                         n.rstd, (const T*)n.gamma, (const T*)n.dOut, n.lddo, (T*)n.dX, n.lddx, n.dg_partial, b, d, rpw);
+    };
+    auto parts = [&](auto type, auto v, auto iters) {
+      if (n.parts == 2) go(type, v, iters, std::integral_constant<int, 2>{});
+      else if (n.parts == 3) go(type, v, iters, std::integral_constant<int, 3>{});
+      else if (n.parts == 4) go(type, v, iters, std::integral_constant<int, 4>{});
+      else go(type, v, iters, std::integral_constant<int, 0>{});
+    };
+    if (bf16) dispatch_iters(d / 8, [&](auto iters) {
+      if constexpr (decltype(iters)::value <= 4) parts(__bf16{}, std::integral_constant<int, 8>{}, iters);
+    });
+    else if (vec == 4) dispatch_iters(d / 4, [&](auto iters) { parts(float{}, std::integral_constant<int, 4>{}, iters); });
+    else go(float{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{}, std::integral_constant<int, 0>{});
+    return hipGetLastError();
+  }
+  *nblk = rmsnorm_bwd_blocks(b);
+  if (n.parts > 0) return hipErrorInvalidValue;
+  if (bf16 && d % 8 == 0 && d <= 8192 && n.lddu % 8 == 0 && n.ldh % 8 == 0 && n.lddo % 8 == 0 && n.lddx % 8 == 0) {
     const int nv = d / 8;
-    const dim3 grid((unsigned)rmsnorm_bwd_blocks(b));
+    const dim3 grid((unsigned)*nblk);
 #define MECEFO_NORM_BWD(LDS, ...)                                                                                    \
-  hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(256), LDS, s, (const __bf16*)dU, lddu, (const __bf16*)H, ldh, rstd,   \
-                     (const __bf16*)gamma, (const __bf16*)dOut, lddo, (__bf16*)dX, lddx, dg_partial, b, d)
+  hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(256), LDS, s, (const __bf16*)n.dU, n.lddu, (const __bf16*)n.H, n.ldh, n.rstd,   \
+                     (const __bf16*)n.gamma, (const __bf16*)n.dOut, n.lddo, (__bf16*)n.dX, n.lddx, n.dg_partial, b, d)
     const size_t comb = (size_t)3 * d * 4;
     if (nv <= 64) MECEFO_NORM_BWD(comb, rmsnorm_bwd_fused_kernel<__bf16, 8, 1>);         // a wave per row
     else if (nv <= 128) MECEFO_NORM_BWD(comb, rmsnorm_bwd_fused_kernel<__bf16, 8, 2>);
@@ -532,25 +688,25 @@ hipError_t launch_rmsnorm_bwd(bool bf16, const void* dU, int64_t lddu, const voi
     return hipGetLastError();
   }
   // The gain-gradient partials read dU and H before dX is written (dX may alias dOut only).
-  if (dg_partial) {
+  if (n.dg_partial) {
     if (bf16)
-      hipLaunchKernelGGL((dgamma_partial_kernel<__bf16, 8>), dim3(blocks_for(d / 8), nblk), dim3(256), 0, s,
-                         (const __bf16*)dU, lddu, (const __bf16*)H, ldh, rstd, dg_partial, b, d, kDgammaRows);
+      hipLaunchKernelGGL((dgamma_partial_kernel<__bf16, 8>), dim3(blocks_for(d / 8), *nblk), dim3(256), 0, s,
+                         (const __bf16*)n.dU, n.lddu, (const __bf16*)n.H, n.ldh, n.rstd, n.dg_partial, b, d, kDgammaRows);
     else
-      hipLaunchKernelGGL((dgamma_partial_kernel<float, 1>), dim3(blocks_for(d), nblk), dim3(256), 0, s,
-                         (const float*)dU, lddu, (const float*)H, ldh, rstd, dg_partial, b, d, kDgammaRows);
+      hipLaunchKernelGGL((dgamma_partial_kernel<float, 1>), dim3(blocks_for(d), *nblk), dim3(256), 0, s,
+                         (const float*)n.dU, n.lddu, (const float*)n.H, n.ldh, n.rstd, n.dg_partial, b, d, kDgammaRows);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   const unsigned grid = (unsigned)((b + 3) / 4);
   if (bf16)
-    hipLaunchKernelGGL((rmsnorm_bwd_kernel<__bf16, 8>), dim3(grid), dim3(256), 0, s, (const __bf16*)dU, lddu,
-                       (const __bf16*)H, ldh, rstd, (const __bf16*)gamma, (const __bf16*)dOut, lddo,
-                       (__bf16*)dX, lddx, b, d);
+    hipLaunchKernelGGL((rmsnorm_bwd_kernel<__bf16, 8>), dim3(grid), dim3(256), 0, s, (const __bf16*)n.dU, n.lddu,
+                       (const __bf16*)n.H, n.ldh, n.rstd, (const __bf16*)n.gamma, (const __bf16*)n.dOut, n.lddo,
+                       (__bf16*)n.dX, n.lddx, b, d);
   else
-    hipLaunchKernelGGL((rmsnorm_bwd_kernel<float, 1>), dim3(grid), dim3(256), 0, s, (const float*)dU, lddu,
-                       (const float*)H, ldh, rstd, (const float*)gamma, (const float*)dOut, lddo, (float*)dX,
-                       lddx, b, d);
+    hipLaunchKernelGGL((rmsnorm_bwd_kernel<float, 1>), dim3(grid), dim3(256), 0, s, (const float*)n.dU, n.lddu,
+                       (const float*)n.H, n.ldh, n.rstd, (const float*)n.gamma, (const float*)n.dOut, n.lddo, (float*)n.dX,
+                       n.lddx, b, d);
   return hipGetLastError();
 }
 

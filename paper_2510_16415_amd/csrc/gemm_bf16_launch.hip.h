@@ -211,7 +211,7 @@ inline int bf16_best_tile(const GemmLaunch& g, float* cost = nullptr) {
 // Cuts the problems of a store launch along K (their `splits`) where that makes the launch shorter, into parts of about
 // equal length with four or more stages each, of which `room` fp32 elements can be held.  The parts are written, read
 // back and summed by one more launch: 4 us and their bytes, at about 5 TB/s each way while the cache behind the L2s holds
-// them (the sum of 59 MB takes 11 us, of 4 MB 5 us), at 3 beyond.  Returns the modelled time of it all.
+// them (the sum of 59 MB takes 11 us, of 4 MB 5 us), at 3 beyond; parts that their reader adds up itself cost their bytes.  Returns the modelled time of it all.
 inline float bf16_plan_splits(GemmLaunch& g, int64_t room) {
   int longest = 0;
   for (int i = 0; i < g.nprob; ++i) {
@@ -224,17 +224,20 @@ inline float bf16_plan_splits(GemmLaunch& g, int64_t room) {
   for (int i = 0; i < g.nprob; ++i) best[i] = 1;
   for (int s = 2; s <= kMaxSplits && longest / s >= 4; ++s) {
     const int len = cdiv(longest, s);
-    int64_t out = 0;
+    int64_t out = 0, read = 0;
     for (int i = 0; i < g.nprob; ++i) {
       g.p[i].splits = 1;
       const int whole = bf16_stages(g, i);
-      g.p[i].splits = !g.p[i].whole && whole > len + len / 8 ? cdiv(whole, len) : 1;
-      if (g.p[i].splits > 1) out += (int64_t)g.p[i].splits * g.p[i].M * g.p[i].ldc;
+      int parts = !g.p[i].whole && whole > len + len / 8 ? cdiv(whole, len) : 1;
+      if (g.p[i].read_parts && parts > kMaxNormParts) parts = kMaxNormParts;
+      g.p[i].splits = parts;
+      if (parts > 1) (g.p[i].read_parts ? read : out) += (int64_t)parts * g.p[i].M * g.p[i].ldc;
     }
-    if (out > room) break;
+    if (out + read > room) break;
     float x;
     bf16_best_tile(g, &x);
-    x += 4.f + (float)out * (out < 32 << 20 ? 1.0e-6f : 2.7e-6f);
+    if (out > 0) x += 4.f;
+    x += (float)out * (out < 32 << 20 ? 1.0e-6f : 2.7e-6f) + (float)read * (read < 32 << 20 ? 0.6e-6f : 2.0e-6f);
     if (x < t) {
       t = x;
       for (int i = 0; i < g.nprob; ++i) best[i] = g.p[i].splits;

@@ -48,6 +48,7 @@ struct GemmProblem {
   int kpad_ok;     // K-contiguous operands: bytes between K and the next multiple of 8 are known to be zero
   int splits;      // EPI_STORE: parts the contraction is cut into (0, 1: whole)
   bool whole;      // host side: never cut (the sum of the parts writes rows of ldc elements, padding included)
+  bool read_parts; // host side: cut into up to kMaxNormParts parts, which the kernel behind it adds up itself
   int chunk;       // device side: K stages of a workgroup
   // Batched products (attention: one product per (sequence, head)): `batch` independent products of
   // identical size; product z = zo * batch_inner + zi reads A + zo*a_bo + zi*a_bi, etc.; all six
@@ -121,16 +122,28 @@ hipError_t launch_gemm(GemmLaunch& g, hipStream_t stream);
 hipError_t launch_gemm_bf16(GemmLaunch& g, hipStream_t stream);
 hipError_t launch_gemm_f32(GemmLaunch& g, hipStream_t stream);
 void f32_plan_splits(GemmLaunch& g, int most);   // cuts every problem of the launch into the same number of parts
+void f32_plan_parts(GemmLaunch& g, int64_t room);   // cuts the problem with read_parts, into `room` fp32 elements at most
 bool f32_far(const GemmLaunch& g);
 
 // Elementwise / reduction kernels (elementwise.hip).  `bf16` selects the storage type.
 hipError_t launch_rmsnorm_fwd(bool bf16, const void* H, int64_t ldh, const void* gamma, float eps,
                               void* U, int64_t ldu, float* rstd, int64_t b, int d, hipStream_t s);
-// dX = dOut + rmsnorm_backward(dU); per-block partial sums of dgamma go to dg_partial [nblk x d].
-hipError_t launch_rmsnorm_bwd(bool bf16, const void* dU, int64_t lddu, const void* H, int64_t ldh,
-                              const float* rstd, const void* gamma, const void* dOut, int64_t lddo,
-                              void* dX, int64_t lddx, float* dg_partial, int nblk, int64_t b, int d,
-                              hipStream_t s);
+// dX = dOut + rmsnorm_backward(dU); sums of the gain gradient over groups of rows go to dg_partial [nblk x d], of which
+// the launch says how many there are (rmsnorm_bwd_blocks, or more where dg_room, in floats, has space for them).  dU: in
+// the storage type (parts 0), or the sum of `parts` fp32 products [b x lddu], part_stride elements apart
+// (rmsnorm_bwd_takes_parts).
+struct NormBwd {
+  const void* dU; int64_t lddu; int parts; int64_t part_stride;
+  const void* H; int64_t ldh;
+  const float* rstd; const void* gamma;
+  const void* dOut; int64_t lddo;
+  void* dX; int64_t lddx;
+  float* dg_partial; int64_t dg_room;
+  int64_t b; int d;
+};
+constexpr int kMaxNormParts = 4;
+bool rmsnorm_bwd_takes_parts(bool bf16, const NormBwd& n);
+hipError_t launch_rmsnorm_bwd(bool bf16, const NormBwd& n, int* nblk, hipStream_t s);
 int rmsnorm_bwd_blocks(int64_t b);
 hipError_t launch_dgamma_reduce(const float* dg_partial, int nblk, int d, void* dgamma, bool out_f32,
                                 bool bf16, int accumulate, hipStream_t s);
