@@ -164,8 +164,8 @@ struct StageTimer {
 // ---- workspace ------------------------------------------------------------------------
 struct Workspace {
   // offsets in bytes from the (256-byte aligned) workspace base
-  size_t U, rstd, DG, DZ, AA, dU, T[3], C[3], partial, dgp, total;
-  int64_t room;      // fp32 elements of the partial buffer
+  size_t U, rstd, DG, DZ, AA, dU, T[3], C[3], partial, dgp, parts, total;
+  int64_t room, parts_room;      // fp32 elements of the partial buffer, and of the one that keeps the parts of dU
   int splits;
   int64_t c_elems[3];
 };
@@ -230,7 +230,14 @@ int store_splits_project(const Ctx& c, const int r[3], mecefo_side_t side) {   /
   return sp < 1 ? 1 : sp;
 }
 
-Workspace layout(const Ctx& c, const int r[3], mecefo_side_t side, int force_splits) {
+// Parts of dU that the norm backward adds up: where there are any they outlive the token contraction, which has the
+// partial buffer, so they have a buffer of their own.  Workspaces sized without it are taken too (with_parts = false).
+int kept_parts(const Ctx& c) {
+  if (c.bf16) return store_splits_du(c) > 1 ? kMaxNormParts : 0;
+  return (c.b + 31) / 32 * ((c.dm + 31) / 32) <= kCUs / 2 ? kMaxNormParts : 0;
+}
+
+Workspace layout(const Ctx& c, const int r[3], mecefo_side_t side, int force_splits, bool with_parts) {
   Workspace w;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += (size_t)up((int64_t)bytes, 256); return o; };
@@ -266,6 +273,8 @@ Workspace layout(const Ctx& c, const int r[3], mecefo_side_t side, int force_spl
   w.partial = take(partial);
   w.room = (int64_t)(partial / 4);
   w.dgp = take((size_t)rmsnorm_bwd_blocks(c.b) * c.dm * 4);
+  w.parts_room = with_parts ? kept_parts(c) * c.b * c.dm : 0;
+  w.parts = take((size_t)w.parts_room * 4);
   w.total = off + 256;   // slack for aligning the caller's base pointer
   return w;
 }
@@ -273,8 +282,9 @@ Workspace layout(const Ctx& c, const int r[3], mecefo_side_t side, int force_spl
 struct Bufs { char* base; Workspace w; };
 
 mecefo_status_t carve(const Ctx& c, const int r[3], mecefo_side_t side, void* ws, size_t ws_bytes, Bufs* out) {
-  Workspace w = layout(c, r, side, 0);
-  while (w.total > ws_bytes && w.splits > 1) w = layout(c, r, side, w.splits - 1);
+  Workspace w = layout(c, r, side, 0, true);
+  if (w.total > ws_bytes) w = layout(c, r, side, 0, false);
+  while (w.total > ws_bytes && w.splits > 1) w = layout(c, r, side, w.splits - 1, false);
   if (w.total > ws_bytes)
     return fail(MECEFO_ERR_WORKSPACE_TOO_SMALL, "workspace has %zu bytes, %zu needed", ws_bytes, w.total);
   if (!ws) return fail(MECEFO_ERR_INVALID_ARG, "workspace is NULL");
@@ -309,7 +319,7 @@ GemmProblem prob(const void* A0, const void* A1, int64_t lda, const void* B0, co
 
 // A store launch into the library's own buffers, its problems cut along K as their `splits` say (bf16_plan_splits):
 // those write fp32 parts into `partial`, one problem's behind the other's, which one more launch sums.
-// A problem with read_parts keeps them: `kept` says where they are.
+// A problem with read_parts writes them into `parts`, and `kept` says how many there are.
 struct Parts { const float* p = nullptr; int n = 0; };
 mecefo_status_t launch_store(const Ctx& c, const Bufs& bf, GemmLaunch& g, hipStream_t s, Parts* kept = nullptr) {
   SumJob jobs[kMaxProblems];
@@ -318,8 +328,12 @@ mecefo_status_t launch_store(const Ctx& c, const Bufs& bf, GemmLaunch& g, hipStr
   for (int i = 0; i < g.nprob; ++i) {
     GemmProblem& p = g.p[i];
     if (p.splits <= 1) continue;
-    if (p.read_parts && kept) *kept = Parts{partial, p.splits};
-    else jobs[n++] = SumJob{partial, p.C[0], (int64_t)p.M * p.ldc, p.splits};
+    if (p.read_parts) {
+      p.C[0] = bf.base + bf.w.parts;
+      *kept = Parts{(const float*)p.C[0], p.splits};
+      continue;
+    }
+    jobs[n++] = SumJob{partial, p.C[0], (int64_t)p.M * p.ldc, p.splits};
     p.C[0] = partial;
     partial += (int64_t)p.splits * p.M * p.ldc;
   }
@@ -328,23 +342,41 @@ mecefo_status_t launch_store(const Ctx& c, const Bufs& bf, GemmLaunch& g, hipStr
   return MECEFO_OK;
 }
 
+// ---- norm recompute ----
+SideJob norm_job(const Ctx& c, const void* H, int64_t ldh, const void* gamma, void* U, float* rstd) {
+  SideJob j = {SIDE_NORM, c.dm, 0, 0, 0, c.d->rms_eps, c.b, ldh, c.dm, H, gamma, U, rstd};
+  return j;
+}
+mecefo_status_t norm_forward(const Ctx& c, const SideJob& j, hipStream_t s) {
+  STAGE(MECEFO_STAGE_NORM_FWD, s);
+  HIP_TRY(launch_rmsnorm_fwd(c.bf16, j.in, j.ld_in, j.gamma, j.eps, j.out, j.ld_out, j.rstd, j.rows, j.d, s));
+  return MECEFO_OK;
+}
+// dA does not read U: the norm recompute of a small layer rides on its launch (a launch less, 3.5 us).  Larger ones keep
+// their own, with more waves in flight than the LDS of the product leaves room for.
+bool norm_rides(const Ctx& c) { return c.b * c.dm * c.esz <= (int64_t)4 << 20; }
+
 // dA = dY Wd  ->  recompute G, Z from U and apply the SwiGLU backward in the epilogue
 // (DG = dG, DZ = dZ, AA = A).   Sec. 3.3 (Rcomp).
 mecefo_status_t recompute(const Ctx& c, const Bufs& bf, const void* U, int64_t ldu, const void* dY,
                                     int64_t lddy, const void* Wg, const void* Wu, const void* Wd,
-                                    const void* Gsaved, const void* Zsaved, hipStream_t s) {
+                                    const void* Gsaved, const void* Zsaved, hipStream_t s, const SideJob* norm = nullptr) {
   const mecefo_ffn_desc_t& d = *c.d;
   char* base = bf.base;
   void* DG = base + bf.w.DG; void* DZ = base + bf.w.DZ; void* AA = base + bf.w.AA;
   const int b = (int)c.b;
   if (b == 0) return MECEFO_OK;
+  bool norm_done;
   {  // dA = dY Wd   [b x f], K = d
     STAGE(MECEFO_STAGE_DGRAD_DOWN, s);
     GemmLaunch g = new_launch(c, true, false, EPI_STORE);
     g.nprob = 1;
     g.p[0] = prob(dY, nullptr, lddy, Wd, nullptr, d.ld_w_df, DG, nullptr, nullptr, c.ldf, b, c.ff, c.dm, 1);
+    if (norm) g.side = *norm;
     HIP_TRY(launch_gemm(g, s));
+    norm_done = g.side_done;
   }
+  if (norm && !norm_done) TRY(norm_forward(c, *norm, s));
   if (Gsaved) {
     STAGE(MECEFO_STAGE_SWIGLU_BWD, s);
     HIP_TRY(launch_swiglu_bwd(c.bf16, Gsaved, Zsaved, d.ld_act_f, DG, DZ, AA, c.ldf, c.b, c.ff, (int)c.ldf, s));
@@ -375,14 +407,14 @@ mecefo_status_t dgrad(const Ctx& c, const Bufs& bf, const void* Wg, const void* 
   g.nprob = 1;
   g.p[0] = dgrad_problem(c, bf, Wg, Wu, dU, lddu);
   g.p[0].read_parts = kept != nullptr;
-  if (c.bf16) bf16_plan_splits(g, bf.w.room);
-  else if (kept) f32_plan_parts(g, bf.w.room);
+  if (c.bf16) bf16_plan_splits(g, bf.w.room, bf.w.parts_room);
+  else if (kept) f32_plan_parts(g, bf.w.parts_room);
   return launch_store(c, bf, g, s, kept);
 }
 
 // ---- norm backward ----
-// dX = dOut + normbwd(dU) and the gain gradient.  dU is the workspace's own [b x d] buffer, or parts of it in the partial
-// buffer.  Where it is in parts, its buffer takes the sums of the gain gradient; the partial buffer does where it is free.
+// dX = dOut + normbwd(dU) and the gain gradient.  dU is the workspace's own [b x d] buffer, or parts of it, and then that
+// buffer takes the sums of the gain gradient.
 NormBwd norm_bwd_args(const Ctx& c, const Bufs& bf, const Workspace& w, const Parts& parts, const void* H, int64_t ldh,
                       const void* gamma, const void* dOut, int64_t lddo, void* dX, int64_t lddx, bool want_dgamma) {
   char* base = bf.base;
@@ -394,23 +426,24 @@ NormBwd norm_bwd_args(const Ctx& c, const Bufs& bf, const Workspace& w, const Pa
       n.dg_partial = (float*)(base + w.dU);
       n.dg_room = c.b * c.dm * c.esz / 4;
     }
-  } else if (w.room > n.dg_room) {
-    n.dg_partial = (float*)(base + w.partial);
-    n.dg_room = w.room;
   }
   if (!want_dgamma) n.dg_partial = nullptr;
   return n;
 }
-mecefo_status_t norm_backward(const Ctx& c, const NormBwd& n, void* dgamma, int accumulate, hipStream_t s) {
+// `later`: receives the sum of the gain gradient as a side job for a launch behind this one, else it is launched here.
+mecefo_status_t norm_backward(const Ctx& c, const NormBwd& n, void* dgamma, int accumulate, hipStream_t s, SideJob* later = nullptr) {
   STAGE(MECEFO_STAGE_NORM_BWD, s);
   int nblk = 0;
   if (c.b > 0) HIP_TRY(launch_rmsnorm_bwd(c.bf16, n, &nblk, s));
-  if (dgamma) HIP_TRY(launch_dgamma_reduce(n.dg_partial, nblk, c.dm, dgamma, c.grad_f32, c.bf16, accumulate, s));
+  if (!dgamma) return MECEFO_OK;
+  if (later) *later = SideJob{SIDE_DGAMMA, c.dm, nblk, c.grad_f32, accumulate, 0.f, 0, 0, 0, n.dg_partial, nullptr, dgamma, nullptr};
+  else HIP_TRY(launch_dgamma_reduce(n.dg_partial, nblk, c.dm, dgamma, c.grad_f32, c.bf16, accumulate, s));
   return MECEFO_OK;
 }
-// Whether these arguments suit the kernel that adds up parts.
+// Whether these arguments suit the kernel that adds up parts, and the workspace keeps them.
 bool norm_bwd_reads_parts(const Ctx& c, const Bufs& bf, NormBwd n) {
-  n.dU = bf.base + bf.w.partial;
+  if (bf.w.parts_room == 0) return false;
+  n.dU = bf.base + bf.w.parts;
   n.parts = 2;
   n.part_stride = c.b * c.dm;
   return rmsnorm_bwd_takes_parts(c.bf16, n);
@@ -466,27 +499,28 @@ mecefo_status_t dgrad_and_project(const Ctx& c, const Bufs& bf, const LowRank& q
     alone.nprob = 1;
     // large layers, where the two launches fill the chip by themselves, keep them (1456 us against 1474 for 8192 tokens,
     // d 4096, f 11008)
-    const bool merge = c.bf16 ? bf16_plan_splits(both, bf.w.room) <
-                                    0.95f * (bf16_plan_splits(alone, bf.w.room) + bf16_plan_splits(project, bf.w.room))
+    const bool merge = c.bf16 ? bf16_plan_splits(both, bf.w.room, bf.w.parts_room) <
+                                    0.95f * (bf16_plan_splits(alone, bf.w.room, bf.w.parts_room) +
+                                             bf16_plan_splits(project, bf.w.room, 0))
                               : !f32_far(both);
     if (merge) {
       STAGE(MECEFO_STAGE_DGRAD_GATE_UP, s);
       both.clk = g_prof.cur_clk;
-      if (!c.bf16 && kept) f32_plan_parts(both, bf.w.room);
+      if (!c.bf16 && kept) f32_plan_parts(both, bf.w.parts_room);
       return launch_store(c, bf, both, s, kept);
     }
   }
-  if (kept && q.n_lr > 0) kept = nullptr;      // the projections may need the partial buffer next
   TRY(dgrad(c, bf, Wg, Wu, dU, lddu, s, kept));
   if (q.n_lr == 0) return MECEFO_OK;
   STAGE(MECEFO_STAGE_PROJECT, s);
   project.clk = g_prof.cur_clk;
-  if (c.bf16) bf16_plan_splits(project, bf.w.room);
+  if (c.bf16) bf16_plan_splits(project, bf.w.room, 0);
   return launch_store(c, bf, project, s);
 }
 
-// The weight gradients: exact ones, and Eq. (2) from the projections on.
-mecefo_status_t lowrank_wgrad(const Ctx& c, const Bufs& bf, const LowRank& q, void* dW[3], int accumulate, hipStream_t s) {
+// The weight gradients: exact ones, and Eq. (2) from the projections to the contraction over tokens.  Everything that
+// reads dY and U is enqueued behind this.
+mecefo_status_t wgrad_contract(const Ctx& c, const Bufs& bf, const LowRank& q, void* dW[3], int accumulate, hipStream_t s) {
   const int b = (int)c.b;
   if (q.n_ex > 0) {  // exact Wgrad: dW = Gy^T X, contraction over tokens
     STAGE(MECEFO_STAGE_WGRAD_EXACT, s);
@@ -512,25 +546,36 @@ mecefo_status_t lowrank_wgrad(const Ctx& c, const Bufs& bf, const LowRank& q, vo
     }
     // no more parts than the workspace holds
     if (b > 0) {
-      if (c.bf16) bf16_plan_splits(g, bf.w.room);
+      if (c.bf16) bf16_plan_splits(g, bf.w.room, bf.w.parts_room);
       else f32_plan_splits(g, bf.w.splits);
     }
     TRY(launch_store(c, bf, g, s));
   }
-  {  // expand: dW = C P^T (SIDE_INPUT) or P C^T (SIDE_OUTPUT), K = r, into the gradient buffers
+  return MECEFO_OK;
+}
+// expand: dW = C P^T (SIDE_INPUT) or P C^T (SIDE_OUTPUT), K = r, into the gradient buffers, and a side job
+mecefo_status_t wgrad_expand(const Ctx& c, const LowRank& q, void* dW[3], int accumulate, hipStream_t s,
+                             const SideJob* side = nullptr) {
+  GemmLaunch g = new_launch(c, true, true, EPI_GRAD);
+  g.nprob = q.n_lr;
+  g.accumulate = accumulate;
+  for (int j = 0; j < q.n_lr; ++j) {
+    const int i = q.lr[j];
+    const mecefo_proj_t& P = q.P[i];
+    g.p[j] = q.in ? prob(q.C[i], nullptr, q.ldt[i], P.P, nullptr, P.ld, dW[i], nullptr, nullptr, q.lddw[i], q.m_out[i],
+                         q.n_in[i], P.r, 1)
+                  : prob(P.P, nullptr, P.ld, q.C[i], nullptr, q.ldt[i], dW[i], nullptr, nullptr, q.lddw[i], q.m_out[i],
+                         q.n_in[i], P.r, 1);
+  }
+  if (side) g.side = *side;
+  if (q.n_lr > 0) {
     STAGE(MECEFO_STAGE_EXPAND, s);
-    GemmLaunch g = new_launch(c, true, true, EPI_GRAD);
-    g.nprob = q.n_lr;
-    g.accumulate = accumulate;
-    for (int j = 0; j < q.n_lr; ++j) {
-      const int i = q.lr[j];
-      const mecefo_proj_t& P = q.P[i];
-      g.p[j] = q.in ? prob(q.C[i], nullptr, q.ldt[i], P.P, nullptr, P.ld, dW[i], nullptr, nullptr, q.lddw[i], q.m_out[i],
-                           q.n_in[i], P.r, 1)
-                    : prob(P.P, nullptr, P.ld, q.C[i], nullptr, q.ldt[i], dW[i], nullptr, nullptr, q.lddw[i], q.m_out[i],
-                           q.n_in[i], P.r, 1);
-    }
+    g.clk = g_prof.cur_clk;
     HIP_TRY(launch_gemm(g, s));
+  }
+  if (side && side->kind == SIDE_DGAMMA && !g.side_done) {
+    STAGE(MECEFO_STAGE_NORM_BWD, s);
+    HIP_TRY(launch_dgamma_reduce((const float*)side->in, side->nblk, side->d, side->out, side->out_f32, c.bf16, side->accumulate, s));
   }
   return MECEFO_OK;
 }
@@ -776,8 +821,8 @@ mecefo_status_t mecefo_workspace_bytes(const mecefo_ffn_desc_t* desc, int r_gate
   if (!out_bytes) return fail(MECEFO_ERR_INVALID_ARG, "out_bytes is NULL");
   if (r_gate < 0 || r_up < 0 || r_down < 0) return fail(MECEFO_ERR_INVALID_ARG, "ranks must be >= 0");
   const int r[3] = {r_gate, r_up, r_down};
-  const size_t a = layout(c, r, MECEFO_SIDE_INPUT, 0).total;
-  const size_t b2 = layout(c, r, MECEFO_SIDE_OUTPUT, 0).total;
+  const size_t a = layout(c, r, MECEFO_SIDE_INPUT, 0, true).total;
+  const size_t b2 = layout(c, r, MECEFO_SIDE_OUTPUT, 0, true).total;
   *out_bytes = a > b2 ? a : b2;
   return MECEFO_OK;
 }
@@ -865,7 +910,8 @@ mecefo_status_t mecefo_ffn_bwd_lowrank(const mecefo_ffn_desc_t* desc, const void
   TRY(recompute(c, bf, U, desc->ld_act_d, dY, desc->ld_act_d, Wg, Wu, Wd, nullptr, nullptr, s));
   TRY(dgrad_and_project(c, bf, q, Wg, Wu, dU, desc->ld_act_d, s));
   void* dW[3] = {dWg, dWu, dWd};
-  return lowrank_wgrad(c, bf, q, dW, accumulate, s);
+  TRY(wgrad_contract(c, bf, q, dW, accumulate, s));
+  return wgrad_expand(c, q, dW, accumulate, s);
 }
 
 mecefo_status_t mecefo_block_bwd_skip_ex(const mecefo_ffn_desc_t* desc, const void* H, const void* dOut,
@@ -899,39 +945,40 @@ mecefo_status_t mecefo_block_bwd_skip_ex(const mecefo_ffn_desc_t* desc, const vo
   char* base = bf.base;
   const void* U = H;
   int64_t ldu = desc->ld_act_d;
-  float* rstd = (float*)(base + bf.w.rstd);
+  const SideJob norm = norm_job(c, H, desc->ld_act_d, gamma, base + bf.w.U, (float*)(base + bf.w.rstd));
+  const bool rides = gamma && c.b > 0 && norm_rides(c);
   if (gamma && c.b > 0) {  // recompute the norm output from the stored tensor
-    STAGE(MECEFO_STAGE_NORM_FWD, s);
-    HIP_TRY(launch_rmsnorm_fwd(c.bf16, H, desc->ld_act_d, gamma, desc->rms_eps, base + bf.w.U, c.dm, rstd, c.b, c.dm, s));
+    if (!rides) TRY(norm_forward(c, norm, s));
     U = base + bf.w.U;
     ldu = c.dm;
   }
   void* dUb = base + bf.w.dU;
   const LowRank q = low_rank(c, bf, U, ldu, dOut, desc->ld_act_d, P, side, exact_mask);
-  TRY(recompute(c, bf, U, ldu, dOut, desc->ld_act_d, Wg, Wu, Wd, Gs, Zs, s));
+  TRY(recompute(c, bf, U, ldu, dOut, desc->ld_act_d, Wg, Wu, Wd, Gs, Zs, s, rides ? &norm : nullptr));
   // Eq. (2) reads dOut (the down projection's output gradient) and, without a norm, H itself: when dX
-  // is a buffer of its own the norm backward goes first, while dU is still in the caches and before
-  // the weight gradients flood them; when dX overwrites dOut (or H) it has to wait for Eq. (2), which needs the
-  // partial buffer.
+  // is a buffer of its own the norm backward goes first, while dU is still in the caches; when dX overwrites dOut (or H)
+  // it has to wait for the contraction, which needs the partial buffer.  The expand launch carries the sum of the gain
+  // gradient.
   const bool dx_first = dX != dOut && dX != H;
   Parts parts;
   auto norm_args = [&]() {
     return norm_bwd_args(c, bf, bf.w, parts, H, desc->ld_act_d, gamma, dOut, desc->ld_act_d, dX, desc->ld_act_d, dgamma != nullptr);
   };
-  const bool read_parts = gamma && dx_first && c.b > 0 && norm_bwd_reads_parts(c, bf, norm_args());
+  const bool read_parts = gamma && c.b > 0 && norm_bwd_reads_parts(c, bf, norm_args());
   TRY(dgrad_and_project(c, bf, q, Wg, Wu, dUb, c.dm, s, read_parts ? &parts : nullptr));
   // Skip the MHA connection: the gradient handed to the previous layer is dH = dOut + normbwd(dU).
+  SideJob later = {};
   auto norm_bwd = [&]() -> mecefo_status_t {
-    if (gamma) return norm_backward(c, norm_args(), dgamma, accumulate, s);
+    if (gamma) return norm_backward(c, norm_args(), dgamma, accumulate, s, &later);
     STAGE(MECEFO_STAGE_NORM_BWD, s);
     if (c.b > 0) HIP_TRY(launch_add(c.bf16, dOut, desc->ld_act_d, dUb, c.dm, dX, desc->ld_act_d, c.b, c.dm, s));
     return MECEFO_OK;
   };
   if (dx_first) TRY(norm_bwd());
   void* dW[3] = {dWg, dWu, dWd};
-  TRY(lowrank_wgrad(c, bf, q, dW, accumulate, s));
+  TRY(wgrad_contract(c, bf, q, dW, accumulate, s));
   if (!dx_first) TRY(norm_bwd());
-  return MECEFO_OK;
+  return wgrad_expand(c, q, dW, accumulate, s, &later);
 }
 
 mecefo_status_t mecefo_block_bwd_skip(const mecefo_ffn_desc_t* desc, const void* H, const void* dOut,
@@ -950,7 +997,7 @@ mecefo_status_t mecefo_block_full_workspace_bytes(const mecefo_ffn_desc_t* desc,
   TRY(check_attn(c, attn));
   if (!out_bytes) return fail(MECEFO_ERR_INVALID_ARG, "out_bytes is NULL");
   const int r0[3] = {0, 0, 0};
-  *out_bytes = full_layout(c, *attn, layout(c, r0, MECEFO_SIDE_INPUT, 0).total).total;
+  *out_bytes = full_layout(c, *attn, layout(c, r0, MECEFO_SIDE_INPUT, 0, true).total).total;
   return MECEFO_OK;
 }
 
@@ -975,8 +1022,12 @@ mecefo_status_t mecefo_block_bwd_full(const mecefo_ffn_desc_t* desc, const mecef
     if (c.bf16 && ((uintptr_t)g % 16)) return fail(MECEFO_ERR_INVALID_ARG, "gradient buffers must be 16-byte aligned");
   }
   const int r0[3] = {0, 0, 0};
-  const Workspace fw = layout(c, r0, MECEFO_SIDE_INPUT, 0);
-  const FullWs w = full_layout(c, *attn, fw.total);
+  Workspace fw = layout(c, r0, MECEFO_SIDE_INPUT, 0, true);
+  FullWs w = full_layout(c, *attn, fw.total);
+  if (w.total > ws_bytes) {
+    fw = layout(c, r0, MECEFO_SIDE_INPUT, 0, false);
+    w = full_layout(c, *attn, fw.total);
+  }
   if (w.total > ws_bytes) return fail(MECEFO_ERR_WORKSPACE_TOO_SMALL, "workspace has %zu bytes, %zu needed", ws_bytes, w.total);
   if (!ws) return fail(MECEFO_ERR_INVALID_ARG, "workspace is NULL");
   Bufs bf;
@@ -997,11 +1048,10 @@ mecefo_status_t mecefo_block_bwd_full(const mecefo_ffn_desc_t* desc, const mecef
   float* cs = (float*)(base + w.cs); float* sn = (float*)(base + w.sn);
 
   // ---- FFN module, exact: dH = dOut + normbwd(dU), dWg, dWu, dWd, dg_ffn
-  if (any) {
-    STAGE(MECEFO_STAGE_NORM_FWD, s);
-    HIP_TRY(launch_rmsnorm_fwd(c.bf16, in->H, d.ld_act_d, in->g_ffn, d.rms_eps, Ub, dm, rstd, c.b, dm, s));
-  }
-  TRY(recompute(c, bf, Ub, dm, in->dOut, d.ld_act_d, in->Wg, in->Wu, in->Wd, nullptr, nullptr, s));
+  const SideJob norm = norm_job(c, in->H, d.ld_act_d, in->g_ffn, Ub, rstd);
+  const bool rides = any && norm_rides(c);
+  if (any && !rides) TRY(norm_forward(c, norm, s));
+  TRY(recompute(c, bf, Ub, dm, in->dOut, d.ld_act_d, in->Wg, in->Wu, in->Wd, nullptr, nullptr, s, rides ? &norm : nullptr));
   Parts parts;
   auto ffn_norm = [&]() {
     return norm_bwd_args(c, bf, fw, parts, in->H, d.ld_act_d, in->g_ffn, in->dOut, d.ld_act_d, dH, dm, true);
@@ -1138,8 +1188,8 @@ mecefo_status_t mecefo_block_bwd_full(const mecefo_ffn_desc_t* desc, const mecef
     g.p[0].A[2] = dV; g.p[0].B[2] = in->Wv;
     if (norm_bwd_reads_parts(c, bf, attn_norm())) {
       g.p[0].read_parts = true;
-      if (c.bf16) bf16_plan_splits(g, fw.room);
-      else f32_plan_parts(g, fw.room);
+      if (c.bf16) bf16_plan_splits(g, fw.room, fw.parts_room);
+      else f32_plan_parts(g, fw.parts_room);
     }
     TRY(launch_store(c, bf, g, s, &parts));
   }
@@ -1353,8 +1403,11 @@ mecefo_status_t mecefo_block_bwd_skip_noalloc(const mecefo_ffn_desc_t* desc, con
                                               mecefo_proj_t Pg, mecefo_proj_t Pu, mecefo_proj_t Pd, mecefo_side_t side,
                                               void* dX, void* dgamma, void* dWg, void* dWu, void* dWd, int accumulate,
                                               void* hip_stream) {
-  size_t need = 0;
-  TRY(mecefo_workspace_bytes(desc, Pg.r > 0 ? Pg.r : 0, Pu.r > 0 ? Pu.r : 0, Pd.r > 0 ? Pd.r : 0, &need));
+  Ctx c;
+  TRY(check_desc(desc, &c));
+  const int r[3] = {Pg.r > 0 ? Pg.r : 0, Pu.r > 0 ? Pu.r : 0, Pd.r > 0 ? Pd.r : 0};
+  const size_t in = layout(c, r, MECEFO_SIDE_INPUT, 0, false).total, other = layout(c, r, MECEFO_SIDE_OUTPUT, 0, false).total;
+  const size_t need = in > other ? in : other;
   if (need > (size_t)MECEFO_NOALLOC_SCRATCH_BYTES)
     return fail(MECEFO_ERR_WORKSPACE_TOO_SMALL,
                 "this shape needs %zu bytes of scratch; the static buffer of mecefo_block_bwd_skip_noalloc holds %zu "

@@ -367,7 +367,7 @@ __device__ __forceinline__ void dtl_tile(const KHead& head, GemmProblem p, int m
   // row keeps every shared line in use for at most eight stages, well inside the 4 MB L2 (larger
   // strides measured slower).  Measured on the 7B-shaped layer: recompute launch -3.5 %, the others
   // -1 % to 0.  The summation order over K depends on the tile row only, so reruns stay bit-equal.
-  int rot = head.krot > 0 ? m0 / BM & (head.krot - 1) : 0;      // krot: a power of two
+  int rot = m0 / BM & 7;
   while (rot >= nst && rot > 0) rot = nst > 0 ? rot - nst : 0;
   auto kmap = [&](int turn) {
     const int i = KG > 1 ? turn * KG + group : turn;
@@ -531,10 +531,16 @@ struct WorkgroupClock {
 };
 
 template <class Cfg, class Pipe, bool AKC, bool BKC, int EPI, bool RAGGED>
-__global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const KArgs) {
+__global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const KArgs args) {
   constexpr int BM = Cfg::BM, BN_OUT = epi_is_dual(EPI) ? Cfg::BN / 2 : Cfg::BN;
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
   const KHead head = load_head();
+  if constexpr (side_kind(AKC, BKC, EPI) != SIDE_NONE) {
+    if ((int)blockIdx.x >= head.gemm_blocks) {
+      run_side<__bf16, side_kind(AKC, BKC, EPI)>(args, blockIdx.x - head.gemm_blocks, smem);
+      return;
+    }
+  }
   WorkgroupClock clock;
   clock.start(head);
   int index;
@@ -553,11 +559,17 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const K
 // which walk K two to six times as fast.  head.total counts the workgroups of the full rounds, the tail's tiles are the
 // last of the problem with the most.
 template <class Cfg, class Pipe, class C2, class P2, class C4, class P4, class C16, class P16, bool AKC, bool BKC, int EPI>
-__global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_tail_kernel(const KArgs) {
+__global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_tail_kernel(const KArgs args) {
   static_assert(P2::THREADS == Pipe::THREADS && P4::THREADS == Pipe::THREADS && P16::THREADS == Pipe::THREADS, "one launch");
   constexpr int BM = Cfg::BM, BN_OUT = epi_is_dual(EPI) ? Cfg::BN / 2 : Cfg::BN;
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
   const KHead head = load_head();
+  if constexpr (side_kind(AKC, BKC, EPI) != SIDE_NONE) {
+    if ((int)blockIdx.x >= head.gemm_blocks) {
+      run_side<__bf16, side_kind(AKC, BKC, EPI)>(args, blockIdx.x - head.gemm_blocks, smem);
+      return;
+    }
+  }
   WorkgroupClock clock;
   clock.start(head);
   const int bid = blockIdx.x, extra = bid - head.total;
@@ -572,7 +584,7 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_tail_kernel(const 
     return;
   }
   const int prob = head.tail >> 28, shift = head.tail >> 24 & 15, first = head.tail & 0xFFFFFF;
-  const int e = xcd_remap(extra, (int)gridDim.x - head.total);
+  const int e = xcd_remap(extra, head.gemm_blocks - head.total);
   const KProblem kp = load_problem(prob);
   const TileCoord tc = map_tile<BM, BN_OUT>(head, kp, prob, first + (e >> shift));
   const GemmProblem p = product_view<2>(head, kp, 0);

@@ -79,7 +79,6 @@ inline const TileModel& tile_model(int c) {
                                           {32, 32, 2.4f, 0.9f, 0.10f, 0.15f, 0.15f}};
   return m[c];
 }
-constexpr int kCUs = 256;
 
 // What the 192-row tile and the cut-up last round are built for: operands whose rows can be cut anywhere, and the
 // epilogues of launches that can be large.
@@ -209,10 +208,10 @@ inline int bf16_best_tile(const GemmLaunch& g, float* cost = nullptr) {
 }
 
 // Cuts the problems of a store launch along K (their `splits`) where that makes the launch shorter, into parts of about
-// equal length with four or more stages each, of which `room` fp32 elements can be held.  The parts are written, read
+// equal length with four or more stages each, of which `room` fp32 elements can be held (parts_room for read_parts).  The parts are written, read
 // back and summed by one more launch: 4 us and their bytes, at about 5 TB/s each way while the cache behind the L2s holds
 // them (the sum of 59 MB takes 11 us, of 4 MB 5 us), at 3 beyond; parts that their reader adds up itself cost their bytes.  Returns the modelled time of it all.
-inline float bf16_plan_splits(GemmLaunch& g, int64_t room) {
+inline float bf16_plan_splits(GemmLaunch& g, int64_t room, int64_t parts_room = 0) {
   int longest = 0;
   for (int i = 0; i < g.nprob; ++i) {
     g.p[i].splits = 1;
@@ -233,7 +232,7 @@ inline float bf16_plan_splits(GemmLaunch& g, int64_t room) {
       g.p[i].splits = parts;
       if (parts > 1) (g.p[i].read_parts ? read : out) += (int64_t)parts * g.p[i].M * g.p[i].ldc;
     }
-    if (out + read > room) break;
+    if (out > room || read > parts_room) break;
     float x;
     bf16_best_tile(g, &x);
     if (out > 0) x += 4.f;
@@ -270,11 +269,12 @@ hipError_t run_bf16(GemmLaunch& g, hipStream_t stream) {
   constexpr int LDS = Kern::LDS;
   constexpr bool DUAL = epi_is_dual(EPI);
   KArgs a;
-  fill_kargs(a, g, Cfg::BM, DUAL ? Cfg::BN / 2 : Cfg::BN, kBK, 8);
+  fill_kargs(a, g, Cfg::BM, DUAL ? Cfg::BN / 2 : Cfg::BN, kBK);
   if (a.h.total == 0) return hipSuccess;
   const hipError_t e = Kern::prepare();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(Kern::entry(), dim3(a.h.total), dim3(Kern::DTL ? Pipe::THREADS : Cfg::NT), LDS, stream, a);
+  const unsigned side = add_side(a, g, Kern::DTL ? side_kind(AKC, BKC, EPI) : SIDE_NONE, Pipe::THREADS);
+  hipLaunchKernelGGL(Kern::entry(), dim3(a.h.total + side), dim3(Kern::DTL ? Pipe::THREADS : Cfg::NT), LDS, stream, a);
   return hipGetLastError();
 }
 
@@ -295,7 +295,7 @@ template <bool AKC, bool BKC, int EPI>
 hipError_t run_bf16_tail(GemmLaunch& g, const TailPlan& plan, hipStream_t stream) {
   using Kern = TailKernel<AKC, BKC, EPI>;
   KArgs a;
-  fill_kargs(a, g, CfgL8::BM, epi_is_dual(EPI) ? CfgL8::BN / 2 : CfgL8::BN, kBK, 8);
+  fill_kargs(a, g, CfgL8::BM, epi_is_dual(EPI) ? CfgL8::BN / 2 : CfgL8::BN, kBK);
   for (int s = 0; s < kMaxProblems; ++s)
     if ((a.h.order >> (4 * s) & 15) == plan.prob) {
       a.h.units[s] -= plan.tiles;
@@ -305,7 +305,9 @@ hipError_t run_bf16_tail(GemmLaunch& g, const TailPlan& plan, hipStream_t stream
     }
   const hipError_t e = Kern::prepare();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(Kern::entry(), dim3(a.h.total + (plan.tiles << plan.shift)), dim3(PipeL::THREADS), Kern::LDS, stream, a);
+  a.h.gemm_blocks = a.h.total + (plan.tiles << plan.shift);
+  const unsigned side = add_side(a, g, side_kind(AKC, BKC, EPI), PipeL::THREADS);
+  hipLaunchKernelGGL(Kern::entry(), dim3(a.h.gemm_blocks + side), dim3(PipeL::THREADS), Kern::LDS, stream, a);
   return hipGetLastError();
 }
 

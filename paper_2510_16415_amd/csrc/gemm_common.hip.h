@@ -36,7 +36,7 @@ __host__ __device__ inline int div_by(int x, int n, uint32_t magic) {
 struct KHead {
   int nprob, total;        // problems; workgroups: the sum over problems of tiles * splits (* batch)
   int accumulate, out_f32;
-  int krot;                // direct-to-LDS kernel: tile row tm starts its K loop at stage tm % krot (0: off)
+  int gemm_blocks;         // workgroups of the products; those behind them run the side job
   int order;               // problem indices, four bits each, most work per workgroup first
   int units[kMaxProblems]; // workgroups of the problems in that order
   int batch, batch_inner, causal, rope_seq;
@@ -53,6 +53,7 @@ struct KArgs {
   KHead h;
   KProblem p[kMaxProblems];
   int64_t b_bo, c_bo;
+  SideJob side;
 };
 static_assert(sizeof(KHead) == 128 && sizeof(KProblem) == 128 && offsetof(KArgs, p) == 128, "whole lines of 64 bytes");
 
@@ -60,12 +61,11 @@ static_assert(sizeof(KHead) == 128 && sizeof(KProblem) == 128 && offsetof(KArgs,
 // order of the workgroups is eight consecutive segments, one per XCD; segment x lists, heaviest problem first, the
 // x-th eighth of every problem's workgroups.  Longest-processing-time-first inside each segment keeps the tail of a
 // grouped launch short when the problems differ in K.
-inline void fill_kargs(KArgs& args, const GemmLaunch& g, int bm, int bn, int bk, int krot) {
+inline void fill_kargs(KArgs& args, const GemmLaunch& g, int bm, int bn, int bk) {
   KHead& a = args.h;
   a.nprob = g.nprob;
   a.accumulate = g.accumulate;
   a.out_f32 = g.out_f32;
-  a.krot = krot;
   a.clk = g.clk;
   const GemmProblem& f = g.p[0];      // what every problem of a launch shares
   a.batch = f.batch; a.batch_inner = f.batch_inner; a.causal = f.causal; a.rope_seq = f.rope_seq;
@@ -110,6 +110,20 @@ inline void fill_kargs(KArgs& args, const GemmLaunch& g, int bm, int bn, int bk,
     a.order |= idx[s] << (4 * s);
     a.units[s] = units[idx[s]];
   }
+  a.gemm_blocks = a.total;
+  args.side.kind = SIDE_NONE;
+}
+
+// Adds the side job of a launch whose kernel carries jobs of kind `kind`; returns its workgroups, of `threads` threads.
+inline unsigned add_side(KArgs& args, GemmLaunch& g, int kind, int threads) {
+  g.side_done = g.side.kind == SIDE_NONE || g.side.kind == kind;
+  if (g.side.kind == SIDE_NONE || g.side.kind != kind) return 0;
+  args.side = g.side;
+  if (kind == SIDE_DGAMMA) return (unsigned)((g.side.d + 31) / 32);
+  return (unsigned)((g.side.rows + threads / 64 - 1) / (threads / 64));
+}
+constexpr int side_kind(bool akc, bool bkc, int epi) {
+  return akc && bkc && epi == EPI_GRAD ? SIDE_DGAMMA : akc && !bkc && epi == EPI_STORE ? SIDE_NORM : SIDE_NONE;
 }
 
 // The hardware hands consecutive workgroup ids to the 8 XCDs round-robin.  Renumber so
@@ -139,6 +153,74 @@ __device__ inline KProblem load_problem(int prob) {
   KWords w = {k[2 + 2 * prob], k[3 + 2 * prob]};
   asm volatile("" : "+s"(w.lo), "+s"(w.hi));
   return __builtin_bit_cast(KProblem, w);
+}
+
+__device__ inline float wave_total(float v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// Gain gradient, 32 columns per workgroup: the threads' 32-column groups share out the rows of sums, and are added in a
+// fixed order.  Its own launch takes 4 us behind the norm backward.
+template <typename T>
+__device__ inline void side_dgamma(const SideJob& j, int block, float* red) {
+  const int cl = threadIdx.x & 31, g = threadIdx.x >> 5, groups = blockDim.x >> 5;
+  const int c = block * 32 + cl;
+  const float* partial = (const float*)j.in;
+  float s = 0.f;
+  if (c < j.d) {
+#pragma unroll 16
+    for (int k = g; k < j.nblk; k += groups) s += partial[(int64_t)k * j.d + c];
+  }
+  red[g * 32 + cl] = s;
+  __syncthreads();
+  if (g != 0 || c >= j.d) return;
+  for (int k = 1; k < groups; ++k) s += red[k * 32 + cl];
+  if (j.out_f32) {
+    float* o = (float*)j.out;
+    o[c] = j.accumulate ? o[c] + s : s;
+  } else {
+    T* o = (T*)j.out;
+    o[c] = (T)(j.accumulate ? (float)o[c] + s : s);
+  }
+}
+
+// U = norm(H) gamma and rstd, a wave per row, the sums in the order of the kernel that does only this.
+template <typename T, int VEC>
+__device__ inline void side_norm(const SideJob& j, int block) {
+  struct alignas(sizeof(T) * VEC) V { T e[VEC]; };
+  const int lane = threadIdx.x & 63;
+  const int64_t row = (int64_t)block * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  if (row >= j.rows) return;
+  const T* h = (const T*)j.in + row * j.ld_in;
+  T* u = (T*)j.out + row * j.ld_out;
+  const int nv = j.d / VEC;
+  float ss = 0.f;
+#pragma unroll 4
+  for (int i = lane; i < nv; i += 64) {
+    const V x = *(const V*)(h + i * VEC);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) { const float f = (float)x.e[e]; ss += f * f; }
+  }
+  ss = wave_total(ss);
+  const float rs = 1.0f / sqrtf(ss / (float)j.d + j.eps);
+  if (lane == 0) j.rstd[row] = rs;
+#pragma unroll 4
+  for (int i = lane; i < nv; i += 64) {
+    const V x = *(const V*)(h + i * VEC), g = *(const V*)((const T*)j.gamma + i * VEC);
+    V o;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) o.e[e] = (T)((float)x.e[e] * rs * (float)g.e[e]);
+    *(V*)(u + i * VEC) = o;
+  }
+}
+
+// The side job of a workgroup behind those of the products.
+template <typename T, int KIND>
+__device__ inline void run_side(const KArgs& args, int block, void* smem) {
+  if constexpr (KIND == SIDE_DGAMMA) side_dgamma<T>(args.side, block, (float*)smem);
+  else if constexpr (KIND == SIDE_NORM) side_norm<T, sizeof(T) == 2 ? 8 : 1>(args.side, block);
 }
 
 struct TileCoord { int prob, tm, tn, split, z; };
@@ -273,11 +355,6 @@ template <int EPI> constexpr bool kUnhandledEpilogue = false;
 
 // 1 / sqrt of a squared norm; a zero matrix is left unchanged.
 __device__ inline float inv_norm(float sq) { return sq > 0.f ? 1.0f / sqrtf(sq) : 1.0f; }
-__device__ inline float wave_total(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
 // From the kNormBlocks partial sums of a squared norm, and from the trace of a Gram matrix; every wave for itself, in a
 // fixed order.
 __device__ inline float inv_norm_of_partials(const float* partial, int lane) {

@@ -138,7 +138,7 @@ __device__ inline void sum_quarters(const GemmProblem& p, const KHead& head, int
 }
 
 template <class Cfg, int EPI, bool AKC, bool BKC>
-__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const KArgs) {
+__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const KArgs args) {
   constexpr bool DUAL = epi_is_dual(EPI);
   constexpr int FT = Cfg::FT, FK = Cfg::FK, FS = Cfg::FS;
   constexpr int NB = DUAL ? 2 : 1, MATS = 1 + NB;
@@ -146,6 +146,12 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const KArgs) {
   __shared__ __attribute__((aligned(16))) float lds[2][MATS][FT * FS];
   static_assert(!Cfg::KSPLIT || 4 * NB * FT * (FT + 1) <= 2 * MATS * FT * FS, "the partial tiles reuse the operand buffers");
   const KHead head = load_head();
+  if constexpr (side_kind(AKC, BKC, EPI) != SIDE_NONE) {
+    if ((int)blockIdx.x >= head.gemm_blocks) {
+      run_side<float, side_kind(AKC, BKC, EPI)>(args, blockIdx.x - head.gemm_blocks, &lds[0][0][0]);
+      return;
+    }
+  }
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   int index;
@@ -300,12 +306,18 @@ template <int EPI> struct DirectF32 {
 };
 
 template <int EPI, bool AKC, bool BKC>
-__global__ __launch_bounds__(256, 2) void gemm_f32_direct_kernel(const KArgs) {
+__global__ __launch_bounds__(256, 2) void gemm_f32_direct_kernel(const KArgs args) {
   using D = DirectF32<EPI>;
   constexpr bool DUAL = epi_is_dual(EPI);
   constexpr int NB = D::NB, NS = D::NS, FT = 32, FK = 64, FPS = 2 * (1 + NB);
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
   const KHead head = load_head();
+  if constexpr (side_kind(AKC, BKC, EPI) != SIDE_NONE) {
+    if ((int)blockIdx.x >= head.gemm_blocks) {
+      run_side<float, side_kind(AKC, BKC, EPI)>(args, blockIdx.x - head.gemm_blocks, smem);
+      return;
+    }
+  }
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   int index;
@@ -423,11 +435,11 @@ inline int f32_tiles(const GemmLaunch& g, int ft) {
 template <class Cfg, int EPI>
 hipError_t run_f32_cfg(GemmLaunch& g, hipStream_t stream) {
   KArgs a;
-  fill_kargs(a, g, Cfg::FT, Cfg::FT, Cfg::FK, 0);
+  fill_kargs(a, g, Cfg::FT, Cfg::FT, Cfg::FK);
   a.h.out_f32 = 1;
   a.h.clk = nullptr;
   if (a.h.total == 0) return hipSuccess;
-  const dim3 grid(a.h.total);
+  const dim3 grid(a.h.total + add_side(a, g, side_kind(g.a_kcontig, g.b_kcontig, EPI), 256));
   if (g.a_kcontig && g.b_kcontig) hipLaunchKernelGGL((gemm_f32_kernel<Cfg, EPI, true, true>), grid, dim3(256), 0, stream, a);
   else if constexpr (f32_nt_only(EPI)) return hipErrorInvalidValue;
   else if (g.a_kcontig) hipLaunchKernelGGL((gemm_f32_kernel<Cfg, EPI, true, false>), grid, dim3(256), 0, stream, a);
@@ -464,7 +476,7 @@ struct DirectKernelF32 {
   }
   static hipError_t run(GemmLaunch& g, hipStream_t stream) {
     KArgs a;
-    fill_kargs(a, g, 32, 32, 64, 0);
+    fill_kargs(a, g, 32, 32, 64);
     a.h.out_f32 = 1;
     a.h.clk = nullptr;
     if (a.h.total == 0) return hipSuccess;
@@ -474,8 +486,9 @@ struct DirectKernelF32 {
     using D = DirectF32<EPI>;
     int stages = 1;
     for (int i = 0; i < g.nprob; ++i) stages = (a.p[i].chunk_nseg >> 2) > stages ? a.p[i].chunk_nseg >> 2 : stages;
+    const unsigned side = add_side(a, g, side_kind(AKC, BKC, EPI), 256);
     const int ring = (stages < D::NS ? stages : D::NS) * D::STAGE, sum = 4 * D::NB * 32 * 33 * 4;
-    hipLaunchKernelGGL((gemm_f32_direct_kernel<EPI, AKC, BKC>), dim3(a.h.total), dim3(256), ring > sum ? ring : sum, stream, a);
+    hipLaunchKernelGGL((gemm_f32_direct_kernel<EPI, AKC, BKC>), dim3(a.h.total + side), dim3(256), ring > sum ? ring : sum, stream, a);
     return hipGetLastError();
   }
 };
@@ -529,8 +542,8 @@ void f32_plan_parts(GemmLaunch& g, int64_t room) {
   const int stages = (p.K + 63) / 64 * (p.nseg > 1 ? p.nseg : 1);
   float best = 0.f;
   for (int s = 1; s <= kMaxNormParts && s <= stages; ++s) {
-    if (s > 1 && (int64_t)s * p.M * p.ldc > room) break;
-    const float n = (float)((tiles * s + others + 255) / 256), x = (float)((stages + s - 1) / s) * 0.45f * n + 0.5f * s;
+    if (s > 1 && ((int64_t)s * p.M * p.ldc > room || tiles * s + others > kCUs)) break;
+    const float x = (float)((stages + s - 1) / s) * 0.45f + 0.5f * s;
     if (s == 1 || x < best) { best = x; p.splits = s; }
   }
 }

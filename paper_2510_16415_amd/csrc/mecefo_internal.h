@@ -23,6 +23,7 @@ enum Epilogue : int {
 };
 
 constexpr int kMaxProblems = 4;   // of one launch
+constexpr int kCUs = 256;         // compute units of the chip
 constexpr int kNormBlocks = 256;  // partial sums of a squared norm
 
 enum CausalK : int {
@@ -65,6 +66,25 @@ struct GemmProblem {
   int causal;            // CausalK
 };
 
+// Small work of another kind that goes out in the same launch, on workgroups behind those of the products.
+enum Side : int {
+  SIDE_NONE = 0,
+  SIDE_DGAMMA = 1,   // gain gradient from the norm backward's sums (launch_dgamma_reduce): with EPI_GRAD, both K-contiguous
+  SIDE_NORM = 2,     // norm recompute (launch_rmsnorm_fwd): with EPI_STORE, B K-strided
+};
+struct SideJob {
+  int kind;
+  int d;               // columns
+  int nblk;            // SIDE_DGAMMA: rows of sums
+  int out_f32, accumulate;
+  float eps;           // SIDE_NORM
+  int64_t rows, ld_in, ld_out;
+  const void* in;      // the sums [nblk x d], or H
+  const void* gamma;
+  void* out;           // dgamma, or U
+  float* rstd;
+};
+
 struct GemmLaunch {
   GemmProblem p[kMaxProblems];   // batch, causal and the epilogues' scalars and vectors: those of p[0] hold for all
   int nprob;
@@ -74,6 +94,8 @@ struct GemmLaunch {
   bool out_f32;     // EPI_GRAD: gradient buffer dtype is fp32 (else same as operands)
   int accumulate;   // EPI_GRAD
   int tile;         // EPI_ROPE: the configuration that gemm_bf16_rope_tile found for this launch
+  SideJob side;
+  bool side_done;   // set by the launcher: the side job is part of the launch
   uint32_t* clk;    // measurement: 64 (cycles, wall ticks) pairs written by the direct-to-LDS kernel, or NULL
 };
 
