@@ -1,5 +1,6 @@
 // Host-side launch helpers for the bf16 MFMA GEMM instantiations.
 #pragma once
+#include <float.h>
 #include <math.h>
 
 #include "gemm_bf16_dtl.hip.h"
@@ -134,18 +135,36 @@ inline TailPlan bf16_tail(const GemmLaunch& g) {
   return plan;
 }
 
-// Modelled time in us of the launch on configuration c.
-inline float bf16_tile_cost(const GemmLaunch& g, int c) {
-  const TileModel& m = tile_model(c);
-  int units[kMaxProblems], stages[kMaxProblems], total = 0, longest = 0;
+// The K stages of a launch's workgroups, the same on every configuration.
+struct Stages {
+  int of[kMaxProblems], longest = 0;
   bool equal = true;
+  explicit Stages(const GemmLaunch& g) {
+    for (int i = 0; i < g.nprob; ++i) {
+      of[i] = bf16_stages(g, i);
+      longest = of[i] > longest ? of[i] : longest;
+      equal &= of[i] == of[0];
+    }
+  }
+};
+
+// Modelled time in us of the launch on configuration c.  Where it is seen early that this is not below `bound`, some value
+// that is not below it either: laying out problems of different length takes 0.1 to 0.4 us, most of the planning of a launch.
+inline float bf16_tile_cost(const GemmLaunch& g, int c, const Stages& st, float bound) {
+  const TileModel& m = tile_model(c);
+  const int* stages = st.of;
+  const int longest = st.longest;
+  const bool equal = st.equal;
+  int units[kMaxProblems], total = 0;
+  int64_t sum = 0;
   for (int i = 0; i < g.nprob; ++i) {
     units[i] = bf16_units(g, i, m.bm, m.bn);
-    stages[i] = bf16_stages(g, i);
     total += units[i];
-    if (stages[i] > longest) longest = stages[i];
-    equal &= stages[i] == stages[0];
+    sum += (int64_t)units[i] * stages[i];
   }
+  // up to a workgroup per CU: a stage takes longer the more of them there are (256 x 256: 1.45 us up to 96, 1.65 with 176)
+  const float full = fminf(fmaxf((total - 96) / 160.f, 0.f), 1.f);
+  const float alone = m.stage_alone + full * (m.stage_full - m.stage_alone);
   float n = total / 256.f, load;               // workgroups and K stages of the fullest CU
   if (equal || n >= 4.f) {
     if (n < 4.f) n = (float)(int)(n + 0.999f);   // few workgroups per CU: the fullest CU sets the time
@@ -153,6 +172,9 @@ inline float bf16_tile_cost(const GemmLaunch& g, int c) {
     for (int i = 0; i < g.nprob; ++i) load += (float)units[i] * stages[i];
     load *= n / total;
   } else {
+    const float least = fmaxf((float)longest, sum / 256.f);   // the fullest CU holds the longest problem's stages, and the mean
+    const float t = m.fixed + m.per_round + (total <= kCUs ? least * alone : fmaxf(longest * m.stage_alone, least * m.stage_shared));
+    if (t >= bound * 1.0001f) return t;
     // Problems of different length, the longest first, each workgroup to the CU with the least to do.  At most
     // 2 * kMaxProblems * 4 groups of equally loaded CUs come about: a problem fills whole groups, and splits one.
     struct { int load, cus, wgs; } q[64] = {{0, 256, 0}};
@@ -184,23 +206,22 @@ inline float bf16_tile_cost(const GemmLaunch& g, int c) {
     load = (float)q[at].load;
     n = (float)q[at].wgs;
   }
-  // up to a workgroup per CU: a stage takes longer the more of them there are (256 x 256: 1.45 us up to 96, 1.65 with 176)
-  const float full = fminf(fmaxf((total - 96) / 160.f, 0.f), 1.f);
-  const float alone = m.stage_alone + full * (m.stage_full - m.stage_alone);
   const float time = total <= kCUs ? load * alone : fmaxf(longest * m.stage_alone, load * m.stage_shared);
-  return m.fixed + m.per_round * n + time - (c == TILE_L && n < 4.f ? bf16_tail(g).saved : 0.f);
+  return m.fixed + m.per_round * n + time - (c == TILE_L && n < 4.f && equal ? bf16_tail(g).saved : 0.f);
 }
-inline int bf16_best_tile(const GemmLaunch& g, float* cost = nullptr) {
-  int best = TILE_L;
-  float t = bf16_tile_cost(g, TILE_L);
+inline float bf16_tile_cost(const GemmLaunch& g, int c) { return bf16_tile_cost(g, c, Stages(g), FLT_MAX); }
+
+// The configuration of the smallest modelled time; with a `bound`, only if that is below it.
+inline int bf16_best_tile(const GemmLaunch& g, float* cost = nullptr, float bound = FLT_MAX) {
+  const Stages st(g);
   const bool ragged = bf16_ragged(g);
-  int longest = 0;
-  for (int i = 0; i < g.nprob; ++i) longest = bf16_stages(g, i) > longest ? bf16_stages(g, i) : longest;
-  for (int c = 1; c < TILE_COUNT; ++c) {
+  int best = TILE_L;
+  float t = bound;
+  for (int c = 0; c < TILE_COUNT; ++c) {
     if (c == TILE_X && !has_tile_x(g.epi)) continue;
     if (c == TILE_K && (ragged || !has_tile_k(g.a_kcontig, g.b_kcontig, g.epi))) continue;
     // with a ragged K the groups of waves meet one more barrier per stage: a third of what they save
-    const float x = bf16_tile_cost(g, c) + (c == TILE_T2 && ragged ? 0.05f * longest : 0.f);
+    const float x = bf16_tile_cost(g, c, st, t) + (c == TILE_T2 && ragged ? 0.05f * st.longest : 0.f);
     if (x < t) { t = x; best = c; }
   }
   if (cost) *cost = t;
@@ -232,13 +253,14 @@ inline float bf16_plan_splits(GemmLaunch& g, int64_t room, int64_t parts_room = 
       g.p[i].splits = parts;
       if (parts > 1) (g.p[i].read_parts ? read : out) += (int64_t)parts * g.p[i].M * g.p[i].ldc;
     }
-    if (out > room || read > parts_room) break;
+    const float extra = (out > 0 ? 4.f : 0.f) + (float)out * (out < 32 << 20 ? 1.0e-6f : 2.7e-6f) +
+                        (float)read * (read < 32 << 20 ? 0.6e-6f : 2.0e-6f);
+    if (out > room || read > parts_room || extra >= t) break;   // more parts are more bytes
     float x;
-    bf16_best_tile(g, &x);
-    if (out > 0) x += 4.f;
-    x += (float)out * (out < 32 << 20 ? 1.0e-6f : 2.7e-6f) + (float)read * (read < 32 << 20 ? 0.6e-6f : 2.0e-6f);
-    if (x < t) {
-      t = x;
+    const float bound = t - extra;
+    bf16_best_tile(g, &x, bound);
+    if (x < bound) {
+      t = x + extra;
       for (int i = 0; i < g.nprob; ++i) best[i] = g.p[i].splits;
     }
   }
