@@ -440,6 +440,14 @@ mecefo_status_t norm_backward(const Ctx& c, const NormBwd& n, void* dgamma, int 
   else HIP_TRY(launch_dgamma_reduce(n.dg_partial, nblk, c.dm, dgamma, c.grad_f32, c.bf16, accumulate, s));
   return MECEFO_OK;
 }
+// The sum of the gain gradient, where the launch that was to carry it as its side job did not.
+mecefo_status_t dgamma_left(const Ctx& c, const GemmLaunch& g, hipStream_t s) {
+  const SideJob& j = g.side;
+  if (j.kind != SIDE_DGAMMA || g.side_done) return MECEFO_OK;
+  STAGE(MECEFO_STAGE_NORM_BWD, s);
+  HIP_TRY(launch_dgamma_reduce((const float*)j.in, j.nblk, j.d, j.out, j.out_f32, c.bf16, j.accumulate, s));
+  return MECEFO_OK;
+}
 // Whether these arguments suit the kernel that adds up parts, and the workspace keeps them.
 bool norm_bwd_reads_parts(const Ctx& c, const Bufs& bf, NormBwd n) {
   if (bf.w.parts_room == 0) return false;
@@ -573,11 +581,7 @@ mecefo_status_t wgrad_expand(const Ctx& c, const LowRank& q, void* dW[3], int ac
     g.clk = g_prof.cur_clk;
     HIP_TRY(launch_gemm(g, s));
   }
-  if (side && side->kind == SIDE_DGAMMA && !g.side_done) {
-    STAGE(MECEFO_STAGE_NORM_BWD, s);
-    HIP_TRY(launch_dgamma_reduce((const float*)side->in, side->nblk, side->d, side->out, side->out_f32, c.bf16, side->accumulate, s));
-  }
-  return MECEFO_OK;
+  return dgamma_left(c, g, s);
 }
 
 
@@ -1057,36 +1061,33 @@ mecefo_status_t mecefo_block_bwd_full(const mecefo_ffn_desc_t* desc, const mecef
     return norm_bwd_args(c, bf, fw, parts, in->H, d.ld_act_d, in->g_ffn, in->dOut, d.ld_act_d, dH, dm, true);
   };
   TRY(dgrad(c, bf, in->Wg, in->Wu, dUb, dm, s, any && norm_bwd_reads_parts(c, bf, ffn_norm()) ? &parts : nullptr));
+  SideJob later = {};   // the sums of the gain gradients ride on the weight gradients' launches
+  TRY(norm_backward(c, ffn_norm(), out->dg_ffn, accumulate, s, &later));
   {
     STAGE(MECEFO_STAGE_WGRAD_EXACT, s);
     GemmLaunch g = new_launch(c, false, false, EPI_GRAD);
     g.nprob = 3;
     g.accumulate = accumulate;
+    g.side = later;
     g.p[0] = prob(base + fw.DG, nullptr, c.ldf, Ub, nullptr, dm, out->dWg, nullptr, nullptr, d.ld_w_fd, c.ff, dm, b, 1);
     g.p[1] = prob(base + fw.DZ, nullptr, c.ldf, Ub, nullptr, dm, out->dWu, nullptr, nullptr, d.ld_w_fd, c.ff, dm, b, 1);
     g.p[2] = prob(in->dOut, nullptr, d.ld_act_d, base + fw.AA, nullptr, c.ldf, out->dWd, nullptr, nullptr, d.ld_w_df, dm, c.ff, b, 1);
     HIP_TRY(launch_gemm(g, s));
+    TRY(dgamma_left(c, g, s));
   }
-  TRY(norm_backward(c, ffn_norm(), out->dg_ffn, accumulate, s));
 
   // ---- attention module
   if (any) {
     STAGE(MECEFO_STAGE_NORM_FWD, s);
-    HIP_TRY(launch_rmsnorm_fwd(c.bf16, in->X, d.ld_act_d, in->g_attn, d.rms_eps, Ub, dm, rstd, c.b, dm, s));
+    const RopeTables tables = {cs, sn, S, dh / 2, (double)a.rope_theta};
+    HIP_TRY(launch_rmsnorm_fwd(c.bf16, in->X, d.ld_act_d, in->g_attn, d.rms_eps, Ub, dm, rstd, c.b, dm, s, &tables));
   }
-  {  // dWo = dH^T O  [d x d], K = tokens;  dO = dH Wo  [b x d], K = d
+  if (any) {  // dO = dH Wo  [b x d], K = d
     STAGE(MECEFO_STAGE_ATTN_OUT_BWD, s);
-    GemmLaunch g = new_launch(c, false, false, EPI_GRAD);
+    GemmLaunch g = new_launch(c, true, false, EPI_STORE);
     g.nprob = 1;
-    g.accumulate = accumulate;
-    g.p[0] = prob(dH, nullptr, dm, in->O, nullptr, d.ld_act_d, out->dWo, nullptr, nullptr, a.ld_w_dd, dm, dm, b, 1);
+    g.p[0] = prob(dH, nullptr, dm, in->Wo, nullptr, a.ld_w_dd, dUb, nullptr, nullptr, dm, b, dm, dm, 1);
     HIP_TRY(launch_gemm(g, s));
-    if (any) {
-      GemmLaunch h = new_launch(c, true, false, EPI_STORE);
-      h.nprob = 1;
-      h.p[0] = prob(dH, nullptr, dm, in->Wo, nullptr, a.ld_w_dd, dUb, nullptr, nullptr, dm, b, dm, dm, 1);
-      HIP_TRY(launch_gemm(h, s));
-    }
   }
   if (any) {
     const void* dO = dUb;
@@ -1160,22 +1161,29 @@ mecefo_status_t mecefo_block_bwd_full(const mecefo_ffn_desc_t* desc, const mecef
     }
     {
       STAGE(MECEFO_STAGE_ROPE_BWD, s);
-      HIP_TRY(launch_rope_tables(cs, sn, S, dh, (double)a.rope_theta, s));
-      HIP_TRY(launch_rope(c.bf16, dQ, dm, cs, sn, c.b, S, a.heads, dh, true, s));
-      HIP_TRY(launch_rope(c.bf16, dK, dm, cs, sn, c.b, S, a.heads, dh, true, s));
+      HIP_TRY(launch_rope(c.bf16, dQ, dK, dm, cs, sn, c.b, S, a.heads, dh, true, s));
     }
   }
-  {  // dWq, dWk, dWv = (dQ, dK, dV)^T Xn   [d x d], K = tokens
+  // dWq, dWk, dWv = (dQ, dK, dV)^T Xn and dWo = dH^T O, all [d x d], K = tokens: one launch fills the chip where three and
+  // one leave parts of it idle (2048 tokens, d 2048: 256 tiles of 256 x 256, WGRAD4_MEASURED).
+  auto wgrads = [&](const SideJob& side) -> mecefo_status_t {
     STAGE(MECEFO_STAGE_QKV_WGRAD, s);
     GemmLaunch g = new_launch(c, false, false, EPI_GRAD);
-    g.nprob = 3;
+    g.nprob = 4;
     g.accumulate = accumulate;
+    g.side = side;
     void* dst[3] = {out->dWq, out->dWk, out->dWv};
     const void* src[3] = {dQ, dK, dV};
     for (int i = 0; i < 3; ++i)
       g.p[i] = prob(src[i], nullptr, dm, Ub, nullptr, dm, dst[i], nullptr, nullptr, a.ld_w_dd, dm, dm, b, 1);
+    g.p[3] = prob(dH, nullptr, dm, in->O, nullptr, d.ld_act_d, out->dWo, nullptr, nullptr, a.ld_w_dd, dm, dm, b, 1);
     HIP_TRY(launch_gemm(g, s));
-  }
+    return dgamma_left(c, g, s);
+  };
+  // The sum of the gain gradient rides on them, behind the norm backward; a dX that lies over O is written when O was read.
+  const uintptr_t x0 = (uintptr_t)out->dX, o0 = (uintptr_t)in->O, span = (uintptr_t)(c.b * d.ld_act_d * c.esz);
+  const bool dx_last = x0 < o0 + span && o0 < x0 + span;
+  if (dx_last) TRY(wgrads(SideJob{}));
   parts = Parts();
   auto attn_norm = [&]() {
     return norm_bwd_args(c, bf, fw, parts, in->X, d.ld_act_d, in->g_attn, dH, dm, out->dX, d.ld_act_d, true);
@@ -1194,7 +1202,9 @@ mecefo_status_t mecefo_block_bwd_full(const mecefo_ffn_desc_t* desc, const mecef
     TRY(launch_store(c, bf, g, s, &parts));
   }
   // dX = dH + normbwd(dXn), dg_attn
-  return norm_backward(c, attn_norm(), out->dg_attn, accumulate, s);
+  later = SideJob{};
+  TRY(norm_backward(c, attn_norm(), out->dg_attn, accumulate, s, dx_last ? nullptr : &later));
+  return dx_last ? MECEFO_OK : wgrads(later);
 }
 
 mecefo_status_t mecefo_block_fwd_workspace_bytes(const mecefo_ffn_desc_t* desc, const mecefo_attn_desc_t* attn,
@@ -1253,8 +1263,8 @@ mecefo_status_t block_fwd(const mecefo_ffn_desc_t* desc, const mecefo_attn_desc_
   float* S32 = (float*)(base + w.S32);
   void* P = base + w.P;
 
-  HIP_TRY(launch_rmsnorm_fwd(c.bf16, in->X, d.ld_act_d, in->g_attn, d.rms_eps, Xn, dm, rstd, c.b, dm, s));
-  if (!tables_ready) HIP_TRY(launch_rope_tables(cs, sn, S, dh, (double)a.rope_theta, s));
+  const RopeTables tables = {cs, sn, S, dh / 2, (double)a.rope_theta};
+  HIP_TRY(launch_rmsnorm_fwd(c.bf16, in->X, d.ld_act_d, in->g_attn, d.rms_eps, Xn, dm, rstd, c.b, dm, s, tables_ready ? nullptr : &tables));
   {  // Q, K, V = Xn Wq^T, Xn Wk^T, Xn Wv^T  [b x d], K = d; Q and K rotated in the epilogue where its waves hold whole heads
     GemmLaunch g = new_launch(c, true, true, EPI_STORE);
     g.nprob = 3;
@@ -1269,8 +1279,7 @@ mecefo_status_t block_fwd(const mecefo_ffn_desc_t* desc, const mecefo_attn_desc_
     }
     HIP_TRY(launch_gemm(g, s));
     if (!rotate) {
-      HIP_TRY(launch_rope(c.bf16, Q, ldq, cs, sn, c.b, S, a.heads, dh, false, s));
-      HIP_TRY(launch_rope(c.bf16, K, ldq, cs, sn, c.b, S, a.heads, dh, false, s));
+      HIP_TRY(launch_rope(c.bf16, Q, K, ldq, cs, sn, c.b, S, a.heads, dh, false, s));
     }
   }
   const float scale = 1.0f / sqrtf((float)dh);

@@ -1,5 +1,4 @@
-// HBM-bound helpers of the standard-mode attention backward (Alg. 3, first branch): the rotary
-// angle tables, the inverse rotation applied to dQ and dK, and the per-row dot product
+// HBM-bound helpers of the standard-mode attention backward (Alg. 3, first branch): the inverse rotation applied to dQ and dK, and the per-row dot product
 // D = rowsum(dO * O) that the softmax backward subtracts.  The matrix products of the attention
 // backward run in the GEMM core as batched products.
 #include "mecefo_internal.h"
@@ -9,23 +8,11 @@ namespace {
 
 template <typename T, int VEC> struct alignas(sizeof(T) * VEC) Vec { T e[VEC]; };
 
-// cos / sin of position * theta^(-2j/dh), j < dh/2, evaluated in fp64 and stored as fp32.
-__global__ __launch_bounds__(256) void rope_table_kernel(float* __restrict__ cs, float* __restrict__ sn,
-                                                         int seq, int half, double theta) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= seq * half) return;
-  const int s = i / half, j = i - s * half;
-  const double inv = pow(theta, -(double)j / (double)half);   // 2j / dh with dh = 2 * half
-  const double ang = (double)s * inv;
-  cs[i] = (float)cos(ang);
-  sn[i] = (float)sin(ang);
-}
-
-// In-place rotation of the pairs (x[j], x[j + dh/2]) of every head of a token-major [tokens x d]
-// tensor by the position angle (sgn = +1: the forward rotation of Q and K) or by its negative
+// In-place rotation of the pairs (x[j], x[j + dh/2]) of every head of two token-major [tokens x d]
+// tensors (one launch: the second takes 6 us and a gap of its own at 2048 tokens, d 2048) by the position angle (sgn = +1: the forward rotation of Q and K) or by its negative
 // (sgn = -1: the transpose, applied to the gradients dQ and dK).  One thread per VEC consecutive pairs.
 template <typename T, int VEC>
-__global__ __launch_bounds__(256) void rope_kernel(T* __restrict__ X, int64_t ldx,
+__global__ __launch_bounds__(256) void rope_kernel(T* __restrict__ X0, T* __restrict__ X1, int64_t ldx,
                                                    const float* __restrict__ cs,
                                                    const float* __restrict__ sn, int64_t tokens, int seq,
                                                    int heads, int half, float sgn) {
@@ -37,7 +24,7 @@ __global__ __launch_bounds__(256) void rope_kernel(T* __restrict__ X, int64_t ld
   const int r = (int)(i - t * per_tok);
   const int h = r / per_head, j0 = (r - h * per_head) * VEC;
   const int s = (int)(t % seq);
-  T* x1p = X + t * ldx + (int64_t)h * 2 * half + j0;
+  T* x1p = (blockIdx.y ? X1 : X0) + t * ldx + (int64_t)h * 2 * half + j0;
   T* x2p = x1p + half;
   const Vec<T, VEC> a = *(const Vec<T, VEC>*)x1p;
   const Vec<T, VEC> b = *(const Vec<T, VEC>*)x2p;
@@ -143,30 +130,22 @@ hipError_t launch_softmax_rows(bool bf16, const float* S, int64_t lds, void* P, 
   return hipGetLastError();
 }
 
-hipError_t launch_rope_tables(float* cs, float* sn, int seq, int dh, double theta, hipStream_t s) {
-  const int half = dh / 2;
-  const int n = seq * half;
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, s, cs, sn, seq, half, theta);
-  return hipGetLastError();
-}
-
-hipError_t launch_rope(bool bf16, void* X, int64_t ldx, const float* cs, const float* sn, int64_t tokens,
+hipError_t launch_rope(bool bf16, void* X0, void* X1, int64_t ldx, const float* cs, const float* sn, int64_t tokens,
                        int seq, int heads, int dh, bool inverse, hipStream_t s) {
   const float sgn = inverse ? -1.f : 1.f;
   const int half = dh / 2;
   if (tokens == 0 || half == 0) return hipSuccess;
-  auto grid = [&](int vec) { return dim3((unsigned)((tokens * heads * (half / vec) + 255) / 256)); };
+  auto grid = [&](int vec) { return dim3((unsigned)((tokens * heads * (half / vec) + 255) / 256), 2); };
   if (bf16) {
     if (half % 8 == 0 && ldx % 8 == 0)
-      hipLaunchKernelGGL((rope_kernel<__bf16, 8>), grid(8), dim3(256), 0, s, (__bf16*)X, ldx, cs, sn, tokens, seq, heads, half, sgn);
+      hipLaunchKernelGGL((rope_kernel<__bf16, 8>), grid(8), dim3(256), 0, s, (__bf16*)X0, (__bf16*)X1, ldx, cs, sn, tokens, seq, heads, half, sgn);
     else
-      hipLaunchKernelGGL((rope_kernel<__bf16, 1>), grid(1), dim3(256), 0, s, (__bf16*)X, ldx, cs, sn, tokens, seq, heads, half, sgn);
+      hipLaunchKernelGGL((rope_kernel<__bf16, 1>), grid(1), dim3(256), 0, s, (__bf16*)X0, (__bf16*)X1, ldx, cs, sn, tokens, seq, heads, half, sgn);
   } else {
     if (half % 4 == 0 && ldx % 4 == 0)
-      hipLaunchKernelGGL((rope_kernel<float, 4>), grid(4), dim3(256), 0, s, (float*)X, ldx, cs, sn, tokens, seq, heads, half, sgn);
+      hipLaunchKernelGGL((rope_kernel<float, 4>), grid(4), dim3(256), 0, s, (float*)X0, (float*)X1, ldx, cs, sn, tokens, seq, heads, half, sgn);
     else
-      hipLaunchKernelGGL((rope_kernel<float, 1>), grid(1), dim3(256), 0, s, (float*)X, ldx, cs, sn, tokens, seq, heads, half, sgn);
+      hipLaunchKernelGGL((rope_kernel<float, 1>), grid(1), dim3(256), 0, s, (float*)X0, (float*)X1, ldx, cs, sn, tokens, seq, heads, half, sgn);
   }
   return hipGetLastError();
 }

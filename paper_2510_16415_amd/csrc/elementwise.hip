@@ -21,13 +21,27 @@ __device__ inline float wave_sum(float v) {
 // Vector of VEC elements of T, loaded/stored with one instruction when VEC > 1.
 template <typename T, int VEC> struct alignas(sizeof(T) * VEC) Vec { T e[VEC]; };
 
+// One entry per thread, evaluated in fp64 and stored as fp32.
+__device__ inline void rope_table_block(const RopeTables& t, unsigned block) {
+  const int i = block * 256 + threadIdx.x;
+  if (i >= t.seq * t.half) return;
+  const int s = i / t.half, j = i - s * t.half;
+  const double inv = pow(t.theta, -(double)j / (double)t.half);   // 2j / dh with dh = 2 * half
+  const double ang = (double)s * inv;
+  t.cs[i] = (float)cos(ang);
+  t.sn[i] = (float)sin(ang);
+}
+
+// U = norm(H) gamma, a wave per row; the first `table_blocks` workgroups write the rotary tables instead.
 template <typename T, int VEC>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const T* __restrict__ H, int64_t ldh,
                                                           const T* __restrict__ gamma, float eps,
                                                           T* __restrict__ U, int64_t ldu,
-                                                          float* __restrict__ rstd, int64_t b, int d) {
+                                                          float* __restrict__ rstd, int64_t b, int d,
+                                                          RopeTables tables, unsigned table_blocks) {
+  if (blockIdx.x < table_blocks) return rope_table_block(tables, blockIdx.x);
   const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t row = (int64_t)(blockIdx.x - table_blocks) * 4 + (threadIdx.x >> 6);
   if (row >= b) return;
   const T* h = H + row * ldh;
   const int nv = d / VEC;
@@ -57,9 +71,11 @@ template <typename T, int VEC, int ITERS>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_row_kernel(const T* __restrict__ H, int64_t ldh,
                                                               const T* __restrict__ gamma, float eps,
                                                               T* __restrict__ U, int64_t ldu,
-                                                              float* __restrict__ rstd, int64_t b, int d) {
+                                                              float* __restrict__ rstd, int64_t b, int d,
+                                                              RopeTables tables, unsigned table_blocks) {
+  if (blockIdx.x < table_blocks) return rope_table_block(tables, blockIdx.x);
   const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t row = (int64_t)(blockIdx.x - table_blocks) * 4 + (threadIdx.x >> 6);
   if (row >= b) return;
   const T* h = H + row * ldh;
   const int nv = d / VEC;
@@ -601,20 +617,22 @@ template <typename F> void dispatch_iters(int nv, F&& f) {
 }  // namespace
 
 hipError_t launch_rmsnorm_fwd(bool bf16, const void* H, int64_t ldh, const void* gamma, float eps, void* U,
-                              int64_t ldu, float* rstd, int64_t b, int d, hipStream_t s) {
-  const unsigned grid = (unsigned)((b + 3) / 4);
+                              int64_t ldu, float* rstd, int64_t b, int d, hipStream_t s,
+                              const RopeTables* tables) {
+  const RopeTables t = tables ? *tables : RopeTables{};
+  const unsigned nt = rope_table_blocks(t), grid = nt + (unsigned)((b + 3) / 4);
   if (bf16 && row_fits(d, ldh, ldu, ldu, ldu)) {
     auto go = [&](auto iters) {
       hipLaunchKernelGGL((rmsnorm_fwd_row_kernel<__bf16, 8, decltype(iters)::value>), dim3(grid), dim3(256), 0, s,
-                         (const __bf16*)H, ldh, (const __bf16*)gamma, eps, (__bf16*)U, ldu, rstd, b, d);
+                         (const __bf16*)H, ldh, (const __bf16*)gamma, eps, (__bf16*)U, ldu, rstd, b, d, t, nt);
     };
     dispatch_iters(d / 8, go);
   } else if (bf16)
     hipLaunchKernelGGL((rmsnorm_fwd_kernel<__bf16, 8>), dim3(grid), dim3(256), 0, s, (const __bf16*)H, ldh,
-                       (const __bf16*)gamma, eps, (__bf16*)U, ldu, rstd, b, d);
+                       (const __bf16*)gamma, eps, (__bf16*)U, ldu, rstd, b, d, t, nt);
   else
     hipLaunchKernelGGL((rmsnorm_fwd_kernel<float, 1>), dim3(grid), dim3(256), 0, s, (const float*)H, ldh,
-                       (const float*)gamma, eps, (float*)U, ldu, rstd, b, d);
+                       (const float*)gamma, eps, (float*)U, ldu, rstd, b, d, t, nt);
   return hipGetLastError();
 }
 

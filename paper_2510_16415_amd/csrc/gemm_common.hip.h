@@ -123,7 +123,7 @@ inline unsigned add_side(KArgs& args, GemmLaunch& g, int kind, int threads) {
   return (unsigned)((g.side.rows + threads / 64 - 1) / (threads / 64));
 }
 constexpr int side_kind(bool akc, bool bkc, int epi) {
-  return akc && bkc && epi == EPI_GRAD ? SIDE_DGAMMA : akc && !bkc && epi == EPI_STORE ? SIDE_NORM : SIDE_NONE;
+  return akc == bkc && epi == EPI_GRAD ? SIDE_DGAMMA : akc && !bkc && epi == EPI_STORE ? SIDE_NORM : SIDE_NONE;
 }
 
 // The hardware hands consecutive workgroup ids to the 8 XCDs round-robin.  Renumber so

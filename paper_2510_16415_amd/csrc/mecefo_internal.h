@@ -69,7 +69,7 @@ struct GemmProblem {
 // Small work of another kind that goes out in the same launch, on workgroups behind those of the products.
 enum Side : int {
   SIDE_NONE = 0,
-  SIDE_DGAMMA = 1,   // gain gradient from the norm backward's sums (launch_dgamma_reduce): with EPI_GRAD, both K-contiguous
+  SIDE_DGAMMA = 1,   // gain gradient from the norm backward's sums (launch_dgamma_reduce): with EPI_GRAD, both operands K-contiguous or neither
   SIDE_NORM = 2,     // norm recompute (launch_rmsnorm_fwd): with EPI_STORE, B K-strided
 };
 struct SideJob {
@@ -148,8 +148,15 @@ void f32_plan_parts(GemmLaunch& g, int64_t room);   // cuts the problem with rea
 bool f32_far(const GemmLaunch& g);
 
 // Elementwise / reduction kernels (elementwise.hip).  `bf16` selects the storage type.
+// cos / sin of position * theta^(-2j/dh) for every position < seq and j < half = dh / 2.
+struct RopeTables { float* cs; float* sn; int seq, half; double theta; };
+inline unsigned rope_table_blocks(const RopeTables& t) { return (unsigned)((t.seq * t.half + 255) / 256); }
+
+// `tables`: written by workgroups of their own in the same launch (4 us and a launch gap less than in one of their own:
+// their blocks spend it on fp64 powers and sines that wait for no memory), or NULL.
 hipError_t launch_rmsnorm_fwd(bool bf16, const void* H, int64_t ldh, const void* gamma, float eps,
-                              void* U, int64_t ldu, float* rstd, int64_t b, int d, hipStream_t s);
+                              void* U, int64_t ldu, float* rstd, int64_t b, int d, hipStream_t s,
+                              const RopeTables* tables = nullptr);
 // dX = dOut + rmsnorm_backward(dU); sums of the gain gradient over groups of rows go to dg_partial [nblk x d], of which
 // the launch says how many there are (rmsnorm_bwd_blocks, or more where dg_room, in floats, has space for them).  dU: in
 // the storage type (parts 0), or the sum of `parts` fp32 products [b x lddu], part_stride elements apart
@@ -181,9 +188,8 @@ hipError_t launch_swiglu_bwd(bool bf16, const void* G, const void* Z, int64_t ld
 
 
 // Attention helpers (attention.hip).
-hipError_t launch_rope_tables(float* cs, float* sn, int seq, int dh, double theta, hipStream_t s);
-// In-place rotary rotation of a token-major [tokens x heads*dh] tensor (inverse: the transpose, for gradients).
-hipError_t launch_rope(bool bf16, void* X, int64_t ldx, const float* cs, const float* sn, int64_t tokens,
+// In-place rotary rotation of two token-major [tokens x heads*dh] tensors (inverse: the transpose, for gradients).
+hipError_t launch_rope(bool bf16, void* X0, void* X1, int64_t ldx, const float* cs, const float* sn, int64_t tokens,
                        int seq, int heads, int dh, bool inverse, hipStream_t s);
 // Causal row softmax of `nprod` fp32 score matrices [seq x lds]: P (storage type) and the log-sum-exp L.
 hipError_t launch_softmax_rows(bool bf16, const float* S, int64_t lds, void* P, int64_t ldp, float* L, int nprod,
