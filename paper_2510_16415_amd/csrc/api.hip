@@ -366,26 +366,34 @@ mecefo_status_t recompute(const Ctx& c, const Bufs& bf, const void* U, int64_t l
   void* DG = base + bf.w.DG; void* DZ = base + bf.w.DZ; void* AA = base + bf.w.AA;
   const int b = (int)c.b;
   if (b == 0) return MECEFO_OK;
-  bool norm_done;
-  {  // dA = dY Wd   [b x f], K = d
-    STAGE(MECEFO_STAGE_DGRAD_DOWN, s);
-    GemmLaunch g = new_launch(c, true, false, EPI_STORE);
-    g.nprob = 1;
-    g.p[0] = prob(dY, nullptr, lddy, Wd, nullptr, d.ld_w_df, DG, nullptr, nullptr, c.ldf, b, c.ff, c.dm, 1);
-    if (norm) g.side = *norm;
-    HIP_TRY(launch_gemm(g, s));
-    norm_done = g.side_done;
+  GemmLaunch down = new_launch(c, true, false, EPI_STORE);      // dA = dY Wd   [b x f], K = d
+  down.nprob = 1;
+  down.p[0] = prob(dY, nullptr, lddy, Wd, nullptr, d.ld_w_df, DG, nullptr, nullptr, c.ldf, b, c.ff, c.dm, 1);
+  GemmLaunch rec = new_launch(c, true, true, EPI_SWIGLU_BWD);   // G = U Wg^T, Z = U Wu^T, the SwiGLU backward in the epilogue
+  rec.nprob = 1;
+  rec.p[0] = prob(U, nullptr, ldu, Wg, Wu, d.ld_w_fd, DG, DZ, AA, c.ldf, b, c.ff, c.dm, 1, (int)c.ldf);
+  // (a norm recompute that rides on dA saves a launch as well)
+  const int pair = c.bf16 && !Gsaved && !norm ? gemm_bf16_pair_tile(down, rec) : -1;
+  if (pair >= 0) {
+    STAGE(MECEFO_STAGE_RECOMPUTE, s);
+    rec.clk = nullptr;
+    HIP_TRY(launch_gemm_bf16_pair(down, rec, pair, s));
+    return MECEFO_OK;
   }
-  if (norm && !norm_done) TRY(norm_forward(c, *norm, s));
+  {
+    STAGE(MECEFO_STAGE_DGRAD_DOWN, s);
+    down.clk = g_prof.cur_clk;
+    if (norm) down.side = *norm;
+    HIP_TRY(launch_gemm(down, s));
+  }
+  if (norm && !down.side_done) TRY(norm_forward(c, *norm, s));
   if (Gsaved) {
     STAGE(MECEFO_STAGE_SWIGLU_BWD, s);
     HIP_TRY(launch_swiglu_bwd(c.bf16, Gsaved, Zsaved, d.ld_act_f, DG, DZ, AA, c.ldf, c.b, c.ff, (int)c.ldf, s));
-  } else {  // G = U Wg^T, Z = U Wu^T with the SwiGLU backward fused into the epilogue
+  } else {
     STAGE(MECEFO_STAGE_RECOMPUTE, s);
-    GemmLaunch g = new_launch(c, true, true, EPI_SWIGLU_BWD);
-    g.nprob = 1;
-    g.p[0] = prob(U, nullptr, ldu, Wg, Wu, d.ld_w_fd, DG, DZ, AA, c.ldf, b, c.ff, c.dm, 1, (int)c.ldf);
-    HIP_TRY(launch_gemm(g, s));
+    rec.clk = g_prof.cur_clk;
+    HIP_TRY(launch_gemm(rec, s));
   }
   return MECEFO_OK;
 }
@@ -1165,7 +1173,7 @@ mecefo_status_t mecefo_block_bwd_full(const mecefo_ffn_desc_t* desc, const mecef
     }
   }
   // dWq, dWk, dWv = (dQ, dK, dV)^T Xn and dWo = dH^T O, all [d x d], K = tokens: one launch fills the chip where three and
-  // one leave parts of it idle (2048 tokens, d 2048: 256 tiles of 256 x 256, WGRAD4_MEASURED).
+  // one leave parts of it idle (2048 tokens, d 2048: 256 tiles of 256 x 256, 82 us instead of 71 and 34).
   auto wgrads = [&](const SideJob& side) -> mecefo_status_t {
     STAGE(MECEFO_STAGE_QKV_WGRAD, s);
     GemmLaunch g = new_launch(c, false, false, EPI_GRAD);

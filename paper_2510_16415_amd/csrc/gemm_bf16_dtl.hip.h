@@ -554,6 +554,24 @@ __global__ __launch_bounds__(Pipe::THREADS, 2) void gemm_bf16_dtl_kernel(const K
   clock.stop(head);
 }
 
+// The recompute with the SwiGLU backward (problem 0, dual) and the dA = dY Wd (problem 1) that its epilogue reads, tile by
+// tile in one workgroup: a launch less for calls of few tiles.  dA goes through memory as between the two launches, from
+// and to the same lane; its tile has the recompute's rows and half its columns, in waves that hold the same elements.
+// K = d is a multiple of 8 in both.
+template <class C1, class P1, class C2, class P2>
+__global__ __launch_bounds__(P2::THREADS, 2) void gemm_bf16_pair_kernel(const KArgs args) {
+  static_assert(P1::THREADS == P2::THREADS && P1::LDS_BYTES <= P2::LDS_BYTES && C1::BM == C2::BM && 2 * C1::BN == C2::BN &&
+                C1::WAVES_M == C2::WAVES_M && C1::WAVES_N == C2::WAVES_N, "the same outputs");
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+  const KHead head = load_head();
+  const KProblem kp = load_problem(0), kd = load_problem(1);
+  const TileCoord tc = map_tile<C1::BM, C1::BN>(head, kp, 0, xcd_remap(blockIdx.x, head.total));
+  const int m0 = tc.tm * C1::BM, n0 = tc.tn * C1::BN;
+  dtl_tile<C1, P1, true, false, EPI_STORE, false, false>(head, product_view<2>(head, kd, 0), m0, n0, 0, smem);
+  __syncthreads();      // the second product fills the LDS that the first one's epilogue reads
+  dtl_tile<C2, P2, true, true, EPI_SWIGLU_BWD, false, false>(head, product_view<2>(head, kp, 0), m0, n0, 0, smem);
+}
+
 // Launches whose 256 x 256 tiles leave a last round of at most 128: the workgroups of the full rounds compute such
 // tiles (Cfg), and the last round's tiles are shared out over the chip in halves, quarters or sixteenths (C2, C4, C16),
 // which walk K two to six times as fast.  head.total counts the workgroups of the full rounds, the tail's tiles are the

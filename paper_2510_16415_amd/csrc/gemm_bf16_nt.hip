@@ -31,6 +31,54 @@ static hipError_t run_rope(GemmLaunch& g, hipStream_t s) {
     default: return hipErrorInvalidValue;
   }
 }
+template <class C2, class P2> struct PairKernel {
+  using C1 = TileCfg<C2::BM, C2::BN / 2, C2::WAVES_M, C2::WAVES_N>;
+  using P1 = DtlPipe<C1, P2::NS, P2::KG>;
+  static hipError_t prepare() {
+    static LdsLimitOnce limit;
+    return limit.ensure((const void*)gemm_bf16_pair_kernel<C1, P1, C2, P2>, P2::LDS_BYTES);
+  }
+  static hipError_t run(const GemmLaunch& dA, const GemmLaunch& rec, hipStream_t s) {
+    KArgs a, b;
+    fill_kargs(a, rec, C1::BM, C1::BN, kBK);
+    fill_kargs(b, dA, C1::BM, C1::BN, kBK);
+    a.p[1] = b.p[0];
+    if (a.h.total == 0) return hipSuccess;
+    const hipError_t e = prepare();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((gemm_bf16_pair_kernel<C1, P1, C2, P2>), dim3(a.h.total), dim3(P2::THREADS), P2::LDS_BYTES, s, a);
+    return hipGetLastError();
+  }
+};
+// FFN backwards with two launches and with one, us, [tokens x d], f: [16 x 256], 128: 23.6 / 20.1; [129 x 512], 200: 23.2 /
+// 20.7; [256 x 1024], 1000: 37.1 / 35.0; [512 x 512], 1024: 34.3 / 31.4; [1024 x 1024], 1024: 47.9 / 47.3; [2048 x 512], 1376:
+// 61.8 / 56.0; but [128 x 1024], 1024: 28.6 / 28.9 and [777 x 768], 700: 36.0 / 36.1, where 64 x 64 tiles walk what 32 x 32
+// ones would share out, and larger layers fill the chip twice: they keep two, and what the model sees as a gain below 1.4 us.
+int gemm_bf16_pair_tile(const GemmLaunch& dA, const GemmLaunch& rec) {
+  if (bf16_forced_tile() >= 0) return -1;
+  float apart, first;
+  bf16_best_tile(dA, &first);
+  bf16_best_tile(rec, &apart);
+  apart += first;
+  // its stages move half the columns of B: three quarters of the recompute's bytes
+  GemmLaunch both = rec;
+  both.p[0].K += dA.p[0].K / 4 * 3;
+  int best = -1;
+  for (int c : {TILE_M2, TILE_M4, TILE_T, TILE_T2}) {
+    const float t = bf16_tile_cost(both, c) + 1.4f;
+    if (t < apart) { apart = t; best = c; }
+  }
+  return best;
+}
+hipError_t launch_gemm_bf16_pair(const GemmLaunch& dA, const GemmLaunch& rec, int tile, hipStream_t s) {
+  switch (tile) {
+    case TILE_M2: return PairKernel<CfgM, PipeM2>::run(dA, rec, s);
+    case TILE_M4: return PairKernel<CfgM8, PipeM4>::run(dA, rec, s);
+    case TILE_T: return PairKernel<CfgT, PipeT>::run(dA, rec, s);
+    case TILE_T2: return PairKernel<CfgT, PipeT2>::run(dA, rec, s);
+    default: return hipErrorInvalidValue;
+  }
+}
 hipError_t launch_gemm_bf16_nt(GemmLaunch& g, hipStream_t s) {
   switch (g.epi) {
     case EPI_STORE: return run_bf16_auto<true, true, EPI_STORE>(g, s);
@@ -57,6 +105,10 @@ hipError_t prepare_gemm_bf16_nt() {
   if (e == hipSuccess) e = prepare_bf16<true, true, EPI_POLY>();
   if (e == hipSuccess) e = prepare_bf16<true, true, EPI_HILO>();
   if (e == hipSuccess) e = prepare_bf16<true, true, EPI_RESID>();
+  if (e == hipSuccess) e = PairKernel<CfgM, PipeM2>::prepare();
+  if (e == hipSuccess) e = PairKernel<CfgM8, PipeM4>::prepare();
+  if (e == hipSuccess) e = PairKernel<CfgT, PipeT>::prepare();
+  if (e == hipSuccess) e = PairKernel<CfgT, PipeT2>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgL8, true, true, EPI_ROPE, PipeL, false>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgM, true, true, EPI_ROPE, PipeM2, true>::prepare();
   if (e == hipSuccess) e = Bf16Kernel<CfgM8, true, true, EPI_ROPE, PipeM4, true>::prepare();

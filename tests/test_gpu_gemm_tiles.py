@@ -172,3 +172,11 @@ def test_f32_projection_whose_tile_rows_span_more_than_32_bits(ld, side):
         out.append(g)
     for x, y in zip(*out):
         assert torch.equal(x, y)
+
+
+# dA and the recompute in one launch: 64 x 64 tiles with two groups of waves and with one, 128 x 128 tiles on four waves
+# and on eight, with rows, columns and contractions that end inside a tile
+@pytest.mark.parametrize("b,d,f", [(16, 256, 128), (65, 520, 201), (37, 72, 15), (306, 552, 1899), (534, 24, 4481),
+                                   (2047, 520, 1371), (2078, 1016, 594), (3835, 712, 369)])
+def test_backward_products_with_the_recompute_in_one_launch(b, d, f):
+    check_exact_backward(b, d, f)
