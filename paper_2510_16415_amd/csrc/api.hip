@@ -372,9 +372,10 @@ mecefo_status_t recompute(const Ctx& c, const Bufs& bf, const void* U, int64_t l
   GemmLaunch rec = new_launch(c, true, true, EPI_SWIGLU_BWD);   // G = U Wg^T, Z = U Wu^T, the SwiGLU backward in the epilogue
   rec.nprob = 1;
   rec.p[0] = prob(U, nullptr, ldu, Wg, Wu, d.ld_w_fd, DG, DZ, AA, c.ldf, b, c.ff, c.dm, 1, (int)c.ldf);
-  // (a norm recompute that rides on dA saves a launch as well)
-  const int pair = c.bf16 && !Gsaved && !norm ? gemm_bf16_pair_tile(down, rec) : -1;
+  // a norm recompute that would ride on dA is a launch of its own then
+  const int pair = c.bf16 && !Gsaved ? gemm_bf16_pair_tile(down, rec, norm ? 3.2f : 0.f) : -1;
   if (pair >= 0) {
+    if (norm) TRY(norm_forward(c, *norm, s));
     STAGE(MECEFO_STAGE_RECOMPUTE, s);
     rec.clk = nullptr;
     HIP_TRY(launch_gemm_bf16_pair(down, rec, pair, s));

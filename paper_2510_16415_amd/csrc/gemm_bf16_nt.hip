@@ -51,22 +51,25 @@ template <class C2, class P2> struct PairKernel {
   }
 };
 // FFN backwards with two launches and with one, us, [tokens x d], f: [16 x 256], 128: 23.6 / 20.1; [129 x 512], 200: 23.2 /
-// 20.7; [256 x 1024], 1000: 37.1 / 35.0; [512 x 512], 1024: 34.3 / 31.4; [1024 x 1024], 1024: 47.9 / 47.3; [2048 x 512], 1376:
-// 61.8 / 56.0; but [128 x 1024], 1024: 28.6 / 28.9 and [777 x 768], 700: 36.0 / 36.1, where 64 x 64 tiles walk what 32 x 32
-// ones would share out, and larger layers fill the chip twice: they keep two, and what the model sees as a gain below 1.4 us.
-int gemm_bf16_pair_tile(const GemmLaunch& dA, const GemmLaunch& rec) {
+// 20.7; [256 x 1024], 1000: 37.1 / 35.0; [777 x 768], 700: 35.3 / 32.4; [2048 x 512], 1376: 61.8 / 55.6; [1024 x 1024], 2736: 87.7
+// / 82.7; [4096 x 1024], 1024: 89.1 / 84.6: the one launch takes 2 to 5 us less than the model says, on 64 x 64 tiles 0
+// to 2.  Not so where the two
+// go out on 32 x 32 tiles, with twice as many workgroups to share out K ([128 x 1024], 1024: 28.6 / 28.9), or on ones of 192 and
+// 256 rows, which take fewer bytes ([2048 x 1024], 2736: 120.5 / 126.4; [2048 x 768], 2050: 92.2 / 95.7).
+int gemm_bf16_pair_tile(const GemmLaunch& dA, const GemmLaunch& rec, float cost) {
   if (bf16_forced_tile() >= 0) return -1;
-  float apart, first;
-  bf16_best_tile(dA, &first);
-  bf16_best_tile(rec, &apart);
-  apart += first;
-  // its stages move half the columns of B: three quarters of the recompute's bytes
+  float t1, t2;
+  const int c1 = bf16_best_tile(dA, &t1), c2 = bf16_best_tile(rec, &t2);
+  auto same = [](int c) { return c == TILE_M2 || c == TILE_M4 || c == TILE_T || c == TILE_T2; };
+  const bool alike = same(c1) && same(c2);
+  // the first product's stages move half the columns of B: three quarters of the recompute's bytes
   GemmLaunch both = rec;
   both.p[0].K += dA.p[0].K / 4 * 3;
+  float t = t1 + t2;
   int best = -1;
   for (int c : {TILE_M2, TILE_M4, TILE_T, TILE_T2}) {
-    const float t = bf16_tile_cost(both, c) + 1.4f;
-    if (t < apart) { apart = t; best = c; }
+    const float x = bf16_tile_cost(both, c) + cost + (!alike ? 1.4f : c == TILE_M2 || c == TILE_M4 ? -2.f : 0.5f);
+    if (x < t) { t = x; best = c; }
   }
   return best;
 }

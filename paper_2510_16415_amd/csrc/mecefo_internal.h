@@ -137,8 +137,8 @@ hipError_t prepare_gemm_f32();
 // The configuration with which the bf16 launch (NT layout) carries EPI_ROPE for heads of dimension dh; -1: none.
 int gemm_bf16_rope_tile(const GemmLaunch& g, int dh);
 // The tile on which dA = dY Wd and the recompute whose epilogue reads it (one bf16 product each) go out as one launch, -1
-// where two are shorter.
-int gemm_bf16_pair_tile(const GemmLaunch& dA, const GemmLaunch& rec);
+// where two are shorter.  cost: us that the one launch costs besides.
+int gemm_bf16_pair_tile(const GemmLaunch& dA, const GemmLaunch& rec, float cost);
 hipError_t launch_gemm_bf16_pair(const GemmLaunch& dA, const GemmLaunch& rec, int tile, hipStream_t s);
 hipError_t prepare_attention_fwd();
 hipError_t prepare_attention_bwd();
