@@ -1,11 +1,11 @@
 // bf16 MFMA GEMM for gfx950 with direct-to-LDS operand staging.
 //
-// One workgroup computes a 256 x 256 (eight wavefronts of 64 x 128), 128 x 128 (four of 64 x 64 with two LDS
-// stages, or eight of 32 x 64 with four) or 64 x 64 output tile (four of 32 x 32, or two groups of four that share out
-// K), or 32 x 32 (eight waves that share out K, each with buffers of its own).  Two differences to gemm_bf16.hip.h.  The products run on v_mfma_f32_16x16x32_bf16: on Gaussian operands a
-// loop of nothing but MFMAs is power-limited, and this shape moves half the accumulator bytes per multiply-add
-// of the 32x32x16 one -- 2100 TFLOP/s at 2.1 GHz on random operands against 1860 at 1.83 GHz.  And the operand
-// tiles never pass through registers:
+// One workgroup computes a tile of 256 x 256 (eight wavefronts of 64 x 128), 192 x 256 (eight of 96 x 64), 128 x 128 (four of
+// 64 x 64 with two LDS stages, or eight of 32 x 64 with four), 64 x 64 (four of 32 x 32, or two groups of four that share
+// out K) or 32 x 32 (eight waves that share out K, each with buffers of its own).  Two differences to
+// gemm_bf16.hip.h.  The products run on v_mfma_f32_16x16x32_bf16: on Gaussian operands a loop of nothing but MFMAs is
+// power-limited, and this shape moves half the accumulator bytes per multiply-add of the 32x32x16 one -- 2100 TFLOP/s
+// at 2.1 GHz on random operands against 1860 at 1.83 GHz.  And the operand tiles never pass through registers:
 // `buffer_load_dwordx4 ... lds` writes 1 KiB per wavefront instruction straight into LDS
 // (lane i lands at base + 16 i).  K is cut into stages of BK (32 or 64) held in a ring of NS
 // LDS buffers; a buffer is refilled as soon as the barrier that ends its last use has passed,
