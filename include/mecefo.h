@@ -366,24 +366,24 @@ mecefo_status_t mecefo_block_bwd_skip_ex(const mecefo_ffn_desc_t* desc, const vo
 typedef enum {
   MECEFO_STAGE_NORM_FWD = 0,       /* RMSNorm recompute from the stored tensor               */
   MECEFO_STAGE_DGRAD_DOWN = 1,     /* dA = dY Wd                                             */
-  MECEFO_STAGE_RECOMPUTE = 2,      /* G, Z = U Wg^T, U Wu^T with fused SwiGLU backward       */
+  MECEFO_STAGE_RECOMPUTE = 2,      /* G, Z = U Wg^T, U Wu^T with fused SwiGLU backward (small calls: and dA, in one launch) */
   MECEFO_STAGE_SWIGLU_BWD = 3,     /* standalone SwiGLU backward (saved activations given)   */
-  MECEFO_STAGE_DGRAD_GATE_UP = 4,  /* dU = dG Wg + dZ Wu                                     */
+  MECEFO_STAGE_DGRAD_GATE_UP = 4,  /* dU = dG Wg + dZ Wu (small calls: and T = X P, in one launch) */
   MECEFO_STAGE_PROJECT = 5,        /* Eq. (2): T = X P (three matrices, one launch)          */
   MECEFO_STAGE_CONTRACT = 6,       /* Eq. (2): C = Gy^T T over tokens                        */
-  MECEFO_STAGE_SPLITK_REDUCE = 7,  /* sum of the split partials of C                         */
-  MECEFO_STAGE_EXPAND = 8,         /* Eq. (2): dW = C P^T                                    */
-  MECEFO_STAGE_NORM_BWD = 9,       /* dX = dOut + normbwd(dU), dgamma                        */
+  MECEFO_STAGE_SPLITK_REDUCE = 7,  /* not used: the sum of cut products counts as part of their stage */
+  MECEFO_STAGE_EXPAND = 8,         /* Eq. (2): dW = C P^T, and the sum of dgamma             */
+  MECEFO_STAGE_NORM_BWD = 9,       /* dX = dOut + normbwd(dU), sums for dgamma               */
   MECEFO_STAGE_WGRAD_EXACT = 10,   /* exact dW = Gy^T X (comparator)                         */
-  MECEFO_STAGE_ATTN_OUT_BWD = 11,  /* dWo = dH^T O and dO = dH Wo                             */
+  MECEFO_STAGE_ATTN_OUT_BWD = 11,  /* dO = dH Wo                                             */
   MECEFO_STAGE_ATTN_ROWDOT = 12,   /* D = rowsum(dO * O)                                     */
   MECEFO_STAGE_ATTN_PROBS = 13,    /* P = exp(scale Q K^T - L), causal                       */
   MECEFO_STAGE_ATTN_DV = 14,       /* dV = P^T dO                                            */
   MECEFO_STAGE_ATTN_DS = 15,       /* dS = P * (dO V^T - D) * scale                          */
   MECEFO_STAGE_ATTN_DQ = 16,       /* dQ = dS K                                              */
   MECEFO_STAGE_ATTN_DK = 17,       /* dK = dS^T Q                                            */
-  MECEFO_STAGE_ROPE_BWD = 18,      /* inverse rotation of dQ, dK (and the angle tables)      */
-  MECEFO_STAGE_QKV_WGRAD = 19,     /* dWq, dWk, dWv = (dQ, dK, dV)^T Xn                      */
+  MECEFO_STAGE_ROPE_BWD = 18,      /* inverse rotation of dQ, dK                             */
+  MECEFO_STAGE_QKV_WGRAD = 19,     /* dWq, dWk, dWv = (dQ, dK, dV)^T Xn, dWo = dH^T O        */
   MECEFO_STAGE_QKV_DGRAD = 20,     /* dXn = dQ Wq + dK Wk + dV Wv                            */
   MECEFO_STAGE_ATTN_FUSED_KV = 21, /* dK, dV and dS in one kernel (P kept in registers)      */
   MECEFO_STAGE_COUNT = 22
