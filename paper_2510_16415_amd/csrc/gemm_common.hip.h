@@ -42,7 +42,7 @@ struct KHead {
   int batch, batch_inner, causal, rope_seq;
   float scale, poly_a, poly_b;
   int tail;                // launches that cut up their last round: problem, log2 of the parts of a tile, first tile;
-                           // EPI_POLY, EPI_HILO: fold_norm
+                           // EPI_HILO: fold_norm
   uint32_t* clk;           // measurement (NULL otherwise): every 64th workgroup stores its shader-clock cycles and
                            // its 100 MHz wall ticks, pair number (workgroup / 64) % 64
   const float* rowvec;
@@ -355,30 +355,17 @@ template <int EPI> constexpr bool kUnhandledEpilogue = false;
 
 // 1 / sqrt of a squared norm; a zero matrix is left unchanged.
 __device__ inline float inv_norm(float sq) { return sq > 0.f ? 1.0f / sqrtf(sq) : 1.0f; }
-// From the kNormBlocks partial sums of a squared norm, and from the trace of a Gram matrix; every wave for itself, in a
-// fixed order.
-__device__ inline float inv_norm_of_partials(const float* partial, int lane) {
+// From the norms of the kNormBlocks parts of a matrix; every wave for itself, in a fixed order.
+__device__ inline float inv_norm_of_parts(const float* norms, int lane) {
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < kNormBlocks / 64; ++i) s += partial[64 * i + lane];
+  for (int i = 0; i < kNormBlocks / 64; ++i) s += norms[64 * i + lane] * norms[64 * i + lane];
   return inv_norm(wave_total(s));
 }
-__device__ inline float inv_norm_of_gram(const float* gram, int64_t ld, int n, int lane) {
-  float s = 0.f;
-#pragma unroll 8
-  for (int i = lane; i < n; i += 64) s += gram[i * (ld + 1)];
-  return inv_norm(wave_total(s));
-}
-// The norm that an epilogue folds into its coefficients (EPI_POLY) or its result (EPI_HILO, through poly_a).
+// The norm that the epilogue EPI_HILO divides its result by, through poly_a.
 template <int EPI>
 __device__ inline void fold_norm(GemmProblem& p, int lane) {
-  if (EPI == EPI_POLY && p.fold_norm) {
-    const float k = inv_norm_of_gram(p.addend, p.ldc, p.N, lane), k2 = k * k;
-    p.poly_a *= k;
-    p.poly_b *= k * k2;
-    p.scale *= k * k2 * k2;
-  }
-  if (EPI == EPI_HILO) p.poly_a = p.fold_norm ? inv_norm_of_partials(p.rowvec, lane) : 1.f;
+  if (EPI == EPI_HILO) p.poly_a = p.fold_norm ? inv_norm_of_parts(p.rowvec, lane) : 1.f;
 }
 
 // One output element (single products) or one (gate, up) pair (dual products).

@@ -15,16 +15,15 @@ enum Epilogue : int {
   EPI_ATTN_P = 5,      // C0[row, col] = col <= row ? exp(scale * acc - rowvec[row]) : 0   (softmax from saved logsumexp)
   EPI_ATTN_DS = 6,     // C0[row, col] = C0[row, col] * (acc - rowvec[row]) * scale         (softmax backward, in place on P)
   EPI_POLY = 7,        // C0[row, col] = poly_a * (row == col) + poly_b * addend[row, col] + scale * acc; C1 (fp32) = acc
-                       // fold_norm (bf16): the polynomial in addend / t, over sqrt(t), t the trace of addend
   EPI_HILO = 8,        // x = acc + addend[row, col]: C0 (fp32) = x, C1 = bf16(x), C2 = bf16(x - C1); C0 and C2 may be NULL
-                       // fold_norm (bf16): x = acc / sqrt(sum of the kNormBlocks values of rowvec)
+                       // fold_norm (bf16): x = acc / (norm of a matrix whose kNormBlocks parts have the norms in rowvec)
   EPI_RESID = 9,       // C0[row, col] = acc + C1[row, col]   (activation dtype; C1 may be C0)
   EPI_ROPE = 10,       // C0 = acc rotated: pairs (j, j + rope_half) of every head by the angle of position row % rope_seq
 };
 
 constexpr int kMaxProblems = 4;   // of one launch
 constexpr int kCUs = 256;         // compute units of the chip
-constexpr int kNormBlocks = 256;  // partial sums of a squared norm
+constexpr int kNormBlocks = 256;  // parts of a matrix whose norms are taken first
 
 enum CausalK : int {
   CAUSAL_NONE = 0,
@@ -60,7 +59,7 @@ struct GemmProblem {
   float scale;           // attention epilogues, EPI_POLY
   const float* addend;   // EPI_POLY, EPI_HILO: fp32 [M x ldc], may be NULL (zero); may be C0 of EPI_HILO itself
   float poly_a, poly_b;  // EPI_POLY
-  bool fold_norm;        // EPI_POLY, EPI_HILO: see there
+  bool fold_norm;        // EPI_HILO: see there
   int rope_half, rope_seq;   // EPI_ROPE: half the head dimension (0: plain store) and the sequence length; rowvec and
                              // addend are the cosine and sine tables [rope_seq][rope_half]
   int causal;            // CausalK

@@ -39,18 +39,12 @@ struct SplitSum {
   __bf16 *hi, *lo;         // EPI_HILO: the two halves; EPI_POLY: hi is the polynomial
   const float* addend;
   float a, b, c;           // EPI_POLY
-  const float* norm;       // EPI_HILO: partial sums of the squared norm to divide by, or NULL
-  int fold, n;             // EPI_POLY: fold_norm and the order of the matrix
+  const float* norm;       // EPI_HILO: the norms of the parts of the matrix whose norm it divides by, or NULL
 };
 template <int EPI>
-__global__ __launch_bounds__(256) void split_sum_kernel(SplitSum q) {
-  const int lane = threadIdx.x & 63;
+__global__ __launch_bounds__(256) void split_sum_kernel(const SplitSum q) {
   float k = 1.f;
-  if (EPI == EPI_HILO && q.norm) k = inv_norm_of_partials(q.norm, lane);
-  if (EPI == EPI_POLY && q.fold) {
-    k = inv_norm_of_gram(q.addend, q.ld, q.n, lane);
-    q.a *= k; q.b *= k * k * k; q.c *= k * (k * k) * (k * k);
-  }
+  if (EPI == EPI_HILO && q.norm) k = inv_norm_of_parts(q.norm, threadIdx.x & 63);
   const int64_t i4 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;     // mn is a multiple of 8
   if (i4 >= q.mn) return;
   typedef __attribute__((ext_vector_type(4))) float f4;
@@ -78,20 +72,22 @@ __global__ __launch_bounds__(256) void split_sum_kernel(SplitSum q) {
   }
 }
 
-// Block b sums rows b, b + gridDim.x, ... in a fixed order, thread t the groups of four columns t, t + 256, ...
-// and the rows four at a time, so that four loads are in flight (one scalar load after another: 8.5 us for
-// [5461 x 512]; the refresh with nine of them went from 2435 to 2377 us).
+// The Frobenius norm of the part of X that a block has, in norms[block].  Block b sums rows b, b + gridDim.x, ... in a
+// fixed order, thread t the groups of four columns t, t + 256, ... and the rows four at a time, so that four loads are in
+// flight (one scalar load after another: 8.5 us for [5461 x 512]; the refresh with nine of them went from 2435 to 2377 us).
+// The squares are summed in 64 bits: those of W^T W X are fourth powers of W's scale, which leave fp32's range for weights
+// below 1e-10 and above 1e9; the norms themselves are as far inside it as X is.
 template <typename T>
-__global__ __launch_bounds__(256) void sumsq_partial_kernel(const T* __restrict__ X, int64_t ld, int64_t rows,
-                                                            int cols, float* __restrict__ partial) {
-  __shared__ float red[256];
+__global__ __launch_bounds__(256) void norm_parts_kernel(const T* __restrict__ X, int64_t ld, int64_t rows,
+                                                         int cols, float* __restrict__ norms) {
+  __shared__ double red[256];
   typedef __attribute__((ext_vector_type(4))) T t4;
   // columns [cols, ld) hold anything: groups of four that reach behind `cols` are cut off element by element
   const int groups = (cols + 3) / 4;
   // a block row is wide enough for `lanes` groups; the other threads take further rows of the block
   const int lanes = groups < 256 ? groups : 256, per = 256 / lanes;
   const int sub = threadIdx.x / lanes, lane = threadIdx.x - sub * lanes;
-  float acc = 0.f;
+  double acc = 0.0;
   if (sub < per) {
     const int64_t step = (int64_t)gridDim.x * per;
     for (int64_t row0 = (int64_t)blockIdx.x * per + sub; row0 < rows; row0 += 4 * step)
@@ -106,7 +102,7 @@ __global__ __launch_bounds__(256) void sumsq_partial_kernel(const T* __restrict_
         for (int q = 0; q < 4; ++q)
           if (row0 + q * step < rows) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc += 4 * g + e < cols ? (float)v[q][e] * (float)v[q][e] : 0.f;
+            for (int e = 0; e < 4; ++e) acc += 4 * g + e < cols ? (double)(float)v[q][e] * (double)(float)v[q][e] : 0.0;
           }
       }
   }
@@ -116,29 +112,29 @@ __global__ __launch_bounds__(256) void sumsq_partial_kernel(const T* __restrict_
     if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
     __syncthreads();
   }
-  if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) norms[blockIdx.x] = (float)sqrt(red[0]);
 }
 
-// X *= 1 / sqrt(sum of the partial sums); a zero matrix is left unchanged.  Every block adds the kNormBlocks
-// partial sums by itself, as a tree over its threads (one thread adding them one by one took 12 to 20 us).
-// With hi the halves of the result go out as well (X is a multiple of four elements: padded rows).
+// X / |X| from the norms of its parts; a zero matrix is left unchanged.  Every block adds the kNormBlocks squares by
+// itself, as a tree over its threads (one thread adding them one by one took 12 to 20 us).  The result goes back to X
+// (keep) and, with hi, out as halves (X is a multiple of four elements: padded rows).
 __global__ __launch_bounds__(256) void scale_by_inv_norm_kernel(float* __restrict__ X, int64_t n,
-                                                                const float* __restrict__ partial,
+                                                                const float* __restrict__ norms, bool keep,
                                                                 __bf16* __restrict__ hi, __bf16* __restrict__ lo) {
-  __shared__ float red[256];
-  static_assert(kNormBlocks == 256, "one partial sum per thread");
-  red[threadIdx.x] = partial[threadIdx.x];
+  __shared__ double red[256];
+  static_assert(kNormBlocks == 256, "one norm per thread");
+  red[threadIdx.x] = (double)norms[threadIdx.x] * (double)norms[threadIdx.x];
   __syncthreads();
   for (int o = 128; o > 0; o >>= 1) {
     if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
     __syncthreads();
   }
-  const float k = inv_norm(red[0]);
+  const float k = red[0] > 0.0 ? (float)(1.0 / sqrt(red[0])) : 1.f;
   typedef __attribute__((ext_vector_type(4))) float f4;
   typedef __attribute__((ext_vector_type(4))) __bf16 h4;
   for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; i < n; i += (int64_t)gridDim.x * 1024) {
     const f4 x = *(const f4*)(X + i) * k;
-    *(f4*)(X + i) = x;
+    if (keep) *(f4*)(X + i) = x;
     if (!hi) continue;
     h4 h, l;
 #pragma unroll
@@ -247,7 +243,7 @@ hipError_t run_product(const Plan& pl, char* base, GemmLaunch& g, hipStream_t s)
   }
   const dim3 grid((unsigned)((mn + 1023) / 1024));
   SplitSum q{partial, splits, mn, p.ldc, nullptr, nullptr, nullptr, p.addend, p.poly_a, p.poly_b, p.scale,
-             p.fold_norm ? p.rowvec : nullptr, p.fold_norm, p.N};
+             p.fold_norm ? p.rowvec : nullptr};
   if (epi == EPI_POLY) {
     q.raw = (float*)p.C[1]; q.hi = (__bf16*)p.C[0];
     hipLaunchKernelGGL(split_sum_kernel<EPI_POLY>, grid, dim3(256), 0, s, q);
@@ -286,21 +282,22 @@ struct Refresh {
     g.p[0].addend = addend; g.p[0].poly_a = a; g.p[0].poly_b = b; g.p[0].scale = c;
   }
 
-  hipError_t normalise() const {  // X /= ||X||_F, so that every singular value is <= 1
+  // X /= ||X||_F, so that every singular value is <= 1.  keep32: the bf16 path keeps the fp32 copy as well as the halves
+  hipError_t normalise(bool keep32) const {
     float* part = (float*)(base + pl.part);
     const int64_t n = (int64_t)pl.dim * pl.ldx;
-    hipLaunchKernelGGL(sumsq_partial_kernel<float>, dim3(kNormBlocks), dim3(256), 0, s, X32(), pl.ldx, (int64_t)pl.dim, pl.r, part);
+    hipLaunchKernelGGL(norm_parts_kernel<float>, dim3(kNormBlocks), dim3(256), 0, s, X32(), pl.ldx, (int64_t)pl.dim, pl.r, part);
     hipLaunchKernelGGL(scale_by_inv_norm_kernel, dim3((unsigned)(n < 1024 * 1024 ? (n + 1023) / 1024 : 1024)), dim3(256), 0, s, X32(), n, part,
+                       keep32 || !pl.bf16,
                        (__bf16*)(pl.bf16 ? base + pl.Xh[cur] : nullptr), (__bf16*)(pl.bf16 ? base + pl.Xl[cur] : nullptr));
     return hipGetLastError();
   }
 
   // One Newton-Schulz step X <- X (a I + b A + c A^2), A = X^T X; `additive` (c == 0): X <- X + X E
   // with E = (a - 1) I + b A.  A, A^2 and the polynomial only shape the conditioning and are taken
-  // in the storage type; the product with X keeps the split operand.  The fp32 master copy of the result is written when
-  // it will be read (keep32); `fold`: X is not normalised yet, the polynomial takes A / tr A for A and is divided by
-  // sqrt(tr A), tr A = |X|_F^2.  out: where the bf16 half hi goes instead of the workspace (the result's last step).
-  mecefo_status_t ns_step(float a, float b, float c, bool additive, bool keep32, bool fold = false, void* out = nullptr) {
+  // in the storage type; the product with X keeps the split operand.  The fp32 copy of the result is written when it
+  // will be read (keep32).  out: where the bf16 half hi goes instead of the workspace (the result's last step).
+  mecefo_status_t ns_step(float a, float b, float c, bool additive, bool keep32, void* out) {
     const int r = pl.r, dim = pl.dim;
     float* A32 = (float*)(base + pl.A32);
     void* M16 = base + pl.M16;
@@ -315,7 +312,6 @@ struct Refresh {
     if (!additive) {  // a I + b A + c A^2, A^2 = A A^T (A is symmetric)
       GemmLaunch g = product(pl, true, true, A16, nullptr, pl.ldx, A16, nullptr, pl.ldx, nullptr, r, r, r);
       to_poly(g, M16, nullptr, A32, a, b, c);
-      g.p[0].fold_norm = fold;
       HIP_TRY(run_product(pl, base, g, s));
     }
     // the polynomial of the symmetric A is symmetric: X M = X M^T, so M is the K-contiguous operand
@@ -330,19 +326,18 @@ struct Refresh {
   // Quintic steps with slope 3.4445 at zero: a small singular value grows by that factor per step,
   // values near 1 stay within about [0.7, 1.2] (the odd quintic used for low-precision
   // orthogonalisation; it does not converge to exactly 1, the cubic steps do).
-  mecefo_status_t condition(int steps, bool normalised, bool keep32, void* out) {
+  mecefo_status_t condition(int steps, bool keep32, void* out) {
     for (int i = 0; i < steps; ++i) {
       const bool last = i == steps - 1;
-      mecefo_status_t e = ns_step(3.4445f, -4.7750f, 2.0315f, false, last && keep32, i == 0 && !normalised, last ? out : nullptr);
+      mecefo_status_t e = ns_step(3.4445f, -4.7750f, 2.0315f, false, last && keep32, last ? out : nullptr);
       if (e != MECEFO_OK) return e;
     }
     return MECEFO_OK;
   }
 
-  // X <- W^T (W X).  start: the start basis in the caller's memory (bf16), which Y takes over 1 / its norm (`part` holds
-  // the partial sums), else NULL.  halves: the result goes out as bf16 halves, to be normalised by the first
-  // conditioning step; else as fp32, to be normalised next.
-  mecefo_status_t power_round(const void* W, int64_t ldw, int left, const void* start, int64_t ldstart, bool halves) {
+  // X <- W^T (W X), in fp32, to be normalised next.  start: the start basis in the caller's memory (bf16), which Y takes
+  // over 1 / its norm (`part` holds the norms of its parts), else NULL.
+  mecefo_status_t power_round(const void* W, int64_t ldw, int left, const void* start, int64_t ldstart) {
     const int m = pl.m, n = pl.n, r = pl.r;
     const Operand x = start ? Operand{start, nullptr} : opX();
     const int64_t ldx = start ? ldstart : pl.ldx;
@@ -356,7 +351,6 @@ struct Refresh {
     const Operand y = opY();
     GemmLaunch g2 = left ? product(pl, true, false, W, nullptr, ldw, y.hi, y.lo, pl.ldx, X32_next(), m, r, n)
                          : product(pl, false, false, W, nullptr, ldw, y.hi, y.lo, pl.ldx, X32_next(), n, r, m);
-    if (halves) to_iterate(g2, nullptr, pl.Xh[cur ^ 1], pl.Xl[cur ^ 1], nullptr);
     HIP_TRY(run_product(pl, base, g2, s));
     cur ^= 1;
     return MECEFO_OK;
@@ -417,39 +411,39 @@ mecefo_status_t mecefo_projection_refresh(mecefo_dtype_t dtype, const void* W, i
   const int64_t ldx = pl.ldx;
   const unsigned gx = grid_for((int64_t)dim * ldx);
 
-  // bf16: the start basis is an operand of the first product where it lies (its rows keep 16-byte alignment), the norm of
-  // a power round's result is folded into the first conditioning step, and the last step writes P where its rows have no padding.  Three matrices of
-  // [5461 x 2048], rank 512: 18 launches and the second K segment of the first products fewer.
+  // bf16: the start basis is an operand of the first product where it lies (its rows keep 16-byte alignment), and the last
+  // step writes P where its rows have no padding.
   const bool direct = bf16 && power_iters > 0 && ldv % 8 == 0;
-  const bool fold = bf16 && cond_steps > 0;
   void* const out = bf16 && ldp == ldx && r == ldx && (polish_steps > 0 || cond_steps > 0) ? P : nullptr;
   if (direct) {
-    hipLaunchKernelGGL(sumsq_partial_kernel<__bf16>, dim3(kNormBlocks), dim3(256), 0, R.s, (const __bf16*)V0, ldv, (int64_t)dim, r, (float*)(R.base + pl.part));
+    hipLaunchKernelGGL(norm_parts_kernel<__bf16>, dim3(kNormBlocks), dim3(256), 0, R.s, (const __bf16*)V0, ldv, (int64_t)dim, r, (float*)(R.base + pl.part));
     HIP_TRY(hipGetLastError());
   } else {
     // start basis -> fp32 master copy (padding columns zeroed: they are contracted as K padding)
     if (bf16) hipLaunchKernelGGL((convert2d_kernel<float, __bf16>), dim3(gx), dim3(256), 0, R.s, R.X32(), ldx, (const __bf16*)V0, ldv, (int64_t)dim, r, (int)ldx);
     else hipLaunchKernelGGL((convert2d_kernel<float, float>), dim3(gx), dim3(256), 0, R.s, R.X32(), ldx, (const float*)V0, ldv, (int64_t)dim, r, (int)ldx);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(R.normalise());
+    HIP_TRY(R.normalise(power_iters == 0 && cond_steps == 0));
   }
   // The start basis is only normalised: a previous projection is orthonormal already and Gaussian
   // noise is well conditioned; without power rounds it is conditioned for the polishing steps.
   if (power_iters == 0) {
-    st = R.condition(cond_steps, true, polish_steps > 0 || !out, polish_steps == 0 ? out : nullptr);
+    st = R.condition(cond_steps, polish_steps > 0 || !out, polish_steps == 0 ? out : nullptr);
     if (st != MECEFO_OK) return st;
   }
   for (int it = 0; it < power_iters; ++it) {
     const bool last = it == power_iters - 1;
-    st = R.power_round(W, ldw, left, direct && it == 0 ? V0 : nullptr, ldv, fold);
+    st = R.power_round(W, ldw, left, direct && it == 0 ? V0 : nullptr, ldv);
     if (st != MECEFO_OK) return st;
-    if (!fold) HIP_TRY(R.normalise());
-    st = R.condition(cond_steps, !fold, last && (polish_steps > 0 || !out), last && polish_steps == 0 ? out : nullptr);
+    // Before it is split into halves and multiplied with itself: squares and fifth powers of its scale, which is that of
+    // W^T W, would leave fp32's range.  The fp32 copy is read by a first polishing step and by the conversion to P.
+    HIP_TRY(R.normalise(last && cond_steps == 0));
+    st = R.condition(cond_steps, last && (polish_steps > 0 || !out), last && polish_steps == 0 ? out : nullptr);
     if (st != MECEFO_OK) return st;
   }
   for (int i = 0; i < polish_steps; ++i) {  // cubic steps X <- X + X (I - X^T X) / 2
     const bool last = i == polish_steps - 1;
-    st = R.ns_step(1.5f, -0.5f, 0.f, true, !last || !out, false, last ? out : nullptr);
+    st = R.ns_step(1.5f, -0.5f, 0.f, true, !last || !out, last ? out : nullptr);
     if (st != MECEFO_OK) return st;
   }
   if (out) return MECEFO_OK;

@@ -9,9 +9,9 @@ pytestmark = pytest.mark.gpu
 M, N, R = 700, 384, 40
 
 
-def refresh(V0, ldv, ldp, r, left=0, iters=2, cond=8, polish=3, in_place=False, scale=1.0):
+def refresh(V0, ldv, ldp, r, left=0, iters=2, cond=8, polish=3, in_place=False, scale=1.0, wscale=1.0):
     gen = torch.Generator(device="cuda").manual_seed(5)
-    W = (torch.randn(M, N, generator=gen, device="cuda") * 0.02).to(torch.bfloat16)
+    W = (torch.randn(M, N, generator=gen, device="cuda") * 0.02).to(torch.bfloat16) * wscale
     dim = M if left else N
     V = torch.full((dim, ldv), float("nan"), dtype=torch.bfloat16, device="cuda")
     V[:, :r] = (V0[:dim, :r].float() * scale).to(torch.bfloat16)
@@ -42,6 +42,17 @@ def test_where_the_result_goes_does_not_change_it(r, cond, polish, left):
 def test_the_scale_of_the_start_basis_does_not_matter(scale):
     V0 = start(R)
     assert torch.equal(refresh(V0, 40, 40, R, scale=scale), refresh(V0, 40, 40, R))
+
+
+@pytest.mark.parametrize("left", [0, 1])
+@pytest.mark.parametrize("cond,polish", [(8, 3), (8, 0), (0, 3)])
+@pytest.mark.parametrize("wscale", [2.0 ** -40, 2.0 ** -20, 2.0 ** 20, 2.0 ** 40])
+def test_the_scale_of_the_weights_does_not_matter(wscale, cond, polish, left):
+    """A power of two in W is one in W^T W X, which its norm takes out again: the same bits, for weights near 1e-14 (a
+    down projection that started at zero) as for weights near 1e10."""
+    V0 = start(R)
+    assert torch.equal(refresh(V0, 40, 40, R, left, cond=cond, polish=polish, wscale=wscale),
+                       refresh(V0, 40, 40, R, left, cond=cond, polish=polish))
 
 
 @pytest.mark.parametrize("left", [0, 1])
