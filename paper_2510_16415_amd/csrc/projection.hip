@@ -411,9 +411,10 @@ mecefo_status_t mecefo_projection_refresh(mecefo_dtype_t dtype, const void* W, i
   const int64_t ldx = pl.ldx;
   const unsigned gx = grid_for((int64_t)dim * ldx);
 
-  // bf16: the start basis is an operand of the first product where it lies (its rows keep 16-byte alignment), and the last
-  // step writes P where its rows have no padding.
-  const bool direct = bf16 && power_iters > 0 && ldv % 8 == 0;
+  // bf16: the start basis is an operand of the first product where it lies (its rows keep 16-byte alignment, and the
+  // product's 32-bit offsets reach all of them), and the last step writes P where its rows have no padding.
+  const bool reached = dim == 1 || ldv <= (0x7FFFFFFF / 2 - r) / (dim - 1);
+  const bool direct = bf16 && power_iters > 0 && ldv % 8 == 0 && reached;
   void* const out = bf16 && ldp == ldx && r == ldx && (polish_steps > 0 || cond_steps > 0) ? P : nullptr;
   if (direct) {
     hipLaunchKernelGGL(norm_parts_kernel<__bf16>, dim3(kNormBlocks), dim3(256), 0, R.s, (const __bf16*)V0, ldv, (int64_t)dim, r, (float*)(R.base + pl.part));

@@ -80,3 +80,21 @@ def test_without_power_rounds(cond, polish):
 def test_a_zero_matrix_gives_finite_results():
     V0 = torch.zeros(M, R, dtype=torch.bfloat16, device="cuda")
     assert bool((refresh(V0, 40, 40, R) == 0).all())
+
+
+def test_a_start_basis_whose_rows_lie_far_apart():
+    """48 rows that span 2 GiB, further than a product's 32-bit offsets reach: converted first, like rows of 41 elements."""
+    dim, r, ldv = 48, 40, 22900000
+    rows = start(r)[:dim]
+    flat = torch.empty((dim - 1) * ldv + r, dtype=torch.bfloat16, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    W = torch.randn(200, dim, generator=gen, device="cuda").to(torch.bfloat16)
+    out = []
+    for V0, ld in ((flat.as_strided((dim, r), (ldv, 1)), ldv), (torch.empty(dim, r + 1, dtype=torch.bfloat16, device="cuda")[:, :r], r + 1)):
+        V0.copy_(rows)
+        ws = torch.full((B.mecefo_projection_workspace_bytes(B.BF16, 200, dim, r, 0),), 255, dtype=torch.uint8, device="cuda")
+        P = torch.empty(dim, r, dtype=torch.bfloat16, device="cuda")
+        B.mecefo_projection_refresh(B.BF16, W, 200, dim, dim, 0, V0, ld, r, 2, 8, 3, P, r, ws)
+        torch.cuda.synchronize()
+        out.append(P)
+    assert torch.equal(*out)
