@@ -109,6 +109,13 @@ inline bool bf16_ragged(const GemmLaunch& g) {
   return false;
 }
 
+// Whether the launch may go out on the 192-row tile.  Not a causal product whose contraction ends at the diagonal: its first
+// operand (probabilities, dS) is written up to the end of the 256-block of the diagonal, and a tile with rows of two such
+// blocks would read on, behind that, for the rows of the first.
+inline bool bf16_takes_k(const GemmLaunch& g, bool ragged) {
+  return has_tile_k(g.a_kcontig, g.b_kcontig, g.epi) && !ragged && g.p[0].causal != CAUSAL_K_UPTO_M;
+}
+
 // The last round of a launch on 256 x 256 tiles, when it holds at most 128 of them: each takes a CU the length of K at
 // 1.75 us a stage while half the chip and more is idle.  Cut into halves, quarters or sixteenths the same tiles go to all
 // CUs, which walk K at 1.0, 0.72 or 0.45 us a stage; whatever takes the least time, `saved` us less than the whole ones.
@@ -219,7 +226,7 @@ inline int bf16_best_tile(const GemmLaunch& g, float* cost = nullptr, float boun
   float t = bound;
   for (int c = 0; c < TILE_COUNT; ++c) {
     if (c == TILE_X && !has_tile_x(g.epi)) continue;
-    if (c == TILE_K && (ragged || !has_tile_k(g.a_kcontig, g.b_kcontig, g.epi))) continue;
+    if (c == TILE_K && !bf16_takes_k(g, ragged)) continue;
     // with a ragged K the groups of waves meet one more barrier per stage: a third of what they save
     const float x = bf16_tile_cost(g, c, st, t) + (c == TILE_T2 && ragged ? 0.05f * st.longest : 0.f);
     if (x < t) { t = x; best = c; }
@@ -387,7 +394,7 @@ hipError_t run_bf16_auto(GemmLaunch& g, hipStream_t stream) {
         if (c == TILE_X) return run_bf16<CfgX, AKC, BKC, EPI, PipeX>(g, stream);
       }
       if constexpr (has_tile_k(AKC, BKC, EPI)) {
-        if (c == TILE_K && !bf16_ragged(g)) return run_bf16<CfgK, AKC, BKC, EPI, PipeK, false>(g, stream);
+        if (c == TILE_K && bf16_takes_k(g, bf16_ragged(g))) return run_bf16<CfgK, AKC, BKC, EPI, PipeK, false>(g, stream);
       }
       if constexpr (has_tail(AKC, BKC, EPI)) {
         const TailPlan plan = bf16_tail(g);

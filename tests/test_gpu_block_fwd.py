@@ -60,7 +60,7 @@ def test_block_fwd_bf16_ragged(batch, seq, d, f, heads, pad):
     print(run_fwd(22, batch, seq, d, f, heads, "bf16", pad=pad)[-1])
 
 
-@pytest.mark.parametrize("tile", ["S", "S4", "T", "T2", "L8R", "L8"])
+@pytest.mark.parametrize("tile", ["S", "S4", "T", "T2", "X", "K", "LT", "L8R", "L8"])
 def test_block_fwd_bf16_forced_tiles_cross_the_diagonal(tile, mecefo_option):
     mecefo_option("tile", tile)
     print(tile, run_fwd(23, 2, 523, 256, 344, 2, "bf16")[-1])
@@ -75,11 +75,12 @@ def test_block_fwd_bf16_fused_attention_shapes(batch, seq, d, heads, pad):
     print(run_fwd(29, batch, seq, d, 200, heads, "bf16", pad=pad)[-1])
 
 
-@pytest.mark.parametrize("tile", ["S", "S4", "T", "T2", "L8"])
+@pytest.mark.parametrize("tile", ["S", "S4", "T", "T2", "X", "K", "LT", "L8"])
 def test_block_fwd_bf16_materialised_scores_on_every_tile(tile, mecefo_option):
     mecefo_option("attention", "gemm")
     mecefo_option("tile", tile)
     print(tile, run_fwd(31, 2, 523, 256, 344, 2, "bf16")[-1])
+    print(tile, run_fwd(33, 1, 520, 256, 344, 2, "bf16")[-1])      # a contraction that the 192-row tile takes
 
 
 @pytest.mark.parametrize("batch,seq,d,heads", [(2, 523, 256, 2), (1, 768, 256, 4)])

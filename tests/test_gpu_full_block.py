@@ -109,7 +109,7 @@ def test_full_block_bf16_ragged(batch, seq, d, f, heads):
     print(errs)
 
 
-@pytest.mark.parametrize("tile", ["S", "S4", "T", "T2", "L4", "L8R", "L8"])
+@pytest.mark.parametrize("tile", ["S", "S4", "T", "T2", "X", "K", "LT", "L4", "L8R", "L8"])
 def test_full_block_bf16_forced_tiles_cross_the_diagonal(tile, mecefo_option):
     """Sequences longer than two tiles of every configuration, so that the causal clipping of the
     K loops and the skipped tiles above the diagonal are exercised; seq is not a multiple of 8."""
@@ -134,7 +134,7 @@ def test_full_block_bf16_five_product_attention_path(batch, seq, d, heads, mecef
     print(errs)
 
 
-@pytest.mark.parametrize("tile", ["S", "S4", "T", "T2", "L8"])
+@pytest.mark.parametrize("tile", ["S", "S4", "T", "T2", "X", "K", "LT", "L8"])
 def test_full_block_bf16_five_product_attention_on_every_tile(tile, mecefo_option):
     """The softmax products, whose epilogues and causal clipping know the tile: seq ends inside every tile and, odd,
     inside a 16-byte chunk of the contraction."""
@@ -142,6 +142,13 @@ def test_full_block_bf16_five_product_attention_on_every_tile(tile, mecefo_optio
     mecefo_option("tile", tile)
     _, _, errs = run_case(10, 2, 523, 256, 344, 2, "bf16")
     print(tile, errs)
+    print(tile, run_case(14, 1, 520, 256, 344, 2, "bf16")[-1])      # a contraction that the 192-row tile takes
+
+
+def test_full_block_bf16_head_dimension_beyond_the_fused_kernels():
+    """96 products of [320 x 320] by [320 x 192], for which the 192-row tile would be the shortest: its second row of tiles
+    has rows on both sides of 256, where the written part of dS ends in two places."""
+    print(run_case(13, 24, 320, 768, 64, 4, "bf16")[-1])
 
 
 def test_full_block_accumulate_alias_and_bf16_grads():
