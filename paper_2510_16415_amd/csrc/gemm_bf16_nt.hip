@@ -10,18 +10,22 @@ namespace mecefo {
 // d = 512, 2048 tokens, whose 64 x 64 and 128 x 128 tiles are a tie: 1201 -> 1183 us).  Forwards with no allowance and
 // with no limit against this one, us: 64 tokens, two heads of 64: 38.9 / 33.4 against 33.5; 256 tokens, eight of 64:
 // 48.6 / 50.9 against 50.9 (the one where it costs); 2048 tokens, eight of 64: 63.0 / 61.5 against 61.5; 256 tokens, four
-// of 128: 48.3 / 60.3 against 48.3; 512 tokens, sixteen of 128: 141 / 173 against 141; larger ones are equal.
+// of 128: 48.3 / 60.3 against 48.3; 512 tokens, sixteen of 128: 141 / 173 against 141.  On large ones the rotation launch
+// takes more (16 us for [3584 x 3584]), but the model of the tiles is no better than that either: with an allowance of
+// 5 + 1.1e-6 b d, which follows the launch, [3072 x 2048] with heads of 64 takes 191 us instead of 181, the others the same.
 int gemm_bf16_rope_tile(const GemmLaunch& g, int dh) {
   const int forced = bf16_forced_tile();
   if (forced >= 0)
     return (forced == TILE_L && (dh == 64 || dh == 128)) || (dh == 64 && (forced == TILE_M2 || forced == TILE_M4)) ? forced : -1;
   if (dh != 64 && dh != 128) return -1;
+  GemmLaunch rot = g;      // costed as what would go out: a launch that rotates has no last round that is cut up
+  rot.epi = EPI_ROPE;
   int best = TILE_L;
   for (int c : {TILE_M2, TILE_M4})
-    if (dh == 64 && bf16_tile_cost(g, c) < bf16_tile_cost(g, best)) best = c;
+    if (dh == 64 && bf16_tile_cost(rot, c) < bf16_tile_cost(rot, best)) best = c;
   float least;
   bf16_best_tile(g, &least);
-  return bf16_tile_cost(g, best) <= least + 6.f ? best : -1;
+  return bf16_tile_cost(rot, best) <= least + 6.f ? best : -1;
 }
 static hipError_t run_rope(GemmLaunch& g, hipStream_t s) {
   switch (g.tile) {

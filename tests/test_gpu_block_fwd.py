@@ -91,6 +91,12 @@ def test_block_fwd_bf16_materialised_scores_path(batch, seq, d, heads, mecefo_op
     print(run_fwd(30, batch, seq, d, 344, heads, "bf16")[-1])
 
 
+@pytest.mark.parametrize("heads", [8, 16])
+def test_block_fwd_bf16_last_round_of_the_qkv_products(heads):
+    """264 tiles of 256 x 256 for Q, K and V, 8 more than the CUs: cut up with the rotation behind, or on tiles that rotate."""
+    print(run_fwd(34, 22, 256, 1024, 64, heads, "bf16")[-1])
+
+
 def test_fused_attention_random_shapes_forward_then_backward():
     """Seeded sweep over sequence lengths, batch sizes, head counts and both fused head dimensions: the
     forward on the GPU, then the standard-mode backward fed with the tensors that forward kept, each
