@@ -142,19 +142,21 @@ struct Profiler {
 
 struct StageTimer {
   hipStream_t s;
+  size_t at = 0;      // first event of the pair, this stage's from here on
   bool active;
   StageTimer(int stage, hipStream_t stream) : s(stream), active(false) {
     if (g_prof.on && g_prof.used + 2 <= g_prof.ev.size()) {
       active = true;
-      g_prof.stage[g_prof.used / 2] = stage;
-      g_prof.cur_clk = g_prof.clk ? g_prof.clk + (g_prof.used / 2) * kClkPairs * 2 : nullptr;
-      (void)hipEventRecord(g_prof.ev[g_prof.used], s);
+      at = g_prof.used;
+      g_prof.used += 2;
+      g_prof.stage[at / 2] = stage;
+      g_prof.cur_clk = g_prof.clk ? g_prof.clk + (at / 2) * kClkPairs * 2 : nullptr;
+      (void)hipEventRecord(g_prof.ev[at], s);
     }
   }
   ~StageTimer() {
     if (active) {
-      (void)hipEventRecord(g_prof.ev[g_prof.used + 1], s);
-      g_prof.used += 2;
+      (void)hipEventRecord(g_prof.ev[at + 1], s);
       g_prof.cur_clk = nullptr;
     }
   }
@@ -1072,18 +1074,19 @@ mecefo_status_t mecefo_block_bwd_full(const mecefo_ffn_desc_t* desc, const mecef
   TRY(dgrad(c, bf, in->Wg, in->Wu, dUb, dm, s, any && norm_bwd_reads_parts(c, bf, ffn_norm()) ? &parts : nullptr));
   SideJob later = {};   // the sums of the gain gradients ride on the weight gradients' launches
   TRY(norm_backward(c, ffn_norm(), out->dg_ffn, accumulate, s, &later));
+  GemmLaunch g = new_launch(c, false, false, EPI_GRAD);
   {
     STAGE(MECEFO_STAGE_WGRAD_EXACT, s);
-    GemmLaunch g = new_launch(c, false, false, EPI_GRAD);
     g.nprob = 3;
     g.accumulate = accumulate;
     g.side = later;
+    g.clk = g_prof.cur_clk;
     g.p[0] = prob(base + fw.DG, nullptr, c.ldf, Ub, nullptr, dm, out->dWg, nullptr, nullptr, d.ld_w_fd, c.ff, dm, b, 1);
     g.p[1] = prob(base + fw.DZ, nullptr, c.ldf, Ub, nullptr, dm, out->dWu, nullptr, nullptr, d.ld_w_fd, c.ff, dm, b, 1);
     g.p[2] = prob(in->dOut, nullptr, d.ld_act_d, base + fw.AA, nullptr, c.ldf, out->dWd, nullptr, nullptr, d.ld_w_df, dm, c.ff, b, 1);
     HIP_TRY(launch_gemm(g, s));
-    TRY(dgamma_left(c, g, s));
   }
+  TRY(dgamma_left(c, g, s));
 
   // ---- attention module
   if (any) {
@@ -1176,7 +1179,6 @@ mecefo_status_t mecefo_block_bwd_full(const mecefo_ffn_desc_t* desc, const mecef
   // dWq, dWk, dWv = (dQ, dK, dV)^T Xn and dWo = dH^T O, all [d x d], K = tokens: one launch fills the chip where three and
   // one leave parts of it idle (2048 tokens, d 2048: 256 tiles of 256 x 256, 82 us instead of 71 and 34).
   auto wgrads = [&](const SideJob& side) -> mecefo_status_t {
-    STAGE(MECEFO_STAGE_QKV_WGRAD, s);
     GemmLaunch g = new_launch(c, false, false, EPI_GRAD);
     g.nprob = 4;
     g.accumulate = accumulate;
@@ -1186,7 +1188,11 @@ mecefo_status_t mecefo_block_bwd_full(const mecefo_ffn_desc_t* desc, const mecef
     for (int i = 0; i < 3; ++i)
       g.p[i] = prob(src[i], nullptr, dm, Ub, nullptr, dm, dst[i], nullptr, nullptr, a.ld_w_dd, dm, dm, b, 1);
     g.p[3] = prob(dH, nullptr, dm, in->O, nullptr, d.ld_act_d, out->dWo, nullptr, nullptr, a.ld_w_dd, dm, dm, b, 1);
-    HIP_TRY(launch_gemm(g, s));
+    {
+      STAGE(MECEFO_STAGE_QKV_WGRAD, s);
+      g.clk = g_prof.cur_clk;
+      HIP_TRY(launch_gemm(g, s));
+    }
     return dgamma_left(c, g, s);
   };
   // The sum of the gain gradient rides on them, behind the norm backward; a dX that lies over O is written when O was read.

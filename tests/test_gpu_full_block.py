@@ -204,6 +204,24 @@ def test_full_block_matches_skip_plus_attention_branch():
     assert np.linalg.norm(branch - want["dX_branch"]) <= bound
 
 
+@pytest.mark.parametrize("tile,own", [("auto", 0), ("L4", 2)])
+def test_stage_times_of_a_full_backward(tile, own, mecefo_option):
+    """Every stage is timed for itself: the register-staged kernels carry no side jobs, and the sums of the two gain
+    gradients, stages of their own then, follow the weight gradients' launches."""
+    p, X, dOut = make_case(16, 2, 200, 128, 344, 2, "bf16")
+    blk = FullBlock(p, X, dOut, 2, 2, 200, "bf16")
+    blk.run()
+    mecefo_option("tile", tile)
+    B.mecefo_profile_enable(64)
+    blk.run()
+    prof = B.mecefo_profile_collect()
+    once = ("wgrad_exact", "qkv_wgrad", "qkv_dgrad", "attn_out_bwd", "attn_rowdot", "attn_fused_kv", "attn_dq", "rope_bwd",
+            "dgrad_gate_up", "recompute")
+    assert {k: prof[k][1] for k in once} == dict.fromkeys(once, 1), prof
+    assert prof["norm_bwd"][1] == 2 + own, prof
+    assert all(0 < ms < 100 for ms, _ in prof.values()), prof
+
+
 def test_config_c1_full_block():
     cfg = I.CONFIGS["C1"]
     _, _, errs = run_case(11, cfg.batch, cfg.seq, cfg.d_model, cfg.d_ff, cfg.heads, cfg.dtype)
