@@ -88,7 +88,10 @@ typedef struct {
 typedef struct { const void* P; int32_t r; int64_t ld; } mecefo_proj_t;
 
 /* Bytes of workspace that any of the calls below needs for this descriptor and these
- * ranks (pass the largest ranks you will use; 0 if only the non-low-rank calls are used). */
+ * ranks (pass the largest ranks you will use; 0 if only the non-low-rank calls are used).
+ * For d_model up to 2048 and too few tokens to fill the chip they include 16 * tokens * d_model
+ * bytes for fp32 parts of dU, which the norm backward adds up itself.  A workspace without them
+ * is accepted as well: the parts are then summed by a launch of their own. */
 mecefo_status_t mecefo_workspace_bytes(const mecefo_ffn_desc_t* desc, int r_gate, int r_up,
                                        int r_down, size_t* out_bytes);
 
@@ -133,8 +136,8 @@ mecefo_status_t mecefo_block_bwd_skip(const mecefo_ffn_desc_t* desc, const void*
  * capture, tight serving or training loops and harnesses that forbid hipMalloc.  Same arguments and results
  * as mecefo_block_bwd_skip without ws / ws_bytes: the scratch is a buffer of MECEFO_NOALLOC_SCRATCH_BYTES
  * that the library holds in static device memory on every GPU it is loaded on (until the process ends), so
- * the call itself allocates and frees nothing.  Shapes whose workspace (mecefo_workspace_bytes) exceeds that
- * size are rejected with MECEFO_ERR_WORKSPACE_TOO_SMALL before anything is enqueued (64 MiB covers e.g.
+ * the call itself allocates and frees nothing.  Shapes whose workspace (mecefo_workspace_bytes; less the
+ * parts of dU if they do not fit) exceeds that size are rejected with MECEFO_ERR_WORKSPACE_TOO_SMALL before anything is enqueued (64 MiB covers e.g.
  * 2048 tokens at d = 512, f = 1376, r = 128; the 7B-shaped layer needs 0.75 GiB and the caller's own
  * workspace).  All calls on one GPU share that GPU's buffer and it keeps the last call's contents: calls
  * that overlap in time on one GPU (different streams or host threads) race; order them on one stream. */

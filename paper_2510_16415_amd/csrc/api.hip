@@ -235,6 +235,7 @@ int store_splits_project(const Ctx& c, const int r[3], mecefo_side_t side) {   /
 // Parts of dU that the norm backward adds up: where there are any they outlive the token contraction, which has the
 // partial buffer, so they have a buffer of their own.  Workspaces sized without it are taken too (with_parts = false).
 int kept_parts(const Ctx& c) {
+  if (!rmsnorm_bwd_parts_width(c.bf16, c.dm)) return 0;
   if (c.bf16) return store_splits_du(c) > 1 ? kMaxNormParts : 0;
   return (c.b + 31) / 32 * ((c.dm + 31) / 32) <= kCUs / 2 ? kMaxNormParts : 0;
 }

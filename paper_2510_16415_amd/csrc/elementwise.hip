@@ -644,8 +644,8 @@ namespace {
 int rows_kernel_vec(bool bf16, const NormBwd& n) {
   const int v = bf16 ? 8 : 4;
   const uintptr_t bits = (uintptr_t)n.dU | (uintptr_t)n.H | (uintptr_t)n.gamma | (uintptr_t)n.dOut | (uintptr_t)n.dX;
-  const bool aligned = n.d % v == 0 && n.lddu % v == 0 && n.ldh % v == 0 && n.lddo % v == 0 && n.lddx % v == 0 && bits % 16 == 0;
-  if (aligned && n.d <= 2048) return v;
+  const bool aligned = n.lddu % v == 0 && n.ldh % v == 0 && n.lddo % v == 0 && n.lddx % v == 0 && bits % 16 == 0;
+  if (aligned && rmsnorm_bwd_parts_width(bf16, n.d)) return v;
   return !bf16 && n.parts == 0 && n.d <= 512 ? 1 : 0;
 }
 // Rows per wave: few enough for 512 workgroups, as far as there is room for a row of gain-gradient sums from each.

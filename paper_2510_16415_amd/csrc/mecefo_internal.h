@@ -174,6 +174,7 @@ struct NormBwd {
   int64_t b; int d;
 };
 constexpr int kMaxNormParts = 4;
+inline bool rmsnorm_bwd_parts_width(bool bf16, int d) { return d <= 2048 && d % (bf16 ? 8 : 4) == 0; }   // what is built
 bool rmsnorm_bwd_takes_parts(bool bf16, const NormBwd& n);
 hipError_t launch_rmsnorm_bwd(bool bf16, const NormBwd& n, int* nblk, hipStream_t s);
 int rmsnorm_bwd_blocks(int64_t b);

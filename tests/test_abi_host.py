@@ -30,6 +30,15 @@ def test_workspace_bytes_grows_with_the_problem():
     assert big >= 3 * 8192 * 11008 * 2
 
 
+@pytest.mark.parametrize("dtype,b,f,taken,wider", [(B.BF16, 512, 11008, 2048, 2056), (B.F32, 32, 688, 2048, 2052),
+                                                  (B.F32, 64, 688, 512, 513)])
+def test_workspace_keeps_parts_of_du_only_where_the_norm_backward_takes_them(dtype, b, f, taken, wider):
+    """Four fp32 parts of dU, 16 bytes per token and column, up to d = 2048 (and for fp32 whole vectors of four): a wider
+    layer needs less."""
+    small, large = (B.mecefo_workspace_bytes(B.make_desc(b, d, f, dtype), 32, 32, 32) for d in (taken, wider))
+    assert 0 < small - large < 16 * b * taken
+
+
 def _err(fn, *a):
     with pytest.raises(B.MecefoError) as e:
         fn(*a)
