@@ -518,7 +518,10 @@ mecefo_status_t dgrad_and_project(const Ctx& c, const Bufs& bf, const LowRank& q
     both.p[both.nprob++] = alone.p[0];
     alone.nprob = 1;
     // large layers, where the two launches fill the chip by themselves, keep them (1456 us against 1474 for 8192 tokens,
-    // d 4096, f 11008)
+    // d 4096, f 11008).  fp32 always merges: calls with two launches / one, us, [256 x 256], f 688: 42.6 / 36.8;
+    // [1024 x 512], f 1376: 190 / 188; [4096 x 512], f 1376: 488 / 475; [4096 x 1024], f 2752: 1481 / 1467; [2048 x 2048], f 5461:
+    // 2929 / 2929; one of 19 sizes is slower, [2048 x 1024], f 2752, rank 64: 750 / 784, whose dU alone fills two whole rounds of
+    // 64 x 64 tiles (rank 256: 924 / 913).
     const bool merge = c.bf16 ? bf16_plan_splits(both, bf.w.room, bf.w.parts_room) <
                                     0.95f * (bf16_plan_splits(alone, bf.w.room, bf.w.parts_room) +
                                              bf16_plan_splits(project, bf.w.room, 0))

@@ -448,10 +448,6 @@ hipError_t run_f32_cfg(GemmLaunch& g, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// 64 x 64 tiles once they give every CU two workgroups.  Skip backwards with the line at 256 / 1024 / 2048 tiles against
-// 512, us: [1024 x 512], f 1376: 185 / 178 / 178 against 175; [1024 x 1024], f 2752 (688 tiles): 536 / 484 / 484 against
-// 516; [2048 x 512], f 1376 (704): 290 / 272 / 271 against 282; [4096 x 512], f 1376: 451 / 464 / 473 against 452;
-// [4096 x 1024], f 2752: 1515 / 1490 / 1539 against 1487.
 // Whether every operand of the launch can go to LDS in 16-byte pieces: rows (and the products of a batch) that start on
 // 16 bytes, whole pieces along a contiguous K, and less than 2 GiB.
 inline bool f32_direct(const GemmLaunch& g) {
@@ -516,6 +512,18 @@ hipError_t prepare_f32() {
   return e;
 }
 
+// 64 x 64 tiles once they give every CU two workgroups.  Skip backwards of rank d / 4 to d / 8 with the line at 256 / 1024 / 2048
+// tiles against 512, us: [1024 x 512], f 1376: 178 / 166 / 166 against 164; [4096 x 512], f 1376: 476 / 480 / 487 against
+// 477; [4096 x 1024], f 2752: 1457 / 1458 / 1498 against 1457; [8192 x 256], f 688: 271 / 249 / 256 against 256.  Up to 1024 the
+// smaller tiles are ahead where the launches that lie between are most of the call ([1024 x 1024], f 2752: 523 / 440 / 440
+// against 474; [2048 x 512], f 1376: 297 / 262 / 262 against 278), behind where one of them is dU ([4096 x 512] with
+// SIDE_OUTPUT: 476 / 495 / 505 against 476).
+// Below that, 32 x 32 tiles, straight to LDS while the launch gives a CU at most two workgroups: its ring leaves room for one
+// of them (two of short ones), and more of them run one after the other where the kernel with stages in registers has
+// four at a time.  Direct to LDS against it, us: dU of [1024 x 1024], f 2752 (1024 tiles) 175 / 162, its token contraction
+// of rank 256 (1632) 71 / 59, the recompute of [1024 x 512], f 1376 (1376) 52 / 42; but its projections (384) 13.8 / 19.4 and
+// its dU (512) 46 / 49.  Skip backwards with the line at 512 tiles / 1024 / none: [512 x 512], f 1376: 99 / 107 / 107;
+// [1024 x 512], f 1376: 162 / 167 / 189; [1024 x 1024], f 2752: 471 / 478 / 498; [2048 x 512], f 1376: 277 / 277 / 300.
 template <int EPI>
 hipError_t run_f32(GemmLaunch& g, hipStream_t stream) {
   if (f32_far(g)) {
@@ -523,7 +531,7 @@ hipError_t run_f32(GemmLaunch& g, hipStream_t stream) {
     else return hipErrorInvalidValue;
   }
   if (f32_tiles(g, 64) >= 512) return run_f32_cfg<CfgWide, EPI>(g, stream);
-  return f32_direct(g) ? run_f32_direct<EPI>(g, stream) : run_f32_cfg<CfgSmall, EPI>(g, stream);
+  return f32_tiles(g, 32) <= 2 * kCUs && f32_direct(g) ? run_f32_direct<EPI>(g, stream) : run_f32_cfg<CfgSmall, EPI>(g, stream);
 }
 }  // namespace
 

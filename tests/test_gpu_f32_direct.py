@@ -20,7 +20,9 @@ def relerr(got, want):
 
 # stages of 64 K: one, fewer than the ring holds, one more than it holds (dual 5, other 6), many; ragged rows and tokens
 @pytest.mark.parametrize("b,d,f,r", [(1, 4, 4, 1), (33, 36, 68, 5), (64, 64, 32, 32), (130, 324, 388, 12), (257, 388, 452, 31),
-                                     (70, 1000, 1364, 44), (700, 96, 100, 8)])
+                                     (70, 1000, 1364, 44), (700, 96, 100, 8),
+                                     # 512 tiles of dA and of the recompute go straight to LDS, 544 do not
+                                     (512, 64, 1024, 8), (513, 64, 1024, 8)])
 @pytest.mark.parametrize("side", [B.SIDE_INPUT, B.SIDE_OUTPUT])
 def test_both_stagings_give_the_same_sums(b, d, f, r, side):
     up = lambda x: (x + 3) // 4 * 4   # noqa: E731
