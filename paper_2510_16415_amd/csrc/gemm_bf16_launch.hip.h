@@ -119,8 +119,14 @@ inline bool bf16_takes_k(const GemmLaunch& g, bool ragged) {
 // The last round of a launch on 256 x 256 tiles, when it holds at most 128 of them: each takes a CU the length of K at
 // 1.75 us a stage while half the chip and more is idle.  Cut into halves, quarters or sixteenths the same tiles go to all
 // CUs, which walk K at 1.0, 0.72 or 0.45 us a stage; whatever takes the least time, `saved` us less than the whole ones.
+// Gradients with a short K are paced by their stores: there the rounds run into each other, the last one costs less than
+// its length and the kernel that cuts it up 1 to 3 us a round.  Whole / cut up, us, fp32 gradients: expansions of 528 tiles
+// and 8 stages 66.6 / 62.7, 612 and 8: 79 / 86, 600 and 16: 109 / 114, 1152 and 2: 77 / 92, 2064 and 16: 296 / 318; exact
+// gradients of 360 and 16: 71 / 68, 288 and 24: 92 / 76, 1920 and 4: 147 / 156; bf16 ones: 528 and 8: 61.5 / 52,
+// 1152 and 4: 79 / 85, 336 and 16: 61 / 57.  So below 24 stages only with one or two full rounds, and only where what is saved is more than
+// that.  (forced: wherever it is shorter by the stages alone.)
 struct TailPlan { int tiles, shift, prob; float saved; };
-inline TailPlan bf16_tail(const GemmLaunch& g) {
+inline TailPlan bf16_tail(const GemmLaunch& g, bool forced = false) {
   TailPlan plan = {0, 0, 0, 0.f};
   if (!has_tail(g.a_kcontig, g.b_kcontig, g.epi) || bf16_ragged(g)) return plan;
   int total = 0, most = 0;
@@ -134,9 +140,14 @@ inline TailPlan bf16_tail(const GemmLaunch& g) {
   const int rest = total % kCUs;
   if (total < kCUs || rest == 0 || rest > kCUs / 2 || rest >= most || total >= 1 << 24) return plan;
   const float st = (float)bf16_stages(g, 0), rate[3] = {1.0f, 0.72f, 0.45f};
-  const int shift[3] = {1, 2, 4};
+  const int shift[3] = {1, 2, 4}, rounds = total / kCUs;
+  float lost = 0.f;
+  if (g.epi == EPI_GRAD && st < 24.f && !forced) {
+    if (rounds > 2) return plan;
+    lost = g.out_f32 ? 4.f + 0.08f * rest + 1.2f * rounds : 2.f + 0.03f * rest + 0.5f * rounds;
+  }
   for (int k = 0; k < 3; ++k) {
-    const float saved = 4.f + 1.75f * st - cdiv(rest << shift[k], kCUs) * (4.f + rate[k] * st);
+    const float saved = 4.f + 1.75f * st - lost - cdiv(rest << shift[k], kCUs) * (4.f + rate[k] * st);
     if (saved > plan.saved) { plan.saved = saved; plan.shift = shift[k]; plan.tiles = rest; }
   }
   return plan;
@@ -397,7 +408,7 @@ hipError_t run_bf16_auto(GemmLaunch& g, hipStream_t stream) {
         if (c == TILE_K && bf16_takes_k(g, bf16_ragged(g))) return run_bf16<CfgK, AKC, BKC, EPI, PipeK, false>(g, stream);
       }
       if constexpr (has_tail(AKC, BKC, EPI)) {
-        const TailPlan plan = bf16_tail(g);
+        const TailPlan plan = bf16_tail(g, forced == TILE_LT);
         if (plan.saved > 0.f && (forced < 0 || forced == TILE_LT)) return run_bf16_tail<AKC, BKC, EPI>(g, plan, stream);
       }
       if (bf16_ragged(g)) return run_bf16<CfgL8, AKC, BKC, EPI, PipeL, AKC || BKC>(g, stream);

@@ -1,0 +1,46 @@
+"""What the model of the GEMM tiles chooses, over the sizes of layers and against times measured on the chip.  No GPU: the
+planning functions of the library run on the host."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2510_16415_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+GRAD, SWIGLU_BWD, STORE = 2, 4, 0
+K_TILE = 5
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc) or not os.path.exists(build.LIB):
+        pytest.skip("needs hipcc and the built library")
+    exe = str(tmp_path_factory.mktemp("rules") / "tile_rules")
+    r = subprocess.run([hipcc, "-x", "hip", *build.FLAGS[:1], "--offload-host-only", "-O1", "-std=c++17", "-I", build.CSRC,
+                        os.path.join(HERE, "tile_rules.cpp"), "-x", "none", build.LIB, "-Wl,-rpath," + build.LIBDIR,
+                        "-o", exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return lambda *a: [line.split() for line in subprocess.run([exe, *(str(int(x)) if not isinstance(x, str) else x for x in a)],
+                                                               capture_output=True, text=True, check=True).stdout.splitlines()]
+
+
+def test_a_rotating_launch_is_never_much_longer_than_one_without(rules):
+    rows = rules("rope")
+    assert len(rows) == 2 * 32 * 29
+    # the allowance for the rotation's own launch is 6 us
+    late = [r for r in rows if float(r[4]) > float(r[5]) + 6.01]
+    assert not late, f"{len(late)} of {len(rows)}: {late[:5]}"
+    assert {int(r[3]) for r in rows} >= {-1, 0, 1}      # a launch of its own, 256 x 256 and 128 x 128 tiles are all taken
+
+
+# us of three expansions [f x d] of rank r with a whole last round and with one that is cut up, measured
+@pytest.mark.parametrize("f,d,r,f32,whole,cut", [(11008, 4096, 1024, 1, 296, 318), (8192, 3072, 384, 1, 96, 118),
+                                                 (4352, 3072, 512, 1, 79, 86), (2560, 5120, 1024, 1, 109, 114),
+                                                 (5461, 2048, 512, 1, 66.6, 62.7), (5461, 2048, 512, 0, 61.5, 52),
+                                                 (1792, 4096, 1024, 0, 61, 57), (6144, 4096, 256, 0, 79, 85)])
+def test_the_last_round_of_short_gradients(rules, f, d, r, f32, whole, cut):
+    saved = float(rules("cost", GRAD, 1, 1, 3, f, d, r, f32)[0][2])
+    assert (saved > 0) == (cut < whole)
