@@ -184,8 +184,11 @@ inline float bf16_tile_cost(const GemmLaunch& g, int c, const Stages& st, float 
   const float full = fminf(fmaxf((total - 96) / 160.f, 0.f), 1.f);
   const float alone = m.stage_alone + full * (m.stage_full - m.stage_alone);
   float n = total / 256.f, load;               // workgroups and K stages of the fullest CU
-  if (equal || n >= 4.f) {
-    if (n < 4.f) n = (float)(int)(n + 0.999f);   // few workgroups per CU: the fullest CU sets the time
+  const bool few = n < 4.f;                    // workgroups per CU: the fullest CU sets the time
+  if (equal || !few) {
+    // the 192-row tile's last round counts in full behind more of them as well, and is never cut up: 1045 such tiles with 64
+    // stages take 478 us, five rounds of 95, where 4.1 would be 390
+    if (few || c == TILE_K) n = (float)(int)(n + 0.999f);
     load = 0.f;
     for (int i = 0; i < g.nprob; ++i) load += (float)units[i] * stages[i];
     load *= n / total;
@@ -225,7 +228,7 @@ inline float bf16_tile_cost(const GemmLaunch& g, int c, const Stages& st, float 
     n = (float)q[at].wgs;
   }
   const float time = total <= kCUs ? load * alone : fmaxf(longest * m.stage_alone, load * m.stage_shared);
-  return m.fixed + m.per_round * n + time - (c == TILE_L && n < 4.f && equal ? bf16_tail(g).saved : 0.f);
+  return m.fixed + m.per_round * n + time - (c == TILE_L && few && equal ? bf16_tail(g).saved : 0.f);
 }
 inline float bf16_tile_cost(const GemmLaunch& g, int c) { return bf16_tile_cost(g, c, Stages(g), FLT_MAX); }
 

@@ -36,6 +36,18 @@ def test_a_rotating_launch_is_never_much_longer_than_one_without(rules):
     assert {int(r[3]) for r in rows} >= {-1, 0, 1}      # a launch of its own, 256 x 256 and 128 x 128 tiles are all taken
 
 
+# (epilogue, second operand K-contiguous, M, N, K): us measured on the 192-row tile, and on 256 x 256 tiles, last round cut up
+@pytest.mark.parametrize("epi,bkc,M,N,K,k_tile,large", [(SWIGLU_BWD, 1, 3584, 7168, 4096, 467, 360),
+                                                        (SWIGLU_BWD, 1, 4352, 6144, 3072, 348, 293),
+                                                        (SWIGLU_BWD, 1, 4864, 5888, 5120, 579, 508),
+                                                        (STORE, 0, 6656, 7936, 3072, 343, 295)])
+def test_rounds_of_the_192_row_tile(rules, epi, bkc, M, N, K, k_tile, large):
+    """More than four rounds of them: the last one counts in full, like the first ones.  The model is good to 20 %."""
+    k, l, _, taken = map(float, rules("cost", epi, 1, bkc, 1, M, N, K, 0)[0])
+    assert abs(k / k_tile - 1) <= 0.2 and abs(l / large - 1) <= 0.2
+    assert int(taken) != K_TILE
+
+
 # us of three expansions [f x d] of rank r with a whole last round and with one that is cut up, measured
 @pytest.mark.parametrize("f,d,r,f32,whole,cut", [(11008, 4096, 1024, 1, 296, 318), (8192, 3072, 384, 1, 96, 118),
                                                  (4352, 3072, 512, 1, 79, 86), (2560, 5120, 1024, 1, 109, 114),
