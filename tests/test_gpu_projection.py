@@ -79,7 +79,7 @@ def test_refresh_bf16_planted_gap(m, n, r, left, pad):
     assert orth_defect(P) < 1e-2
 
 
-@pytest.mark.parametrize("tile", ["S", "S4", "T", "T2", "L8"])
+@pytest.mark.parametrize("tile", ["S", "S4", "T", "T2", "X", "L8"])
 @pytest.mark.parametrize("m,n,r,left", [(344, 128, 33, 0), (200, 333, 40, 1)])
 def test_refresh_bf16_on_every_tile(m, n, r, left, tile, mecefo_option):
     """The polynomial and the hi + lo halves as epilogues of every tile, with ranks, rows and contractions that end
