@@ -10,9 +10,12 @@ namespace mecefo {
 // d = 512, 2048 tokens, whose 64 x 64 and 128 x 128 tiles are a tie: 1201 -> 1183 us).  Forwards with no allowance and
 // with no limit against this one, us: 64 tokens, two heads of 64: 38.9 / 33.4 against 33.5; 256 tokens, eight of 64:
 // 48.6 / 50.9 against 50.9 (the one where it costs); 2048 tokens, eight of 64: 63.0 / 61.5 against 61.5; 256 tokens, four
-// of 128: 48.3 / 60.3 against 48.3; 512 tokens, sixteen of 128: 141 / 173 against 141.  On large ones the rotation launch
-// takes more (16 us for [3584 x 3584]), but the model of the tiles is no better than that either: with an allowance of
-// 5 + 1.1e-6 b d, which follows the launch, [3072 x 2048] with heads of 64 takes 191 us instead of 181, the others the same.
+// of 128: 48.3 / 60.3 against 48.3; 512 tokens, sixteen of 128: 141 / 173 against 141.
+// The best one is looked for among the tiles that a rotating launch is costed with.  A plain launch may be shorter, with its
+// last round cut up, on 192-row or 32-row tiles: forwards that rotate against that, us: [1024 x 2944], heads of 64: 141 / 133;
+// [3072 x 2048], 64: 187 / 177; [2816 x 1920], 64: 163 / 163; [5632 x 3072], 64: 541 / 518; [7936 x 2304], 128: 475 / 470.
+// But the rotation behind it rounds Q and K to bf16 a second time, which the one on the fp32 accumulators does not (their
+// error times sqrt 2), so that is not weighed against a few percent of time.
 int gemm_bf16_rope_tile(const GemmLaunch& g, int dh) {
   const int forced = bf16_forced_tile();
   if (forced >= 0)
@@ -24,7 +27,7 @@ int gemm_bf16_rope_tile(const GemmLaunch& g, int dh) {
   for (int c : {TILE_M2, TILE_M4})
     if (dh == 64 && bf16_tile_cost(rot, c) < bf16_tile_cost(rot, best)) best = c;
   float least;
-  bf16_best_tile(g, &least);
+  bf16_best_tile(rot, &least);
   return bf16_tile_cost(rot, best) <= least + 6.f ? best : -1;
 }
 static hipError_t run_rope(GemmLaunch& g, hipStream_t s) {

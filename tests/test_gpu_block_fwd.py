@@ -97,6 +97,35 @@ def test_block_fwd_bf16_last_round_of_the_qkv_products(heads):
     print(run_fwd(34, 22, 256, 1024, 64, heads, "bf16")[-1])
 
 
+@pytest.mark.parametrize("b,heads,dh", [(1024, 46, 64), (768, 29, 128), (2816, 30, 64)])
+def test_block_fwd_bf16_rotates_before_it_rounds(b, heads, dh):
+    """Sizes whose plain launch for Q, K and V would be shorter on tiles that cannot rotate: Q and K are rounded to bf16 once
+    all the same.  One rounding leaves 2^-7 / sqrt 12 = 2.26e-3 of the power of two below each value, 1.66e-3 of the norm for
+    values spread over the binades; two leave sqrt 2 times that, 2.35e-3."""
+    d, seq = heads * dh, 256
+    gen = torch.Generator(device="cuda").manual_seed(b)
+    rnd = lambda n, k, s=1.0: (torch.randn(n, k, generator=gen, device="cuda") * s).to(torch.bfloat16)   # noqa: E731
+    inp = dict(X=rnd(b, d), g_attn=torch.ones(d, dtype=torch.bfloat16, device="cuda"),
+               g_ffn=torch.ones(d, dtype=torch.bfloat16, device="cuda"), **{k: rnd(d, d, d ** -0.5) for k in ("Wq", "Wk", "Wv", "Wo")},
+               Wg=rnd(64, d), Wu=rnd(64, d), Wd=rnd(d, 64))
+    desc, attn = B.make_desc(b, d, 64, B.BF16), B.make_attn_desc(b // seq, seq, heads, d)
+    out = {k: torch.empty(b, d, dtype=torch.bfloat16, device="cuda") for k in ("Out", "H", "Q", "K", "V", "O")}
+    out["L"] = torch.empty(b * heads, device="cuda")
+    B.mecefo_block_fwd(desc, attn, inp, out, poisoned_ws(B.mecefo_block_fwd_workspace_bytes(desc, attn)))
+    torch.cuda.synchronize()
+    x = inp["X"].double()
+    xn = (x * torch.rsqrt(x.square().mean(1, keepdim=True) + 1e-6)).to(torch.bfloat16).double()      # the operand of the products
+    inv = 10000.0 ** (-torch.arange(dh // 2, device="cuda", dtype=torch.float64) / (dh // 2))
+    ang = torch.arange(seq, device="cuda", dtype=torch.float64)[:, None] * inv
+    c, s = (t.repeat(b // seq, 1)[:, None, :] for t in (ang.cos(), ang.sin()))
+    for k in ("Q", "K"):
+        v = (xn @ inp["W" + k.lower()].double().T).view(b, heads, 2, dh // 2)
+        want = torch.stack((v[:, :, 0] * c - v[:, :, 1] * s, v[:, :, 1] * c + v[:, :, 0] * s), 2).reshape(b, d)
+        err = float((out[k].double() - want).norm() / want.norm())
+        print(k, err)
+        assert err <= 1.2 * 1.66e-3
+
+
 def test_fused_attention_random_shapes_forward_then_backward():
     """Seeded sweep over sequence lengths, batch sizes, head counts and both fused head dimensions: the
     forward on the GPU, then the standard-mode backward fed with the tensors that forward kept, each

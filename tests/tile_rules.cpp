@@ -1,6 +1,6 @@
 // What the planning functions choose, on the host.
-//   tile_rules rope        every forward [b x d] with heads of 64 and 128: "b d dh configuration, its modelled time, the time
-//                          of the best tiles without rotation" of the launch that goes out for Q, K and V
+//   tile_rules rope        every forward [b x d] with heads of 64 and 128: "b d dh configuration, modelled time of the shortest
+//                          launch that rotates, of that configuration, of the best whole tiles" for Q, K and V
 //   tile_rules cost EPI AKC BKC NPROB M N K F32     "modelled time on the 192-row tile, on 256 x 256 tiles, what cutting up
 //                          their last round saves, the configuration taken" of a launch of NPROB equal products
 #include <stdio.h>
@@ -39,9 +39,10 @@ int main(int argc, char** argv) {
       for (int d = 512; d <= 4096; d += 128) {
         const GemmLaunch plain = launch(EPI_STORE, true, true, 3, b, d, d), rot = launch(EPI_ROPE, true, true, 3, b, d, d);
         const int c = gemm_bf16_rope_tile(plain, dh);
-        float least;
-        bf16_best_tile(plain, &least);
-        printf("%d %d %d %d %.2f %.2f\n", b, d, dh, c, c < 0 ? least : bf16_tile_cost(rot, c), least);
+        float least, best = bf16_tile_cost(rot, TILE_L);
+        bf16_best_tile(rot, &least);
+        if (dh == 64) best = fminf(best, fminf(bf16_tile_cost(rot, TILE_M2), bf16_tile_cost(rot, TILE_M4)));
+        printf("%d %d %d %d %.2f %.2f %.2f\n", b, d, dh, c, best, c < 0 ? best : bf16_tile_cost(rot, c), least);
       }
   return 0;
 }
