@@ -48,7 +48,8 @@ def test_last_round_of_the_forward_products(b, d, f, mecefo_option):
 @pytest.mark.parametrize("grad", [B.F32, B.BF16])
 @pytest.mark.parametrize("f", [22000, 24600, 27600])      # 258, 291 and 324 tiles: sixteenths, quarters, halves
 def test_last_round_of_the_expansion(f, grad, accumulate, mecefo_option):
-    """K = r is one stage, so every tile adds up in the same order: the gradients equal those of whole tiles."""
+    """K = r is one stage, so every tile adds up in the same order: the gradients equal those of whole tiles, and those on
+    tiles of 192 rows."""
     b, d, r = 16, 64, 16
     gen = torch.Generator(device="cuda").manual_seed(f)
     U, dY = padded(b, d, 1.0, gen), padded(b, d, 1.0, gen)
@@ -58,7 +59,7 @@ def test_last_round_of_the_expansion(f, grad, accumulate, mecefo_option):
     gt = torch.float32 if grad == B.F32 else torch.bfloat16
     old = [torch.randn(*s, generator=gen, device="cuda").to(gt) for s in ((f, d), (f, d), (d, f))]
     out = []
-    for tile in ("L8", "LT"):
+    for tile in ("L8", "LT", "K"):
         mecefo_option("tile", tile)
         ws = torch.full((B.mecefo_workspace_bytes(desc, r, r, r),), 255, dtype=torch.uint8, device="cuda")
         dU = torch.empty(b, d, dtype=torch.bfloat16, device="cuda")
@@ -66,8 +67,10 @@ def test_last_round_of_the_expansion(f, grad, accumulate, mecefo_option):
         B.mecefo_ffn_bwd_lowrank(desc, U, dY, Wg, Wu, Wd, *(B.proj(p, r) for p in P), B.SIDE_INPUT, dU, *g, accumulate, ws)
         torch.cuda.synchronize()
         out.append([dU, *g])
-    for x, y in zip(*out):
-        assert bool(x.isfinite().all()) and torch.equal(x, y)
+    for x, *others in zip(*out):
+        assert bool(x.isfinite().all())
+        for y in others:
+            assert torch.equal(x, y)
 
 
 def test_last_round_of_the_residual_products(mecefo_option):
