@@ -5,10 +5,10 @@
 namespace mecefo {
 // The rotation pairs columns of one head: a wave of the epilogue must hold whole heads, which the 128 columns
 // of a 256 x 256 tile's wave and the 64 of a 128 x 128 one do for head dimensions 64 and 128 or 64.
-// The two rotations as launches cost about 7 us in all on small calls (3.4 us each and the gap), more on large
-// ones: a tile that can rotate is taken when the model puts it within 6 us of the best one (an 8-layer stack of
+// The rotation as a launch of its own takes 4 to 6 us with the gap in front of it on small calls, 17 for [3584 x 3584]: a tile
+// that can rotate is taken when the model puts it within 6 us of the best one (an 8-layer stack of
 // d = 512, 2048 tokens, whose 64 x 64 and 128 x 128 tiles are a tie: 1201 -> 1183 us).  Forwards with no allowance and
-// with no limit against this one, us: 64 tokens, two heads of 64: 38.9 / 33.4 against 33.5; 256 tokens, eight of 64:
+// with no limit against this one, us, two launches for the rotation then: 64 tokens, two heads of 64: 38.9 / 33.4 against 33.5; 256 tokens, eight of 64:
 // 48.6 / 50.9 against 50.9 (the one where it costs); 2048 tokens, eight of 64: 63.0 / 61.5 against 61.5; 256 tokens, four
 // of 128: 48.3 / 60.3 against 48.3; 512 tokens, sixteen of 128: 141 / 173 against 141.
 // The best one is looked for among the tiles that a rotating launch is costed with.  A plain launch may be shorter, with its

@@ -17,17 +17,19 @@ namespace {
 
 constexpr int kHeldSplits = 8;
 
-// The iterate is kept as an fp32 master copy.  For bf16 weights it enters the MFMA products as the
+// For fp32 weights the iterate is one fp32 matrix.  For bf16 weights it enters the MFMA products as the
 // sum of two bf16 matrices (hi = bf16(x), lo = bf16(x - hi): 16 mantissa bits), contracted as two K
 // segments of one launch: a single bf16 rounding of the iterate would drown the weakest of the r
 // directions, whose share of X after one application of W^T W is (s_r/s_1)^2.  The halves are written by
-// whatever produces the iterate: the product's epilogue, the sum of its K splits, the normalisation.
+// whatever produces the iterate: the product's epilogue, the sum of its K splits, the normalisation.  An fp32 copy is
+// written where something reads it: the result of a power round (normalised next), of a step in front of a polishing step
+// (which adds to it) and of the last step unless that writes P itself.
 //
 // A refresh is a chain of some 60 dependent products of a few microseconds each, so launches count: with
 // the polynomial and the halves in the epilogues a Newton-Schulz step is three products (four launches where
 // the Gram matrix is cut along K) instead of three products, two or three elementwise kernels and a copy.
 // Three matrices of [5461 x 2048], rank 512, two rounds of eight steps and three polishing steps: 406 launches and
-// 6760 us on the register-staged kernels with separate elementwise launches, 219 and 2380 us now (3390 -> 2650 us by the
+// 6760 us on the register-staged kernels with separate elementwise launches, 218 and 1970 us now (3390 -> 2650 us by the
 // epilogues alone).
 
 // Sum of the K splits of a product, finished like its epilogue would (EPI_POLY or EPI_HILO; fixed order).
