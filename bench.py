@@ -179,7 +179,7 @@ def main():
     if "norm_bwd" in stage_report:
         hbm["norm_bwd_GBs"] = round(4 * b * d * 2 / (stage_report["norm_bwd"]["ms"] * 1e-3) / 1e9, 1)
 
-    # What a plain device copy of tensors of this size reaches on this machine (rotating buffers, HIP events):
+    # What a plain device copy of tensors of this size reaches on this card (rotating buffers, HIP events):
     # the practical ceiling for the two norm kernels, whose tensors are 64 MiB at C5.
     nb = b * d * 2
     srcs = [torch.empty(nb, dtype=torch.uint8, device=dev) for _ in range(6)]
@@ -351,7 +351,7 @@ def overhead(B, torch, desc, b, d, f, r, ldf, U, dY, Wg, Wu, Wd, projs, dU, dWg,
 
 def vendor_gemm_reference(torch, b, d, f, data):
     """Context, not a target and not on the product path: the vendor GEMM library (torch.matmul on bf16
-    tensors) on the three large products of the step, same shapes, same kind of operands, same box and
+    tensors) on the three large products of the step, same shapes, same kind of operands, same card and
     minute.  The matrix cores are power-limited on Gaussian operands (the shader clock drops well below
     2.4 GHz), so what any kernel can reach on this workload is best read next to this line."""
     dev, bf = torch.device("cuda:0"), torch.bfloat16

@@ -343,7 +343,7 @@ __device__ __forceinline__ void dtl_tile(const KHead& head, GemmProblem p, int m
       }
     }
     // The scheduler's built-in pattern that alternates single MFMAs with single LDS reads.  Measured
-    // against its other pattern, none, and an order pinned column by column (same box, alternating
+    // against its other pattern, none, and an order pinned column by column (same card, alternating
     // runs): the large launches +4 to +9 %.
     __builtin_amdgcn_iglp_opt(1);
   };

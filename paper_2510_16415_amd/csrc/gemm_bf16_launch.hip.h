@@ -28,7 +28,7 @@ constexpr int kMaxSplits = 16;   // parts a product may be cut into along K
 // layer takes 7 % longer on Gaussian than on all-zero operands.
 using PipeL = DtlPipe<CfgL8, 2>;
 // 64 KiB: two workgroups per CU cover each other's waits.  Four waves of 64 x 64 against eight of 32 x 64 (fewer LDS bytes
-// per multiply-add, fewer waves to cover latency): a draw.  Calls with four waves, on two boxes: [4096 x 1024] skip
+// per multiply-add, fewer waves to cover latency): a draw.  Calls with four waves, on two cards: [4096 x 1024] skip
 // backward of two micro-batches 0.3 % slower and 1.5 % faster, [2048 x 2048] skip 1.8 and 1.1 % slower, 8-layer stack
 // of [2048 x 512] 2.4 % slower on both, [4096 x 1024] forward equal and 1.4 % faster; mean of 16 and of 23 cases
 // 0.6 and 0.3 % slower.
